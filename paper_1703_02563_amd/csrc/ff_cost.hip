@@ -19,6 +19,8 @@
 // the adding thread sees a signed overflow) and counted in an overflow word
 // after the accumulators; a nonzero count turns every gradient output into
 // NaN instead of a wrapped value.
+#include <algorithm>
+
 #include "ff_device.h"
 #include "ff_internal.h"
 
@@ -28,40 +30,49 @@ using ffk::clampi;
 
 constexpr double kFix = 4294967296.0;  // 2^32
 
+// A quad of lanes per entry: lane k owns channels 4k .. 4k+3, so one load of a
+// quad covers a pixel's 64 bytes and the four partial sums of the fixed order
+// are the four lanes' own.  Latency-bound (49 dependent additions per lane):
+// four times the lanes of one thread per entry hide it better: 62 -> 12 us for
+// 2,048 entries at radius 3 on 1024 x 436 (65,536 scattered entries: 64 us
+// either way, 411 MB of patch rows at 6.3 TB/s).
 template <int R>
 __global__ __launch_bounds__(256) void k_cost_fwd(ffh::CostArgs a) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= a.count) return;
+  const long long gid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  const int e = (int)min(gid >> 2, (long long)a.count - 1), k = (int)(gid & 3);
   const int4 en = a.entries[e];
   const int n = a.n, Wm = a.W - 1, Hm = a.H - 1;
-  const float4 *f1 = reinterpret_cast<const float4 *>(a.f1);
-  const float4 *f2 = reinterpret_cast<const float4 *>(a.f2);
-  float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+  const float4 *f1 = reinterpret_cast<const float4 *>(a.f1) + k;
+  const float4 *f2 = reinterpret_cast<const float4 *>(a.f2) + k;
+  float acc = 0.0f;
   for (int v = -R; v <= R; ++v) {
     const size_t qrow = (size_t)clampi(en.y + n * v, Hm) * a.W;
     const size_t trow = (size_t)clampi(en.y + en.w + n * v, Hm) * a.W;
+    float4 x[2 * R + 1], y[2 * R + 1];
 #pragma unroll
     for (int u = -R; u <= R; ++u) {
-      const float4 *pa = f1 + (qrow + clampi(en.x + n * u, Wm)) * 4;
-      const float4 *pb = f2 + (trow + clampi(en.x + en.z + n * u, Wm)) * 4;
+      x[u + R] = f1[(qrow + clampi(en.x + n * u, Wm)) * 4];
+      y[u + R] = f2[(trow + clampi(en.x + en.z + n * u, Wm)) * 4];
+    }
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const float4 x = pa[k], y = pb[k];
-        float d = x.x - y.x;
-        acc[k] = __fmaf_rn(d, d, acc[k]);
-        d = x.y - y.y;
-        acc[k] = __fmaf_rn(d, d, acc[k]);
-        d = x.z - y.z;
-        acc[k] = __fmaf_rn(d, d, acc[k]);
-        d = x.w - y.w;
-        acc[k] = __fmaf_rn(d, d, acc[k]);
-      }
+    for (int u = 0; u <= 2 * R; ++u) {
+      float d = x[u].x - y[u].x;
+      acc = __fmaf_rn(d, d, acc);
+      d = x[u].y - y[u].y;
+      acc = __fmaf_rn(d, d, acc);
+      d = x[u].z - y[u].z;
+      acc = __fmaf_rn(d, d, acc);
+      d = x[u].w - y[u].w;
+      acc = __fmaf_rn(d, d, acc);
     }
   }
-  a.cost[e] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+  acc += __shfl_xor(acc, 1);  // s0 + s1 (and s2 + s3 in the quad's upper half)
+  acc += __shfl_xor(acc, 2);
+  if (k == 0 && (gid >> 2) < a.count) a.cost[e] = acc;
 }
 
-// One thread per (entry, patch position).
+// Atomic form (see launch_cost_bwd for when it runs): one thread per (entry,
+// patch position).
 __global__ __launch_bounds__(256) void k_cost_bwd(ffh::CostArgs a) {
   const int side = 2 * a.radius + 1, P = side * side;
   const long long gid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -103,6 +114,234 @@ __global__ __launch_bounds__(256) void k_fixed_to_float(const int64_t *acc, cons
   if (i < count) out[i] = *overflow ? __builtin_nanf("") : (float)((double)acc[i] * (1.0 / kFix));
 }
 
+// ---- backward by gathering ------------------------------------------------
+//
+// The atomic form issues 2 * 16 64-bit atomics per entry and patch position
+// (103 M for 65,536 entries at radius 3: 4.54 ms, bound by the L2's atomic
+// rate).  The sums are integers, so any order gives the same bits: here the
+// entries are sorted into bins by their patch centre (p for f1's gradient, the
+// target p + f for f2's), and every pixel adds the entries whose patch covers
+// it in registers and writes its gradient once.
+//
+// Bins: one per centre of [-rn, W + rn) x [-rn, H + rn) (rn = radius * n; a
+// centre further out is binned at the edge, which reaches the same border
+// pixels), each row in phase order (desc_col), so that the 2 radius + 1 centres
+// x - n u of a patch row are adjacent bins and their entries one range of
+// records.  A row's records are contiguous, the rows' places are handed out by
+// an atomic cursor.
+struct CostBins {
+  int32_t *start[2];  // [Hb][Wb + 1]: counts, then first records (last column: end of the row)
+  int32_t *rank[2];   // [count]: the entry's place inside its bin, -1: no contribution
+  int4 *rec[2];       // [count]: (flow to the other map, gradient bits, entry)
+  int32_t *cursor;    // [2]
+  int Wb, Hb, rn, log2n;
+};
+
+// Index of the entry's bin on one side.
+__device__ __forceinline__ size_t cost_bin(const CostBins &b, int4 en, int side, int W, int H) {
+  const int cx = side ? en.x + en.z : en.x, cy = side ? en.y + en.w : en.y;
+  const int x = clampi(cx + b.rn, b.Wb - 1), y = clampi(cy + b.rn, b.Hb - 1);
+  return (size_t)y * (b.Wb + 1) + ffk::desc_col(x, b.log2n, b.Wb);
+}
+
+__global__ __launch_bounds__(256) void k_cost_count(ffh::CostArgs a, CostBins b) {
+  const int e = blockIdx.x * blockDim.x + threadIdx.x, side = blockIdx.y;
+  if (e == 0 && side == 0) *a.overflow = 0;
+  if (e >= a.count) return;
+  b.rank[side][e] =
+      a.grad_cost[e] == 0.0f ? -1 : atomicAdd(b.start[side] + cost_bin(b, a.entries[e], side, a.W, a.H), 1);
+}
+
+// One workgroup per row of bins: exclusive sums of its counts from a place
+// of its own.
+__global__ __launch_bounds__(256) void k_cost_rows(CostBins b) {
+  __shared__ int wsum[4], base;
+  const int side = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int32_t *row = b.start[side] + (size_t)blockIdx.x * (b.Wb + 1);
+  const int per = (b.Wb + 255) / 256, c0 = min(tid * per, b.Wb), c1 = min(c0 + per, b.Wb);
+  int sum = 0;
+  for (int c = c0; c < c1; ++c) sum += row[c];
+  int incl = sum;
+  for (int off = 1; off < 64; off <<= 1) {
+    const int o = __shfl_up(incl, off);
+    if (lane >= off) incl += o;
+  }
+  if (lane == 63) wsum[wave] = incl;
+  __syncthreads();
+  if (tid == 0) {
+    const int total = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+    base = total ? atomicAdd(b.cursor + side, total) : 0;
+    row[b.Wb] = base + total;
+  }
+  __syncthreads();
+  int at = base + incl - sum;
+  for (int w = 0; w < wave; ++w) at += wsum[w];
+  for (int c = c0; c < c1; ++c) {
+    const int k = row[c];
+    row[c] = at;
+    at += k;
+  }
+}
+
+__global__ __launch_bounds__(256) void k_cost_fill(ffh::CostArgs a, CostBins b) {
+  const int e = blockIdx.x * blockDim.x + threadIdx.x, side = blockIdx.y;
+  if (e >= a.count) return;
+  const int rank = b.rank[side][e];
+  if (rank < 0) return;
+  const int4 en = a.entries[e];
+  const int at = b.start[side][cost_bin(b, en, side, a.W, a.H)] + rank;
+  const int g = __float_as_int(a.grad_cost[e]);
+  b.rec[side][at] = side ? make_int4(-en.z, -en.w, g, e) : make_int4(en.z, en.w, g, e);
+}
+
+// Sum of one lane's four channels with the checks of the atomic form.
+struct CostSum {
+  long long s[4] = {0, 0, 0, 0};
+  unsigned terms = 0, sums = 0;  // terms out of range; sums that left the int64 range
+  __device__ __forceinline__ void add(float g, float4 own, float4 other) {
+    const double g2 = 2.0 * (double)g;
+    const float p[4] = {own.x, own.y, own.z, own.w}, q[4] = {other.x, other.y, other.z, other.w};
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const double d = g2 * ((double)p[c] - (double)q[c]);
+      if (!(fabs(d) < 2147483648.0)) {  // |term| >= 2^31 (or NaN): no int64 fixed-point value
+        ++terms;
+        continue;
+      }
+      const long long fx = __double2ll_rn(d * kFix);
+      const long long t = (long long)((unsigned long long)s[c] + (unsigned long long)fx);
+      sums += ((s[c] ^ t) & (fx ^ t)) < 0;
+      s[c] = t;
+    }
+  }
+};
+
+// Gradient of one side (blockIdx.z): a workgroup takes 16 x 4 pixels, four
+// lanes per pixel with four channels each.  Bound by float64 arithmetic (a
+// term is formed and rounded in float64 as in the atomic form) and by the
+// latency of record -> other map's pixel, both prefetched one term ahead.
+// The terms of the 2R + 1 ranges run as one sequence, so that the 16 pixels
+// of a wave differ only in their total.  With every |term| below 2^19 (51
+// bits of fixed point) adding 3 * 2^51 rounds it to an integer whose bits are
+// summed as they are; a pixel with a larger term, or with so many that the
+// sum could leave 63 bits, takes the checked additions.
+// 65,536 entries at radius 3 on 1024 x 436: the whole backward, sorting
+// included, 4.59 ms -> 0.33 ms
+// (this kernel 0.29 ms, both sides).
+template <int R>
+__global__ __launch_bounds__(256) void k_cost_gather(ffh::CostArgs a, CostBins b) {
+  constexpr int K = 2 * R + 1;
+  constexpr double kMagic = 6755399441055744.0;  // 3 * 2^51: adding it rounds to an integer
+  const int k = threadIdx.x & 3, side = blockIdx.z;
+  const int x = blockIdx.x * 16 + ((threadIdx.x >> 2) & 15), y = blockIdx.y * 4 + (threadIdx.x >> 6);
+  if (x >= a.W || y >= a.H) return;
+  const int W = a.W, H = a.H, Wm = W - 1, Hm = H - 1, n = a.n;
+  const size_t px = ((size_t)y * W + x) * 4 + k;
+  const float4 *fo = reinterpret_cast<const float4 *>(side ? a.f1 : a.f2) + k;
+  const float4 own = reinterpret_cast<const float4 *>(side ? a.f2 : a.f1)[px];
+  const int4 *rec = b.rec[side];
+  const int32_t *start = b.start[side];
+  const int stride = b.Wb + 1;
+  CostSum sum;
+  if (x > 0 && x < Wm && y > 0 && y < Hm) {
+    // every sample that lands here is exactly (x, y): one term per entry of
+    // the 2R + 1 ranges, against the other map at (x, y) + flow
+    int first[K], at[K + 1];  // term i of the sequence in row v is record first[v] + i, at[v] <= i < at[v + 1]
+    const int32_t *row = start + (size_t)y * stride + ffk::desc_col(x, b.log2n, b.Wb);
+    at[0] = 0;
+#pragma unroll
+    for (int v = 0; v < K; ++v) {
+      const int lo = row[(size_t)v * n * stride], hi = row[(size_t)v * n * stride + K];
+      first[v] = lo - at[v];
+      at[v + 1] = at[v] + (hi - lo);
+    }
+    const int total = at[K];
+    auto record = [&](int i) {
+      int f = first[0];
+#pragma unroll
+      for (int v = 1; v < K; ++v) f = i >= at[v] ? first[v] : f;
+      return rec[f + i];
+    };
+    auto other = [&](int4 r) { return fo[((size_t)clampi(y + r.y, Hm) * W + clampi(x + r.x, Wm)) * 4]; };
+    bool checked = total > 2047;
+    if (total > 0 && !checked) {
+      const double o0 = own.x, o1 = own.y, o2 = own.z, o3 = own.w;
+      int4 r0 = record(0), r1 = record(min(1, total - 1));
+      float4 q0 = other(r0);
+      bool small = true;
+      unsigned long long acc[4] = {0, 0, 0, 0};
+      for (int i = 0; i < total; ++i) {
+        const float4 q1 = other(r1);
+        const int4 r2 = record(min(i + 2, total - 1));
+        {
+#pragma clang fp contract(off)
+          const double g = (double)__int_as_float(r0.z) * (2.0 * kFix);
+          const double d0 = g * (o0 - (double)q0.x), d1 = g * (o1 - (double)q0.y);
+          const double d2 = g * (o2 - (double)q0.z), d3 = g * (o3 - (double)q0.w);
+          constexpr double kSmall = 2251799813685248.0;  // 2^51
+          small = small && fabs(d0) < kSmall && fabs(d1) < kSmall && fabs(d2) < kSmall && fabs(d3) < kSmall;
+          acc[0] += (unsigned long long)__double_as_longlong(d0 + kMagic);
+          acc[1] += (unsigned long long)__double_as_longlong(d1 + kMagic);
+          acc[2] += (unsigned long long)__double_as_longlong(d2 + kMagic);
+          acc[3] += (unsigned long long)__double_as_longlong(d3 + kMagic);
+        }
+        r0 = r1;
+        r1 = r2;
+        q0 = q1;
+      }
+      const unsigned long long bias = (unsigned long long)__double_as_longlong(kMagic) * (unsigned long long)total;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) sum.s[c] = (long long)(acc[c] - bias);
+      checked = !small;
+    }
+    if (checked) {
+      sum = CostSum();
+      for (int i = 0; i < total; ++i) {
+        const int4 r = record(i);
+        sum.add(__int_as_float(r.z), own, other(r));
+      }
+    }
+  } else {
+    // border pixels also take the samples outside the image that clamp to
+    // them: all bins within rn of the pixel along the axis it borders
+    const int sy = (y == 0 || y == Hm) ? 1 : n, np = R > 0 && (x == 0 || x == Wm) ? n : 1;
+    for (int yb = y; yb <= y + 2 * b.rn; yb += sy)
+      for (int ph = 0; ph < np; ++ph) {
+        // centres x - rn + ph, then every n-th: at most K adjacent bins, one more for phase 0
+        const int32_t *p = start + (size_t)yb * stride + ffk::desc_col(x + ph, b.log2n, b.Wb);
+        const int lo = p[0], hi = p[ph == 0 ? K : K - 1];
+        for (int i = lo; i < hi; ++i) {
+          const int4 r = rec[i], en = a.entries[r.w];
+          const int cx = side ? en.x + en.z : en.x, cy = side ? en.y + en.w : en.y;
+          const float g = __int_as_float(r.z);
+          for (int v = -R; v <= R; ++v) {
+            if (clampi(cy + n * v, Hm) != y) continue;
+            const size_t orow = (size_t)clampi(cy + n * v + r.y, Hm) * W;
+            for (int u = -R; u <= R; ++u)
+              if (clampi(cx + n * u, Wm) == x) sum.add(g, own, fo[(orow + clampi(cx + n * u + r.x, Wm)) * 4]);
+          }
+        }
+      }
+  }
+  // a term out of range is seen from both sides and counted on the first
+  const unsigned bad = sum.sums + (side == 0 ? sum.terms : 0u);
+  if (bad) atomicAdd(reinterpret_cast<unsigned long long *>(a.overflow), (unsigned long long)bad);
+  constexpr double inv = 1.0 / kFix;
+  float4 *out = reinterpret_cast<float4 *>(side ? a.grad_f2 : a.grad_f1);
+  out[px] = make_float4((float)((double)sum.s[0] * inv), (float)((double)sum.s[1] * inv),
+                        (float)((double)sum.s[2] * inv), (float)((double)sum.s[3] * inv));
+}
+
+// Both gradients become NaN when the overflow word is nonzero.
+__global__ __launch_bounds__(256) void k_cost_poison(ffh::CostArgs a, long long count) {
+  if (*a.overflow == 0) return;
+  const long long step = (long long)gridDim.x * blockDim.x;
+  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += step) {
+    a.grad_f1[i] = __builtin_nanf("");
+    a.grad_f2[i] = __builtin_nanf("");
+  }
+}
+
 // Padded, phase-ordered copy of a float feature map (the layout of the
 // descriptor maps with 64-byte entries): one thread per 16-byte quarter of a
 // stored entry, so consecutive lanes store consecutive bytes.
@@ -129,7 +368,7 @@ hipError_t launch_pad_features(const float *f, int W, int H, int n, float *out, 
 
 hipError_t launch_cost_fwd(const CostArgs &a, hipStream_t stream) {
   if (a.count <= 0) return hipSuccess;
-  const dim3 grid((a.count + 255) / 256);
+  const dim3 grid((unsigned)(((long long)a.count * 4 + 255) / 256));
   switch (a.radius) {
     case 0: hipLaunchKernelGGL(k_cost_fwd<0>, grid, dim3(256), 0, stream, a); break;
     case 1: hipLaunchKernelGGL(k_cost_fwd<1>, grid, dim3(256), 0, stream, a); break;
@@ -144,8 +383,67 @@ hipError_t launch_cost_fwd(const CostArgs &a, hipStream_t stream) {
   return hipGetLastError();
 }
 
+// Places the bins in the accumulator scratch (2 * W * H * 16 words, whose
+// last word, the overflow count, lies behind them); false if they do not fit.
+static bool cost_bins(const CostArgs &a, CostBins *b, size_t *clear_words) {
+  b->rn = a.radius * a.n;
+  b->Wb = a.W + 2 * b->rn;
+  b->Hb = a.H + 2 * b->rn;
+  b->log2n = __builtin_ctz(a.n);
+  const size_t bins = ((size_t)b->Hb * (b->Wb + 1) + 1) & ~(size_t)1, entries = ((size_t)a.count + 1) & ~(size_t)1;
+  // records first (16-byte aligned), then the counts and the cursor, then the ranks
+  const uintptr_t base = ((uintptr_t)a.acc1 + 15) & ~(uintptr_t)15;
+  const size_t total = (base - (uintptr_t)a.acc1) + 2 * entries * 16 + (2 * bins + 2) * 4 + 2 * entries * 4;
+  if (total > (size_t)2 * a.W * a.H * 16 * 8) return false;
+  b->rec[0] = reinterpret_cast<int4 *>(base);
+  b->rec[1] = b->rec[0] + entries;
+  b->start[0] = reinterpret_cast<int32_t *>(b->rec[1] + entries);
+  b->start[1] = b->start[0] + bins;
+  b->cursor = b->start[1] + bins;
+  b->rank[0] = b->cursor + 2;
+  b->rank[1] = b->rank[0] + entries;
+  *clear_words = bins + 1;
+  return true;
+}
+
+static hipError_t launch_cost_gather(const CostArgs &a, const CostBins &b, hipStream_t stream) {
+  const dim3 grid((a.W + 15) / 16, (a.H + 3) / 4, 2);
+  switch (a.radius) {
+    case 0: hipLaunchKernelGGL(k_cost_gather<0>, grid, dim3(256), 0, stream, a, b); break;
+    case 1: hipLaunchKernelGGL(k_cost_gather<1>, grid, dim3(256), 0, stream, a, b); break;
+    case 2: hipLaunchKernelGGL(k_cost_gather<2>, grid, dim3(256), 0, stream, a, b); break;
+    case 3: hipLaunchKernelGGL(k_cost_gather<3>, grid, dim3(256), 0, stream, a, b); break;
+    case 4: hipLaunchKernelGGL(k_cost_gather<4>, grid, dim3(256), 0, stream, a, b); break;
+    case 5: hipLaunchKernelGGL(k_cost_gather<5>, grid, dim3(256), 0, stream, a, b); break;
+    case 6: hipLaunchKernelGGL(k_cost_gather<6>, grid, dim3(256), 0, stream, a, b); break;
+    case 7: hipLaunchKernelGGL(k_cost_gather<7>, grid, dim3(256), 0, stream, a, b); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
 hipError_t launch_cost_bwd(const CostArgs &a, hipStream_t stream) {
   const long long px = (long long)a.W * a.H * 16;
+  // Gathering needs the bins to fit the scratch (they do unless the image is
+  // tiny against the patch or holds more than about 6 entries per pixel), 16-byte loads of
+  // the maps, and few phases (a corner pixel walks n (2 n radius + 1) ranges
+  // one after another, 0.3 us each: n <= 4 keeps that below 70 us).
+  CostBins b;
+  size_t clear = 0;
+  const uintptr_t align = (uintptr_t)a.f1 | (uintptr_t)a.f2 | (uintptr_t)a.grad_f1 | (uintptr_t)a.grad_f2;
+  if (a.n <= 4 && (align & 15) == 0 && cost_bins(a, &b, &clear)) {
+    hipError_t e = launch_fill_u64(reinterpret_cast<uint64_t *>(b.start[0]), 0, (int64_t)clear, stream);
+    if (e != hipSuccess) return e;
+    const dim3 ge((unsigned)std::max(((long long)a.count + 255) / 256, 1ll), 2);
+    hipLaunchKernelGGL(k_cost_count, ge, dim3(256), 0, stream, a, b);
+    hipLaunchKernelGGL(k_cost_rows, dim3(b.Hb, 2), dim3(256), 0, stream, b);
+    hipLaunchKernelGGL(k_cost_fill, ge, dim3(256), 0, stream, a, b);
+    e = launch_cost_gather(a, b, stream);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_cost_poison, dim3((unsigned)std::min<long long>((px + 255) / 256, 1024)), dim3(256), 0,
+                       stream, a, px);
+    return hipGetLastError();
+  }
   // acc1, acc2 and the overflow word after them are one array
   hipError_t e = launch_fill_u64(reinterpret_cast<uint64_t *>(a.acc1), 0, 2 * px + 1, stream);
   if (e != hipSuccess) return e;
