@@ -145,7 +145,7 @@ Layout layout(int W, int H, const ff_params *p) {
   l.keys = off; off = align256(off + 2 * l.M * sizeof(uint64_t));
   // seed rerank: bound, collection and ranked candidates of both directions
   l.topl = off;
-  if (p->nn_l > 1) off = align256(off + 2 * ffh::topl_scratch_bytes((int)l.M));
+  if (p->nn_l > 1) off = align256(off + 2 * ffh::topl_scratch_bytes((int)l.M, (long long)l.N));
   l.cand = off;
   if (p->nn_l > 1) off = align256(off + 2 * l.M * p->nn_l * sizeof(uint64_t));
   l.grids = off;
@@ -424,48 +424,28 @@ ff_status ff_init_nn(const uint8_t *desc_a1, const uint8_t *desc_b1, const uint8
   if (e != hipSuccess) return FF_ERR_LAUNCH;
   ffh::LevelArgs a = one_dir_args(desc_ac, desc_bc, W, H, nc, radius, flow, cost, n_evals);
   a.dir[0].nn_key = nn_key;
-  a.dir[0].Dq1 = desc_a1;
   return from_hip(ffh::launch_init_coarse(a, s));
 }
 
 size_t ff_nn_topl_scratch_bytes(int32_t W, int32_t H, int32_t nc) {
   if (!nn_dims_ok(W, H) || !is_pow2(nc) || nc > (1 << (kMaxLevels - 1))) return 0;
   const size_t M = (size_t)ceil_div(W, nc) * ceil_div(H, nc);
-  return align256(M * sizeof(uint64_t)) + ffh::topl_scratch_bytes((int)M) +
-         align256(M * ffh::kTopLMax * sizeof(uint64_t));
+  return ffh::topl_scratch_bytes((int)M, (long long)W * H) + align256(M * ffh::kTopLMax * sizeof(uint64_t));
 }
 
-// The NN keys, then the l ranked candidates of every cell (scratch: keys,
-// the top-l pass's parts, and -- when cand is NULL -- the candidates).
+// The l ranked candidates of every cell (scratch: the group scores).
 static hipError_t nn_topl_run(const uint8_t *desc_a1, const uint8_t *desc_b1, int W, int H, int nc, int l,
-                              int32_t *nb_scratch, char *scratch, uint64_t *keys, uint64_t *cand, hipStream_t s) {
-  ffh::NNArgs nn{};
-  nn.ndir = 1;
-  nn.W = W;
-  nn.H = H;
-  nn.nc = nc;
-  nn.Wc = ceil_div(W, nc);
-  nn.M = nn.Wc * ceil_div(H, nc);
-  nn.N = W * H;
-  nn.dir[0] = {desc_a1, desc_b1, nb_scratch, keys};
-  hipError_t e = ffh::launch_nn(nn, s);
-  if (e != hipSuccess) return e;
+                              char *scratch, uint64_t *cand, hipStream_t s) {
   ffh::TopLArgs tl{};
   tl.ndir = 1;
   tl.l = l;
   tl.W = W;
   tl.H = H;
   tl.nc = nc;
-  tl.Wc = nn.Wc;
-  tl.M = nn.M;
-  tl.N = nn.N;
-  ffh::TopLDir &d = tl.dir[0];
-  d.Dq = desc_a1;
-  d.Dr = desc_b1;
-  d.nb = nb_scratch;
-  d.nn_key = keys;
-  d.keys = reinterpret_cast<uint64_t *>(scratch + align256((size_t)nn.M * sizeof(uint64_t)));
-  d.cand = cand;
+  tl.Wc = ceil_div(W, nc);
+  tl.M = tl.Wc * ceil_div(H, nc);
+  tl.N = W * H;
+  tl.dir[0] = {desc_a1, desc_b1, reinterpret_cast<int32_t *>(scratch), cand};
   return ffh::launch_topl(tl, s);
 }
 
@@ -475,9 +455,7 @@ ff_status ff_nn_topl(const uint8_t *desc_a1, const uint8_t *desc_b1, int32_t W, 
       nc > (1 << (kMaxLevels - 1)) || l < 1 || l > ffh::kTopLMax)
     return FF_ERR_ARG;
   if (!scratch || scratch_bytes < ff_nn_topl_scratch_bytes(W, H, nc)) return FF_ERR_WORKSPACE;
-  char *sp = static_cast<char *>(scratch);
-  return from_hip(nn_topl_run(desc_a1, desc_b1, W, H, nc, l, nb_scratch, sp, reinterpret_cast<uint64_t *>(sp), cand,
-                              (hipStream_t)stream));
+  return from_hip(nn_topl_run(desc_a1, desc_b1, W, H, nc, l, static_cast<char *>(scratch), cand, (hipStream_t)stream));
 }
 
 ff_status ff_init_nn_l(const uint8_t *desc_a1, const uint8_t *desc_b1, const uint8_t *desc_ac, const uint8_t *desc_bc,
@@ -495,13 +473,11 @@ ff_status ff_init_nn_l(const uint8_t *desc_a1, const uint8_t *desc_b1, const uin
   hipStream_t s = (hipStream_t)stream;
   char *sp = static_cast<char *>(scratch);
   const int M = ceil_div(W, nc) * ceil_div(H, nc);
-  uint64_t *cand =
-      reinterpret_cast<uint64_t *>(sp + align256((size_t)M * sizeof(uint64_t)) + ffh::topl_scratch_bytes(M));
-  hipError_t e = nn_topl_run(desc_a1, desc_b1, W, H, nc, nn_l, nb_scratch, sp, nn_key, cand, s);
+  uint64_t *cand = reinterpret_cast<uint64_t *>(sp + ffh::topl_scratch_bytes(M, (long long)W * H));
+  hipError_t e = nn_topl_run(desc_a1, desc_b1, W, H, nc, nn_l, sp, cand, s);
   if (e != hipSuccess) return FF_ERR_LAUNCH;
   ffh::LevelArgs a = one_dir_args(desc_ac, desc_bc, W, H, nc, radius, flow, cost, n_evals);
   a.dir[0].nn_key = nn_key;
-  a.dir[0].Dq1 = desc_a1;
   const uint64_t *cands[1] = {cand};
   if ((e = ffh::launch_rerank(a, cands, nn_l, s)) != hipSuccess) return FF_ERR_LAUNCH;
   return from_hip(ffh::launch_init_coarse(a, s));
@@ -881,20 +857,20 @@ ff_status ff_flow_fields_batched(const ff_pair *pairs, int32_t npairs, const ff_
   // descriptors: (pair, image * L + scale, row)
   fill([&](int, int H) { return 2 * L * H; });
   if ((e = ffh::launch_batch_descriptors(st, s)) != hipSuccess) return FF_ERR_LAUNCH;
-  // NN: norms (pair, image, 256 refs), keys (pair, direction, 256 queries), NN items
-  ffh::BatchStage norms = st, keysf = st, nn = st;
-  norms.n = keysf.n = nn.n = nc;
+  // NN: keys (pair, direction, 256 queries), search items, resolve items
+  ffh::BatchStage keysf = st, nn = st, resolve = st;
+  keysf.n = nn.n = resolve.n = nc;
   {
     auto set = [&](ffh::BatchStage &b, auto items_of) {
       b.prefix[0] = 0;
       for (int i = 0; i < npairs; ++i) b.prefix[i + 1] = b.prefix[i] + items_of(pairs[i].W, pairs[i].H);
       b.total = b.prefix[npairs];
     };
-    set(norms, [&](int W, int H) { return 2 * (int)((((size_t)W * H + 31) / 32 * 32 + 255) / 256); });
     set(keysf, [&](int W, int H) { return 2 * ((ceil_div(W, nc) * ceil_div(H, nc) + 255) / 256); });
     set(nn, [&](int W, int H) { return ffh::batch_nn_items(W, H, L); });
+    set(resolve, [&](int W, int H) { return ffh::batch_nn_resolve_items(W, H, L); });
   }
-  if ((e = ffh::launch_batch_nn(norms, keysf, nn, s)) != hipSuccess) return FF_ERR_LAUNCH;
+  if ((e = ffh::launch_batch_nn(keysf, nn, resolve, s)) != hipSuccess) return FF_ERR_LAUNCH;
   // scales, coarse to fine: one persistent launch per run of passes
   const ffh::Tuning tun = tuning_of(params->tuning);
   for (int lv = L - 1; lv >= 0; --lv) {
@@ -1088,7 +1064,6 @@ ff_status ff_flow_fields_f32(const float *const *feat1, const float *const *feat
       a.dir[dr].flow = gflow[lv][dr];
       a.dir[dr].cost = gcost[lv][dr];
       a.dir[dr].nn_key = keys + (size_t)dr * lay.M;
-      a.dir[dr].Dq1 = q[dr];
       a.dir[dr].cflow = lv + 1 < L ? gflow[lv + 1][dr] : nullptr;
       a.dir[dr].ccost = lv + 1 < L ? gcost[lv + 1][dr] : nullptr;
     }
@@ -1372,13 +1347,11 @@ ff_status ff_flow_fields(const uint8_t *img1, const uint8_t *img2, int32_t W, in
       if ((e = ffh::launch_gather_even(desc1[im], ev, W, H, s)) != hipSuccess) return FF_ERR_LAUNCH;
       refs[im] = ev;
     }
+    nn.even_refs = 1;
   }
   for (int dr = 0; dr < nd; ++dr)
     nn.dir[dr] = {desc1[dr], refs[dr ^ 1], nb + (size_t)dr * lay.Npad, keys + (size_t)dr * lay.M};
-  if ((e = ffh::launch_nn(nn, s)) != hipSuccess) return FF_ERR_LAUNCH;
-  if (params->fast_x2 && params->nn_l <= 1)
-    for (int dr = 0; dr < nd; ++dr)
-      if ((e = ffh::launch_remap_even(keys + (size_t)dr * lay.M, nn.M, W, s)) != hipSuccess) return FF_ERR_LAUNCH;
+  if (params->nn_l <= 1 && (e = ffh::launch_nn(nn, s)) != hipSuccess) return FF_ERR_LAUNCH;
   if (params->nn_l > 1) {
     // seed rerank among the nn_l nearest pixels (Eq. 1, Eq. 4)
     ffh::TopLArgs tl{};
@@ -1396,9 +1369,8 @@ ff_status ff_flow_fields(const uint8_t *img1, const uint8_t *img2, int32_t W, in
       ffh::TopLDir &d = tl.dir[dr];
       d.Dq = desc1[dr];
       d.Dr = refs[dr ^ 1];
-      d.nb = nb + (size_t)dr * lay.Npad;
-      d.nn_key = keys + (size_t)dr * lay.M;
-      d.keys = reinterpret_cast<uint64_t *>(base + lay.topl + (size_t)dr * ffh::topl_scratch_bytes((int)lay.M));
+      d.gmax = reinterpret_cast<int32_t *>(base + lay.topl +
+                                           (size_t)dr * ffh::topl_scratch_bytes((int)lay.M, (long long)lay.N));
       d.cand = reinterpret_cast<uint64_t *>(base + lay.cand) + (size_t)dr * lay.M * params->nn_l;
       cand[dr] = d.cand;
     }
@@ -1415,7 +1387,6 @@ ff_status ff_flow_fields(const uint8_t *img1, const uint8_t *img2, int32_t W, in
     for (int dr = 0; dr < nd; ++dr) {
       ra.dir[dr].Da = desc[dr][L - 1];
       ra.dir[dr].Db = desc[dr ^ 1][L - 1];
-      ra.dir[dr].Dq1 = desc1[dr];
       ra.dir[dr].nn_key = keys + (size_t)dr * lay.M;
       ra.dir[dr].n_evals = reinterpret_cast<unsigned long long *>(evals + dr);
     }
@@ -1485,7 +1456,7 @@ ff_status ff_flow_fields(const uint8_t *img1, const uint8_t *img2, int32_t W, in
         for (int dr = 0; dr < nd; ++dr) {
           const ffh::LevelKDir &kd = k.dir[dr];
           a.dir[dr] = {sub ? sdesc[dr][lv] : kd.Da, sub ? sdesc[dr ^ 1][lv] : kd.Db, kd.flow, kd.cost, kd.cflow,
-                       kd.ccost, kd.nn_key, desc1[dr], kd.n_evals, nullptr, dr};
+                       kd.ccost, kd.nn_key, kd.n_evals, nullptr, dr};
         }
         if (sub || stepwise) {
           if ((e = run_stage(a, W, H, lv, m, entry, st == nst - 1, params, s)) != hipSuccess) return FF_ERR_LAUNCH;
@@ -1534,7 +1505,6 @@ ff_status ff_flow_fields(const uint8_t *img1, const uint8_t *img2, int32_t W, in
         a.dir[dr].flow = gflow[lv][dr];
         a.dir[dr].cost = gcost[lv][dr];
         a.dir[dr].nn_key = keys + (size_t)dr * lay.M;
-        a.dir[dr].Dq1 = desc1[dr];
         a.dir[dr].cflow = lv + 1 < L ? gflow[lv + 1][dr] : nullptr;
         a.dir[dr].ccost = lv + 1 < L ? gcost[lv + 1][dr] : nullptr;
       }
@@ -1549,7 +1519,6 @@ ff_status ff_flow_fields(const uint8_t *img1, const uint8_t *img2, int32_t W, in
         a.dir[dr].flow = gflow[lv][dr];
         a.dir[dr].cost = gcost[lv][dr];
         a.dir[dr].nn_key = keys + (size_t)dr * lay.M;
-        a.dir[dr].Dq1 = desc1[dr];
         a.dir[dr].cflow = lv + 1 < L ? gflow[lv + 1][dr] : nullptr;
         a.dir[dr].ccost = lv + 1 < L ? gcost[lv + 1][dr] : nullptr;
       }

@@ -35,27 +35,26 @@ hipError_t launch_fill_u64(uint64_t *dst, uint64_t value, int64_t count, hipStre
 struct NNDir {
   const uint8_t *Dq;   // level-1 descriptors of the image holding the query cells
   const uint8_t *Dr;   // level-1 descriptors of the reference image
-  int32_t *nb;         // per-reference squared norm of (d - 128), padded to a multiple of 32
-  uint64_t *keys;      // per-query packed result (see ff_nn.hip)
+  int32_t *nb;         // scratch: N words rounded up to a multiple of 32 (the chunks' results)
+  uint64_t *keys;      // per query (squared distance << 32) | reference pixel
 };
 struct NNArgs {
   NNDir dir[kMaxDirs];
   int ndir;
   int W, H, nc, Wc, M, N;
-  int chunk_tiles;  // reference tiles (32 each) per workgroup; set by launch_nn
+  int even_refs;    // 1: the references are the even-pixel subset (launch_gather_even), N of them
+  int chunk_tiles, nchunk, atomic;  // reference tiles (32 each) per workgroup and their merge; set by launch_nn
 };
 hipError_t launch_nn(const NNArgs &args, hipStream_t stream);
 
-// The l nearest references of every query (1 <= l <= kTopLMax), after
-// launch_nn: l - 1 more passes of the NN kernel, pass k leaving out the
-// references up to pass k-1's key (see ff_nn.hip).
+// The l nearest references of every query (1 <= l <= kTopLMax): the NN
+// kernel's scores per group of references, then the groups that can hold the
+// l nearest ranked (see ff_nn.hip).
 constexpr int kTopLMax = 8;
 struct TopLDir {
   const uint8_t *Dq;       // level-1 row-major descriptors of the query image
   const uint8_t *Dr;       // the same of the reference image
-  const int32_t *nb;       // reference norms of launch_nn
-  const uint64_t *nn_key;  // launch_nn's keys (pass 0)
-  uint64_t *keys;          // [kTopLMax - 1][M] scratch: keys of passes 1 ..
+  int32_t *gmax;           // scratch of topl_scratch_bytes: [groups][M] largest scores
   uint64_t *cand;          // [M][l] output: (squared distance << 32) | q, ranked; ~0 past N
 };
 struct TopLArgs {
@@ -63,16 +62,12 @@ struct TopLArgs {
   int ndir, l;
   int W, H, nc, Wc, M, N;
   int even_refs;  // 1: the references are the even-pixel subset (launch_gather_even)
+  int chunk_tiles, nchunk, group, ngroups;  // set by launch_topl
 };
-struct TopLPrev {
-  const uint64_t *key[kMaxDirs];
-};
-size_t topl_scratch_bytes(int M);  // the keys of passes 1 .. kTopLMax - 1 of one direction
+size_t topl_scratch_bytes(int M, long long N);  // of one direction
 // Flow Fields+ Fast x2: the level-1 descriptors of the pixels with even x
-// and y ([ceil(H/2)][ceil(W/2)][16], the NN's references), and the NN keys
-// over that subset turned into keys naming image pixels.
+// and y ([ceil(H/2)][ceil(W/2)][16], the NN's references).
 hipError_t launch_gather_even(const uint8_t *desc1, uint8_t *out, int W, int H, hipStream_t stream);
-hipError_t launch_remap_even(uint64_t *keys, int M, int W, hipStream_t stream);
 hipError_t launch_topl(const TopLArgs &args, hipStream_t stream);
 
 // Launch tables of the temporally blocked level kernels, per scale log2 n
@@ -99,7 +94,6 @@ struct LevelDir {
   const int32_t *cflow;   // coarser grid (seeding only)
   const uint32_t *ccost;
   const uint64_t *nn_key; // coarsest init only
-  const uint8_t *Dq1;     // level-1 descriptors of the source image (coarsest init only)
   unsigned long long *n_evals;
   unsigned long long *n_work;  // nullable [2]: evaluations computed (all of them count in both entries here)
   int stream_id;
@@ -119,8 +113,7 @@ hipError_t launch_propagate(const LevelArgs &a, hipStream_t stream);  // both ha
 hipError_t launch_random_search(const LevelArgs &a, hipStream_t stream);
 // Seed rerank (Eq. 1, Eq. 4) at the coarsest scale: per cell the candidate
 // of cand[dir] ([cells][l], launch_topl's output) with the lowest E_nc, the
-// earlier rank on equal cost, written to nn_key in launch_nn's format for
-// the initialisation; counts every candidate but the winner (the
+// earlier rank on equal cost, written to nn_key for the initialisation; counts every candidate but the winner (the
 // initialisation evaluates the winner again).
 hipError_t launch_rerank(const LevelArgs &a, const uint64_t *const *cand, int l, hipStream_t stream);
 // One propagation step in serial order (anti-diagonal wavefronts over tiles;
@@ -238,11 +231,13 @@ struct BatchStage {
   int prefix[kMaxBatch + 1];
 };
 hipError_t launch_batch_descriptors(const BatchStage &rows, hipStream_t stream);
-hipError_t launch_batch_nn(const BatchStage &norms, const BatchStage &fill, const BatchStage &nn, hipStream_t stream);
+hipError_t launch_batch_nn(const BatchStage &fill, const BatchStage &nn, const BatchStage &resolve,
+                           hipStream_t stream);
 hipError_t launch_batch_level(const LevelKArgs &base, const BatchStage &tiles, bool maps_fit, hipStream_t stream);
 hipError_t launch_batch_consistency(const BatchStage &rows, float eps, hipStream_t stream);
 // items per pair of each stage (host)
 int batch_nn_items(int W, int H, int L);
+int batch_nn_resolve_items(int W, int H, int L);
 // tiles of one direction for the kernel that runs at that scale (the current
 // variant, or its fallback when a map does not fit the quad addressing)
 int level_tiles(int Wn, int Hn, int variant, bool maps_fit);

@@ -1,27 +1,35 @@
 // Exact brute-force nearest neighbour of the coarsest-grid cells (stands in
 // for the kd-tree candidate search of Sec. 3.1 with one candidate; the
-// initial flow of Eq. 1 / Eq. 4 is F = q - p).
+// initial flow of Eq. 1 / Eq. 4 is F = q - p), and the l nearest references
+// (a kd-tree leaf of size l).
 //
 // ||a - b||^2 = |a|^2 + |b|^2 - 2 a.b is a dense contraction over the 16
 // descriptor bytes.  Bytes v are shifted to int8 (v - 128, a plain xor with
-// 0x80), which leaves the distance unchanged, and the dot products of 32
-// queries x 32 references run on v_mfma_i32_32x32x16_i8 (exact in int32).
+// 0x80), which leaves the distance unchanged.  v_mfma_i32_32x32x32_i8 has
+// K = 32: both halves of K hold the same 16 bytes, so one instruction gives
+// 2 a.b, and with the accumulator initialised to -|b|^2 the score
+//     s = 2 a.b - |b|^2 = |a|^2 - dist
+// comes out of the matrix core finished.  References are the rows and queries
+// the columns of the product: a lane then holds 16 references of one query,
+// and the maximum over two tiles (64 references, a unit) is 16 v_max3 and one
+// compare and select for the unit's index -- 0.6 VALU operations per pair
+// instead of the 1.5 that scoring (index and distance in one word) and a
+// running maximum per query row cost with queries as the rows.  Which of a
+// unit's references it was is found afterwards for the one winning unit per
+// query (k_nn_resolve).  1024 x 436, 16-pixel grid, both directions:
+// norms + search @NN0@ -> search + resolve @NN1@ us; 1920 x 1080,
+// 32-pixel grid: @NN2@ -> @NN3@ us.
 //
-// Argmin with ties to the smallest reference index, without a compare and
-// select per pair: per (query, reference) the lane forms the score
-//     s = 4096 * dot - (2048 * |b|^2 + t) = -(2048 * (|b|^2 - 2 dot) + t)
-// with t the tile index inside the current chunk (t < 2048), one
-// v_lshl_add per pair, and keeps max(s) with v_max3 over two tiles.  Since
-// |b|^2 - 2 dot = dist - |a|^2 lies in [-2^18, 2^20), s never overflows and
-// max(s) is the smallest distance, then the smallest tile.  Within a lane
-// the reference column is fixed, so (distance, tile) orders references by
-// index.  At the end of the chunk each lane decodes its best, the 32 lanes
-// holding the same queries reduce (distance, index) as one 64-bit key, and
-// one atomicMin per query merges chunks and waves.
+// A workgroup takes 4 waves x 32 QB queries against one chunk of references,
+// staged in LDS (stages of 32 tiles, double-buffered; the norms are computed
+// while staging).  With QB = 4 query blocks per wave each tile's five 16-byte
+// LDS reads feed four products: LDS, VALU and matrix cores are then about
+// equally busy (40, 38 and 32 clocks per tile and block).
 //
-// Key written to global memory: ((dist - |a|^2 + 2^20) << 32) | index; the
-// init kernel adds |a|^2 back.  Padding references (index >= N) carry
-// |b|^2 = 2^20 - 1 and zero bytes, so their score is below every real one.
+// Ties: within a lane the first unit that reaches the maximum is kept, units
+// merge by (score, unit), and inside the unit the smallest index of that
+// score is taken: the smallest reference index of the smallest distance.
+// References at or beyond N score -(2^20 - 1), below every real one.
 #include <algorithm>
 #include <climits>
 
@@ -30,258 +38,296 @@
 
 namespace {
 
+typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 
-constexpr int kTilesPerChunk = 512;   // batches; <= kMaxChunkTiles
-constexpr int kMaxChunkTiles = 2048;  // the tile index inside a chunk must fit 11 bits
-constexpr int kQB = 2;                // 32-query blocks per wave (B operand reuse)
 constexpr int kWaves = 4;
-constexpr int kNbPad = (1 << 20) - 1;
-
-// Also clears the direction's NN keys (M <= N cells) for k_nn's atomicMin.
-__global__ __launch_bounds__(256) void k_nn_norms(ffh::NNArgs a) {
-  const ffh::NNDir d = a.dir[blockIdx.y];
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  const int Npad = (a.N + 31) & ~31;
-  if (idx < a.M) d.keys[idx] = ~0ull;
-  if (idx >= Npad) return;
-  int s = kNbPad;
-  if (idx < a.N) {
-    const uint4 v = reinterpret_cast<const uint4 *>(d.Dr)[idx];
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-    s = 0;
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-#pragma unroll
-      for (int b = 0; b < 4; ++b) {
-        const int e = (int)((w[k] >> (8 * b)) & 0xFF) - 128;
-        s += e * e;
-      }
-  }
-  d.nb[idx] = s;
-}
+constexpr int kStageTiles = 32, kStageRefs = kStageTiles * 32;
+constexpr int kPad = -((1 << 20) - 1);  // score of a padding reference
+constexpr int kMaxChunkTiles = 4096;    // a unit's index inside its chunk must fit 11 bits
+constexpr int kBatchChunkTiles = 128;   // batches: reference tiles per work item
+constexpr int kBatchQB = 8;
+// Waves per SIMD a kernel of QB query blocks per wave is compiled for
+constexpr int nn_waves(int qb) { return qb >= 4 ? 2 : qb == 2 ? 3 : 4; }
 
 __global__ __launch_bounds__(256) void k_fill_u64(uint64_t *dst, uint64_t value, int64_t count) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < count) dst[i] = value;
 }
 
-// Negation the compiler cannot see through: with an opaque addend,
-// (acc << 12) + nk stays one v_lshl_add_u32 instead of a shift and a
-// subtract.  Only the addend goes through asm; the matrix-core results are
-// read by ordinary instructions, so the compiler keeps its MFMA
-// read-after-write wait states.
-__device__ __forceinline__ int opaque_neg(int v) {
-  int r;
-  asm("v_sub_u32 %0, 0, %1" : "=v"(r) : "v"(v));
-  return r;
+__device__ __forceinline__ uint4 to_i8(uint4 v) {
+  return make_uint4(v.x ^ 0x80808080u, v.y ^ 0x80808080u, v.z ^ 0x80808080u, v.w ^ 0x80808080u);
+}
+__device__ __forceinline__ int dot16(uint4 a, uint4 b) {
+  int s = __builtin_amdgcn_sdot4((int)a.x, (int)b.x, 0, false);
+  s = __builtin_amdgcn_sdot4((int)a.y, (int)b.y, s, false);
+  s = __builtin_amdgcn_sdot4((int)a.z, (int)b.z, s, false);
+  return __builtin_amdgcn_sdot4((int)a.w, (int)b.w, s, false);
+}
+__device__ __forceinline__ int max3(int a, int b, int c) { return max(max(a, b), c); }
+
+struct NNStage {
+  uint4 desc[2][kStageRefs];
+  int norm[2][kStageRefs];  // -|b|^2
+};
+
+// int8 descriptor of query m.
+__device__ __forceinline__ uint4 query_desc(const uint8_t *Dq, int W, int nc, int Wc, int m) {
+  const int i = m % Wc, j = m / Wc;
+  return to_i8(reinterpret_cast<const uint4 *>(Dq)[(size_t)(j * nc) * W + (size_t)(i * nc)]);
 }
 
-// Pins a loaded value to a register after `after` is computed (an empty
-// asm with register operands; it touches no memory), so the load that
-// produces it is waited for only at the end of the iteration that
-// prefetches it.
-__device__ __forceinline__ int pin(int v, int after) {
-  asm volatile("" : "+v"(v) : "v"(after));
-  return v;
-}
-
-__device__ __forceinline__ long load_i8x8(const uint8_t *p) {
-  // 8 descriptor bytes -> 8 int8 (v - 128)
-  return (long)(*reinterpret_cast<const unsigned long long *>(p) ^ 0x8080808080808080ull);
-}
-
-// Query block `qblk` (32 * kQB queries) against reference chunk `chunk` of
-// one direction.  All threads of the workgroup call it.  kExcl: the next
-// nearest reference instead of the nearest -- every reference whose key
-// (distance, index) is at most the query's key in prev (the previous
-// pass's result) is left out; prev[m] = ~0 leaves out all.
-template <bool kExcl = false>
-__device__ __forceinline__ void nn_body(const ffh::NNDir &d, int M, int N, int W, int nc, int Wc, int qblk,
-                                        int chunk, int chunk_tiles, const uint64_t *prev = nullptr) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+// 32 QB queries per wave (block qblk) against the reference tiles [t0, t1)
+// (t0 even) of one direction; the whole workgroup calls it.  kTop: instead of
+// the best unit, the largest score of every group of `group` tiles goes to
+// gmax[group index][M] (t0 and group even, t0 a multiple of group).
+template <int QB, bool kTop>
+__device__ __forceinline__ void nn_body(NNStage &sm, const ffh::NNDir &d, int M, int N, int W, int nc, int Wc, int qblk,
+                                        int t0, int t1, uint32_t *part, int group, int32_t *gmax) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int col = lane & 31, kh = lane >> 5;
-  const int ntiles = (N + 31) >> 5;
-  const int m0 = qblk * (32 * kQB);
-  const int t0 = chunk * chunk_tiles;
-  const int t1 = min(t0 + chunk_tiles, ntiles);
-  if (t0 + wave >= t1) return;  // wave-uniform: no tile for this wave
-  struct {
-    int Wc, nc;
-  } a = {Wc, nc};
+  const int m0 = (qblk * kWaves + wave) * (32 * QB);
+  const bool active = m0 < M;  // wave-uniform; idle waves still help staging
+  const uint4 *Dr = reinterpret_cast<const uint4 *>(d.Dr);
+  const int lim = min(N, t1 * 32);
 
-  long aop[kQB];
+  v4i bq[QB];
 #pragma unroll
-  for (int qb = 0; qb < kQB; ++qb) {
-    const int m = min(m0 + qb * 32 + col, M - 1);
-    const int i = m % a.Wc, j = m / a.Wc;
-    const size_t pix = (size_t)(j * a.nc) * W + (size_t)(i * a.nc);
-    aop[qb] = load_i8x8(d.Dq + pix * 16 + kh * 8);
+  for (int qb = 0; qb < QB; ++qb) {
+    const uint4 q = query_desc(d.Dq, W, nc, Wc, min(m0 + qb * 32 + col, M - 1));
+    bq[qb] = v4i{(int)q.x, (int)q.y, (int)q.z, (int)q.w};
+  }
+  int best[QB], unit[QB];
+#pragma unroll
+  for (int qb = 0; qb < QB; ++qb) {
+    best[qb] = INT_MIN;
+    unit[qb] = 0;
   }
 
-  int best[kQB][16];
+  uint4 v[4];
+  auto load = [&](int b) {
 #pragma unroll
-  for (int qb = 0; qb < kQB; ++qb)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) best[qb][r] = INT_MIN;
-  // Exclusion as a score bound per (query row, lane): a reference of this
-  // lane (column col, chunk tile tl, index (t0 + tl) * 32 + col) has a key
-  // at most (dd*, q*) iff 2048 dd + tl <= K = 2048 dd* + floor((q* - col) /
-  // 32) - t0 (the tile term clamped to [-1, 2047]), i.e. iff its score
-  // -(2048 dd + tl) >= -K; it is kept iff the score is below thr = -K.
-  int thr[kQB][16];
-  if constexpr (kExcl) {
-#pragma unroll
-    for (int qb = 0; qb < kQB; ++qb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = m0 + qb * 32 + 8 * (r >> 2) + 4 * kh + (r & 3);
-        int t = INT_MAX;  // padding rows: nothing left out (they write nothing)
-        if (m < M) {
-          const uint64_t pk = prev[m];
-          if (pk == ~0ull) {
-            t = INT_MIN;  // nothing left to find
-          } else {
-            const int dd = (int)(uint32_t)(pk >> 32) - (1 << 20);
-            int tl = ((int)(uint32_t)pk - col) >> 5;  // floor: the shift is arithmetic
-            tl = tl - t0 < -1 ? -1 : (tl - t0 > 2047 ? 2047 : tl - t0);
-            t = (int)-(2048ll * dd + tl);  // 2048 dd + tl <= 2^31 - 1
-          }
-        }
-        thr[qb][r] = t;
-      }
-  }
-
-  const v16i zero = {0};
-  // Operands of the two tiles of step t (the second repeats the first at the
-  // odd tail).  The tile index is wave-uniform (scalar registers) and rides
-  // in the buffer loads' scalar offset; references at or beyond N lie outside
-  // the descriptor buffer's range (the loads return zeros, kept as zero
-  // int8 bytes), and their padded norm keeps them below every real one.
-  const __amdgpu_buffer_rsrc_t rdesc =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(d.Dr), (short)0, N * 16, 0x00020000);
-  const __amdgpu_buffer_rsrc_t rnorm =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t *>(d.nb), (short)0, ((N + 31) & ~31) * 4, 0x00020000);
-  const int voff_desc = col * 16 + kh * 8, voff_norm = col * 4;
-  struct Step {
-    long ba, bb;
-    int na, nb;
+    for (int k = 0; k < 4; ++k) {
+      const int ref = b * 32 + tid + 256 * k;
+      v[k] = Dr[min(ref, N - 1)];
+    }
   };
-  constexpr long kFlip = (long)0x8080808080808080ull;  // bytes v -> int8 v - 128
-  auto fetch = [&](int t, int tb) {
-    Step st;
-    st.ba = (long)__builtin_amdgcn_raw_buffer_load_b64(rdesc, voff_desc, t * 512, 0) ^ (t * 32 + col < N ? kFlip : 0);
-    st.bb = (long)__builtin_amdgcn_raw_buffer_load_b64(rdesc, voff_desc, tb * 512, 0) ^ (tb * 32 + col < N ? kFlip : 0);
-    st.na = (int)__builtin_amdgcn_raw_buffer_load_b32(rnorm, voff_norm, t * 128, 0);
-    st.nb = (int)__builtin_amdgcn_raw_buffer_load_b32(rnorm, voff_norm, tb * 128, 0);
-    return st;
+  auto store = [&](int b, int buf) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int r = tid + 256 * k;
+      const bool in = b * 32 + r < lim;
+      uint4 w = to_i8(v[k]);
+      if (!in) w = make_uint4(0, 0, 0, 0);
+      sm.desc[buf][r] = w;
+      sm.norm[buf][r] = in ? -dot16(w, w) : kPad;
+    }
   };
-  const int tw0 = t0 + __builtin_amdgcn_readfirstlane(wave);
-  auto second = [&](int t) { return (t + kWaves < t1) ? t + kWaves : t; };
-  Step cur = fetch(tw0, second(tw0));
-  for (int t = tw0; t < t1; t += 2 * kWaves) {
-    // the next step's operands are in flight while this step computes
-    const int tn = t + 2 * kWaves < t1 ? t + 2 * kWaves : t;
-    const Step nxt = fetch(tn, second(tn));
-    const int tb = second(t);
-    const long ba = cur.ba, bb = cur.bb;
-    const int nka = opaque_neg((cur.na << 11) | (t - t0));
-    const int nkb = opaque_neg((cur.nb << 11) | (tb - t0));
-    // all four products first: the second pair runs on the matrix core
-    // while the first pair's scores are reduced
-    v16i acc_a[kQB], acc_b[kQB];
+  // Operands of one unit (two tiles): the tiles' descriptors and the
+  // accumulators' initial values.
+  struct Unit {
+    v4i a0, a1;
+    v16i c0, c1;
+  };
+  auto fetch = [&](Unit &u, int buf, int t) {
+    const v4i *da = reinterpret_cast<const v4i *>(&sm.desc[buf][t * 32 + col]);
+    u.a0 = da[0];
+    u.a1 = da[32];
+    const v4i *cn = reinterpret_cast<const v4i *>(&sm.norm[buf][t * 32 + 4 * kh]);
 #pragma unroll
-    for (int qb = 0; qb < kQB; ++qb) {
-      acc_a[qb] = __builtin_amdgcn_mfma_i32_32x32x16_i8(aop[qb], ba, zero, 0, 0, 0);
-      acc_b[qb] = __builtin_amdgcn_mfma_i32_32x32x16_i8(aop[qb], bb, zero, 0, 0, 0);
+    for (int g = 0; g < 4; ++g) {
+      const v4i x = cn[2 * g], y = cn[8 + 2 * g];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        u.c0[4 * g + r] = x[r];
+        u.c1[4 * g + r] = y[r];
+      }
     }
-    __builtin_amdgcn_sched_barrier(0);
+  };
+  // Products of query block qb + 1 are issued before block qb's maxima, so the
+  // matrix core works while the VALU reduces.
+  auto score = [&](const Unit &u, int tile) {
+    v16i p = __builtin_amdgcn_mfma_i32_32x32x32_i8(u.a0, bq[0], u.c0, 0, 0, 0);
+    v16i q = __builtin_amdgcn_mfma_i32_32x32x32_i8(u.a1, bq[0], u.c1, 0, 0, 0);
 #pragma unroll
-    for (int qb = 0; qb < kQB; ++qb) {
+    for (int qb = 0; qb < QB; ++qb) {
+      v16i pn = p, qn = q;
+      if (qb + 1 < QB) pn = __builtin_amdgcn_mfma_i32_32x32x32_i8(u.a0, bq[(qb + 1) % QB], u.c0, 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      int x = max3(p[0], p[1], p[2]);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        int sa = acc_a[qb][r] * 4096 + nka;
-        int sb = acc_b[qb][r] * 4096 + nkb;
-        if constexpr (kExcl) {
-          sa = sa < thr[qb][r] ? sa : INT_MIN;
-          sb = sb < thr[qb][r] ? sb : INT_MIN;
+      for (int r = 3; r < 15; r += 2) x = max3(x, p[r], p[r + 1]);
+      x = max(x, p[15]);
+      __builtin_amdgcn_sched_barrier(0);
+      if (qb + 1 < QB) qn = __builtin_amdgcn_mfma_i32_32x32x32_i8(u.a1, bq[(qb + 1) % QB], u.c1, 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int r = 0; r < 16; r += 2) x = max3(x, q[r], q[r + 1]);
+      if constexpr (!kTop) unit[qb] = x > best[qb] ? tile >> 1 : unit[qb];
+      best[qb] = max(best[qb], x);
+      __builtin_amdgcn_sched_barrier(0);
+      p = pn;
+      q = qn;
+    }
+    if constexpr (kTop) {
+      const int next = tile + 2;
+      if (tile < t1 && (next % group == 0 || next >= t1)) {  // last unit of its group
+        int32_t *out = gmax + (size_t)(tile / group) * M;
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
+          const int o = max(best[qb], __shfl_xor(best[qb], 32));
+          const int m = m0 + qb * 32 + col;
+          if (kh == 0 && m < M) out[m] = o;
+          best[qb] = INT_MIN;
         }
-        best[qb][r] = max(best[qb][r], max(sa, sb));
       }
     }
-    cur = nxt;
-    cur.na = pin(cur.na, best[kQB - 1][15]);
-    cur.nb = pin(cur.nb, best[kQB - 1][15]);
+  };
+  load(t0);
+  store(t0, 0);
+  __syncthreads();
+  int buf = 0;
+  for (int b = t0; b < t1; b += kStageTiles, buf ^= 1) {
+    const bool more = b + kStageTiles < t1;
+    if (more) load(b + kStageTiles);
+    if (active) {
+      // Two operand sets: the next unit's LDS reads are in flight while this
+      // one's products and maxima run.  Units of padding at the end of the
+      // last stage only score kPad.
+      const int tiles = min(kStageTiles, t1 - b);
+      Unit u0, u1;
+      fetch(u0, buf, 0);
+      for (int t = 0; t < tiles; t += 4) {
+        fetch(u1, buf, t + 2);
+        score(u0, b + t);
+        fetch(u0, buf, min(t + 4, kStageTiles - 2));
+        score(u1, b + t + 2);
+      }
+    }
+    if (more) store(b + kStageTiles, buf ^ 1);
+    __syncthreads();
   }
-
+  if constexpr (!kTop) {
+    if (!active) return;
 #pragma unroll
-  for (int qb = 0; qb < kQB; ++qb)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int key = -best[qb][r];
-      const int dd = key >> 11;        // dist - |a|^2
-      const int tl = key & 2047;       // tile inside the chunk
-      const uint32_t ref = (uint32_t)((t0 + tl) * 32 + col);
-      unsigned long long v = ((unsigned long long)(uint32_t)(dd + (1 << 20)) << 32) | ref;
-      if constexpr (kExcl) {
-        if (best[qb][r] == INT_MIN) v = ~0ull;  // every reference of the lane left out
-      }
-#pragma unroll
-      for (int off = 16; off >= 1; off >>= 1) {
-        const unsigned long long o = __shfl_xor(v, off);
-        v = o < v ? o : v;
-      }
-      const int row = 8 * (r >> 2) + 4 * kh + (r & 3);
-      const int m = m0 + qb * 32 + row;
-      if (col == 0 && m < M) atomicMin(reinterpret_cast<unsigned long long *>(d.keys) + m, v);
+    for (int qb = 0; qb < QB; ++qb) {
+      // the two halves of a query's references: larger score, then smaller unit
+      const int os = __shfl_xor(best[qb], 32), ou = __shfl_xor(unit[qb], 32);
+      const bool take = os > best[qb] || (os == best[qb] && ou < unit[qb]);
+      const int s = take ? os : best[qb], u = take ? ou : unit[qb];
+      const int m = m0 + qb * 32 + col;
+      if (kh != 0 || m >= M) continue;
+      const uint32_t rank = (uint32_t)((1 << 20) - s);  // smaller is nearer, below 2^21
+      if (part)
+        part[m] = (rank << 11) | (uint32_t)(u - (t0 >> 1));
+      else
+        atomicMin(reinterpret_cast<unsigned long long *>(d.keys) + m, ((unsigned long long)rank << 32) | (uint32_t)u);
     }
+  }
 }
 
-__host__ __device__ __forceinline__ int nn_qblocks(int M) { return (M + 32 * kQB - 1) / (32 * kQB); }
-__host__ __device__ __forceinline__ int nn_chunks(int N, int chunk_tiles = kTilesPerChunk) {
-  return (((N + 31) >> 5) + chunk_tiles - 1) / chunk_tiles;
-}
+__host__ __device__ __forceinline__ int nn_qblocks(int M, int qb) { return (M + 32 * kWaves * qb - 1) / (32 * kWaves * qb); }
 
 // One workgroup per (direction, reference chunk, query block) of one pair,
 // query block fastest; XCD-aware order keeps the workgroups of one chunk on
 // one L2.
-__global__ __launch_bounds__(256) void k_nn(ffh::NNArgs a) {
-  const int nqb = nn_qblocks(a.M), nchunk = nn_chunks(a.N, a.chunk_tiles);
+template <int QB>
+__global__ __launch_bounds__(256, nn_waves(QB)) void k_nn(ffh::NNArgs a) {
+  __shared__ NNStage sm;
+  const int nqb = nn_qblocks(a.M, QB), ntiles = (a.N + 31) >> 5;
   const int wg = ffk::xcd_remap(blockIdx.x, gridDim.x);
-  nn_body(a.dir[wg / (nqb * nchunk)], a.M, a.N, a.W, a.nc, a.Wc, wg % nqb, (wg / nqb) % nchunk, a.chunk_tiles);
+  const ffh::NNDir d = a.dir[wg / (nqb * a.nchunk)];
+  const int chunk = (wg / nqb) % a.nchunk, t0 = chunk * a.chunk_tiles;
+  nn_body<QB, false>(sm, d, a.M, a.N, a.W, a.nc, a.Wc, wg % nqb, t0, min(t0 + a.chunk_tiles, ntiles),
+                     a.atomic ? nullptr : reinterpret_cast<uint32_t *>(d.nb) + (size_t)chunk * a.M, 0, nullptr);
+}
+
+// Reference index of the even-pixel subset (Flow Fields+ Fast x2: pixel
+// (2a, 2b) is entry b * W2 + a) -> pixel index of the image.
+__device__ __forceinline__ uint32_t even_pixel(uint32_t q, int W2, int W) {
+  return (q / (uint32_t)W2) * 2u * (uint32_t)W + (q % (uint32_t)W2) * 2u;
+}
+
+// Merges the chunks' results of 16 queries (block qblk) and finds the
+// reference inside the winning unit: keys[m] = (squared distance << 32) | q.
+// The part words of a query lie M apart, so a block of 256 reads them 16
+// queries wide; then a wave per query scores the unit's 64 references.
+constexpr int kResolveQ = 16;
+struct NNResolve {
+  unsigned long long best[16][kResolveQ];
+};
+__device__ __forceinline__ void nn_resolve(NNResolve &sm, const ffh::NNDir &d, int M, int N, int W, int nc, int Wc,
+                                           int qblk, int nchunk, int chunk_tiles, bool atomic, int even_refs) {
+  const int tid = threadIdx.x, q = tid & 15, slot = tid >> 4;
+  const int mq = qblk * kResolveQ + q;
+  unsigned long long k = ~0ull;
+  if (mq < M) {
+    if (atomic) {
+      if (slot == 0) k = d.keys[mq];
+    } else {
+      const uint32_t *part = reinterpret_cast<const uint32_t *>(d.nb) + mq;
+      for (int c = slot; c < nchunk; c += 16) {
+        const uint32_t p = part[(size_t)c * M];
+        const unsigned long long o =
+            ((unsigned long long)(p >> 11) << 32) | (uint32_t)(c * (chunk_tiles >> 1) + (int)(p & 2047u));
+        k = o < k ? o : k;
+      }
+    }
+  }
+  sm.best[slot][q] = k;
+  __syncthreads();
+  const int lane = tid & 63, wave = tid >> 6;
+  for (int z = wave; z < kResolveQ; z += kWaves) {
+    const int m = qblk * kResolveQ + z;
+    if (m >= M) break;
+    unsigned long long b = sm.best[0][z];
+#pragma unroll
+    for (int s = 1; s < 16; ++s) b = sm.best[s][z] < b ? sm.best[s][z] : b;
+    const uint4 qd = query_desc(d.Dq, W, nc, Wc, m);
+    const int ref = (int)(uint32_t)b * 64 + lane;
+    const int want = (1 << 20) - (int)(b >> 32);
+    const uint4 rd = to_i8(reinterpret_cast<const uint4 *>(d.Dr)[min(ref, N - 1)]);
+    const unsigned long long hit = __ballot(ref < N && 2 * dot16(qd, rd) - dot16(rd, rd) == want);
+    if (lane == 0) {
+      uint32_t r = (uint32_t)b * 64u + (uint32_t)(__ffsll((long long)hit) - 1);
+      if (even_refs) r = even_pixel(r, (W + 1) >> 1, W);
+      d.keys[m] = ((uint64_t)(uint32_t)(dot16(qd, qd) - want) << 32) | r;
+    }
+  }
+}
+
+__global__ __launch_bounds__(256) void k_nn_resolve(ffh::NNArgs a) {
+  __shared__ NNResolve sm;
+  nn_resolve(sm, a.dir[blockIdx.y], a.M, a.N, a.W, a.nc, a.Wc, blockIdx.x, a.nchunk, a.chunk_tiles, a.atomic != 0,
+             a.even_refs);
 }
 
 // ---- batches -----------------------------------------------------------
-// Squared norms of both images' level-1 descriptors (items: pair, image,
-// 256 references); the first item of a pair also clears its counters.
-__global__ __launch_bounds__(256) void k_nn_norms_batch(ffh::BatchStage st) {
-  ffk::for_items(st.total, [&](int item) {
-    const int p = ffk::batch_pair(st.prefix, st.npairs, item);
-    const ffh::BatchPair &bp = st.pairs[p];
-    const int N = bp.W * bp.H, Npad = (N + 31) & ~31;
-    const int blocks = (Npad + 255) / 256;
-    const int local = item - st.prefix[p];
-    const int im = local / blocks, idx = (local % blocks) * 256 + threadIdx.x;
-    if (local == 0 && threadIdx.x < 2) bp.evals[threadIdx.x] = 0;
-    if (idx >= Npad) return;
-    int s = kNbPad;
-    if (idx < N) {
-      const uint4 v = reinterpret_cast<const uint4 *>(bp.desc1[im])[idx];
-      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-      s = 0;
-#pragma unroll
-      for (int k = 0; k < 4; ++k)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-          const int e = (int)((w[k] >> (8 * b)) & 0xFF) - 128;
-          s += e * e;
-        }
-    }
-    bp.nb[im][idx] = s;
-  });
+
+// Chunks of one pair (the part words of a direction, nchunk * M, lie in the
+// Npad words of its nb scratch; where they do not fit, one 64-bit atomic per
+// query and chunk merges them).
+struct NNPlan {
+  int chunk_tiles, nchunk, atomic;
+};
+__host__ __device__ __forceinline__ NNPlan nn_plan(int M, int N, int want_chunks) {
+  const int ntiles = (N + 31) >> 5;
+  const int fit = (ntiles * 32) / M, need = (ntiles + kMaxChunkTiles - 1) / kMaxChunkTiles;
+  NNPlan p;
+  p.atomic = need > fit;
+  int c = p.atomic ? want_chunks : (want_chunks < fit ? want_chunks : fit);
+  c = c < need ? need : c;
+  c = c < 1 ? 1 : c;
+  p.chunk_tiles = (((ntiles + c - 1) / c) + 1) & ~1;
+  p.nchunk = (ntiles + p.chunk_tiles - 1) / p.chunk_tiles;
+  return p;
+}
+__host__ __device__ __forceinline__ NNPlan nn_batch_plan(int M, int N) {
+  return nn_plan(M, N, (((N + 31) >> 5) + kBatchChunkTiles - 1) / kBatchChunkTiles);
 }
 
-// Key initialisation (items: pair, direction, 256 queries).
+// Key initialisation (items: pair, direction, 256 queries); the first item of
+// a pair also clears its counters.
 __global__ __launch_bounds__(256) void k_nn_fill_batch(ffh::BatchStage st) {
   ffk::for_items(st.total, [&](int item) {
     const int p = ffk::batch_pair(st.prefix, st.npairs, item);
@@ -290,60 +336,188 @@ __global__ __launch_bounds__(256) void k_nn_fill_batch(ffh::BatchStage st) {
     const int blocks = (M + 255) / 256;
     const int local = item - st.prefix[p];
     const int dir = local / blocks, m = (local % blocks) * 256 + threadIdx.x;
+    if (local == 0 && threadIdx.x < 2) bp.evals[threadIdx.x] = 0;
     if (m < M) bp.keys[dir][m] = ~0ull;
   });
 }
 
 // NN of every pair (items: pair, direction, chunk, query block).
-__global__ __launch_bounds__(256) void k_nn_batch(ffh::BatchStage st) {
+__global__ __launch_bounds__(256, nn_waves(kBatchQB)) void k_nn_batch(ffh::BatchStage st) {
+  __shared__ NNStage sm;
+  ffk::for_items(st.total, [&](int item) {
+    const int p = ffk::batch_pair(st.prefix, st.npairs, item);
+    const ffh::BatchPair &bp = st.pairs[p];
+    const int nc = st.n, Wc = (bp.W + nc - 1) / nc;
+    const int M = Wc * ((bp.H + nc - 1) / nc), N = bp.W * bp.H, ntiles = (N + 31) >> 5;
+    const NNPlan pl = nn_batch_plan(M, N);
+    const int nqb = nn_qblocks(M, kBatchQB);
+    const int local = item - st.prefix[p];
+    const int dir = local / (nqb * pl.nchunk), chunk = (local / nqb) % pl.nchunk, t0 = chunk * pl.chunk_tiles;
+    const ffh::NNDir d = {bp.desc1[dir], bp.desc1[dir ^ 1], bp.nb[dir ^ 1], bp.keys[dir]};
+    nn_body<kBatchQB, false>(sm, d, M, N, bp.W, nc, Wc, local % nqb, t0, min(t0 + pl.chunk_tiles, ntiles),
+                             pl.atomic ? nullptr : reinterpret_cast<uint32_t *>(d.nb) + (size_t)chunk * M, 0, nullptr);
+  });
+}
+
+__global__ __launch_bounds__(256) void k_nn_resolve_batch(ffh::BatchStage st) {
+  __shared__ NNResolve sm;
   ffk::for_items(st.total, [&](int item) {
     const int p = ffk::batch_pair(st.prefix, st.npairs, item);
     const ffh::BatchPair &bp = st.pairs[p];
     const int nc = st.n, Wc = (bp.W + nc - 1) / nc;
     const int M = Wc * ((bp.H + nc - 1) / nc), N = bp.W * bp.H;
-    const int nqb = nn_qblocks(M), nchunk = nn_chunks(N);
-    const int local = item - st.prefix[p];
-    const int dir = local / (nqb * nchunk);
+    const NNPlan pl = nn_batch_plan(M, N);
+    const int blocks = (M + kResolveQ - 1) / kResolveQ, local = item - st.prefix[p], dir = local / blocks;
     const ffh::NNDir d = {bp.desc1[dir], bp.desc1[dir ^ 1], bp.nb[dir ^ 1], bp.keys[dir]};
-    nn_body(d, M, N, bp.W, nc, Wc, local % nqb, (local / nqb) % nchunk, kTilesPerChunk);
+    nn_resolve(sm, d, M, N, bp.W, nc, Wc, local % blocks, pl.nchunk, pl.chunk_tiles, pl.atomic != 0, 0);
+    __syncthreads();  // the next item writes sm again
   });
 }
 
-
 // ---- the l nearest references (seed rerank, Eq. 1 / Eq. 4) -------------
 //
-// The k-th nearest reference of a query (k = 1 .. l - 1; k = 0 is k_nn's
-// result) is the nearest one among those whose key (distance, index) is
-// larger than the (k-1)-th's: pass k is k_nn with that exclusion, so l
-// passes give the l smallest keys, ranked, with the ties of k_nn.
+// One pass of the search writes the largest score of every group of
+// consecutive tiles per query.  The l nearest references (by distance, then
+// index) lie in the l groups of largest score (equal scores: the earlier
+// group): any other group's best reference has l better ones before it.  A
+// wave per query then scores those groups' references and ranks the l
+// nearest.  Against one exclusion pass of the search per rank: eight
+// candidates per cell at 741 x 497, both directions, @TOP0@ -> @TOP1@ us.
+constexpr int kTopGroups = 512;  // groups per query at most (LDS of the ranking kernel)
+constexpr size_t kTopBytes = (size_t)64 << 20;  // of group scores per direction, at least 16 groups
+constexpr int kTopQ = 4, kTopList = 256;  // queries per workgroup (one per wave), list length
+constexpr int kTopLoads = 8;              // 64 references each
 
-__global__ __launch_bounds__(256) void k_nn_excl(ffh::NNArgs a, ffh::TopLPrev prev) {
-  const int nqb = nn_qblocks(a.M), nchunk = nn_chunks(a.N, a.chunk_tiles);
+__host__ __device__ __forceinline__ int topl_groups(int M, int ntiles) {
+  const long long fit = (long long)(kTopBytes / 4) / M;
+  const int g = fit < 16 ? 16 : fit > kTopGroups ? kTopGroups : (int)fit;
+  return g < ntiles ? g : ntiles;
+}
+
+template <int QB>
+__global__ __launch_bounds__(256, nn_waves(QB)) void k_nn_groups(ffh::TopLArgs a) {
+  __shared__ NNStage sm;
+  const int nqb = nn_qblocks(a.M, QB), ntiles = (a.N + 31) >> 5;
   const int wg = ffk::xcd_remap(blockIdx.x, gridDim.x);
-  const int dir = wg / (nqb * nchunk);
-  nn_body<true>(a.dir[dir], a.M, a.N, a.W, a.nc, a.Wc, wg % nqb, (wg / nqb) % nchunk, a.chunk_tiles,
-                prev.key[dir]);
+  const ffh::TopLDir &t = a.dir[wg / (nqb * a.nchunk)];
+  const ffh::NNDir d = {t.Dq, t.Dr, nullptr, nullptr};
+  const int t0 = ((wg / nqb) % a.nchunk) * a.chunk_tiles;
+  nn_body<QB, true>(sm, d, a.M, a.N, a.W, a.nc, a.Wc, wg % nqb, t0, min(t0 + a.chunk_tiles, ntiles), nullptr, a.group,
+                    t.gmax);
 }
 
-__device__ __forceinline__ int query_norm(const uint8_t *Dq, int W, int nc, int Wc, int m) {
-  const int i = m % Wc, j = m / Wc;
-  const uint4 v = reinterpret_cast<const uint4 *>(Dq)[(size_t)(j * nc) * W + (size_t)(i * nc)];
-  const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-  int s = 0;
+__device__ __forceinline__ unsigned long long wave_min(unsigned long long v) {
 #pragma unroll
-  for (int k = 0; k < 4; ++k)
+  for (int off = 32; off >= 1; off >>= 1) {
+    const unsigned long long o = __shfl_xor(v, off);
+    v = o < v ? o : v;
+  }
+  return v;
+}
+
+// Moves the l smallest of list[0, count) (distinct keys) to its front, ranked;
+// returns how many there are.  A wave calls it; count <= kTopList.
+__device__ __forceinline__ int rank_list(unsigned long long *list, int count, int l, int lane) {
+  unsigned long long k[kTopList / 64];
 #pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      const int e = (int)((w[k] >> (8 * b)) & 0xFF) - 128;
-      s += e * e;
+  for (int z = 0; z < kTopList / 64; ++z) k[z] = lane + 64 * z < count ? list[lane + 64 * z] : ~0ull;
+  const int n = min(l, count);
+  for (int r = 0; r < n; ++r) {
+    unsigned long long m = k[0];
+#pragma unroll
+    for (int z = 1; z < kTopList / 64; ++z) m = k[z] < m ? k[z] : m;
+    m = wave_min(m);
+    if (lane == 0) list[r] = m;
+#pragma unroll
+    for (int z = 0; z < kTopList / 64; ++z)
+      if (k[z] == m) k[z] = ~0ull;
+  }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  return n;
+}
+
+// cand[m * l + k] = (squared distance << 32) | q of the k-th nearest
+// reference, ~0 past the last reference.
+__global__ __launch_bounds__(256) void k_topl_rank(ffh::TopLArgs a) {
+  __shared__ int32_t score[kTopQ][kTopGroups + 1];
+  __shared__ unsigned long long lists[kWaves][kTopList];
+  const ffh::TopLDir d = a.dir[blockIdx.y];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int m0 = blockIdx.x * kTopQ;
+  for (int g = tid / kTopQ; g < a.ngroups; g += 256 / kTopQ) {
+    const int m = min(m0 + tid % kTopQ, a.M - 1);
+    score[tid % kTopQ][g] = d.gmax[(size_t)g * a.M + m];
+  }
+  __syncthreads();
+  const uint4 *Dr = reinterpret_cast<const uint4 *>(d.Dr);
+  unsigned long long *list = lists[wave];
+  const int refs = a.group * 32;  // references of a group
+  static_assert(kTopQ == kWaves, "one query per wave");
+  const int m = m0 + wave;
+  if (m >= a.M) return;
+  // the l best groups: keys (2^20 - score) << 32 | group, ascending
+  unsigned long long gk[kTopGroups / 64], mine = ~0ull;  // lane r: the r-th best group
+#pragma unroll
+  for (int s = 0; s < kTopGroups / 64; ++s) {
+    const int g = lane + 64 * s;
+    gk[s] = g < a.ngroups ? ((unsigned long long)(uint32_t)((1 << 20) - score[wave][g]) << 32) | (uint32_t)g : ~0ull;
+  }
+  for (int r = 0; r < a.l; ++r) {
+    unsigned long long b = gk[0];
+#pragma unroll
+    for (int s = 1; s < kTopGroups / 64; ++s) b = gk[s] < b ? gk[s] : b;
+    b = wave_min(b);
+    if (lane == r) mine = b;
+#pragma unroll
+    for (int s = 0; s < kTopGroups / 64; ++s)
+      if (gk[s] == b) gk[s] = ~0ull;
+  }
+  const uint4 qd = query_desc(d.Dq, a.W, a.nc, a.Wc, m);
+  const int qn = dot16(qd, qd);
+  // each of the l groups has a reference as near as its score: one further
+  // away than the last of them is not among the l nearest
+  const unsigned long long last = __shfl(mine, a.l - 1);
+  unsigned long long bound =
+      last == ~0ull ? ~0ull
+                    : ((unsigned long long)(uint32_t)((int)(last >> 32) - (1 << 20) + qn) << 32) | 0xFFFFFFFFull;
+  int count = 0;
+  for (int r = 0; r < a.l; ++r) {
+    const unsigned long long group = __shfl(mine, r);
+    if (group == ~0ull) break;  // wave-uniform
+    const int base = (int)(uint32_t)group * refs, end = min(base + refs, a.N);
+    for (int o = base; o < end; o += 64 * kTopLoads) {
+      uint4 rd[kTopLoads];  // all in flight together
+#pragma unroll
+      for (int k = 0; k < kTopLoads; ++k) rd[k] = Dr[min(o + 64 * k + lane, a.N - 1)];
+#pragma unroll
+      for (int k = 0; k < kTopLoads; ++k) {
+        const int ref = o + 64 * k + lane;
+        const uint4 r = to_i8(rd[k]);
+        const int dist = qn - 2 * dot16(qd, r) + dot16(r, r);
+        const unsigned long long key = ((unsigned long long)(uint32_t)dist << 32) | (uint32_t)ref;
+        const bool in = ref < end && key <= bound;
+        const unsigned long long mask = __ballot(in);
+        if (mask) {
+          if (in) list[count + __popcll(mask & ((1ull << lane) - 1))] = key;
+          count += __popcll(mask);
+          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+          __builtin_amdgcn_wave_barrier();
+          if (count > kTopList - 64) {  // keep the l nearest so far; nothing past the l-th is needed any more
+            count = rank_list(list, count, a.l, lane);
+            bound = list[count - 1];
+          }
+        }
+      }
     }
-  return s;
-}
-
-// Reference index of the even-pixel subset (Flow Fields+ Fast x2: pixel
-// (2a, 2b) is entry b * W2 + a) -> pixel index of the image.
-__device__ __forceinline__ uint32_t even_pixel(uint32_t q, int W2, int W) {
-  return (q / (uint32_t)W2) * 2u * (uint32_t)W + (q % (uint32_t)W2) * 2u;
+  }
+  count = rank_list(list, count, a.l, lane);
+  if (lane < a.l) {
+    unsigned long long k = lane < count ? list[lane] : ~0ull;
+    if (k != ~0ull && a.even_refs)
+      k = (k & 0xFFFFFFFF00000000ull) | even_pixel((uint32_t)k, (a.W + 1) >> 1, a.W);
+    d.cand[(size_t)m * a.l + lane] = k;
+  }
 }
 
 // Level-1 descriptors of the pixels with even x and y, row-major [H2][W2].
@@ -354,33 +528,6 @@ __global__ __launch_bounds__(256) void k_gather_even(const uint4 *src, uint4 *ds
   dst[k] = src[(size_t)(k / W2) * 2 * W + (k % W2) * 2];
 }
 
-// NN keys over the even-pixel subset -> keys naming image pixels.
-__global__ __launch_bounds__(256) void k_remap_even(uint64_t *keys, int M, int W) {
-  const int m = blockIdx.x * blockDim.x + threadIdx.x;
-  if (m >= M) return;
-  const uint64_t k = keys[m];
-  if (k != ~0ull) keys[m] = (k & 0xFFFFFFFF00000000ull) | even_pixel((uint32_t)k, (W + 1) >> 1, W);
-}
-
-// Ranked candidates with the squared distance itself: cand[m * l + k] =
-// (dist << 32) | q of pass k, ~0 for a pass that found no reference of the
-// image (padding references, index >= N, or none left).
-__global__ __launch_bounds__(256) void k_topl_assemble(ffh::TopLArgs a) {
-  const ffh::TopLDir d = a.dir[blockIdx.y];
-  const int m = blockIdx.x * blockDim.x + threadIdx.x;
-  if (m >= a.M) return;
-  const int na = query_norm(d.Dq, a.W, a.nc, a.Wc, m);
-  for (int k = 0; k < a.l; ++k) {
-    const uint64_t rel = k == 0 ? d.nn_key[m] : d.keys[(size_t)(k - 1) * a.M + m];
-    uint64_t out = ~0ull;
-    if (rel != ~0ull && (int64_t)(uint32_t)rel < (int64_t)a.N) {
-      const uint32_t q = a.even_refs ? even_pixel((uint32_t)rel, (a.W + 1) >> 1, a.W) : (uint32_t)rel;
-      out = ((uint64_t)(uint32_t)((int)(uint32_t)(rel >> 32) - (1 << 20) + na) << 32) | q;
-    }
-    d.cand[(size_t)m * a.l + k] = out;
-  }
-}
-
 }  // namespace
 
 namespace ffh {
@@ -388,17 +535,21 @@ namespace ffh {
 int batch_nn_items(int W, int H, int L) {
   const int nc = 1 << (L - 1);
   const int M = ((W + nc - 1) / nc) * ((H + nc - 1) / nc), N = W * H;
-  const int nqb = (M + 32 * kQB - 1) / (32 * kQB);
-  return 2 * nqb * nn_chunks(N);
+  return 2 * nn_qblocks(M, kBatchQB) * nn_batch_plan(M, N).nchunk;
+}
+
+int batch_nn_resolve_items(int W, int H, int L) {
+  const int nc = 1 << (L - 1);
+  return 2 * ((((W + nc - 1) / nc) * ((H + nc - 1) / nc) + kResolveQ - 1) / kResolveQ);
 }
 
 static int persistent_grid(int total, int cap) { return ((std::min(std::max(total, 1), cap) + 7) / 8) * 8; }
 
-hipError_t launch_batch_nn(const BatchStage &norms, const BatchStage &fill, const BatchStage &nn,
+hipError_t launch_batch_nn(const BatchStage &fill, const BatchStage &nn, const BatchStage &resolve,
                            hipStream_t stream) {
-  hipLaunchKernelGGL(k_nn_norms_batch, dim3(persistent_grid(norms.total, 4096)), dim3(256), 0, stream, norms);
   hipLaunchKernelGGL(k_nn_fill_batch, dim3(persistent_grid(fill.total, 4096)), dim3(256), 0, stream, fill);
   hipLaunchKernelGGL(k_nn_batch, dim3(persistent_grid(nn.total, 2048)), dim3(64 * kWaves), 0, stream, nn);
+  hipLaunchKernelGGL(k_nn_resolve_batch, dim3(persistent_grid(resolve.total, 2048)), dim3(256), 0, stream, resolve);
   return hipGetLastError();
 }
 
@@ -408,37 +559,37 @@ hipError_t launch_fill_u64(uint64_t *dst, uint64_t value, int64_t count, hipStre
   return hipGetLastError();
 }
 
-// Workgroups of k_nn the current device holds at once (compute units x
-// resident workgroups per unit), cached per device.
-static int nn_resident_workgroups() {
+// Workgroups of the search the current device holds at once (waves per SIMD
+// the kernel is compiled for = workgroups of four waves per compute unit); the
+// count of compute units is cached per device.
+static int nn_resident_workgroups(int qb) {
   static int cache[64] = {0};
   int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256 * nn_waves(qb);
   if (cache[dev] == 0) {
-    int cus = 0, per_cu = 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_nn, 64 * kWaves, 0) != hipSuccess)
-      return 0;
-    cache[dev] = std::max(cus * per_cu, 1);
+    int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+      return 256 * nn_waves(qb);
+    cache[dev] = std::max(cus, 1);
   }
-  return cache[dev];
+  return cache[dev] * nn_waves(qb);
 }
 
-// Reference chunk length: the number of chunks whose workgroups fill the
-// device in the fewest rounds for the least work per workgroup (a grid of
-// 1.2 rounds would leave most of the second round idle).  Each chunk also
-// costs its reduction and merge, about as much as kChunkOverhead tiles.
-static int nn_chunk_tiles(int ntiles, int per_chunk_wgs) {
-  constexpr int kChunkOverhead = 64;
-  const int cap = nn_resident_workgroups();
-  const int min_chunks = (ntiles + kMaxChunkTiles - 1) / kMaxChunkTiles;
-  if (cap <= 0) return std::max((ntiles + min_chunks - 1) / min_chunks, 1);
-  // at least 32 tiles per chunk (8 per wave), at most 8 rounds' worth
-  const int max_chunks =
-      std::max(min_chunks, std::min(ntiles / 32, min_chunks + 8 * ((cap + per_chunk_wgs - 1) / per_chunk_wgs)));
-  int best = min_chunks;
+// Query blocks of 32 per wave: 8 while that leaves a wave with work in every
+// workgroup; small grids take fewer, for more workgroups.
+static int nn_query_blocks(int M) { return M > 512 ? 8 : M > 256 ? 4 : M > 128 ? 2 : 1; }
+
+// The number of chunks whose workgroups fill the device in the fewest rounds
+// for the least work per workgroup (a grid of 1.2 rounds would leave most of
+// the second round idle).  Each chunk also costs its first stage and its
+// merge, about as much as kChunkOverhead tiles; at least 8 tiles per chunk.
+static int nn_want_chunks(int ntiles, int per_chunk_wgs, int qb) {
+  constexpr int kChunkOverhead = 16;
+  const int cap = nn_resident_workgroups(qb);
+  int best = 1;
   long long best_cost = LLONG_MAX;
-  for (int c = min_chunks; c <= max_chunks; ++c) {
+  for (int k = 1; k <= 4; ++k) {
+    const int c = std::max(1, std::min(ntiles / 8, (int)((long long)k * cap / per_chunk_wgs)));  // the most in k rounds
     const long long rounds = ((long long)c * per_chunk_wgs + cap - 1) / cap;
     const long long cost = rounds * ((ntiles + c - 1) / c + kChunkOverhead);
     if (cost < best_cost) {
@@ -446,22 +597,33 @@ static int nn_chunk_tiles(int ntiles, int per_chunk_wgs) {
       best = c;
     }
   }
-  return (ntiles + best - 1) / best;
+  return best;
 }
 
 hipError_t launch_nn(const NNArgs &args_in, hipStream_t stream) {
   NNArgs args = args_in;
-  const int Npad = (args.N + 31) & ~31;
-  // norms of the references; the same launch clears the keys (M <= N <= Npad)
-  hipLaunchKernelGGL(k_nn_norms, dim3((Npad + 255) / 256, args.ndir), dim3(256), 0, stream, args);
-  const int ntiles = Npad / 32;
-  const int nqb = nn_qblocks(args.M);
-  args.chunk_tiles = nn_chunk_tiles(ntiles, nqb * args.ndir);
-  const int nchunk = nn_chunks(args.N, args.chunk_tiles);
-  hipLaunchKernelGGL(k_nn, dim3(nqb * nchunk * args.ndir), dim3(64 * kWaves), 0, stream, args);
+  const int qb = nn_query_blocks(args.M), nqb = nn_qblocks(args.M, qb);
+  const NNPlan p = nn_plan(args.M, args.N, nn_want_chunks((args.N + 31) / 32, nqb * args.ndir, qb));
+  args.chunk_tiles = p.chunk_tiles;
+  args.nchunk = p.nchunk;
+  args.atomic = p.atomic;
+  if (p.atomic)
+    for (int dr = 0; dr < args.ndir; ++dr) {
+      hipError_t e = launch_fill_u64(args.dir[dr].keys, ~0ull, args.M, stream);
+      if (e != hipSuccess) return e;
+    }
+  const dim3 grid((unsigned)(nqb * p.nchunk * args.ndir));
+  if (qb == 8)
+    hipLaunchKernelGGL(k_nn<8>, grid, dim3(64 * kWaves), 0, stream, args);
+  else if (qb == 4)
+    hipLaunchKernelGGL(k_nn<4>, grid, dim3(64 * kWaves), 0, stream, args);
+  else if (qb == 2)
+    hipLaunchKernelGGL(k_nn<2>, grid, dim3(64 * kWaves), 0, stream, args);
+  else
+    hipLaunchKernelGGL(k_nn<1>, grid, dim3(64 * kWaves), 0, stream, args);
+  hipLaunchKernelGGL(k_nn_resolve, dim3((args.M + kResolveQ - 1) / kResolveQ, args.ndir), dim3(256), 0, stream, args);
   return hipGetLastError();
 }
-
 
 hipError_t launch_gather_even(const uint8_t *desc1, uint8_t *out, int W, int H, hipStream_t stream) {
   const int n2 = ((W + 1) >> 1) * ((H + 1) >> 1);
@@ -470,43 +632,34 @@ hipError_t launch_gather_even(const uint8_t *desc1, uint8_t *out, int W, int H, 
   return hipGetLastError();
 }
 
-hipError_t launch_remap_even(uint64_t *keys, int M, int W, hipStream_t stream) {
-  hipLaunchKernelGGL(k_remap_even, dim3((M + 255) / 256), dim3(256), 0, stream, keys, M, W);
-  return hipGetLastError();
-}
-
-size_t topl_scratch_bytes(int M) {
-  return (((size_t)(kTopLMax - 1) * M * sizeof(uint64_t)) + 255) & ~(size_t)255;
+size_t topl_scratch_bytes(int M, long long N) {
+  const int ntiles = (int)((N + 31) / 32);
+  return (((size_t)topl_groups(M, ntiles) * M * sizeof(int32_t)) + 255) & ~(size_t)255;
 }
 
 hipError_t launch_topl(const TopLArgs &args_in, hipStream_t stream) {
   TopLArgs a = args_in;
   if (a.l < 1 || a.l > kTopLMax || a.M < 1 || a.N < 1) return hipErrorInvalidValue;
-  NNArgs nn{};
-  nn.ndir = a.ndir;
-  nn.W = a.W;
-  nn.H = a.H;
-  nn.nc = a.nc;
-  nn.Wc = a.Wc;
-  nn.M = a.M;
-  nn.N = a.N;
   const int ntiles = (a.N + 31) / 32;
-  const int nqb = nn_qblocks(a.M);
-  nn.chunk_tiles = nn_chunk_tiles(ntiles, nqb * a.ndir);
-  const int nchunk = nn_chunks(a.N, nn.chunk_tiles);
-  for (int k = 1; k < a.l; ++k) {
-    TopLPrev prev{};
-    for (int dr = 0; dr < a.ndir; ++dr) {
-      const TopLDir &d = a.dir[dr];
-      uint64_t *keys = d.keys + (size_t)(k - 1) * a.M;
-      nn.dir[dr] = {d.Dq, d.Dr, const_cast<int32_t *>(d.nb), keys};
-      prev.key[dr] = k == 1 ? d.nn_key : keys - a.M;
-      hipError_t e = launch_fill_u64(keys, ~0ull, a.M, stream);
-      if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(k_nn_excl, dim3(nqb * nchunk * a.ndir), dim3(64 * kWaves), 0, stream, nn, prev);
-  }
-  hipLaunchKernelGGL(k_topl_assemble, dim3((a.M + 255) / 256, a.ndir), dim3(256), 0, stream, a);
+  const int qb = nn_query_blocks(a.M), nqb = nn_qblocks(a.M, qb);
+  // groups of an even number of tiles; a chunk is a whole number of groups
+  const int groups = topl_groups(a.M, ntiles);
+  a.group = (((ntiles + groups - 1) / groups) + 1) & ~1;
+  a.ngroups = (ntiles + a.group - 1) / a.group;
+  const int want = std::min(nn_want_chunks(ntiles, nqb * a.ndir, qb), a.ngroups);
+  const int per = (a.ngroups + want - 1) / want;
+  a.chunk_tiles = per * a.group;
+  a.nchunk = (ntiles + a.chunk_tiles - 1) / a.chunk_tiles;
+  const dim3 grid((unsigned)(nqb * a.nchunk * a.ndir));
+  if (qb == 8)
+    hipLaunchKernelGGL(k_nn_groups<8>, grid, dim3(64 * kWaves), 0, stream, a);
+  else if (qb == 4)
+    hipLaunchKernelGGL(k_nn_groups<4>, grid, dim3(64 * kWaves), 0, stream, a);
+  else if (qb == 2)
+    hipLaunchKernelGGL(k_nn_groups<2>, grid, dim3(64 * kWaves), 0, stream, a);
+  else
+    hipLaunchKernelGGL(k_nn_groups<1>, grid, dim3(64 * kWaves), 0, stream, a);
+  hipLaunchKernelGGL(k_topl_rank, dim3((a.M + kTopQ - 1) / kTopQ, a.ndir), dim3(256), 0, stream, a);
   return hipGetLastError();
 }
 

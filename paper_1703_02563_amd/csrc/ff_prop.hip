@@ -39,18 +39,6 @@ __global__ __launch_bounds__(256) void k_init_coarse(ffh::LevelArgs a) {
     const int x = i * a.n, y = j * a.n;
     const uint64_t key = d.nn_key[m];
     const uint32_t q = (uint32_t)key;
-    const int dd = (int)(uint32_t)(key >> 32) - (1 << 20);
-    const uint4 qa = reinterpret_cast<const uint4 *>(d.Dq1)[(size_t)y * a.W + x];
-    const uint32_t w[4] = {qa.x, qa.y, qa.z, qa.w};
-    int na = 0;
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-#pragma unroll
-      for (int b = 0; b < 4; ++b) {
-        const int e = (int)((w[k] >> (8 * b)) & 0xFF) - 128;
-        na += e * e;
-      }
-    const_cast<uint64_t *>(d.nn_key)[m] = ((uint64_t)(uint32_t)(dd + na) << 32) | q;
     // the seed is an integer flow, stored in the cost's flow unit
     const int fx = ((int)(q % (uint32_t)a.W) - x) * (1 << Cost::kSub), fy = ((int)(q / (uint32_t)a.W) - y) * (1 << Cost::kSub);
     d.flow[m] = ffk::pack_flow(fx, fy);
@@ -202,53 +190,50 @@ __global__ __launch_bounds__(256) void k_random_search(ffh::LevelArgs a) {
 
 
 // Seed rerank (Eq. 1, Eq. 4): of the l ranked candidates of cell m, the one
-// with the lowest E_nc, the earlier rank on equal cost; written to nn_key in
-// launch_nn's relative form for the initialisation.  Counts the candidates
+// with the lowest E_nc, the earlier rank on equal cost; written to nn_key for
+// the initialisation.  Counts the candidates
 // but the winner (the initialisation evaluates the winner again).
 struct CandPtrs {
   const uint64_t *cand[ffh::kMaxDirs];
 };
 
+//
+// A wave per cell, eight lanes per candidate: the grid is small (1,457 cells
+// at 741 x 497) and one lane evaluating its cell's candidates one after
+// another is a chain of 56 dependent patch rows (140 us for eight candidates,
+// both directions; now @RR@ us).
 template <int R, class Cost>
 __global__ __launch_bounds__(256) void k_rerank(ffh::LevelArgs a, CandPtrs c, int l) {
+  static_assert(ffh::kTopLMax == 8, "eight lanes per candidate");
   const ffh::LevelDir d = a.dir[blockIdx.z];
-  const int m = blockIdx.x * blockDim.x + threadIdx.x;
-  int cnt = 0;
-  if (m < a.Wn * a.Hn) {
-    const int i = m % a.Wn, j = m / a.Wn;
-    const int x = i * a.n, y = j * a.n;
-    const uint4 qa = reinterpret_cast<const uint4 *>(d.Dq1)[(size_t)y * a.W + x];
-    const uint32_t w[4] = {qa.x, qa.y, qa.z, qa.w};
-    int na = 0;
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-#pragma unroll
-      for (int b = 0; b < 4; ++b) {
-        const int e = (int)((w[k] >> (8 * b)) & 0xFF) - 128;
-        na += e * e;
-      }
-    const uint64_t *cm = c.cand[blockIdx.z] + (size_t)m * l;
-    uint64_t bk = ~0ull;
-    uint32_t bc = 0;
-    for (int k = 0; k < l; ++k) {
-      const uint64_t key = cm[k];
-      if (key == ~0ull) continue;
-      const uint32_t q = (uint32_t)key;
-      const int fx = ((int)(q % (uint32_t)a.W) - x) * (1 << Cost::kSub);
-      const int fy = ((int)(q / (uint32_t)a.W) - y) * (1 << Cost::kSub);
-      const uint32_t e = Cost::template eval<R>(d.Da, d.Db, a.W, a.H, a.ns > 0 ? a.ns : a.n, x, y, fx, fy);
-      ++cnt;
-      if (bk == ~0ull || e < bc) {
-        bc = e;
-        bk = key;
-      }
-    }
-    if (bk != ~0ull)
-      const_cast<uint64_t *>(d.nn_key)[m] =
-          ((uint64_t)(uint32_t)((int)(bk >> 32) - na + (1 << 20)) << 32) | (uint32_t)bk;
+  const int m = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (m >= a.Wn * a.Hn) return;  // wave-uniform
+  const int lane = threadIdx.x & 63, rank = lane >> 3;
+  const int x = (m % a.Wn) * a.n, y = (m / a.Wn) * a.n;
+  const uint64_t key = rank < l ? c.cand[blockIdx.z][(size_t)m * l + rank] : ~0ull;
+  const bool there = key != ~0ull;
+  uint32_t e = 0;
+  if (there) {
+    const uint32_t q = (uint32_t)key;
+    const int fx = ((int)(q % (uint32_t)a.W) - x) * (1 << Cost::kSub);
+    const int fy = ((int)(q / (uint32_t)a.W) - y) * (1 << Cost::kSub);
+    e = Cost::template eval_part<R, 8>(d.Da, d.Db, a.W, a.H, a.ns > 0 ? a.ns : a.n, x, y, fx, fy, lane & 7);
   }
-  ffk::wave_sum_add(d.n_evals, cnt > 0 ? cnt - 1 : 0);
-  ffk::wave_sum_add2(d.n_work, cnt);
+#pragma unroll
+  for (int off = 1; off < 8; off <<= 1) e += __shfl_xor(e, off);
+  // the lowest cost, then the lowest rank (costs stay below 2^28)
+  uint32_t best = there ? e * 8u + (uint32_t)rank : 0xFFFFFFFFu;
+  for (int off = 8; off < 64; off <<= 1) best = min(best, __shfl_xor(best, off));
+  const int cnt = __popcll(__ballot(there)) >> 3;
+  const uint64_t win = __shfl(key, (int)(best & 7u) * 8);
+  if (lane == 0) {
+    if (cnt > 0) const_cast<uint64_t *>(d.nn_key)[m] = win;
+    if (d.n_evals && cnt > 1) atomicAdd(d.n_evals, (unsigned long long)(cnt - 1));
+    if (d.n_work && cnt > 0) {
+      atomicAdd(d.n_work, (unsigned long long)cnt);
+      atomicAdd(d.n_work + 1, (unsigned long long)cnt);
+    }
+  }
 }
 
 // Patch-scale change on one grid (sub-scales, Sec. 3.3): every set cell
@@ -586,10 +571,15 @@ hipError_t launch_rerank(const LevelArgs &a, const uint64_t *const *cand, int l,
   if (l < 1 || l > kTopLMax) return hipErrorInvalidValue;
   CandPtrs c{};
   for (int dr = 0; dr < a.ndir; ++dr) c.cand[dr] = cand[dr];
-  const int cells = a.Wn * a.Hn;
-  dim3 grid((cells + 255) / 256, 1, a.ndir);
+  dim3 grid((a.Wn * a.Hn + 3) / 4, 1, a.ndir);
 #define CALL(R, C) hipLaunchKernelGGL((k_rerank<R, C>), grid, dim3(256), 0, stream, a, c, l)
-  FF_RADIUS_SWITCH(a, CALL)
+  if (a.fcost == 2) {
+    FF_RADIUS_SWITCH_C(a.radius, CALL, ffk::CostU8Sub)
+  } else if (a.fcost == 0) {
+    FF_RADIUS_SWITCH_C(a.radius, CALL, ffk::CostU8)
+  } else {
+    return hipErrorInvalidValue;
+  }
 #undef CALL
   return hipGetLastError();
 }
