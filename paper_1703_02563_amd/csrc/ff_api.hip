@@ -99,7 +99,7 @@ ScaleSteps scale_steps(const ff_params *p, int lv) {
 
 // Device workspace of ff_flow_fields, carved in this order.
 struct Layout {
-  size_t hsum, blur, desc[2][kMaxLevels], wform[2][kMaxLevels], sdesc[2][kMaxLevels], desc1, desc1e, nb, keys, topl,
+  size_t hsum, blur, desc[2][kMaxLevels], wform[2][kMaxLevels], sdesc[2][kMaxLevels], swform[2][kMaxLevels], desc1, desc1e, nb, keys, topl,
       cand, grids, sgrids, evals, total;
   size_t N, Npad, M;
   int L;
@@ -136,6 +136,8 @@ Layout layout(int W, int H, const ff_params *p) {
     for (int lv = 1; lv + 1 < l.L; ++lv) {
       l.sdesc[im][lv] = off;
       if (p->subscales) off = align256(off + desc_map_bytes(W, H, subscale_of(lv)));
+      l.swform[im][lv] = off;
+      if (p->subscales) off = align256(off + ffk::wform_bytes(W, H, subscale_of(lv)));
     }
   l.desc1 = off; off = align256(off + 2 * l.N * 16);
   // Fast x2: the NN's references, the even pixels of both images
@@ -1266,8 +1268,14 @@ ff_status ff_flow_fields(const uint8_t *img1, const uint8_t *img2, int32_t W, in
   // descriptors of both images at every scale; the weight-class row maps
   // only where the table's level-kernel variant evaluates on them
   const ffh::Tuning tun = tuning_of(params->tuning);
+  // subpixel flows on the blocked kernels: radius 3, checkerboard order, maps
+  // addressed with 32-bit offsets
+  bool spx = sb != 0 && r == 3 && !params->raster && !params->subscales;
+  for (int lv = 0; lv < L; ++lv) spx = spx && ffh::level_map_fits(W, H, lv);
   auto wform_used = [&](int lv) {
-    return lv >= lmin && params->subpixel == 0 && !params->raster && r == 3 && ffh::level_uses_wform(tun.variant[lv]);
+    if (lv < lmin || params->raster) return false;
+    if (sb) return spx;
+    return r >= 2 && r <= 4 && ffh::level_uses_wform(tun.variant[lv], r, lv);
   };
   uint8_t *desc[2][kMaxLevels], *desc1[2];
   ffh::DescJobs jobs{};
@@ -1283,14 +1291,14 @@ ff_status ff_flow_fields(const uint8_t *img1, const uint8_t *img2, int32_t W, in
       jobs.job[z] = {img[im], reinterpret_cast<uint16_t *>(base + lay.hsum) + (size_t)z * lay.N,
                      reinterpret_cast<uint8_t *>(base + lay.blur) + (size_t)z * lay.N,
                      lv < lmin ? nullptr : desc[im][lv], lv == 0 ? desc1[im] : nullptr,
-                     wform_used(lv) ? reinterpret_cast<uint8_t *>(base + lay.wform[im][lv]) : nullptr, 1 << lv};
+                     wform_used(lv) ? reinterpret_cast<uint8_t *>(base + lay.wform[im][lv]) : nullptr, 1 << lv, r};
     }
   }
   hipError_t e = ffh::launch_descriptors(jobs, s);
   if (e != hipSuccess) return FF_ERR_LAUNCH;
   // sub-scales: the maps of patch scale 3n/2 (after the jobs above on the
   // same stream, so their row-sum and blur scratch can be reused)
-  uint8_t *sdesc[2][kMaxLevels] = {};
+  uint8_t *sdesc[2][kMaxLevels] = {}, *swform[2][kMaxLevels] = {};
   if (params->subscales && L > 2) {
     ffh::DescJobs sj{};
     sj.W = W;
@@ -1299,9 +1307,10 @@ ff_status ff_flow_fields(const uint8_t *img1, const uint8_t *img2, int32_t W, in
       for (int lv = 1; lv + 1 < L; ++lv) {
         const int z = sj.count++;
         sdesc[im][lv] = reinterpret_cast<uint8_t *>(base + lay.sdesc[im][lv]);
+        if (r == 3 && !sb && !params->raster) swform[im][lv] = reinterpret_cast<uint8_t *>(base + lay.swform[im][lv]);
         sj.job[z] = {img[im], reinterpret_cast<uint16_t *>(base + lay.hsum) + (size_t)z * lay.N,
-                     reinterpret_cast<uint8_t *>(base + lay.blur) + (size_t)z * lay.N, sdesc[im][lv], nullptr, nullptr,
-                     subscale_of(lv)};
+                     reinterpret_cast<uint8_t *>(base + lay.blur) + (size_t)z * lay.N, sdesc[im][lv], nullptr,
+                     swform[im][lv], subscale_of(lv)};
       }
     if ((e = ffh::launch_descriptors(sj, s)) != hipSuccess) return FF_ERR_LAUNCH;
   }
@@ -1407,15 +1416,15 @@ ff_status ff_flow_fields(const uint8_t *img1, const uint8_t *img2, int32_t W, in
   }
   for (int k = 0; k < nst; ++k) stage_entry[k] = k == 0 ? 0 : (stage_lv[k - 1] == stage_lv[k] ? 1 : 2);
 
-  if (sb == 0 && !params->raster && ffh::level_blocked_ok(W, H, L, r)) {
-    // temporally blocked level kernels: one launch per run of passes (the
-    // sub-scale stages, whose patch scale differs from the grid scale, one
-    // launch per step)
+  if (sb ? spx : !params->raster && ffh::level_blocked_ok(W, H, L, r)) {
+    // temporally blocked level kernels: one launch per run of passes
     int32_t *sflow[kMaxLevels][2];
     uint32_t *scost[kMaxLevels][2];
     carve_second_grids(base, lay.sgrids, W, H, L, sflow, scost);
     ffh::LevelKArgs k{};
     k.ndir = nd;
+    k.spx = spx;
+    k.wradius = r;
     for (int dr = 0; dr < nd; ++dr) {
       k.dir[dr].n_evals = reinterpret_cast<unsigned long long *>(evals + dr);
       k.dir[dr].stream_id = dr;
@@ -1434,8 +1443,8 @@ ff_status ff_flow_fields(const uint8_t *img1, const uint8_t *img2, int32_t W, in
         k.dir[dr].ccost = lv + 1 < L ? gcost[lv + 1][dr] : nullptr;
       }
       const bool sub = m != (1 << lv);
-      const bool stepwise = ffh::level_stepwise(tuning_of(params->tuning).variant[lv]);
-      // a sub-scale stage on the blocked quad kernels: radius 3, its map
+      const bool stepwise = !spx && ffh::level_stepwise(tun.variant[lv]);
+      // a sub-scale stage on the blocked kernels: radius 3, its map
       // addressed with 32-bit offsets, not the last stage (the Fast step
       // count applies there), entered from the coarser grid
       if (sub && !stepwise && r == 3 && entry == 2 && st != nst - 1 &&
@@ -1443,8 +1452,8 @@ ff_status ff_flow_fields(const uint8_t *img1, const uint8_t *img2, int32_t W, in
         for (int dr = 0; dr < nd; ++dr) {
           k.dir[dr].Da = sdesc[dr][lv];
           k.dir[dr].Db = sdesc[dr ^ 1][lv];
-          k.dir[dr].Wa = nullptr;
-          k.dir[dr].Wb = nullptr;
+          k.dir[dr].Wa = swform[dr][lv];
+          k.dir[dr].Wb = swform[dr ^ 1][lv];
         }
         if ((e = run_level_blocked(k, W, H, lv, params, ffh::kLevelSeed, s, sflow[lv], scost[lv], m)) != hipSuccess)
           return FF_ERR_LAUNCH;
@@ -1481,7 +1490,7 @@ ff_status ff_flow_fields(const uint8_t *img1, const uint8_t *img2, int32_t W, in
       return from_hip(ffh::launch_consistency_grid(flow_fwd, cost_fwd, flow_bwd, cost_bwd, W, H, 2, params->eps,
                                                    keep_fwd, keep_bwd, s));
     return from_hip(ffh::launch_consistency(flow_fwd, cost_fwd, flow_bwd, cost_bwd, W, H, params->eps, keep_fwd,
-                                            keep_bwd, s));
+                                            keep_bwd, s, sb));
   }
 
   ffh::LevelArgs a{};

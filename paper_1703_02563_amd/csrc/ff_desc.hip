@@ -112,9 +112,16 @@ __device__ __forceinline__ uint4 descriptor_at(const uint8_t *blurred, int W, in
   return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
-// Weight-class row entry (wform_index) of pixel x of blurred row `row`.
-__device__ __forceinline__ uint4 wform_entry(const uint8_t *row, int W, int n, int x) {
+// Weight-class row entry (wform_index) of pixel x of blurred row `row`, for
+// patch radius r.
+__device__ __forceinline__ uint4 wform_entry(const uint8_t *row, int W, int n, int x, int r = 3) {
   auto at = [&](int a) { return (uint32_t)row[clampi(x + n * a, W - 1)]; };
+  if (r == 4)
+    return make_uint4(at(-7) | at(-6) << 8 | at(6) << 16 | at(7) << 24, at(-5) | at(-4) << 8 | at(4) << 16 | at(5) << 24,
+                      at(-3) | at(-2) << 8 | at(2) << 16 | at(3) << 24, at(-1) | at(0) << 8 | at(1) << 16);
+  if (r == 2)
+    return make_uint4(at(-5) | at(-4) << 8 | at(4) << 16 | at(5) << 24, at(-3) | at(-2) << 8 | at(2) << 16 | at(3) << 24,
+                      at(-1) | at(1) << 8, at(0));
   return make_uint4(at(-6) | at(-5) << 8 | at(5) << 16 | at(6) << 24, at(-4) | at(-3) << 8 | at(3) << 16 | at(4) << 24,
                     at(-2) | at(-1) << 8 | at(1) << 16 | at(2) << 24, at(0));
 }
@@ -158,7 +165,7 @@ __global__ __launch_bounds__(256) void k_desc(ffh::DescJobs jobs) {
   const int ywf = yr + ffk::kWformPad * n;
   if (jb.wform && ywf >= 0 && ywf < H + 2 * ffk::kWformPad * n) {
     uint4 *wout = reinterpret_cast<uint4 *>(jb.wform) + (size_t)ywf * W;
-    for (int x = threadIdx.x; x < W; x += blockDim.x) wout[x] = wform_entry(s_rows + 4 * Ws, W, n, x);
+    for (int x = threadIdx.x; x < W; x += blockDim.x) wout[x] = wform_entry(s_rows + 4 * Ws, W, n, x, jb.wradius);
   }
   uint4 *out = reinterpret_cast<uint4 *>(jb.desc) + (size_t)yp * Wp;
   for (int c = threadIdx.x; c < Wp; c += blockDim.x) {

@@ -81,6 +81,32 @@ __device__ __forceinline__ size_t desc_index(int x, int y, int log2n, int W) {
 // 3 s3 + 4 s4), s_k = the byte SAD of dword k of the entries of rows
 // y + n b of the two maps (each descriptor byte is one blurred sample, so the
 // 784 byte differences of Eq. 3 are the 169 samples counted w(a) w(b) times).
+//
+// Patch radii 2 and 4 have maps of the same form over their 2r + 7 distinct
+// columns a = -(r + 3) .. r + 3 (rows b likewise), cell and target at least
+// r n inside: radius 4 keeps the weights 1 .. 4 per dword (a = -7, -6, 6, 7 |
+// -5, -4, 4, 5 | -3, -2, 2, 3 | -1, 0, 1); radius 2 has a = -5, -4, 4, 5
+// (weight 1) | -3, -2, 2, 3 (weight 2) | -1, 1 (weight 3) | 0 (weight 2).
+template <int R>
+struct WClass;
+template <>
+struct WClass<2> {
+  static constexpr int K = 11;
+  static constexpr int row[K] = {1, 1, 2, 2, 3, 2, 3, 2, 2, 1, 1};  // w(b)
+  static constexpr int dword[4] = {1, 2, 3, 2};
+};
+template <>
+struct WClass<3> {
+  static constexpr int K = 13;
+  static constexpr int row[K] = {1, 1, 2, 2, 3, 3, 4, 3, 3, 2, 2, 1, 1};
+  static constexpr int dword[4] = {1, 2, 3, 4};
+};
+template <>
+struct WClass<4> {
+  static constexpr int K = 15;
+  static constexpr int row[K] = {1, 1, 2, 2, 3, 3, 4, 4, 4, 3, 3, 2, 2, 1, 1};
+  static constexpr int dword[4] = {1, 2, 3, 4};
+};
 constexpr int kWformPad = 3;
 __host__ __device__ __forceinline__ size_t wform_index(int x, int y, int n, int W) {
   return (size_t)(y + kWformPad * n) * W + x;
@@ -239,6 +265,19 @@ __device__ __forceinline__ uint32_t sad_bilinear4(uint32_t a, uint32_t b00, uint
   acc = __builtin_amdgcn_sad_u16(ae, me, acc);
   return __builtin_amdgcn_sad_u16(ao, mo, acc);
 }
+
+// Four samples of a weight-class row entry against the bilinear mix of
+// image b's four corner entries: the even and the odd bytes as 16-bit lanes
+// of 24-bit multiply-adds.
+__device__ __forceinline__ uint32_t mad24(uint32_t a, uint32_t b, uint32_t c) { return __umul24(a, b) + c; }
+// a * wa + b * wb in both 16-bit lanes (weights repeated in both)
+__device__ __forceinline__ uint32_t mix16(uint32_t a, uint32_t wa, uint32_t b, uint32_t wb) {
+  typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2, a) * __builtin_bit_cast(u16x2, wa) +
+                                          __builtin_bit_cast(u16x2, b) * __builtin_bit_cast(u16x2, wb));
+}
+__device__ __forceinline__ uint32_t even_bytes(uint32_t v) { return v & 0x00FF00FFu; }
+__device__ __forceinline__ uint32_t odd_bytes(uint32_t v) { return __builtin_amdgcn_perm(v, v, 0x0C030C01u); }
 
 // Subpixel matching error (random-search offsets with subpixel accuracy,
 // the target patch's colours by bilinear interpolation): flows in 1/8

@@ -20,6 +20,7 @@ struct DescJob {
   uint8_t *compact;  // nullable: row-major [H][W][16] copy (the NN seed's input)
   uint8_t *wform;    // nullable: weight-class row map (see wform_index)
   int n;
+  int wradius;       // patch radius of the weight-class map: 2, 3 or 4 (0 means 3)
 };
 struct DescJobs {
   DescJob job[kMaxJobs];
@@ -165,7 +166,9 @@ struct LevelKArgs {
   int radius;   // patch radius: 3, or 2 and 4 (byte descriptors only); 0 means 3
   int tiles_x;  // set by launch_level
   int halo[4];
-  int sub_m;    // a sub-scale stage's patch scale m (Da/Db: image-order maps of scale m, radius 3); 0: n
+  int sub_m;    // a sub-scale stage's patch scale m (Da/Db/Wa/Wb: maps of scale m, radius 3); 0: n
+  int spx;      // 1: flows in 1/8 px, bilinear targets (radius 3, needs the weight-class maps)
+  int wradius;  // patch radius of the maps Wa/Wb (0 means 3)
 };
 // Padded, phase-ordered copy of a float [H][W][16] feature map of scale n.
 hipError_t launch_pad_features(const float *f, int W, int H, int n, float *out, hipStream_t stream);
@@ -176,7 +179,8 @@ struct BatchStage;
   hipError_t launch_level_scale##k(const LevelKArgs &a, const BatchStage *batch, int variant, hipStream_t s); \
   hipError_t launch_level_f32_scale##k(const LevelKArgs &a, int variant, hipStream_t s); \
   hipError_t launch_level_r2_scale##k(const LevelKArgs &a, int variant, hipStream_t s); \
-  hipError_t launch_level_r4_scale##k(const LevelKArgs &a, int variant, hipStream_t s);
+  hipError_t launch_level_r4_scale##k(const LevelKArgs &a, int variant, hipStream_t s); \
+  hipError_t launch_level_wx_scale##k(const LevelKArgs &a, int variant, hipStream_t s);
 FF_LEVEL_SCALE_DECL(0)
 FF_LEVEL_SCALE_DECL(1)
 FF_LEVEL_SCALE_DECL(2)
@@ -188,7 +192,9 @@ FF_LEVEL_SCALE_DECL(6)
 int level_window_halo(int variant);              // window halo of a byte-descriptor variant
 int level_window_halo_f32(int variant);          // the same for a float-feature variant
 bool level_map_fits(int W, int H, int log2n);  // scale-n map under 2^31 bytes (quad evaluations)
-bool level_uses_wform(int variant);  // the variant evaluates interior cells on weight-class row maps
+// The scale's launches of ff_flow_fields evaluate interior cells on
+// weight-class row maps of the call's radius.
+bool level_uses_wform(int variant, int radius, int log2n);
 void level_halo(int t_begin, int t_end, int halo[4]);
 int level_variant_count();      // byte-descriptor variants + the step-wise schedule
 int level_variant_count_f32();

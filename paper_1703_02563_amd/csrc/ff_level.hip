@@ -48,15 +48,32 @@ constexpr ScaleLaunchF32 kScaleR4[7] = {ffh::launch_level_r4_scale0, ffh::launch
 
 // Radius-2 / radius-4 kernel of a table entry: the descriptor-quad variant
 // with the same window halo (the run lengths follow the table's halo) -- a
-// weight-class variant's quad twin, or for a one-lane variant (all of halo
+// weight-class variant's quad twin, 8x8 tiles for the 4x4 ones, or for a one-lane variant (all of halo
 // kLevelHalo) the quad variant of that halo and a tile of the same class.
 int quad_variant(int v) {
   v = kVariants[v].nowf;
   switch (v) {
     case 11: case 12: case 13: case 14: case 15: case 16: case 17: case 26: case 27: case 30: return v;
+    case 32: return 27;
     default: return kVariants[v].tw >= 16 ? 13 : 14;
   }
 }
+
+constexpr ScaleLaunchF32 kScaleWx[7] = {ffh::launch_level_wx_scale0, ffh::launch_level_wx_scale1,
+                                        ffh::launch_level_wx_scale2, ffh::launch_level_wx_scale3,
+                                        ffh::launch_level_wx_scale4, ffh::launch_level_wx_scale5,
+                                        ffh::launch_level_wx_scale6};
+
+// Tile index of launch_wx for a table entry: the same window halo (the run
+// lengths follow it) and a tile of the same class.
+int wx_variant(int v) {
+  const Variant t = kVariants[v];
+  if (t.halo == 2) return t.tw >= 32 ? 0 : 1;
+  if (t.halo == 4) return t.tw == 4 ? 5 : 4;
+  if (t.tw >= 16) return 2;
+  return v == 14 || v == 22 ? 6 : 3;  // 8x8 with 256 or 1024 threads
+}
+
 constexpr ScaleLaunch kScale[7] = {ffh::launch_level_scale0, ffh::launch_level_scale1, ffh::launch_level_scale2,
                                    ffh::launch_level_scale3, ffh::launch_level_scale4, ffh::launch_level_scale5,
                                    ffh::launch_level_scale6};
@@ -140,7 +157,11 @@ bool level_map_fits(int W, int H, int log2n) {
   return ((size_t)W + 2 * P) * ((size_t)H + 2 * P) * 16 < ((size_t)1 << 31);
 }
 
-bool level_uses_wform(int variant) {
+// Radii 2 and 4: scales whose launches run the weight-class kernels.
+static bool level_wform_rx_scale(int radius, int log2n) { return log2n <= (radius == 4 ? 1 : 0); }
+
+bool level_uses_wform(int variant, int radius, int log2n) {
+  if (radius == 2 || radius == 4) return level_wform_rx_scale(radius, log2n);
   return variant >= 0 && variant < kNumVariants && kVariants[variant].nowf != variant;
 }
 
@@ -175,15 +196,18 @@ hipError_t launch_level(LevelKArgs a, hipStream_t stream) {
     if (l2 < 0 || l2 >= 7) return hipErrorInvalidValue;
     return kScaleF32[l2](a, a.variant, stream);
   }
-  if (a.sub_m) {  // a sub-scale stage: the descriptor-quad kernel of the table's window halo
+  if (a.sub_m || a.spx) {  // a sub-scale stage or subpixel flows: weight-class kernels only
     const int v = blocked_variant(a.variant);
-    if (l2 < 0 || l2 >= 7 || v < 0 || v >= kNumVariants || (a.radius != 0 && a.radius != 3)) return hipErrorInvalidValue;
-    return dispatch(a, nullptr, l2, quad_variant(v), stream);
+    if (l2 < 0 || l2 >= 7 || v < 0 || v >= kNumVariants || (a.radius != 0 && a.radius != 3) || !dirs_have_wform(a))
+      return hipErrorInvalidValue;
+    return kScaleWx[l2](a, wx_variant(v), stream);
   }
   if (a.radius == 2 || a.radius == 4) {
     const int v = blocked_variant(a.variant);
     if (l2 < 0 || l2 >= 7 || v < 0 || v >= kNumVariants || !level_map_fits(a.W, a.H, l2))
       return hipErrorInvalidValue;
+    // maps of another radius (a caller's, of radius 3) are of no use
+    if (a.wradius == a.radius && dirs_have_wform(a)) return kScaleWx[l2](a, wx_variant(v), stream);
     return (a.radius == 2 ? kScaleR2 : kScaleR4)[l2](a, quad_variant(v), stream);
   }
   return dispatch(a, nullptr, l2, launch_variant(a.variant, level_map_fits(a.W, a.H, l2), dirs_have_wform(a)),

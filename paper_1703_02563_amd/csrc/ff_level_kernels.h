@@ -189,6 +189,16 @@ __device__ __forceinline__ uint32_t eval_quad_gg(__amdgpu_buffer_rsrc_t da, __am
     s2 = ffk::sad16(make_uint4(a2[0], a2[1], a2[2], a2[3]), make_uint4(b2[0], b2[1], b2[2], b2[3]), s2);
   }
   uint32_t s = s1 + (r < K - 4 ? s2 : 0u);
+  if constexpr (K > 8) {  // radius 4: the ninth column, by lane 0
+    if (r == 0) {
+#pragma unroll
+      for (int v = 0; v < K; ++v) {
+        const auto a3 = __builtin_amdgcn_raw_buffer_load_b128(da, offa + 8 * 16, v * rowb, 0);
+        const auto b3 = __builtin_amdgcn_raw_buffer_load_b128(db, offb + 8 * 16, v * rowb, 0);
+        s = ffk::sad16(make_uint4(a3[0], a3[1], a3[2], a3[3]), make_uint4(b3[0], b3[1], b3[2], b3[3]), s);
+      }
+    }
+  }
   s += (uint32_t)__builtin_amdgcn_mov_dpp((int)s, 0xB1, 0xF, 0xF, false);  // quad_perm [1,0,3,2]
   s += (uint32_t)__builtin_amdgcn_mov_dpp((int)s, 0x4E, 0xF, 0xF, false);  // quad_perm [2,3,0,1]
   return s;
@@ -225,19 +235,73 @@ __device__ __forceinline__ uint32_t eval_quad_sub(__amdgpu_buffer_rsrc_t da, __a
   return s;
 }
 
-// E_n(p, f) by one lane from the weight-class row maps (wform_index), for a
-// cell p and a target (bx, by) both at least 3n inside the image: the 13
-// rows y + n b (b = -6..6) of image a come from LDS (`pa`: the cell's entry
-// of row b = -6 in a window of row length LW), those of image b from its
-// map (one 16-byte load per row, the row step in the scalar offset); four
-// byte SADs per row go to the accumulator of its (row weight, column
-// weight) class, and E = sum_{l,k} l k T[l][k].
-template <int LOG2N, int LW>
-__device__ __forceinline__ uint32_t eval_wform(const uint4 *pa, __amdgpu_buffer_rsrc_t wb, int W, int bx, int by) {
-  constexpr int n = 1 << LOG2N, K = 13;
-  constexpr int kRowClass[K] = {0, 0, 1, 1, 2, 2, 3, 2, 2, 1, 1, 0, 0};  // w(b) - 1
-  const int rowb = n * W * 16;
-  const int off = (int)ffk::wform_index(bx, by - 6 * n, n, W) * 16;
+// The subpixel form of eval_quad_gg (radius 3): target (bx, by) in 1/8
+// pixel, image b's descriptors mixed from the four pixels around it with
+// integer weights (sad_bilinear4); a corner of weight 0 is read at its
+// neighbour's column or row.
+template <int LOG2N>
+__device__ __forceinline__ uint32_t eval_quad_spx(__amdgpu_buffer_rsrc_t da, __amdgpu_buffer_rsrc_t db, int W, int ax,
+                                                  int ay, int bx, int by, int r) {
+  constexpr int n = 1 << LOG2N, P = ffk::kDescPad * n, K = 7;
+  const int Wp = W + 2 * P, rowb = n * Wp * 16;
+  const int x0 = bx >> 3, y0 = by >> 3, fx = bx & 7, fy = by & 7, dy = fy != 0 ? Wp * 16 : 0;
+  const uint32_t w00 = (8 - fx) * (8 - fy), w10 = fx * (8 - fy), w01 = (8 - fx) * fy, w11 = fx * fy;
+  const int offa = (int)ffk::desc_index(ax - 3 * n, ay - 3 * n, LOG2N, W) * 16;
+  const int off0 = (int)ffk::desc_index(x0 - 3 * n, y0 - 3 * n, LOG2N, W) * 16;
+  const int off1 = (int)ffk::desc_index(x0 + (fx != 0) - 3 * n, y0 - 3 * n, LOG2N, W) * 16;
+  uint32_t s[2] = {0, 0};
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    const int u = 16 * (c == 0 ? r : min(r + 4, K - 1));
+#pragma unroll
+    for (int v = 0; v < K; ++v) {
+      const auto a = __builtin_amdgcn_raw_buffer_load_b128(da, offa + u, v * rowb, 0);
+      const auto b00 = __builtin_amdgcn_raw_buffer_load_b128(db, off0 + u, v * rowb, 0);
+      const auto b10 = __builtin_amdgcn_raw_buffer_load_b128(db, off1 + u, v * rowb, 0);
+      const auto b01 = __builtin_amdgcn_raw_buffer_load_b128(db, off0 + dy + u, v * rowb, 0);
+      const auto b11 = __builtin_amdgcn_raw_buffer_load_b128(db, off1 + dy + u, v * rowb, 0);
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        s[c] = ffk::sad_bilinear4(a[k], b00[k], b10[k], b01[k], b11[k], w00, w10, w01, w11, s[c]);
+    }
+  }
+  uint32_t e = s[0] + (r < K - 4 ? s[1] : 0u);
+  e += (uint32_t)__builtin_amdgcn_mov_dpp((int)e, 0xB1, 0xF, 0xF, false);  // quad_perm [1,0,3,2]
+  e += (uint32_t)__builtin_amdgcn_mov_dpp((int)e, 0x4E, 0xF, 0xF, false);  // quad_perm [2,3,0,1]
+  return e;
+}
+
+// Sum of the class accumulators: T[l][k] collects rows of weight l + 1,
+// dword k.
+template <int RR>
+__device__ __forceinline__ uint32_t wclass_sum(const uint32_t (&T)[4][4]) {
+  using C = ffk::WClass<RR>;
+  uint32_t e = 0;
+#pragma unroll
+  for (int l = 0; l < 4; ++l) {
+    uint32_t r = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) r += (uint32_t)C::dword[k] * T[l][k];
+    e += (uint32_t)(l + 1) * r;
+  }
+  return e;
+}
+
+// E_n(p, f) by one lane from the weight-class row maps of radius RR
+// (wform_index, WClass), for a cell p and a target (bx, by) both at least RR n
+// inside the image: the K = 2 RR + 7 rows y + n b of image a come from LDS
+// (`pa`: the cell's entry of the first row, `step` entries between rows),
+// those of image b from its map (one 16-byte load per row, the row step in
+// the scalar offset); four byte SADs per row go to the accumulator of its
+// (row weight, column weight) class, and E = sum_{l,k} l k T[l][k].  m: the
+// patch scale (n, or a sub-scale stage's).
+template <int RR>
+__device__ __forceinline__ uint32_t eval_wform(const uint4 *pa, int step, __amdgpu_buffer_rsrc_t wb, int W, int m,
+                                               int bx, int by) {
+  using C = ffk::WClass<RR>;
+  constexpr int K = C::K;
+  const int rowb = m * W * 16;
+  const int off = (int)ffk::wform_index(bx, by - (RR + 3) * m, m, W) * 16;
   uint4 B[K];
 #pragma unroll
   for (int b = 0; b < K; ++b) {
@@ -247,17 +311,105 @@ __device__ __forceinline__ uint32_t eval_wform(const uint4 *pa, __amdgpu_buffer_
   uint32_t T[4][4] = {};
 #pragma unroll
   for (int b = 0; b < K; ++b) {
-    const uint4 A = pa[b * LW];
-    const int l = kRowClass[b];
+    const uint4 A = pa[b * step];
+    const int l = C::row[b] - 1;
     T[l][0] = __builtin_amdgcn_sad_u8(A.x, B[b].x, T[l][0]);
     T[l][1] = __builtin_amdgcn_sad_u8(A.y, B[b].y, T[l][1]);
     T[l][2] = __builtin_amdgcn_sad_u8(A.z, B[b].z, T[l][2]);
     T[l][3] = __builtin_amdgcn_sad_u8(A.w, B[b].w, T[l][3]);
   }
-  uint32_t R[4];
+  return wclass_sum<RR>(T);
+}
+
+// The subpixel form (radius 3): target (bx, by) in 1/8 pixel, both of its
+// pixel columns and rows at least 3n inside.  A bilinear mix of descriptors is
+// the descriptor of the mixed image, so the classes stay: E = sum of w(b) k
+// |64 a - mix| over the 13 x 13 samples, four row entries per row instead of
+// the 4 x 49 descriptors of the direct form (about 77 operations per row
+// against 88 per descriptor).  An evaluation is some thousand operations: FL
+// = 4 lets a quad share its rows where the tile's workgroup has lanes to spare
+// and one lane's chain would be a phase's critical path (1024 x 436, per
+// launch at scale 16: 117 -> 70 us, scale 4: 144 -> 113 us); on the 256-thread
+// tiles of the fine scales one lane per evaluation does less work in all
+// (scale 1: 232 against 318 us).  At n = 1 the lower corners of a row are the
+// upper ones of the next, so a quad's lanes take adjacent rows there, else
+// every fourth.
+template <int LOG2N, int FL>
+__device__ __forceinline__ uint32_t eval_wform_spx(const uint4 *pa, int step, __amdgpu_buffer_rsrc_t wb, int W, int bx,
+                                                   int by, int r) {
+  constexpr int n = 1 << LOG2N, K = 13, ROWS = FL == 4 ? 4 : K;  // rows per lane
+  const int rowb = n * W * 16;
+  const int fx = bx & 7, fy = by & 7, dx = fx != 0 ? 16 : 0, dy = fy != 0 ? W * 16 : 0;
+  const int off = (int)ffk::wform_index(bx >> 3, (by >> 3) - 6 * n, n, W) * 16;
+  // row i of this lane, and its weight w(b) = (8 - |b - 6|) / 2 (0 past the
+  // lane's last row)
+  auto row_of = [&](int i) { return FL == 1 ? i : LOG2N == 0 ? min((r == 0 ? 0 : 3 * r + 1) + i, 12) : min(r + 4 * i, 12); };
+  auto weight = [&](int i) {
+    const bool there = FL == 1 || i < 3 || r == 0;
+    return there ? (uint32_t)(8 - abs(row_of(i) - 6)) >> 1 : 0u;
+  };
+  // The mixed entry in even and odd 16-bit lanes: dword k holds samples of
+  // weight k + 1, the last one a single sample in its even lanes.
+  uint32_t e = 0;
+  auto add = [&](int i, const uint32_t (&mix)[7]) {
+    const uint4 A = pa[row_of(i) * step];
+    const uint32_t w[4] = {A.x, A.y, A.z, A.w};
+    uint32_t s[4];
 #pragma unroll
-  for (int l = 0; l < 4; ++l) R[l] = T[l][0] + 2 * T[l][1] + 3 * T[l][2] + 4 * T[l][3];
-  return R[0] + 2 * R[1] + 3 * R[2] + 4 * R[3];
+    for (int k = 0; k < 4; ++k) {
+      s[k] = __builtin_amdgcn_sad_u16(ffk::even_bytes(w[k]) << 6, mix[2 * k], 0);
+      if (k < 3) s[k] = __builtin_amdgcn_sad_u16(ffk::odd_bytes(w[k]) << 6, mix[2 * k + 1], s[k]);
+    }
+    e = ffk::mad24(s[0] + 2 * s[1] + 3 * s[2] + 4 * s[3], weight(i), e);
+  };
+  auto lanes = [](const auto &v, int k) {
+    return (k & 1) ? ffk::odd_bytes(v[k >> 1]) : ffk::even_bytes(v[k >> 1]);
+  };
+  auto load = [&](int row, int o) {
+    if constexpr (FL == 1)
+      return __builtin_amdgcn_raw_buffer_load_b128(wb, off + o, row * rowb, 0);
+    else
+      return __builtin_amdgcn_raw_buffer_load_b128(wb, off + row * rowb + o, 0, 0);
+  };
+  if constexpr (LOG2N == 0) {
+    const uint32_t wx0 = 8 - fx, wx1 = fx, wy0 = (8 - fy) * 0x10001u, wy1 = fy * 0x10001u;
+    auto hmix = [&](int row, uint32_t (&h)[7]) {
+      const auto p = load(row, 0);
+      const auto q = load(row, dx);
+#pragma unroll
+      for (int k = 0; k < 7; ++k) h[k] = ffk::mad24(lanes(q, k), wx1, __umul24(lanes(p, k), wx0));
+    };
+    uint32_t h0[7], h1[7], mix[7];
+    hmix(row_of(0), h0);
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) {
+      hmix(row_of(i) + 1, h1);  // (past the target's own rows only with weight 0)
+#pragma unroll
+      for (int k = 0; k < 7; ++k) {
+        mix[k] = ffk::mix16(h0[k], wy0, h1[k], wy1);  // at most 8 * 2040 a lane
+        h0[k] = h1[k];
+      }
+      add(i, mix);
+    }
+  } else {
+    const uint32_t w00 = (8 - fx) * (8 - fy), w10 = fx * (8 - fy), w01 = (8 - fx) * fy, w11 = fx * fy;
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) {
+      const int b = row_of(i);
+      const auto p = load(b, 0), q = load(b, dx), t = load(b, dy), u = load(b, dx + dy);
+      uint32_t mix[7];
+#pragma unroll
+      for (int k = 0; k < 7; ++k)
+        mix[k] = ffk::mad24(lanes(u, k), w11,
+                            ffk::mad24(lanes(t, k), w01, ffk::mad24(lanes(q, k), w10, __umul24(lanes(p, k), w00))));
+      add(i, mix);
+    }
+  }
+  if constexpr (FL == 4) {
+    e += (uint32_t)__builtin_amdgcn_mov_dpp((int)e, 0xB1, 0xF, 0xF, false);  // quad_perm [1,0,3,2]
+    e += (uint32_t)__builtin_amdgcn_mov_dpp((int)e, 0x4E, 0xF, 0xF, false);  // quad_perm [2,3,0,1]
+  }
+  return e;
 }
 
 // Float learned-feature cost (Eq. 3 with the squared-difference data term)
@@ -302,16 +454,20 @@ __device__ __forceinline__ uint32_t eval_quad_f32(const float4 *pa, const float4
 // The run of passes for tile `tile` of one direction `d` (a holds the
 // pair's sizes and the schedule).  All threads of the workgroup call it.
 template <int LOG2N, int TW, int TH, int kThreads, int EV, bool F32 = false, int HALO = kHalo, int RR = kR,
-          bool SUB = false>
+          bool SUB = false, bool SPX = false>
 __device__ __forceinline__ void level_body(const ffh::LevelKArgs &a, const ffh::LevelKDir &d, int tile) {
-  // SUB: a sub-scale stage (patch scale a.sub_m, image-order maps), descriptor quads at radius 3
-  static_assert(!SUB || (EV == 3 && !F32 && RR == kR), "sub-scale stages run the radius-3 quad kernels");
-  // patch radius RR: 3, or 2 and 4 with the descriptor-quad evaluations
-  // (the weight-class maps and the float path hold radius-3 patches)
+  // SUB: a sub-scale stage (patch scale a.sub_m = 3n/2, maps of that scale);
+  // SPX: flows in 1/8 pixel, bilinear targets
+  static_assert((!SUB && !SPX) || (EV == 4 && !F32 && RR == kR && !(SUB && SPX) && !(SUB && LOG2N == 0)),
+                "sub-scale and subpixel stages run the radius-3 weight-class kernels");
+  // patch radius RR: 3, or 2 and 4 with the descriptor-quad or weight-class
+  // evaluations (the float path holds radius-3 patches)
   static_assert(Geo<TW, TH, HALO, RR>::LW * Geo<TW, TH, HALO, RR>::LH + kThreads < 65536,
                 "the cell index of a half-sweep must stay below 2^16 (cell_of's division)");
-  static_assert(RR == kR || ((RR == 2 || RR == 4) && EV == 3 && !F32),
-                "radii 2 and 4 run the descriptor-quad kernels only");
+  static_assert(RR == kR || ((RR == 2 || RR == 4) && EV >= 3 && !F32),
+                "radii 2 and 4 run the descriptor-quad and weight-class kernels only");
+  constexpr int SB = SPX ? 3 : 0;  // flows in 1/2^SB pixel
+  constexpr int FL = SPX && kThreads > 256 ? 4 : 1;  // lanes per weight-class evaluation
   using G = Geo<TW, TH, HALO, RR>;
   constexpr int n = 1 << LOG2N;
   // EV 3 and float features: every evaluation by a quad of lanes
@@ -331,8 +487,12 @@ __device__ __forceinline__ void level_body(const ffh::LevelKArgs &a, const ffh::
   // byte descriptors of image a on the level lattice (float features are
   // read from their padded map instead); 64-bit keys for float costs
   __shared__ uint4 s_da[(F32 || WF) ? 1 : G::DH * G::DW];
-  // weight-class row entries of image a: window rows gj0 - 6 ... gj0 + LH + 5
-  __shared__ uint4 s_wa[WF ? (G::LH + 12) * G::LW : 1];
+  // weight-class row entries of image a: window rows gj0 - (RR + 3) ... gj0 +
+  // LH + RR + 2; the rows of a sub-scale patch lie 3/2 cells apart, so its
+  // window holds rows half a cell apart from gj0 - 9 on (patch row b of cell
+  // row j is window row 2 (j - gj0) + 3 (b + 6))
+  constexpr int WROWS = SUB ? 2 * G::LH + 35 : G::LH + 2 * (RR + 3);
+  __shared__ uint4 s_wa[WF ? WROWS * G::LW : 1];
   __shared__ float4 s_daf[F32 ? 4 * G::DH * G::DW : 1];
   __shared__ unsigned long long s_key[F32 ? G::LH * G::LW : 1];
   __shared__ uint16_t s_queue[QCAP];  // queued evaluations: cell * 2 + vertical
@@ -361,7 +521,7 @@ __device__ __forceinline__ void level_body(const ffh::LevelKArgs &a, const ffh::
 
   // image-a descriptors on the level lattice around the window: every load
   // of a thread is issued before the first LDS store (one memory round trip)
-  constexpr int NSTAGE = F32 ? 4 * G::DH * G::DW : (WF ? (G::LH + 12) * G::LW : G::DH * G::DW);
+  constexpr int NSTAGE = F32 ? 4 * G::DH * G::DW : (WF ? WROWS * G::LW : G::DH * G::DW);
   constexpr int NS = (NSTAGE + kThreads - 1) / kThreads;
   uint4 sv[F32 ? 1 : NS];
   float4 sf[F32 ? NS : 1];
@@ -370,19 +530,21 @@ __device__ __forceinline__ void level_body(const ffh::LevelKArgs &a, const ffh::
 #pragma unroll
     for (int it = 0; it < NS; ++it) {
       const int k = min(it * kThreads + tid, NSTAGE - 1);
-      const int vi = gi0 + k % G::LW, vj = gj0 - 6 + k / G::LW;
-      sv[it] = Wa[ffk::wform_index(clampi(vi * n, W - 1), clampi(vj * n, H - 1), n, W)];
+      const int vi = gi0 + k % G::LW, vr = k / G::LW;
+      const int y = SUB ? gj0 * n + (vr - 18) * (n / 2) : (gj0 - (RR + 3) + vr) * n;
+      // rows of a patch reach 3 of its scale past the image (kWformPad); the
+      // windows of cells without weight-class evaluations are clamped to that
+      const int sc = SUB ? a.sub_m : n;
+      sv[it] = Wa[ffk::wform_index(clampi(vi * n, W - 1), min(max(y, -3 * sc), H - 1 + 3 * sc), sc, W)];
     }
   } else if constexpr (!F32) {
     const uint4 *Da = reinterpret_cast<const uint4 *>(d.Da);
     uint4 *v = sv;
-    if constexpr (!SUB) {  // a sub-scale stage reads image a from its map instead
 #pragma unroll
-      for (int it = 0; it < NS; ++it) {
-        const int k = min(it * kThreads + tid, G::DH * G::DW - 1);
-        const int vi = gi0 - RR + k % G::DW, vj = gj0 - RR + k / G::DW;
-        v[it] = Da[ffk::desc_index(clampi(vi * n, W - 1), clampi(vj * n, H - 1), LOG2N, W)];
-      }
+    for (int it = 0; it < NS; ++it) {
+      const int k = min(it * kThreads + tid, G::DH * G::DW - 1);
+      const int vi = gi0 - RR + k % G::DW, vj = gj0 - RR + k / G::DW;
+      v[it] = Da[ffk::desc_index(clampi(vi * n, W - 1), clampi(vj * n, H - 1), LOG2N, W)];
     }
   } else {
     const float4 *Da = reinterpret_cast<const float4 *>(d.Da);
@@ -394,6 +556,7 @@ __device__ __forceinline__ void level_body(const ffh::LevelKArgs &a, const ffh::
       v[it] = Da[4 * ffk::desc_index(clampi(vi * n, W - 1), clampi(vj * n, H - 1), LOG2N, W) + (k & 3)];
     }
   }
+  const int pscale = SUB ? a.sub_m : n;  // patch scale
   // E_n of grid cell (i, j) and target pixel (bx, by), one lane per
   // evaluation (byte descriptors, EV 0-2)
   auto evalc = [&](int i, int j, int bx, int by) -> uint32_t {
@@ -401,23 +564,14 @@ __device__ __forceinline__ void level_body(const ffh::LevelKArgs &a, const ffh::
     return eval_cell<LOG2N, G::DW, (EV < 3 ? EV : 1), RR>(pa, Db, W, bx, by);
   };
   // the same by a quad of lanes (QUAD only)
-  [[maybe_unused]] const __amdgpu_buffer_rsrc_t db_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint8_t *>(d.Db), (short)0,
-      (int)((size_t)(H + 2 * ffk::desc_pad(n)) * (W + 2 * ffk::desc_pad(n)) * 16), 0x00020000);
+  [[maybe_unused]] const int map_bytes =
+      (int)((size_t)(H + 2 * ffk::desc_pad(pscale)) * (W + 2 * ffk::desc_pad(pscale)) * 16);
+  [[maybe_unused]] const __amdgpu_buffer_rsrc_t db_rsrc =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(d.Db), (short)0, map_bytes, 0x00020000);
   auto evalq = [&](int i, int j, int bx, int by) -> uint32_t {
     if constexpr (F32) {
       const float4 *pa = s_daf + 4 * ((j - gj0 + RR) * G::DW + (i - gi0 + RR));
       return eval_quad_f32<LOG2N, G::DW>(pa, reinterpret_cast<const float4 *>(d.Db), W, bx, by, qr);
-    } else if constexpr (SUB) {
-      // both maps of patch scale a.sub_m (image order) through resources
-      // of their size
-      const int sm = a.sub_m;
-      const int bytes = (int)((size_t)(H + 2 * ffk::desc_pad(sm)) * (W + 2 * ffk::desc_pad(sm)) * 16);
-      const __amdgpu_buffer_rsrc_t ra =
-          __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(d.Da), (short)0, bytes, 0x00020000);
-      const __amdgpu_buffer_rsrc_t rb =
-          __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(d.Db), (short)0, bytes, 0x00020000);
-      return eval_quad_sub<RR>(ra, rb, W, sm, i * n, j * n, bx, by, qr);
     } else {
       const uint4 *pa = s_da + (j - gj0 + RR) * G::DW + (i - gi0 + RR);
       return eval_quad<LOG2N, G::DW, RR>(pa, db_rsrc, W, bx, by, qr);
@@ -433,22 +587,31 @@ __device__ __forceinline__ void level_body(const ffh::LevelKArgs &a, const ffh::
       atomicAdd(&s_work[1], (unsigned)all);
     }
   };
-  // the weight-class path: interior test, one-lane and all-global quad evaluations
+  // the weight-class path: interior test, one-lane and all-global quad
+  // evaluations; (bx, by): target in 1/2^SB pixel
   [[maybe_unused]] const __amdgpu_buffer_rsrc_t wb_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint8_t *>(d.Wb), (short)0, WF ? (int)ffk::wform_bytes(W, H, n) : 0, 0x00020000);
-  [[maybe_unused]] const __amdgpu_buffer_rsrc_t da_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint8_t *>(d.Da), (short)0,
-      WF ? (int)((size_t)(H + 2 * ffk::desc_pad(n)) * (W + 2 * ffk::desc_pad(n)) * 16) : 0, 0x00020000);
+      const_cast<uint8_t *>(d.Wb), (short)0, WF ? (int)ffk::wform_bytes(W, H, pscale) : 0, 0x00020000);
+  [[maybe_unused]] const __amdgpu_buffer_rsrc_t da_rsrc =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(d.Da), (short)0, WF ? map_bytes : 0, 0x00020000);
   [[maybe_unused]] auto inner = [&](int i, int j, int bx, int by) {
-    const int lo = 3 * n;
-    return i * n >= lo && i * n <= W - 1 - lo && j * n >= lo && j * n <= H - 1 - lo && bx >= lo && bx <= W - 1 - lo &&
-           by >= lo && by <= H - 1 - lo;
+    const int lo = RR * pscale, xh = (W - 1 - lo) << SB, yh = (H - 1 - lo) << SB;
+    return i * n >= lo && i * n <= W - 1 - lo && j * n >= lo && j * n <= H - 1 - lo && bx >= (lo << SB) && bx <= xh &&
+           by >= (lo << SB) && by <= yh;
   };
   [[maybe_unused]] auto evalw = [&](int i, int j, int bx, int by) -> uint32_t {
-    return eval_wform<LOG2N, G::LW>(s_wa + (j - gj0) * G::LW + (i - gi0), wb_rsrc, W, bx, by);
+    if constexpr (SPX)
+      return eval_wform_spx<LOG2N, FL>(s_wa + (j - gj0) * G::LW + (i - gi0), G::LW, wb_rsrc, W, bx, by, qr);
+    else
+      return eval_wform<RR>(s_wa + (SUB ? 2 : 1) * (j - gj0) * G::LW + (i - gi0), (SUB ? 3 : 1) * G::LW, wb_rsrc, W,
+                            pscale, bx, by);
   };
   [[maybe_unused]] auto evalg = [&](int i, int j, int bx, int by) -> uint32_t {
-    return eval_quad_gg<LOG2N, RR>(da_rsrc, db_rsrc, W, i * n, j * n, bx, by, qr);
+    if constexpr (SUB)
+      return eval_quad_sub<RR>(da_rsrc, db_rsrc, W, pscale, i * n, j * n, bx, by, qr);
+    else if constexpr (SPX)
+      return eval_quad_spx<LOG2N>(da_rsrc, db_rsrc, W, i * n, j * n, bx, by, qr);
+    else
+      return eval_quad_gg<LOG2N, RR>(da_rsrc, db_rsrc, W, i * n, j * n, bx, by, qr);
   };
   // append of the lanes with `on` set, at the front (inn) or the back (!inn)
   // of the queue: one LDS atomic per wave and end
@@ -466,36 +629,37 @@ __device__ __forceinline__ void level_body(const ffh::LevelKArgs &a, const ffh::
     if (on && inn) s_queue[q0 + __popcll(bi & below)] = e;
     if (on && !inn) s_queue[QCAP - 1 - (q1 + __popcll(bb & below))] = e;
   };
-  // evaluations of a front/back queue pair: the front entries one lane each
-  // (weight-class), the back entries a quad each.  decode(e, l, i, j, bx, by)
-  // gives an entry's window cell l, grid cell (i, j) and target pixel;
-  // done(e, l, cost) is called once per entry, on the evaluating lane (the
-  // quad's lane 0)
+  // evaluations of a front/back queue pair in one sequence over the threads:
+  // the front entries one lane each (weight-class; a quad each for subpixel
+  // flows) in whole waves, then the back entries a quad each, so that both
+  // kinds run side by side on different waves.  decode(e, l, i, j, bx, by)
+  // gives an entry's window cell l, grid cell (i, j) and target; done(e, l,
+  // cost) is called once per entry, on the evaluating lane (a quad's lane 0)
   [[maybe_unused]] auto run_queues = [&](int flen, int blen, auto decode, auto done) {
-    for (int base = 0; base < flen; base += kThreads) {
+    const int fthreads = (flen * FL + 63) & ~63, total = fthreads + 4 * blen;
+    for (int base = 0; base < total; base += kThreads) {
       const int q = base + tid;
-      bool own = false;
-      if (q < flen) {
-        const int e = s_queue[q];
-        int l, i, j, bx, by;
-        decode(e, l, i, j, bx, by);
-        done(e, l, evalw(i, j, bx, by));
-        own = owned(i, j);
-      }
-      count_work(q < flen, own);
-    }
-    for (int base = 0; base < blen; base += kQuads) {
-      const int q = base + (tid >> 2);
-      bool own = false;
-      if (q < blen) {
-        const int e = s_queue[QCAP - 1 - q];
+      bool own = false, did = false;
+      if (q < fthreads) {  // wave-uniform
+        if (q < flen * FL) {
+          const int e = s_queue[q / FL];
+          int l, i, j, bx, by;
+          decode(e, l, i, j, bx, by);
+          const uint32_t c = evalw(i, j, bx, by);
+          did = q % FL == 0;
+          if (did) done(e, l, c);
+          own = owned(i, j);
+        }
+      } else if (q < total) {
+        const int e = s_queue[QCAP - 1 - ((q - fthreads) >> 2)];
         int l, i, j, bx, by;
         decode(e, l, i, j, bx, by);
         const uint32_t c = evalg(i, j, bx, by);
-        if (qr == 0) done(e, l, c);
+        did = qr == 0;
+        if (did) done(e, l, c);
         own = owned(i, j);
       }
-      count_work(q < blen && qr == 0, own);
+      count_work(did, own);
     }
   };
   // queue append of the lanes with `on` set (one LDS atomic per wave)
@@ -518,11 +682,10 @@ __device__ __forceinline__ void level_body(const ffh::LevelKArgs &a, const ffh::
     const uint32_t c0 = s_cost[l];
     const int32_t f0 = s_flow[l];
     int ox, oy;
-    ffk::rs_offset(a.seed, d.stream_id, a.level, t, j, i, t < a.P ? a.Rnp : a.Rn, ox, oy);
+    ffk::rs_offset(a.seed, d.stream_id, a.level, t, j, i, (t < a.P ? a.Rnp : a.Rn) << SB, ox, oy);
     const int fx = ffk::flow_x(f0) + ox, fy = ffk::flow_y(f0) + oy;
-    const int tx = i * n + fx, ty = j * n + fy;
     fc = ffk::pack_flow(fx, fy);
-    return c0 != kUnset && (ox | oy) != 0 && tx >= 0 && tx < W && ty >= 0 && ty < H;
+    return c0 != kUnset && (ox | oy) != 0 && ffk::target_in<SB>(W, H, i * n, j * n, fx, fy);
   };
 
   // initial state of the valid window: the state of every cell of a thread
@@ -549,7 +712,8 @@ __device__ __forceinline__ void level_body(const ffh::LevelKArgs &a, const ffh::
           cv[it] = d.cost_in[(size_t)j * Wn + i];
         } else if (a.mode == ffh::kLevelInit) {
           const uint32_t q = (uint32_t)d.nn_key[(size_t)j * Wn + i];
-          fv[it] = ffk::pack_flow((int)(q % (uint32_t)W) - i * n, (int)(q / (uint32_t)W) - j * n);
+          fv[it] = ffk::pack_flow(((int)(q % (uint32_t)W) - i * n) * (1 << SB),
+                                  ((int)(q / (uint32_t)W) - j * n) * (1 << SB));
           ev[it] = true;
         } else if (!((i | j) & 1)) {
           const int kc = (j >> 1) * Wc + (i >> 1);
@@ -568,11 +732,9 @@ __device__ __forceinline__ void level_body(const ffh::LevelKArgs &a, const ffh::
       for (int it = 0; it < NS; ++it)
         if (it * kThreads + tid < NSTAGE) s_wa[it * kThreads + tid] = sv[it];
     } else if constexpr (!F32) {
-      if constexpr (!SUB) {
 #pragma unroll
-        for (int it = 0; it < NS; ++it)
-          if (it * kThreads + tid < G::DH * G::DW) s_da[it * kThreads + tid] = sv[it];
-      }
+      for (int it = 0; it < NS; ++it)
+        if (it * kThreads + tid < G::DH * G::DW) s_da[it * kThreads + tid] = sv[it];
     } else {
 #pragma unroll
       for (int it = 0; it < NS; ++it)
@@ -594,7 +756,7 @@ __device__ __forceinline__ void level_body(const ffh::LevelKArgs &a, const ffh::
         s_cost[l] = cv[it];
         if (ev[it]) {
           if constexpr (!QUAD) s_cost[l] = evalc(i, j, i * n + ffk::flow_x(fv[it]), j * n + ffk::flow_y(fv[it]));
-          if constexpr (WF) inn = inner(i, j, i * n + ffk::flow_x(fv[it]), j * n + ffk::flow_y(fv[it]));
+          if constexpr (WF) inn = inner(i, j, ((i * n) << SB) + ffk::flow_x(fv[it]), ((j * n) << SB) + ffk::flow_y(fv[it]));
           cnt = owned(i, j);
         }
       }
@@ -617,8 +779,8 @@ __device__ __forceinline__ void level_body(const ffh::LevelKArgs &a, const ffh::
             i = gi0 + l % G::LW;
             j = gj0 + l / G::LW;
             const int32_t f = s_flow[l];
-            bx = i * n + ffk::flow_x(f);
-            by = j * n + ffk::flow_y(f);
+            bx = ((i * n) << SB) + ffk::flow_x(f);
+            by = ((j * n) << SB) + ffk::flow_y(f);
           },
           [&](int, int l, uint32_t c) { s_cost[l] = c; });
       __syncthreads();
@@ -691,19 +853,19 @@ __device__ __forceinline__ void level_body(const ffh::LevelKArgs &a, const ffh::
           // keeps the compiler from sinking the reads into the branches below
           asm volatile("" : "+v"(c0), "+v"(chs), "+v"(cvs), "+v"(f0), "+v"(fhs), "+v"(fvs));
           const bool set0 = c0 != kUnset;
-          const int x = i * n, y = j * n;
+          const int x = (i * n) << SB, y = (j * n) << SB, xmax = (W - 1) << SB, ymax = (H - 1) << SB;
           bool vb = false, vsame_h = false, vsame_0 = false;
           int32_t fh = 0;
           if (i + hdi >= 0 && i + hdi < Wn && chs != kUnset) {
             fh = fhs;
             const int tx = x + ffk::flow_x(fh), ty = y + ffk::flow_y(fh);
-            hv = !(set0 && fh == f0) && tx >= 0 && tx < W && ty >= 0 && ty < H;
+            hv = !(set0 && fh == f0) && tx >= 0 && tx <= xmax && ty >= 0 && ty <= ymax;
             if constexpr (WF) hin = inner(i, j, tx, ty);
           }
           if (j + vdj >= 0 && j + vdj < Hn && cvs != kUnset) {
             const int32_t fv = fvs;
             const int tx = x + ffk::flow_x(fv), ty = y + ffk::flow_y(fv);
-            vb = tx >= 0 && tx < W && ty >= 0 && ty < H;
+            vb = tx >= 0 && tx <= xmax && ty >= 0 && ty <= ymax;
             vsame_h = hv && fv == fh;
             vsame_0 = set0 && fv == f0;
             if constexpr (WF) vin = inner(i, j, tx, ty);
@@ -754,8 +916,8 @@ __device__ __forceinline__ void level_body(const ffh::LevelKArgs &a, const ffh::
               i = gi0 + l % G::LW;
               j = gj0 + l / G::LW;
               const int32_t f = s_flow[(e & 1) ? l + vdj * G::LW : l + hdi];
-              bx = i * n + ffk::flow_x(f);
-              by = j * n + ffk::flow_y(f);
+              bx = ((i * n) << SB) + ffk::flow_x(f);
+              by = ((j * n) << SB) + ffk::flow_y(f);
             },
             [&](int e, int l, uint32_t c) { atomicMin(&s_cost[l], (c << 2) | (uint32_t)(1 + (e & 1))); });
       } else if constexpr (QUAD) {
@@ -855,9 +1017,10 @@ __device__ __forceinline__ void level_body(const ffh::LevelKArgs &a, const ffh::
             const int tot1 = __popcll(__ballot(act1 && owned(i1, j1)));
             if ((tid & 63) == 0 && tot1) atomicAdd(&s_cnt, (unsigned)tot1);
             if constexpr (WF) {
-              enqueue2(act, act && inner(i, j, i * n + ffk::flow_x(fc), j * n + ffk::flow_y(fc)), (uint16_t)l, s_rlen,
-                       s_rblen);
-              enqueue2(act1, act1 && inner(i1, j1, i1 * n + ffk::flow_x(fc1), j1 * n + ffk::flow_y(fc1)),
+              enqueue2(act, act && inner(i, j, ((i * n) << SB) + ffk::flow_x(fc), ((j * n) << SB) + ffk::flow_y(fc)),
+                       (uint16_t)l, s_rlen, s_rblen);
+              enqueue2(act1,
+                       act1 && inner(i1, j1, ((i1 * n) << SB) + ffk::flow_x(fc1), ((j1 * n) << SB) + ffk::flow_y(fc1)),
                        (uint16_t)l1, s_rlen, s_rblen);
             } else {
               enqueue(act, (uint16_t)l, s_rlen);
@@ -878,8 +1041,8 @@ __device__ __forceinline__ void level_body(const ffh::LevelKArgs &a, const ffh::
             i = gi0 + l % G::LW;
             j = gj0 + l / G::LW;
             const int32_t fc = (int32_t)s_flags[l];
-            bx = i * n + ffk::flow_x(fc);
-            by = j * n + ffk::flow_y(fc);
+            bx = ((i * n) << SB) + ffk::flow_x(fc);
+            by = ((j * n) << SB) + ffk::flow_y(fc);
           },
           [&](int, int l, uint32_t c) {
             if (c < s_cost[l]) {
@@ -971,12 +1134,13 @@ __device__ __forceinline__ void level_body(const ffh::LevelKArgs &a, const ffh::
 // for the smaller weight-class tiles whose window lets six or seven
 // workgroups share a compute unit: the launch is bound by the latency of
 // its barrier-separated phases, which more resident workgroups hide.
-template <int TW, int TH, int kThreads, int EV, int HALO>
+template <int TW, int TH, int kThreads, int EV, int HALO, int RR = kR, bool SUB = false, bool SPX = false>
 constexpr int level_waves() {
   if constexpr (EV == 2) return 2;
-  if constexpr (EV != 4) return 4;
+  if constexpr (EV != 4 || (SPX && kThreads > 256)) return 4;  // (four entries of four rows in flight)
   using G = Geo<TW, TH, HALO>;
-  constexpr int lds = G::LH * G::LW * 14 + (G::LH + 12) * G::LW * 16;  // state, flags, queue; image a's rows
+  // state, flags, queue; image a's rows
+  constexpr int lds = G::LH * G::LW * 14 + (SUB ? 2 * G::LH + 35 : G::LH + 2 * (RR + 3)) * G::LW * 16;
   constexpr int fit = 160 * 1024 / lds * (kThreads / 64) / 4;           // waves per SIMD the LDS allows
   // a tile whose area is not a power of two (32x12) is sized for six or
   // seven resident workgroups
@@ -987,20 +1151,21 @@ constexpr int level_waves() {
 // One workgroup per (direction, tile) of one pair; XCD-aware order.
 template <int LOG2N, int TW, int TH, int kThreads, int EV, int HALO, int RR = kR>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
-    EV >= 3 ? level_waves<TW, TH, kThreads, EV, HALO>() : 1, level_waves<TW, TH, kThreads, EV, HALO>()))) void k_level(ffh::LevelKArgs a) {
+    EV >= 3 ? level_waves<TW, TH, kThreads, EV, HALO, RR>() : 1, level_waves<TW, TH, kThreads, EV, HALO, RR>()))) void k_level(ffh::LevelKArgs a) {
   const int tiles = a.tiles_x * ((a.Hn + TH - 1) / TH);
   const int wg = ffk::xcd_remap(blockIdx.x, gridDim.x);
   level_body<LOG2N, TW, TH, kThreads, EV, false, HALO, RR>(a, a.dir[wg / tiles], wg % tiles);
 }
 
-// A sub-scale stage (Sec. 3.3: patch scale a.sub_m on the grid of scale n):
-// the radius-3 descriptor-quad kernel reading both images' image-order maps.
-template <int LOG2N, int TW, int TH, int kThreads, int HALO>
+// A sub-scale stage (Sec. 3.3: patch scale a.sub_m on the grid of scale n) or
+// a subpixel scale (flows in 1/8 pixel), on the weight-class row maps.
+template <int LOG2N, int TW, int TH, int kThreads, int HALO, bool SPX>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
-    level_waves<TW, TH, kThreads, 3, HALO>(), level_waves<TW, TH, kThreads, 3, HALO>()))) void k_level_sub(ffh::LevelKArgs a) {
+    level_waves<TW, TH, kThreads, 4, HALO, kR, !SPX, SPX>(),
+    level_waves<TW, TH, kThreads, 4, HALO, kR, !SPX, SPX>()))) void k_level_sub(ffh::LevelKArgs a) {
   const int tiles = a.tiles_x * ((a.Hn + TH - 1) / TH);
   const int wg = ffk::xcd_remap(blockIdx.x, gridDim.x);
-  level_body<LOG2N, TW, TH, kThreads, 3, false, HALO, kR, true>(a, a.dir[wg / tiles], wg % tiles);
+  level_body<LOG2N, TW, TH, kThreads, 4, false, HALO, kR, !SPX, SPX>(a, a.dir[wg / tiles], wg % tiles);
 }
 
 // Float learned features (padded float maps in LevelKDir::Da/Db).
@@ -1065,15 +1230,6 @@ hipError_t launch_v(const ffh::LevelKArgs &a, const ffh::BatchStage *batch, hipS
   ffh::LevelKArgs b = a;
   b.tiles_x = (a.Wn + TW - 1) / TW;
   const int tiles = b.tiles_x * ((a.Hn + TH - 1) / TH);
-  if (a.sub_m) {
-    if constexpr (EV == 3 && RR == kR) {
-      hipLaunchKernelGGL((k_level_sub<LOG2N, TW, TH, THREADS, HALO>), dim3(tiles * a.ndir), dim3(THREADS), 0, stream,
-                         b);
-      return hipGetLastError();
-    } else {
-      return hipErrorInvalidValue;
-    }
-  }
   hipLaunchKernelGGL((k_level<LOG2N, TW, TH, THREADS, EV, HALO, RR>), dim3(tiles * a.ndir), dim3(THREADS), 0, stream,
                      b);
   return hipGetLastError();
@@ -1169,5 +1325,39 @@ hipError_t launch_n_rx(const ffh::LevelKArgs &a, int variant, hipStream_t stream
   }
 }
 
+// The weight-class kernels of the forms beside the plain radius-3 one:
+// patch radii 2 and 4 (maps of that radius), sub-scale stages, subpixel
+// flows.  `tile` is an index of wx_variant in ff_level.hip.
+template <int LOG2N, int TW, int TH, int THREADS, int HALO>
+hipError_t launch_wx_tile(const ffh::LevelKArgs &a, hipStream_t stream) {
+  if (a.radius == 2) return launch_v<LOG2N, TW, TH, THREADS, 4, HALO, 2>(a, nullptr, stream);
+  if (a.radius == 4) return launch_v<LOG2N, TW, TH, THREADS, 4, HALO, 4>(a, nullptr, stream);
+  ffh::LevelKArgs b = a;
+  b.tiles_x = (a.Wn + TW - 1) / TW;
+  const dim3 grid(b.tiles_x * ((a.Hn + TH - 1) / TH) * a.ndir);
+  if (a.spx) {
+    hipLaunchKernelGGL((k_level_sub<LOG2N, TW, TH, THREADS, HALO, true>), grid, dim3(THREADS), 0, stream, b);
+  } else if constexpr (LOG2N > 0) {
+    if (!a.sub_m) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_level_sub<LOG2N, TW, TH, THREADS, HALO, false>), grid, dim3(THREADS), 0, stream, b);
+  } else {
+    return hipErrorInvalidValue;  // no sub-scale below the finest scale
+  }
+  return hipGetLastError();
+}
+
+template <int LOG2N>
+hipError_t launch_wx(const ffh::LevelKArgs &a, int tile, hipStream_t stream) {
+  switch (tile) {
+    case 0: return launch_wx_tile<LOG2N, 32, 12, 256, 2>(a, stream);
+    case 1: return launch_wx_tile<LOG2N, 16, 16, 256, 2>(a, stream);
+    case 2: return launch_wx_tile<LOG2N, 16, 16, 1024, ffh::kLevelHalo>(a, stream);
+    case 3: return launch_wx_tile<LOG2N, 8, 8, 1024, ffh::kLevelHalo>(a, stream);
+    case 4: return launch_wx_tile<LOG2N, 8, 8, 1024, 4>(a, stream);
+    case 5: return launch_wx_tile<LOG2N, 4, 4, 1024, 4>(a, stream);
+    case 6: return launch_wx_tile<LOG2N, 8, 8, 256, ffh::kLevelHalo>(a, stream);
+    default: return hipErrorInvalidValue;
+  }
+}
 
 }  // namespace

@@ -19,4 +19,8 @@ hipError_t launch_level_r4_scale0(const LevelKArgs &a, int variant, hipStream_t 
   return launch_n_rx<0, 4>(a, variant, stream);
 }
 
+hipError_t launch_level_wx_scale0(const LevelKArgs &a, int tile, hipStream_t stream) {
+  return launch_wx<0>(a, tile, stream);
+}
+
 }  // namespace ffh

@@ -19,4 +19,8 @@ hipError_t launch_level_r4_scale2(const LevelKArgs &a, int variant, hipStream_t 
   return launch_n_rx<2, 4>(a, variant, stream);
 }
 
+hipError_t launch_level_wx_scale2(const LevelKArgs &a, int tile, hipStream_t stream) {
+  return launch_wx<2>(a, tile, stream);
+}
+
 }  // namespace ffh
