@@ -99,8 +99,9 @@ typedef struct {
      * per-step kernels; ff_flow_fields_batched and ff_flow_fields_f32
      * return FF_ERR_UNSUPPORTED for it. */
     int32_t subpixel;
-    /* host, nullable: launch tables of this call (NULL: the built-in table,
-     * see ff_default_tuning); an entry out of range is FF_ERR_ARG. */
+    /* host, nullable: launch tables of this call; an entry out of range is
+     * FF_ERR_ARG.  NULL: the built-in run lengths, with the byte-descriptor
+     * variant of every scale chosen by its grid's size. */
     const ff_tuning *tuning;
     /* Seed candidates (Sec. 3.1: the l entries of a kd-tree leaf, ranked by
      * matching error, Eq. 1 / Eq. 4; l = 8 in Sec. 4.1): 0 or 1 = the exact
@@ -142,7 +143,8 @@ typedef struct {
     int32_t subscales;
 } ff_params;
 
-/* The built-in launch tables (host): written to *out. */
+/* The built-in launch tables (host; the variants of a 1024 x 436 pair): written
+ * to *out. */
 void ff_default_tuning(ff_tuning *out);
 
 /* Library version (host). */
@@ -222,9 +224,9 @@ size_t ff_nn_topl_scratch_bytes(int32_t W, int32_t H, int32_t nc);
  * nearest neighbours): ranked by (squared L2 distance of the level-1
  * descriptors, q.y*W + q.x).  cand: uint64 [cells][l] output, entry
  * (distance << 32) | q, ~0 where the image has fewer than l pixels.
- * Computed exactly as l passes of ff_init_nn's matrix-core search, pass k
- * leaving out every pixel whose (distance, index) is at most pass k-1's
- * result.  desc_a1, desc_b1: as for ff_init_nn;
+ * Computed exactly: ff_init_nn's matrix-core search leaves the nearest distance
+ * of every group of pixels, and the l groups that can hold the l nearest are
+ * ranked pixel by pixel.  desc_a1, desc_b1: as for ff_init_nn;
  * nb_scratch: as for ff_init_nn; scratch: device, ff_nn_topl_scratch_bytes
  * (FF_ERR_WORKSPACE if smaller); 1 <= l <= 8. */
 ff_status ff_nn_topl(const uint8_t *desc_a1, const uint8_t *desc_b1, int32_t W, int32_t H, int32_t nc, int32_t l,
@@ -475,12 +477,12 @@ ff_status ff_cost_f32_fwd(const float *f1, const float *f2, int32_t W, int32_t H
 
 /* Gradient of sum_e grad_cost[e] * cost[e] with respect to f1 and f2
  * (d/df1 = +2 g (f1 - f2), d/df2 = -2 g (f1 - f2) at every patch position).
- * Contributions are summed in 64-bit fixed point (2^-32 units) with integer
- * atomics, so the result is deterministic.  A term |2 g (f1 - f2)| of 2^31
+ * Contributions are summed in 64-bit fixed point (2^-32 units), in integers,
+ * so the result is deterministic whatever the order.  A term |2 g (f1 - f2)| of 2^31
  * or more, or a partial sum outside the int64 range, is detected and counted in
  * the last word of acc_scratch; when that count is nonzero every value of
  * grad_f1 and grad_f2 is NaN (never a wrapped sum).  acc_scratch: int64
- * [2 * H * W * 16 + 1] scratch (cleared here); grad_f1, grad_f2: float32
+ * [2 * H * W * 16 + 1] scratch (contents on entry do not matter); grad_f1, grad_f2: float32
  * [H][W][16] outputs (overwritten). */
 ff_status ff_cost_f32_bwd(const float *f1, const float *f2, int32_t W, int32_t H, int32_t n, int32_t radius,
                           const int32_t *entries, int32_t count, const float *grad_cost, int64_t *acc_scratch,

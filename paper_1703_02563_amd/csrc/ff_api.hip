@@ -38,6 +38,23 @@ ffh::Tuning tuning_of(const ff_tuning *t) {
   return u;
 }
 
+// The tables of a call on `count` frames (W, H): the caller's, or the built-in
+// run lengths with the variants of these grid sizes.
+ffh::Tuning call_tables(const ff_params *p, const int (*sizes)[2], int count, int ndir) {
+  ffh::Tuning t = tuning_of(p->tuning);
+  if (!p->tuning)
+    for (int lv = 0; lv < ffh::kTuneScales; ++lv) {
+      t.variant[lv] = ffh::level_pick_variant(lv, sizes, count, ndir);
+      t.passes[lv] = 3;
+    }
+  return t;
+}
+
+ffh::Tuning call_tables(const ff_params *p, int W, int H, int ndir) {
+  const int size[1][2] = {{W, H}};
+  return call_tables(p, size, 1, ndir);
+}
+
 bool params_ok(const ff_params *p) {
   return p && p->levels >= 1 && p->levels <= kMaxLevels && p->iters >= 1 && p->iters <= 64 && p->radius >= 0 &&
          p->radius <= 7 && p->R_num >= 0 && p->R_den >= 1 && p->R_num <= 1 << 20 && p->R_den <= 1 << 20 &&
@@ -257,7 +274,7 @@ hipError_t run_level_blocked(ffh::LevelKArgs k, int W, int H, int lv, const ff_p
   k.seed = p->seed;
   k.T = T;
   k.radius = p->radius;
-  const ffh::Tuning tun = tuning_of(p->tuning);
+  const ffh::Tuning tun = call_tables(p, W, H, k.ndir);
   k.variant = k.fcost ? tun.variant_f32[lv] : tun.variant[lv];
   int runs[64][2];
   const int m = level_runs(tun, lv, T, k.fcost, runs);
@@ -874,7 +891,12 @@ ff_status ff_flow_fields_batched(const ff_pair *pairs, int32_t npairs, const ff_
   }
   if ((e = ffh::launch_batch_nn(keysf, nn, resolve, s)) != hipSuccess) return FF_ERR_LAUNCH;
   // scales, coarse to fine: one persistent launch per run of passes
-  const ffh::Tuning tun = tuning_of(params->tuning);
+  int sizes[ffh::kMaxBatch][2];
+  for (int i = 0; i < npairs; ++i) {
+    sizes[i][0] = pairs[i].W;
+    sizes[i][1] = pairs[i].H;
+  }
+  const ffh::Tuning tun = call_tables(params, sizes, npairs, 2);
   for (int lv = L - 1; lv >= 0; --lv) {
     const int n = 1 << lv;
     bool maps_fit = true;
@@ -1267,7 +1289,7 @@ ff_status ff_flow_fields(const uint8_t *img1, const uint8_t *img2, int32_t W, in
 
   // descriptors of both images at every scale; the weight-class row maps
   // only where the table's level-kernel variant evaluates on them
-  const ffh::Tuning tun = tuning_of(params->tuning);
+  const ffh::Tuning tun = call_tables(params, W, H, nd);
   // subpixel flows on the blocked kernels: radius 3, checkerboard order, maps
   // addressed with 32-bit offsets
   bool spx = sb != 0 && r == 3 && !params->raster && !params->subscales;

@@ -118,6 +118,44 @@ namespace ffh {
 
 const Tuning &default_tuning() { return kDefaultTuning; }
 
+// The variant of scale 2^log2n for a call's grids (its pairs and directions
+// together), where the caller gives no table.  What decides is how many
+// workgroups a tile gives the 256 compute units; per scale, the fastest of
+// all variants in a sweep over frames from 96x64 to 1920x1080 (us per call):
+//  * 4x4 tiles with 1024 threads while they fit one round of one workgroup
+//    per unit (1792 cells of 1024x436 at n = 16: 655 against 664 on 8x8; 2040
+//    cells, 270 workgroups: 423 against 398);
+//  * 8x8 tiles with 1024 threads while those fit one round (4800 cells at
+//    160x120, n = 2: 147 against 150 with 256 threads and 170 on 16x16; 8160
+//    cells, 270 workgroups: 429 against 398);
+//  * 16x16 tiles with 1024 threads where those fill three quarters of a round
+//    (27904 cells of 1024x436 at n = 4: 655 as with the next, and the costlier
+//    evaluations gain: 1684 against 1731 for subpixel flows);
+//  * 8x8 tiles with 256 threads while four per unit are resident at once
+//    (19200 cells at 160x120, n = 1: 146 against 158 on 16x16; 32400 cells at
+//    480x270, n = 2: 398 against 418; 49152 cells at 256x192, n = 1: 310
+//    against 288);
+//  * above, 16x16 descriptor quads, and at n = 1 the weight-class kernel on
+//    32x12 tiles once they give four workgroups per unit (640x480: 563 against
+//    602; 480x270: 407 against 400).
+int level_pick_variant(int log2n, const int (*sizes)[2], int count, int ndir) {
+  constexpr long long kUnits = 256;
+  auto workgroups = [&](int tw, int th) {
+    long long t = 0;
+    for (int k = 0; k < count; ++k) {
+      const int Wn = (sizes[k][0] + (1 << log2n) - 1) >> log2n, Hn = (sizes[k][1] + (1 << log2n) - 1) >> log2n;
+      t += (long long)((Wn + tw - 1) / tw) * ((Hn + th - 1) / th);
+    }
+    return t * ndir;
+  };
+  if (workgroups(4, 4) <= kUnits) return 32;
+  if (workgroups(8, 8) <= kUnits) return 27;
+  const long long big = workgroups(16, 16);
+  if (big <= kUnits && 4 * big >= 3 * kUnits) return 30;
+  if (workgroups(8, 8) <= 4 * kUnits) return 14;
+  return log2n == 0 && workgroups(32, 12) >= 4 * kUnits ? 31 : 11;
+}
+
 int level_variant_count() { return kNumVariants + 1; }  // + the step-wise schedule
 
 int level_variant_count_f32() { return kNumVariantsF32; }

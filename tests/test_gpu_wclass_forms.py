@@ -1,7 +1,9 @@
 """The weight-class kernels beside the plain radius-3 one (subpixel flows,
 sub-scale stages, patch radii 2 and 4) on every tile they come in, bit-exact
 against the oracle on frames whose interior (cells and targets the patch
-radius away from the border) is empty, one pixel wide, or larger than a tile."""
+radius away from the border) is empty, one pixel wide, or larger than a tile;
+and the tables chosen by grid size against the same call with an explicit
+table."""
 import os
 
 import numpy as np
@@ -47,3 +49,12 @@ def test_every_tile_equals_the_oracle(form, W, H):
     for v in (31, 11, 30, 26, 27, 32, 14):  # one table index per tile
         tun = ff.default_tuning().replace(variant=[v] * 7, passes=[0] * 7)
         same(ff.flow_fields(da, db, ff.Params(levels=L, iters=T, tuning=tun, **kw)), ref)
+
+
+@pytest.mark.parametrize("form", [None, "subpixel", "subscales", "radius4"])
+@pytest.mark.parametrize("W,H,L", [(97, 65, 3), (160, 120, 3), (321, 243, 4), (513, 261, 5), (640, 485, 5)])
+def test_tables_by_grid_size_leave_results_alone(form, W, H, L):
+    kw = FORMS[form][0] if form else {}
+    a, b = (torch.from_numpy(t).cuda() for t in frames(W, H, W))
+    same(ff.flow_fields(a, b, ff.Params(levels=L, iters=3, **kw)),
+         ff.flow_fields(a, b, ff.Params(levels=L, iters=3, tuning=ff.default_tuning(), **kw)))
