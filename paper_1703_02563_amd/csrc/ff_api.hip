@@ -116,7 +116,7 @@ ScaleSteps scale_steps(const ff_params *p, int lv) {
 
 // Device workspace of ff_flow_fields, carved in this order.
 struct Layout {
-  size_t hsum, blur, desc[2][kMaxLevels], wform[2][kMaxLevels], sdesc[2][kMaxLevels], swform[2][kMaxLevels], desc1, desc1e, nb, keys, topl,
+  size_t blur, desc[2][kMaxLevels], wform[2][kMaxLevels], sdesc[2][kMaxLevels], swform[2][kMaxLevels], desc1, desc1e, nb, keys, topl,
       cand, grids, sgrids, evals, total;
   size_t N, Npad, M;
   int L;
@@ -136,7 +136,6 @@ Layout layout(int W, int H, const ff_params *p) {
   const int nc = 1 << (p->levels - 1);
   l.M = (size_t)ceil_div(W, nc) * ceil_div(H, nc);
   size_t off = 0;
-  l.hsum = off; off = align256(off + 2 * l.L * l.N * sizeof(uint16_t));
   l.blur = off; off = align256(off + 2 * l.L * l.N);
   for (int im = 0; im < 2; ++im)
     for (int lv = 0; lv < l.L; ++lv) {
@@ -419,7 +418,7 @@ ff_status ff_descriptors(const uint8_t *img, int32_t W, int32_t H, int32_t n, ui
   jobs.W = W;
   jobs.H = H;
   jobs.count = 1;
-  jobs.job[0] = {img, hsum, blurred, desc, desc_rowmajor, wform, n};
+  jobs.job[0] = {img, blurred, desc, desc_rowmajor, wform, n};
   return from_hip(ffh::launch_descriptors(jobs, (hipStream_t)stream));
 }
 
@@ -821,7 +820,6 @@ ff_status ff_batch_table(const ff_pair *pairs, int32_t npairs, const ff_params *
     for (int im = 0; im < 2; ++im) {
       for (int lv = 0; lv < L; ++lv) {
         const size_t z = (size_t)(im * L + lv);
-        t.hsum[im][lv] = reinterpret_cast<uint16_t *>(b + lay.hsum) + z * lay.N;
         t.blur[im][lv] = reinterpret_cast<uint8_t *>(b + lay.blur) + z * lay.N;
         t.desc[im][lv] = reinterpret_cast<uint8_t *>(b + lay.desc[im][lv]);
         t.wform[im][lv] = reinterpret_cast<uint8_t *>(b + lay.wform[im][lv]);
@@ -873,9 +871,20 @@ ff_status ff_flow_fields_batched(const ff_pair *pairs, int32_t npairs, const ff_
     st.total = st.prefix[npairs];
   };
   hipError_t e;
-  // descriptors: (pair, image * L + scale, row)
-  fill([&](int, int H) { return 2 * L * H; });
-  if ((e = ffh::launch_batch_descriptors(st, s)) != hipSuccess) return FF_ERR_LAUNCH;
+  int sizes[ffh::kMaxBatch][2], max_width = 0;
+  for (int i = 0; i < npairs; ++i) {
+    sizes[i][0] = pairs[i].W;
+    sizes[i][1] = pairs[i].H;
+    max_width = pairs[i].W > max_width ? pairs[i].W : max_width;
+  }
+  const ffh::Tuning tun = call_tables(params, sizes, npairs, 2);
+  // descriptors: blur (pair, image * L + scale, tile), then the maps' rows
+  fill([&](int W, int H) { return ffh::batch_blur_items(W, H, L); });
+  const ffh::BatchStage blur = st;
+  for (int lv = 0; lv < L; ++lv)
+    if (ffh::level_uses_wform(tun.variant[lv], 3, lv)) st.wform_scales |= 1 << lv;
+  fill([&](int, int H) { return ffh::batch_desc_items(H, L); });
+  if ((e = ffh::launch_batch_descriptors(blur, st, max_width, s)) != hipSuccess) return FF_ERR_LAUNCH;
   // NN: keys (pair, direction, 256 queries), search items, resolve items
   ffh::BatchStage keysf = st, nn = st, resolve = st;
   keysf.n = nn.n = resolve.n = nc;
@@ -891,12 +900,6 @@ ff_status ff_flow_fields_batched(const ff_pair *pairs, int32_t npairs, const ff_
   }
   if ((e = ffh::launch_batch_nn(keysf, nn, resolve, s)) != hipSuccess) return FF_ERR_LAUNCH;
   // scales, coarse to fine: one persistent launch per run of passes
-  int sizes[ffh::kMaxBatch][2];
-  for (int i = 0; i < npairs; ++i) {
-    sizes[i][0] = pairs[i].W;
-    sizes[i][1] = pairs[i].H;
-  }
-  const ffh::Tuning tun = call_tables(params, sizes, npairs, 2);
   for (int lv = L - 1; lv >= 0; --lv) {
     const int n = 1 << lv;
     bool maps_fit = true;
@@ -1310,8 +1313,7 @@ ff_status ff_flow_fields(const uint8_t *img1, const uint8_t *img2, int32_t W, in
       const int z = im * L + lv;
       desc[im][lv] = reinterpret_cast<uint8_t *>(base + lay.desc[im][lv]);
       // scales below lmin only give the NN its level-1 descriptors
-      jobs.job[z] = {img[im], reinterpret_cast<uint16_t *>(base + lay.hsum) + (size_t)z * lay.N,
-                     reinterpret_cast<uint8_t *>(base + lay.blur) + (size_t)z * lay.N,
+      jobs.job[z] = {img[im], reinterpret_cast<uint8_t *>(base + lay.blur) + (size_t)z * lay.N,
                      lv < lmin ? nullptr : desc[im][lv], lv == 0 ? desc1[im] : nullptr,
                      wform_used(lv) ? reinterpret_cast<uint8_t *>(base + lay.wform[im][lv]) : nullptr, 1 << lv, r};
     }
@@ -1330,8 +1332,7 @@ ff_status ff_flow_fields(const uint8_t *img1, const uint8_t *img2, int32_t W, in
         const int z = sj.count++;
         sdesc[im][lv] = reinterpret_cast<uint8_t *>(base + lay.sdesc[im][lv]);
         if (r == 3 && !sb && !params->raster) swform[im][lv] = reinterpret_cast<uint8_t *>(base + lay.swform[im][lv]);
-        sj.job[z] = {img[im], reinterpret_cast<uint16_t *>(base + lay.hsum) + (size_t)z * lay.N,
-                     reinterpret_cast<uint8_t *>(base + lay.blur) + (size_t)z * lay.N, sdesc[im][lv], nullptr,
+        sj.job[z] = {img[im], reinterpret_cast<uint8_t *>(base + lay.blur) + (size_t)z * lay.N, sdesc[im][lv], nullptr,
                      swform[im][lv], subscale_of(lv)};
       }
     if ((e = ffh::launch_descriptors(sj, s)) != hipSuccess) return FF_ERR_LAUNCH;

@@ -30,13 +30,16 @@ using ffk::clampi;
 // definition (exact in any order), in one pass over the image.
 constexpr int kBT = 64, kBHmax = 32, kBS = kBT + 2 * kBHmax;  // tile, largest half-width (n <= 64), staged side
 
-__global__ __launch_bounds__(256) void k_blur(ffh::DescJobs jobs) {
-  __shared__ uint8_t s_in[kBS * kBS];
-  __shared__ uint16_t s_row[kBS * kBT];  // (2h + 1) * 255 fits 16 bits
-  const ffh::DescJob &jb = jobs.job[blockIdx.z];
-  const int W = jobs.W, H = jobs.H;
-  const int h = max(1, jb.n >> 1), S = kBT + 2 * h;  // staged rows and columns
-  const int x0 = blockIdx.x * kBT, y0 = blockIdx.y * kBT;
+struct BlurTile {
+  uint8_t in[kBS * kBS];
+  uint16_t row[kBS * kBT];  // (2h + 1) * 255 fits 16 bits
+};
+
+__device__ __forceinline__ void blur_tile(BlurTile &sm, const uint8_t *img, uint8_t *blurred, int W, int H, int n,
+                                          int x0, int y0) {
+  uint8_t *s_in = sm.in;
+  uint16_t *s_row = sm.row;
+  const int h = max(1, n >> 1), S = kBT + 2 * h;  // staged rows and columns
   const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
   // staged rows ty + 4u, columns tx and tx + 64: 16 loads in flight per
   // thread before their LDS stores (rows past S read a clamped row, unused)
@@ -45,7 +48,7 @@ __global__ __launch_bounds__(256) void k_blur(ffh::DescJobs jobs) {
     uint32_t va[8], vb[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      const uint8_t *row = jb.img + (size_t)clampi(y0 - h + u0 + ty + 4 * u, H - 1) * W;
+      const uint8_t *row = img + (size_t)clampi(y0 - h + u0 + ty + 4 * u, H - 1) * W;
       va[u] = row[xa];
       vb[u] = row[xb];
     }
@@ -93,23 +96,15 @@ __global__ __launch_bounds__(256) void k_blur(ffh::DescJobs jobs) {
         sum -= col[(r - 1) * kBT];
       }
       const int y = y0 + r0 + r;
-      if (x < W && y < H) jb.blurred[(size_t)y * W + x] = (uint8_t)((sum + area / 2) / area);
+      if (x < W && y < H) blurred[(size_t)y * W + x] = (uint8_t)((sum + area / 2) / area);
     }
   }
 }
 
-// The 16 samples of the scale-n descriptor of pixel (x, y) (in the image).
-__device__ __forceinline__ uint4 descriptor_at(const uint8_t *blurred, int W, int H, int n, int x, int y) {
-  uint32_t w[4];
-#pragma unroll
-  for (int gy = 0; gy < 4; ++gy) {
-    const uint8_t *row = blurred + (size_t)clampi(y + n * (2 * gy - 3), H - 1) * W;
-    uint32_t v = 0;
-#pragma unroll
-    for (int gx = 0; gx < 4; ++gx) v |= (uint32_t)row[clampi(x + n * (2 * gx - 3), W - 1)] << (8 * gx);
-    w[gy] = v;
-  }
-  return make_uint4(w[0], w[1], w[2], w[3]);
+__global__ __launch_bounds__(256) void k_blur(ffh::DescJobs jobs) {
+  __shared__ BlurTile sm;
+  const ffh::DescJob &jb = jobs.job[blockIdx.z];
+  blur_tile(sm, jb.img, jb.blurred, jobs.W, jobs.H, jb.n, blockIdx.x * kBT, blockIdx.y * kBT);
 }
 
 // Weight-class row entry (wform_index) of pixel x of blurred row `row`, for
@@ -135,13 +130,10 @@ __device__ __forceinline__ uint4 wform_entry(const uint8_t *row, int W, int n, i
 // blurred row y itself.  Dynamic LDS: 5 * row_stride(W).
 __host__ __device__ __forceinline__ int desc_row_stride(int W) { return (W + 15) & ~15; }
 
-__global__ __launch_bounds__(256) void k_desc(ffh::DescJobs jobs) {
-  extern __shared__ uint8_t s_rows[];
-  const ffh::DescJob &jb = jobs.job[blockIdx.y];
-  const int W = jobs.W, H = jobs.H, n = jb.n, l2 = ffk::map_log2(n);
-  const int P = ffk::desc_pad(n), Wp = W + 2 * P, Hp = H + 2 * P;
-  const int yp = blockIdx.x, Ws = desc_row_stride(W);
-  if (yp >= Hp) return;  // workgroup-uniform
+__device__ __forceinline__ void desc_row(uint8_t *s_rows, const ffh::DescJob &jb, int W, int H, int yp) {
+  const int n = jb.n, l2 = ffk::map_log2(n);
+  const int P = ffk::desc_pad(n), Wp = W + 2 * P;
+  const int Ws = desc_row_stride(W);
   const int yr = yp - P, y = clampi(yr, H - 1);
   // staged rows g = 0..3: y + n(2g - 3); g = 4: y itself (weight-class map)
   const int nrows = jb.wform ? 5 : 4;
@@ -186,78 +178,45 @@ __global__ __launch_bounds__(256) void k_desc(ffh::DescJobs jobs) {
   }
 }
 
-// ---- batches: items = (pair, image * L + scale, row) ---------------------
-struct RowItem {
-  const ffh::BatchPair *bp;
-  int im, lv, y;
-};
-
-__device__ __forceinline__ RowItem row_item(const ffh::BatchStage &st, int item) {
-  const int p = ffk::batch_pair(st.prefix, st.npairs, item);
-  const ffh::BatchPair &bp = st.pairs[p];
-  const int local = item - st.prefix[p];
-  const int z = local / bp.H;
-  return {&bp, z / st.L, z % st.L, local % bp.H};
+__global__ __launch_bounds__(256) void k_desc(ffh::DescJobs jobs) {
+  extern __shared__ uint8_t s_rows[];
+  const ffh::DescJob &jb = jobs.job[blockIdx.y];
+  if ((int)blockIdx.x >= jobs.H + 2 * ffk::desc_pad(jb.n)) return;  // workgroup-uniform
+  desc_row(s_rows, jb, jobs.W, jobs.H, blockIdx.x);
 }
 
-__global__ __launch_bounds__(256) void k_hsum_batch(ffh::BatchStage st) {
+// ---- batches: persistent launches over the same work units ---------------
+// (pixel-wise separable sums through a row-sum buffer and descriptors straight
+// from global memory took 624 us for eight pairs of 2.1 Mpx in all, weight-class
+// maps of every scale included; the units of the single-pair kernels, and
+// those maps only where a variant reads them, 306 us)
+
+// Items (pair, image * L + scale, 64 x 64 tile).
+__global__ __launch_bounds__(256) void k_blur_batch(ffh::BatchStage st) {
+  __shared__ BlurTile sm;
   ffk::for_items(st.total, [&](int item) {
-    const RowItem r = row_item(st, item);
-    const int W = r.bp->W, h = max(1, (1 << r.lv) >> 1);
-    const uint8_t *row = r.bp->img[r.im] + (size_t)r.y * W;
-    uint16_t *out = r.bp->hsum[r.im][r.lv] + (size_t)r.y * W;
-    for (int x = threadIdx.x; x < W; x += blockDim.x) {
-      uint32_t s = 0;
-      for (int dx = -h; dx <= h; ++dx) s += row[clampi(x + dx, W - 1)];
-      out[x] = (uint16_t)s;
-    }
+    const int p = ffk::batch_pair(st.prefix, st.npairs, item);
+    const ffh::BatchPair &bp = st.pairs[p];
+    const int tx = (bp.W + kBT - 1) / kBT, tiles = tx * ((bp.H + kBT - 1) / kBT);
+    const int local = item - st.prefix[p], z = local / tiles, t = local % tiles, im = z / st.L, lv = z % st.L;
+    blur_tile(sm, bp.img[im], bp.blur[im][lv], bp.W, bp.H, 1 << lv, (t % tx) * kBT, (t / tx) * kBT);
+    __syncthreads();  // the next item stages its tile
   });
 }
 
-__global__ __launch_bounds__(256) void k_vsum_batch(ffh::BatchStage st) {
-  ffk::for_items(st.total, [&](int item) {
-    const RowItem r = row_item(st, item);
-    const int W = r.bp->W, H = r.bp->H, h = max(1, (1 << r.lv) >> 1);
-    const uint32_t area = (uint32_t)((2 * h + 1) * (2 * h + 1));
-    const uint16_t *hs = r.bp->hsum[r.im][r.lv];
-    uint8_t *out = r.bp->blur[r.im][r.lv] + (size_t)r.y * W;
-    for (int x = threadIdx.x; x < W; x += blockDim.x) {
-      uint32_t s = 0;
-      for (int dy = -h; dy <= h; ++dy) s += hs[(size_t)clampi(r.y + dy, H - 1) * W + x];
-      out[x] = (uint8_t)((s + area / 2) / area);
-    }
-  });
-}
-
-// Item (pair, image, scale, image row y): padded row y + P, and for the
-// first and last image rows also the border rows they replicate; scale 1
-// items also write the row-major copy used by the NN seed.
+// Items (pair, scale, image, stored row).
 __global__ __launch_bounds__(256) void k_desc_batch(ffh::BatchStage st) {
+  extern __shared__ uint8_t s_rows[];
   ffk::for_items(st.total, [&](int item) {
-    const RowItem r = row_item(st, item);
-    const int W = r.bp->W, H = r.bp->H, n = 1 << r.lv;
-    const int P = ffk::desc_pad(n), Wp = W + 2 * P;
-    const uint8_t *b = r.bp->blur[r.im][r.lv];
-    uint4 *map = reinterpret_cast<uint4 *>(r.bp->desc[r.im][r.lv]);
-    const int yp0 = r.y == 0 ? 0 : r.y + P, yp1 = r.y == H - 1 ? H + 2 * P : r.y + P + 1;
-    for (int c = threadIdx.x; c < Wp; c += blockDim.x) {
-      const int xr = ffk::desc_pixel(c, r.lv, Wp) - P;
-      const uint4 d = descriptor_at(b, W, H, n, clampi(xr, W - 1), r.y);
-      for (int yp = yp0; yp < yp1; ++yp) map[(size_t)yp * Wp + c] = d;
-      if (r.lv == 0 && xr >= 0 && xr < W) reinterpret_cast<uint4 *>(r.bp->desc1[r.im])[(size_t)r.y * W + xr] = d;
-    }
-    // weight-class rows: stored row y + 3n, the first and last image rows
-    // replicated into the 3n border rows
-    uint4 *wmap = reinterpret_cast<uint4 *>(r.bp->wform[r.im][r.lv]);
-    if (wmap) {
-      const int Pw = ffk::kWformPad * n;
-      const int wy0 = r.y == 0 ? 0 : r.y + Pw, wy1 = r.y == H - 1 ? H + 2 * Pw : r.y + Pw + 1;
-      const uint8_t *brow = b + (size_t)r.y * W;
-      for (int x = threadIdx.x; x < W; x += blockDim.x) {
-        const uint4 e = wform_entry(brow, W, n, x);
-        for (int yw = wy0; yw < wy1; ++yw) wmap[(size_t)yw * W + x] = e;
-      }
-    }
+    const int p = ffk::batch_pair(st.prefix, st.npairs, item);
+    const ffh::BatchPair &bp = st.pairs[p];
+    int local = item - st.prefix[p], lv = 0;
+    while (local >= 2 * (bp.H + 2 * ffk::desc_pad(1 << lv))) local -= 2 * (bp.H + 2 * ffk::desc_pad(1 << lv++));
+    const int Hp = bp.H + 2 * ffk::desc_pad(1 << lv), im = local / Hp;
+    const ffh::DescJob jb = {bp.img[im], bp.blur[im][lv], bp.desc[im][lv], lv == 0 ? bp.desc1[im] : nullptr,
+                             (st.wform_scales >> lv) & 1 ? bp.wform[im][lv] : nullptr, 1 << lv, 3};
+    desc_row(s_rows, jb, bp.W, bp.H, local % Hp);
+    __syncthreads();  // the next item stages its rows
   });
 }
 
@@ -265,12 +224,32 @@ __global__ __launch_bounds__(256) void k_desc_batch(ffh::BatchStage st) {
 
 namespace ffh {
 
-hipError_t launch_batch_descriptors(const BatchStage &rows, hipStream_t stream) {
-  if (rows.total <= 0) return hipSuccess;
-  const dim3 grid(((std::min(rows.total, 4096) + 7) / 8) * 8);
-  hipLaunchKernelGGL(k_hsum_batch, grid, dim3(256), 0, stream, rows);
-  hipLaunchKernelGGL(k_vsum_batch, grid, dim3(256), 0, stream, rows);
-  hipLaunchKernelGGL(k_desc_batch, grid, dim3(256), 0, stream, rows);
+int batch_blur_items(int W, int H, int L) { return 2 * L * ((W + kBT - 1) / kBT) * ((H + kBT - 1) / kBT); }
+
+int batch_desc_items(int H, int L) {
+  int rows = 0;
+  for (int lv = 0; lv < L; ++lv) rows += 2 * (H + 2 * ffk::desc_pad(1 << lv));
+  return rows;
+}
+
+// Dynamic LDS of the descriptor rows of a W-wide image.
+static hipError_t desc_lds(const void *kernel, int W, size_t *lds) {
+  *lds = 5 * (size_t)desc_row_stride(W);
+  if (*lds > 160 * 1024) return hipErrorInvalidValue;
+  if (*lds > 64 * 1024)  // rows wider than 12 K pixels
+    return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)*lds);
+  return hipSuccess;
+}
+
+hipError_t launch_batch_descriptors(const BatchStage &tiles, const BatchStage &rows, int max_width,
+                                    hipStream_t stream) {
+  if (tiles.total <= 0 || rows.total <= 0) return hipSuccess;
+  size_t lds;
+  const hipError_t e = desc_lds(reinterpret_cast<const void *>(k_desc_batch), max_width, &lds);
+  if (e != hipSuccess) return e;
+  auto grid = [](int total) { return dim3(((std::min(total, 4096) + 7) / 8) * 8); };
+  hipLaunchKernelGGL(k_blur_batch, grid(tiles.total), dim3(256), 0, stream, tiles);
+  hipLaunchKernelGGL(k_desc_batch, grid(rows.total), dim3(256), lds, stream, rows);
   return hipGetLastError();
 }
 
@@ -282,13 +261,9 @@ hipError_t launch_descriptors(const DescJobs &jobs, hipStream_t stream) {
   hipLaunchKernelGGL(k_blur, gb, dim3(256), 0, stream, jobs);
   int pmax = 0;
   for (int k = 0; k < jobs.count; ++k) pmax = std::max(pmax, ffk::desc_pad(jobs.job[k].n));
-  const size_t lds = 5 * (size_t)desc_row_stride(jobs.W);
-  if (lds > 160 * 1024) return hipErrorInvalidValue;
-  if (lds > 64 * 1024) {  // rows wider than 16 K pixels
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_desc),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-  }
+  size_t lds;
+  const hipError_t e = desc_lds(reinterpret_cast<const void *>(k_desc), jobs.W, &lds);
+  if (e != hipSuccess) return e;
   const dim3 gpad(jobs.H + 2 * pmax, jobs.count);
   hipLaunchKernelGGL(k_desc, gpad, dim3(256), lds, stream, jobs);
   return hipGetLastError();

@@ -14,7 +14,6 @@ constexpr int kMaxDirs = 2;    // forward and backward field in one launch
 // One scale-space descriptor job: image -> blurred -> descriptors at scale n.
 struct DescJob {
   const uint8_t *img;
-  uint16_t *hsum;
   uint8_t *blurred;
   uint8_t *desc;     // padded, phase-ordered map (see desc_index); nullable: only the copies below
   uint8_t *compact;  // nullable: row-major [H][W][16] copy (the NN seed's input)
@@ -216,7 +215,6 @@ constexpr int kMaxScales = 7;
 struct BatchPair {
   const uint8_t *img[2];
   int W, H;
-  uint16_t *hsum[2][kMaxScales];
   uint8_t *blur[2][kMaxScales];
   uint8_t *desc[2][kMaxScales];  // padded maps
   uint8_t *wform[2][kMaxScales]; // weight-class row maps
@@ -236,15 +234,20 @@ struct BatchStage {
   const BatchPair *pairs;
   int npairs, total;
   int L, n, lv;  // scales of the schedule, scale of this stage
+  int wform_scales;  // descriptor stage: bit lv: the weight-class maps of scale 2^lv are read
   int src, dst;  // level stages: grid buffer read (continuing runs) and written, 0 = gflow/gcost, 1 = sflow/scost
   int prefix[kMaxBatch + 1];
 };
-hipError_t launch_batch_descriptors(const BatchStage &rows, hipStream_t stream);
+// tiles: the blur's items, rows: the descriptors'
+hipError_t launch_batch_descriptors(const BatchStage &tiles, const BatchStage &rows, int max_width,
+                                    hipStream_t stream);
 hipError_t launch_batch_nn(const BatchStage &fill, const BatchStage &nn, const BatchStage &resolve,
                            hipStream_t stream);
 hipError_t launch_batch_level(const LevelKArgs &base, const BatchStage &tiles, bool maps_fit, hipStream_t stream);
 hipError_t launch_batch_consistency(const BatchStage &rows, float eps, hipStream_t stream);
 // items per pair of each stage (host)
+int batch_blur_items(int W, int H, int L);
+int batch_desc_items(int H, int L);
 int batch_nn_items(int W, int H, int L);
 int batch_nn_resolve_items(int W, int H, int L);
 // tiles of one direction for the kernel that runs at that scale (the current
