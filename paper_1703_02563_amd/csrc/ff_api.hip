@@ -967,11 +967,11 @@ static LayoutF32 layout_f32(int W, int H, const ff_params *p) {
     off = align256(off + 2 * cells * 2 * sizeof(uint32_t));
   }
   l.evals = off; off = align256(off + 2 * sizeof(uint64_t));
-  if (p->radius == 3)  // padded float maps of the blocked level kernel
+  if (p->radius == 3)  // phase-ordered float maps of the blocked level kernel (n >= 2)
     for (int im = 0; im < 2; ++im)
-      for (int lv = 0; lv < p->levels; ++lv) {
+      for (int lv = 1; lv < p->levels; ++lv) {
         l.pf[im][lv] = off;
-        off = align256(off + desc_map_bytes(W, H, 1 << lv) * 4);
+        off = align256(off + l.N * 64);
       }
   l.total = off;
   return l;
@@ -1038,13 +1038,14 @@ ff_status ff_flow_fields_f32(const float *const *feat1, const float *const *feat
   if ((e = ffh::launch_nn(nn, s)) != hipSuccess) return FF_ERR_LAUNCH;
   const float *const *feat[2] = {feat1, feat2};
   if (r == 3) {
-    // temporally blocked level kernels on padded, phase-ordered float maps
-    const uint8_t *pf[2][kMaxLevels];
+    // temporally blocked level kernels on maps in phase order (image order at n = 1)
+    const float *pf[2][kMaxLevels];
     for (int im = 0; im < 2; ++im)
       for (int lv = 0; lv < L; ++lv) {
-        float *m = reinterpret_cast<float *>(base + lay.pf[im][lv]);
-        if ((e = ffh::launch_pad_features(feat[im][lv], W, H, 1 << lv, m, s)) != hipSuccess) return FF_ERR_LAUNCH;
-        pf[im][lv] = reinterpret_cast<const uint8_t *>(m);
+        float *m = lv ? reinterpret_cast<float *>(base + lay.pf[im][lv]) : nullptr;
+        if (lv && (e = ffh::launch_phase_features(feat[im][lv], W, H, 1 << lv, m, s)) != hipSuccess)
+          return FF_ERR_LAUNCH;
+        pf[im][lv] = lv ? m : feat[im][lv];
       }
     int32_t *sflow[kMaxLevels][2];
     uint32_t *scost[kMaxLevels][2];
@@ -1058,8 +1059,8 @@ ff_status ff_flow_fields_f32(const float *const *feat1, const float *const *feat
     }
     for (int lv = L - 1; lv >= 0; --lv) {
       for (int dr = 0; dr < 2; ++dr) {
-        k.dir[dr].Da = pf[dr][lv];
-        k.dir[dr].Db = pf[dr ^ 1][lv];
+        k.dir[dr].Da = reinterpret_cast<const uint8_t *>(pf[dr][lv]);
+        k.dir[dr].Db = reinterpret_cast<const uint8_t *>(pf[dr ^ 1][lv]);
         k.dir[dr].flow = gflow[lv][dr];
         k.dir[dr].cost = gcost[lv][dr];
         k.dir[dr].nn_key = keys + (size_t)dr * lay.M;

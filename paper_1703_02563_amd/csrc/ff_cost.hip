@@ -342,27 +342,23 @@ __global__ __launch_bounds__(256) void k_cost_poison(ffh::CostArgs a, long long 
   }
 }
 
-// Padded, phase-ordered copy of a float feature map (the layout of the
-// descriptor maps with 64-byte entries): one thread per 16-byte quarter of a
-// stored entry, so consecutive lanes store consecutive bytes.
-__global__ __launch_bounds__(256) void k_pad_features(const float4 *f, int W, int H, int log2n, float4 *out) {
-  const int P = ffk::desc_pad(1 << log2n), Wp = W + 2 * P, Hp = H + 2 * P;
-  const int q = blockIdx.x * blockDim.x + threadIdx.x, yp = blockIdx.y;
-  const int c = q >> 2;
-  if (c >= Wp || yp >= Hp) return;
-  const int x = clampi(ffk::desc_pixel(c, log2n, Wp) - P, W - 1), y = clampi(yp - P, H - 1);
-  out[((size_t)yp * Wp + c) * 4 + (q & 3)] = f[((size_t)y * W + x) * 4 + (q & 3)];
+// Copy of a float feature map with the pixels of every row in phase order
+// (desc_col): one thread per 16-byte quarter of an entry, so consecutive lanes
+// store consecutive bytes.
+__global__ __launch_bounds__(256) void k_phase_features(const float4 *f, int W, int log2n, float4 *out) {
+  const int q = blockIdx.x * blockDim.x + threadIdx.x, c = q >> 2;
+  if (c >= W) return;
+  const size_t row = (size_t)blockIdx.y * W;
+  out[(row + c) * 4 + (q & 3)] = f[(row + ffk::desc_pixel(c, log2n, W)) * 4 + (q & 3)];
 }
 
 }  // namespace
 
 namespace ffh {
 
-hipError_t launch_pad_features(const float *f, int W, int H, int n, float *out, hipStream_t stream) {
-  const int P = ffk::desc_pad(n);
-  const dim3 grid((4 * (W + 2 * P) + 255) / 256, H + 2 * P);
-  hipLaunchKernelGGL(k_pad_features, grid, dim3(256), 0, stream, reinterpret_cast<const float4 *>(f), W, H,
-                     __builtin_ctz(n), reinterpret_cast<float4 *>(out));
+hipError_t launch_phase_features(const float *f, int W, int H, int n, float *out, hipStream_t stream) {
+  hipLaunchKernelGGL(k_phase_features, dim3((4 * W + 255) / 256, H), dim3(256), 0, stream,
+                     reinterpret_cast<const float4 *>(f), W, __builtin_ctz(n), reinterpret_cast<float4 *>(out));
   return hipGetLastError();
 }
 

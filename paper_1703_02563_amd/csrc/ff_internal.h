@@ -163,7 +163,7 @@ struct LevelKArgs {
   uint64_t seed;
   int t_begin, t_end, T;  // T: steps of the scale; no random search after steps P - 1 and T - 1
   int mode;
-  int fcost;    // 0: byte descriptor maps; 1: padded float feature maps (64-byte entries)
+  int fcost;    // 0: byte descriptor maps; 1: float feature maps [H][W][16], rows in phase order
   int variant;  // the launch table's variant of this scale (byte or float table by fcost)
   int radius;   // patch radius: 3, or 2 and 4 (byte descriptors only); 0 means 3
   int tiles_x;  // set by launch_level
@@ -172,8 +172,9 @@ struct LevelKArgs {
   int spx;      // 1: flows in 1/8 px, bilinear targets (radius 3, needs the weight-class maps)
   int wradius;  // patch radius of the maps Wa/Wb (0 means 3)
 };
-// Padded, phase-ordered copy of a float [H][W][16] feature map of scale n.
-hipError_t launch_pad_features(const float *f, int W, int H, int n, float *out, hipStream_t stream);
+// Copy of a float [H][W][16] feature map with its rows in the phase order of
+// scale n.
+hipError_t launch_phase_features(const float *f, int W, int H, int n, float *out, hipStream_t stream);
 hipError_t launch_level(LevelKArgs a, hipStream_t stream);
 // per-scale launchers of the blocked kernels (ff_level_s<log2n>.hip)
 struct BatchStage;

@@ -418,37 +418,62 @@ __device__ __forceinline__ uint32_t eval_wform_spx(const uint4 *pa, int step, __
 // the four partial sums as (s0 + s1) + (s2 + s3) (every lane returns the
 // total, as a bit pattern).  Image a's lattice samples come from LDS (`pa`:
 // the cell's 4 float4 in a window of row length DW cells), image b's from
-// its padded, phase-ordered map (64-byte entries): a quad reads one whole
-// entry per load.
+// its feature map, [H][W][16] with the pixels of a row in phase order
+// (desc_col; at n = 1 image order), positions clamped: a quad reads one whole
+// 64-byte entry per load, the samples of a patch row next to each other.
+//
+// Bound by those reads (49 entries of 64 bytes per evaluation through the
+// vector L1), so they stop once the value cannot be used: `limit` holds the
+// bits of the cost an evaluation has to stay at or below, terms are not
+// negative and rounding keeps the order, so a partial sum above it decides.
+// The wave leaves together, after the row that puts its last quad above; the
+// value returned is then some number above the limit.  A row's loads are
+// issued before the previous row is summed.  Infinities and NaN never decide.
 template <int LOG2N, int DW>
-__device__ __forceinline__ uint32_t eval_quad_f32(const float4 *pa, const float4 *__restrict__ B, int W, int bx,
-                                                  int by, int r) {
-  constexpr int n = 1 << LOG2N, P = ffk::kDescPad * n, K = 2 * kR + 1;
-  const size_t row = (size_t)n * (W + 2 * P) * 4;
-  const float4 *pb = B + 4 * ffk::desc_index(bx - kR * n, by - kR * n, LOG2N, W) + r;
+__device__ __forceinline__ uint32_t eval_quad_f32(const float4 *pa, const float4 *__restrict__ B, int W, int H, int bx,
+                                                  int by, int r, uint32_t limit) {
+  constexpr int n = 1 << LOG2N, K = 2 * kR + 1;
   const float4 *ra = pa + (-kR * DW - kR) * 4 + r;
+  int xo[K];
+#pragma unroll
+  for (int u = 0; u < K; ++u) xo[u] = 4 * ffk::desc_col(clampi(bx + (u - kR) * n, W - 1), LOG2N, W) + r;
+  constexpr int D = 3;  // rows in flight, the summed one included
+  float4 y[D][K];
+  auto fetch = [&](int v, float4 (&row)[K]) {
+    const float4 *p = B + (size_t)clampi(by + (v - kR) * n, H - 1) * W * 4;
+#pragma unroll
+    for (int u = 0; u < K; ++u) row[u] = p[xo[u]];
+  };
+  auto total = [](float s) {
+    s += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(s), 0xB1, 0xF, 0xF, false));  // quad_perm [1,0,3,2]
+    s += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(s), 0x4E, 0xF, 0xF, false));  // quad_perm [2,3,0,1]
+    return s;
+  };
+  const float lim = __uint_as_float(limit);
   float s = 0.0f;
 #pragma unroll
-  for (int v = 0; v < K; ++v) {
-    float4 y[K];
+  for (int v = 0; v + 1 < D; ++v) fetch(v, y[v]);
 #pragma unroll
-    for (int u = 0; u < K; ++u) y[u] = pb[v * row + 4 * u];
+  for (int v = 0; v < K; ++v) {
+    if (v + D - 1 < K) fetch(v + D - 1, y[(v + D - 1) % D]);
 #pragma unroll
     for (int u = 0; u < K; ++u) {
-      const float4 x = ra[(v * DW + u) * 4];
-      float e = x.x - y[u].x;
+      const float4 x = ra[(v * DW + u) * 4], z = y[v % D][u];
+      float e = x.x - z.x;
       s = __fmaf_rn(e, e, s);
-      e = x.y - y[u].y;
+      e = x.y - z.y;
       s = __fmaf_rn(e, e, s);
-      e = x.z - y[u].z;
+      e = x.z - z.z;
       s = __fmaf_rn(e, e, s);
-      e = x.w - y[u].w;
+      e = x.w - z.w;
       s = __fmaf_rn(e, e, s);
     }
+    if (LOG2N <= 2 && v + D < K) {
+      const float t = total(s);
+      if (!__ballot(!(t > lim && t < __builtin_inff()))) return __float_as_uint(t);
+    }
   }
-  s += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(s), 0xB1, 0xF, 0xF, false));  // quad_perm [1,0,3,2]
-  s += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(s), 0x4E, 0xF, 0xF, false));  // quad_perm [2,3,0,1]
-  return __float_as_uint(s);
+  return __float_as_uint(total(s));
 }
 
 // The run of passes for tile `tile` of one direction `d` (a holds the
@@ -484,8 +509,8 @@ __device__ __forceinline__ void level_body(const ffh::LevelKArgs &a, const ffh::
   using FlagT = std::conditional_t<QUAD, uint32_t, uint8_t>;
   __shared__ int32_t s_flow[G::LH * G::LW];
   __shared__ uint32_t s_cost[G::LH * G::LW];
-  // byte descriptors of image a on the level lattice (float features are
-  // read from their padded map instead); 64-bit keys for float costs
+  // byte descriptors of image a on the level lattice; 64-bit keys for float
+  // costs
   __shared__ uint4 s_da[(F32 || WF) ? 1 : G::DH * G::DW];
   // weight-class row entries of image a: window rows gj0 - (RR + 3) ... gj0 +
   // LH + RR + 2; the rows of a sub-scale patch lie 3/2 cells apart, so its
@@ -553,7 +578,7 @@ __device__ __forceinline__ void level_body(const ffh::LevelKArgs &a, const ffh::
     for (int it = 0; it < NS; ++it) {
       const int k = min(it * kThreads + tid, 4 * G::DH * G::DW - 1);
       const int c = k >> 2, vi = gi0 - RR + c % G::DW, vj = gj0 - RR + c / G::DW;
-      v[it] = Da[4 * ffk::desc_index(clampi(vi * n, W - 1), clampi(vj * n, H - 1), LOG2N, W) + (k & 3)];
+      v[it] = Da[4 * ((size_t)clampi(vj * n, H - 1) * W + ffk::desc_col(clampi(vi * n, W - 1), LOG2N, W)) + (k & 3)];
     }
   }
   const int pscale = SUB ? a.sub_m : n;  // patch scale
@@ -568,10 +593,10 @@ __device__ __forceinline__ void level_body(const ffh::LevelKArgs &a, const ffh::
       (int)((size_t)(H + 2 * ffk::desc_pad(pscale)) * (W + 2 * ffk::desc_pad(pscale)) * 16);
   [[maybe_unused]] const __amdgpu_buffer_rsrc_t db_rsrc =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(d.Db), (short)0, map_bytes, 0x00020000);
-  auto evalq = [&](int i, int j, int bx, int by) -> uint32_t {
+  auto evalq = [&](int i, int j, int bx, int by, [[maybe_unused]] uint32_t limit) -> uint32_t {
     if constexpr (F32) {
       const float4 *pa = s_daf + 4 * ((j - gj0 + RR) * G::DW + (i - gi0 + RR));
-      return eval_quad_f32<LOG2N, G::DW>(pa, reinterpret_cast<const float4 *>(d.Db), W, bx, by, qr);
+      return eval_quad_f32<LOG2N, G::DW>(pa, reinterpret_cast<const float4 *>(d.Db), W, H, bx, by, qr, limit);
     } else {
       const uint4 *pa = s_da + (j - gj0 + RR) * G::DW + (i - gi0 + RR);
       return eval_quad<LOG2N, G::DW, RR>(pa, db_rsrc, W, bx, by, qr);
@@ -796,7 +821,7 @@ __device__ __forceinline__ void level_body(const ffh::LevelKArgs &a, const ffh::
         if (q < qlen) {
           const int l = s_queue[q], i = gi0 + l % G::LW, j = gj0 + l / G::LW;
           const int32_t f = s_flow[l];
-          const uint32_t c = evalq(i, j, i * n + ffk::flow_x(f), j * n + ffk::flow_y(f));
+          const uint32_t c = evalq(i, j, i * n + ffk::flow_x(f), j * n + ffk::flow_y(f), kUnset);
           if (qr == 0) s_cost[l] = c;
           own = owned(i, j);
         }
@@ -929,7 +954,12 @@ __device__ __forceinline__ void level_body(const ffh::LevelKArgs &a, const ffh::
             const int e = s_queue[q], l = e >> 1, vert = e & 1;
             const int i = gi0 + l % G::LW, j = gj0 + l / G::LW;
             const int32_t f = s_flow[vert ? l + vdj * G::LW : l + hdi];
-            const uint32_t c = evalq(i, j, i * n + ffk::flow_x(f), j * n + ffk::flow_y(f));
+            uint32_t limit = kUnset;
+            if constexpr (F32) {  // the cell's best so far (another candidate may lower it meanwhile)
+              const unsigned long long key = s_key[l];
+              limit = key == ~0ull ? kUnset : (uint32_t)(key >> 2);
+            }
+            const uint32_t c = evalq(i, j, i * n + ffk::flow_x(f), j * n + ffk::flow_y(f), limit);
             if (qr == 0) {
               if constexpr (F32)
                 atomicMin(&s_key[l], ((unsigned long long)c << 2) | (unsigned long long)(1 + vert));
@@ -1060,7 +1090,7 @@ __device__ __forceinline__ void level_body(const ffh::LevelKArgs &a, const ffh::
         if (q < qlen) {
           const int l = s_queue[q], i = gi0 + l % G::LW, j = gj0 + l / G::LW;
           const int32_t fc = (int32_t)s_flags[l];
-          const uint32_t e = evalq(i, j, i * n + ffk::flow_x(fc), j * n + ffk::flow_y(fc));
+          const uint32_t e = evalq(i, j, i * n + ffk::flow_x(fc), j * n + ffk::flow_y(fc), s_cost[l]);
           if (qr == 0 && e < s_cost[l]) {
             s_cost[l] = e;
             s_flow[l] = fc;
@@ -1168,7 +1198,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
   level_body<LOG2N, TW, TH, kThreads, 4, false, HALO, kR, !SPX, SPX>(a, a.dir[wg / tiles], wg % tiles);
 }
 
-// Float learned features (padded float maps in LevelKDir::Da/Db).
+// Float learned features ([H][W][16] maps, rows in phase order, in
+// LevelKDir::Da/Db).
 template <int LOG2N, int TW, int TH, int kThreads, int HALO>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 3))) void k_level_f32(
     ffh::LevelKArgs a) {
