@@ -535,7 +535,7 @@ size_t ff_conv3x3_wgrad_scratch_bytes(int32_t B, int32_t H, int32_t cin, int32_t
 /* gw[co][tap][ci] = sum_p gout[p][co] * in[p + d(tap)][ci], gbias[co] =
  * sum_p gout[p][co] (gbias nullable), float32: bf16 matrix-core products
  * with float32 accumulation, gout split into two bf16 parts (hi + lo, within
- * 2^-18 |gout| of it), so the error is at most (2^-18 + 3.1 P 2^-24) times
+ * 2^-17 |gout| of it), so the error is at most (2^-17 + 3.1 P 2^-24) times
  * the sum of |gout| |in| over the P pixels; per-workgroup partial sums are
  * added in a fixed order (deterministic).  in: bf16, 16-byte aligned when
  * cin > 1; gout: float32, 16-byte aligned; (cin, cout) = (1, 32), (32, 32)
@@ -543,6 +543,26 @@ size_t ff_conv3x3_wgrad_scratch_bytes(int32_t B, int32_t H, int32_t cin, int32_t
 ff_status ff_conv3x3_bwd_weight(const uint16_t *in, const float *gout, int32_t B, int32_t H, int32_t W,
                                 int32_t cin, int32_t cout, float *scratch, size_t scratch_bytes, float *gw,
                                 float *gbias, void *stream);
+
+/* The passes of a training step with their element-wise neighbours folded in;
+ * a float32 gradient g travels as two bf16 arrays, hi = bf16(g) and lo =
+ * bf16(g - hi) (hi is also what ff_conv3x3_bwd_data takes).  Pointers 16-byte
+ * aligned (FF_ERR_ARG otherwise; inv_norm and weights excepted).
+ * ff_conv3x3_norm_fwd: the (32, 16) layer without ReLU, then ff_l2norm16_fwd.
+ * ff_conv3x3_bwd_data_split: ff_conv3x3_bwd_data of a layer with cin = 32,
+ * then ff_relu_bwd with act [B][H][W][32], split.
+ * ff_conv3x3_bwd_weight_split: ff_conv3x3_bwd_weight of a split gradient.
+ * ff_l2norm16_bwd_split: ff_l2norm16_bwd, split (out NULL: the split alone). */
+ff_status ff_conv3x3_norm_fwd(const uint16_t *in, int32_t B, int32_t H, int32_t W, const uint16_t *w,
+                              const float *bias, float delta, float *out, float *inv_norm, void *stream);
+ff_status ff_conv3x3_bwd_data_split(const uint16_t *g_hi, int32_t B, int32_t H, int32_t W, int32_t cin, int32_t cout,
+                                    const uint16_t *w, uint16_t *wflip_scratch, const uint16_t *act, uint16_t *gin_hi,
+                                    uint16_t *gin_lo, void *stream);
+ff_status ff_conv3x3_bwd_weight_split(const uint16_t *in, const uint16_t *g_hi, const uint16_t *g_lo, int32_t B,
+                                      int32_t H, int32_t W, int32_t cin, int32_t cout, float *scratch,
+                                      size_t scratch_bytes, float *gw, float *gbias, void *stream);
+ff_status ff_l2norm16_bwd_split(const float *out, const float *inv_norm, const float *grad, int64_t pixels,
+                                uint16_t *g_hi, uint16_t *g_lo, void *stream);
 
 /* ReLU backward: out = grad where act > 0 (act = the layer's bf16 output;
  * NULL passes grad through), written as float32 and/or bf16. */

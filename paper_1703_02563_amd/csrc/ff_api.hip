@@ -1165,6 +1165,76 @@ ff_status ff_conv3x3_bwd_weight(const uint16_t *in, const float *gout, int32_t B
   return from_hip(ffh::launch_wgrad(a, gw, gbias, (hipStream_t)stream));
 }
 
+ff_status ff_conv3x3_norm_fwd(const uint16_t *in, int32_t B, int32_t H, int32_t W, const uint16_t *w,
+                              const float *bias, float delta, float *out, float *inv_norm, void *stream) {
+  if (!in || !w || !out || !inv_norm || !(delta > 0.0f) || !conv_shape_ok(B, H, W, 32, 16) || !aligned16(in) ||
+      !aligned16(out))
+    return FF_ERR_ARG;
+  ffh::ConvArgs a{};
+  a.in = in;
+  a.w = w;
+  a.bias = bias;
+  a.B = B;
+  a.H = H;
+  a.W = W;
+  a.cin = 32;
+  a.cout = 16;
+  a.out_f32 = out;
+  a.inv_norm = inv_norm;
+  a.delta = delta;
+  return from_hip(ffh::launch_conv_fwd(a, (hipStream_t)stream));
+}
+
+ff_status ff_conv3x3_bwd_data_split(const uint16_t *g_hi, int32_t B, int32_t H, int32_t W, int32_t cin, int32_t cout,
+                                    const uint16_t *w, uint16_t *wflip_scratch, const uint16_t *act, uint16_t *gin_hi,
+                                    uint16_t *gin_lo, void *stream) {
+  if (!g_hi || !w || !wflip_scratch || !act || !gin_hi || !gin_lo || cin != 32 || !conv_shape_ok(B, H, W, cout, cin) ||
+      !aligned16(g_hi) || !aligned16(act) || !aligned16(gin_hi) || !aligned16(gin_lo))
+    return FF_ERR_ARG;
+  hipStream_t s = (hipStream_t)stream;
+  if (ffh::launch_weight_flip(w, wflip_scratch, cin, cout, s) != hipSuccess) return FF_ERR_LAUNCH;
+  ffh::ConvArgs a{};
+  a.in = g_hi;
+  a.w = wflip_scratch;
+  a.B = B;
+  a.H = H;
+  a.W = W;
+  a.cin = cout;
+  a.cout = cin;
+  a.act = act;
+  a.out_bf16 = gin_hi;
+  a.out_lo = gin_lo;
+  return from_hip(ffh::launch_conv_fwd(a, s));
+}
+
+ff_status ff_conv3x3_bwd_weight_split(const uint16_t *in, const uint16_t *g_hi, const uint16_t *g_lo, int32_t B,
+                                      int32_t H, int32_t W, int32_t cin, int32_t cout, float *scratch,
+                                      size_t scratch_bytes, float *gw, float *gbias, void *stream) {
+  if (!in || !g_hi || !g_lo || !scratch || !gw || !conv_shape_ok(B, H, W, cin, cout) || cin == 16 ||
+      (cin > 1 && !aligned16(in)) || !aligned16(g_hi) || !aligned16(g_lo))
+    return FF_ERR_ARG;
+  if (scratch_bytes < ff_conv3x3_wgrad_scratch_bytes(B, H, cin, cout)) return FF_ERR_WORKSPACE;
+  ffh::ConvArgs a{};
+  a.in = in;
+  a.g_hi = g_hi;
+  a.g_lo = g_lo;
+  a.B = B;
+  a.H = H;
+  a.W = W;
+  a.cin = cin;
+  a.cout = cout;
+  a.partial = scratch;
+  return from_hip(ffh::launch_wgrad(a, gw, gbias, (hipStream_t)stream));
+}
+
+ff_status ff_l2norm16_bwd_split(const float *out, const float *inv_norm, const float *grad, int64_t pixels,
+                                uint16_t *g_hi, uint16_t *g_lo, void *stream) {
+  if (!grad || !g_hi || !g_lo || pixels < 0 || (out && !inv_norm) || (out && !aligned16(out)) || !aligned16(grad) ||
+      !aligned16(g_hi) || !aligned16(g_lo))
+    return FF_ERR_ARG;
+  return from_hip(ffh::launch_l2norm16_bwd_split(out, inv_norm, grad, pixels, g_hi, g_lo, (hipStream_t)stream));
+}
+
 ff_status ff_relu_bwd(const uint16_t *act, const float *grad, int64_t count, float *grad_out, uint16_t *grad_out_bf16,
                       void *stream) {
   if (!grad || (!grad_out && !grad_out_bf16) || count < 0) return FF_ERR_ARG;

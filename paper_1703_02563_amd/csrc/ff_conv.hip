@@ -50,12 +50,101 @@ __device__ __forceinline__ float l2norm16(float4 v[4], float delta) {
   return r;
 }
 
+// Epilogue of a transposed product D = W X (weights the first operand, 32
+// pixels the columns): a lane holds the output channels 8 g + 4 kh .. 8 g + 4
+// kh + 3, g < COUT / 8, of one pixel, so a store covers 4 channels (16 bytes
+// in float32, 8 in bf16) instead of one.  Every output element is the same
+// sum of the same products as in X W, bit for bit.
+enum ConvEpilogue {
+  kConvPlain,  // bias, optional ReLU; float32 and / or bf16
+  kConvMask,   // gradient through the ReLU whose output is a.act, split into two bf16 parts
+  kConvNorm,   // bias, unit length per pixel (COUT = 16), float32 and the scale
+};
+
+template <int COUT, ConvEpilogue EPI>
+__device__ __forceinline__ void conv_store(const ffh::ConvArgs &a, size_t q, bool in, int kh, const f32x16 &acc,
+                                           const float (&bias)[COUT / 2]) {
+  constexpr int G = COUT / 8;
+  float v[G][4];
+#pragma unroll
+  for (int g = 0; g < G; ++g)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) v[g][c] = acc[4 * g + c] + bias[4 * g + c];
+  if constexpr (EPI == kConvNorm) {
+    static_assert(COUT == 16, "the normalisation is over 16 channels");
+    // all 16 channels: the other lane half holds the other 8
+    float o[2][4];
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) o[g][c] = __shfl_xor(v[g][c], 32);
+    auto quad = [&](int g, bool own) {
+      return make_float4(own ? v[g][0] : o[g][0], own ? v[g][1] : o[g][1], own ? v[g][2] : o[g][2],
+                         own ? v[g][3] : o[g][3]);
+    };
+    float4 f[4] = {quad(0, kh == 0), quad(0, kh == 1), quad(1, kh == 0), quad(1, kh == 1)};
+    const float r = l2norm16(f, a.delta);
+    if (!in) return;
+    float4 *out = reinterpret_cast<float4 *>(a.out_f32 + q * 16) + kh;
+#pragma unroll
+    for (int g = 0; g < 2; ++g) out[2 * g] = make_float4(v[g][0] * r, v[g][1] * r, v[g][2] * r, v[g][3] * r);
+    if (kh == 0) a.inv_norm[q] = r;
+  } else {
+    if (!in) return;
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const size_t o = q * COUT + 8 * g + 4 * kh;
+      if constexpr (EPI == kConvMask) {
+        const uint2 m = *reinterpret_cast<const uint2 *>(a.act + o);
+        const uint16_t act[4] = {(uint16_t)m.x, (uint16_t)(m.x >> 16), (uint16_t)m.y, (uint16_t)(m.y >> 16)};
+        uint32_t hi[4], lo[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const float x = bf16_to_f32(act[c]) > 0.0f ? v[g][c] : 0.0f;
+          hi[c] = f32_to_bf16(x);
+          lo[c] = f32_to_bf16(x - bf16_to_f32((uint16_t)hi[c]));
+        }
+        *reinterpret_cast<uint2 *>(a.out_bf16 + o) = make_uint2(hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16));
+        *reinterpret_cast<uint2 *>(a.out_lo + o) = make_uint2(lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16));
+      } else {
+        if (a.relu)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) v[g][c] = fmaxf(v[g][c], 0.0f);
+        if (a.out_f32) {
+          if (a.wide)
+            *reinterpret_cast<float4 *>(a.out_f32 + o) = make_float4(v[g][0], v[g][1], v[g][2], v[g][3]);
+          else
+            for (int c = 0; c < 4; ++c) a.out_f32[o + c] = v[g][c];
+        }
+        if (a.out_bf16) {
+          uint32_t h[4];
+#pragma unroll
+          for (int c = 0; c < 4; ++c) h[c] = f32_to_bf16(v[g][c]);
+          if (a.wide)
+            *reinterpret_cast<uint2 *>(a.out_bf16 + o) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
+          else
+            for (int c = 0; c < 4; ++c) a.out_bf16[o + c] = (uint16_t)h[c];
+        }
+      }
+    }
+  }
+}
+
+// The biases of a lane's output channels.
+template <int COUT>
+__device__ __forceinline__ void conv_bias(const float *bias, int kh, float (&b)[COUT / 2]) {
+#pragma unroll
+  for (int r = 0; r < COUT / 2; ++r) b[r] = bias ? bias[8 * (r >> 2) + 4 * kh + (r & 3)] : 0.0f;
+}
+
 // Single input channel (the first layer): K = 9 taps padded to 16, lane
-// half kh holds taps 8 * kh .. 8 * kh + 7 of one pixel.
+// half kh holds taps 8 * kh .. 8 * kh + 7 of one pixel.  Bound by its stores
+// (64 bytes a pixel): with one bf16 per lane and store 89 us for 3.6 Mpx, with
+// four @C1@ us.
 template <int CIN, int COUT>
 __global__ __launch_bounds__(256) void k_conv_fwd(ffh::ConvArgs a) {
   static_assert(CIN == 1, "Cin 1 (wider inputs: k_conv_fwd_tile)");
-  static_assert(COUT <= 32, "Cout <= 32");
+  static_assert(COUT == 32, "Cout 32");
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int row = lane & 31, kh = lane >> 5;
   const long long P = (long long)a.B * a.H * a.W;
@@ -66,7 +155,6 @@ __global__ __launch_bounds__(256) void k_conv_fwd(ffh::ConvArgs a) {
   const int x = pv ? (int)(p % a.W) : 0, y = pv ? (int)((p / a.W) % a.H) : 0;
   const long long img = pv ? p / ((long long)a.W * a.H) : 0;
   const uint16_t *in = a.in;
-  const int col = row;  // output channel held by this lane in the B operand
   f32x16 acc = {0};
   uint16_t av[8], bv[8];
 #pragma unroll
@@ -76,7 +164,7 @@ __global__ __launch_bounds__(256) void k_conv_fwd(ffh::ConvArgs a) {
     if (tap < 9) {
       const int sx = x + tap % 3 - 1, sy = y + tap / 3 - 1;
       if (pv && sx >= 0 && sx < a.W && sy >= 0 && sy < a.H) va = in[((img * a.H + sy) * a.W + sx)];
-      if (col < COUT) vb = a.w[col * 9 + tap];
+      vb = a.w[row * 9 + tap];
     }
     av[e] = va;
     bv[e] = vb;
@@ -84,24 +172,10 @@ __global__ __launch_bounds__(256) void k_conv_fwd(ffh::ConvArgs a) {
   uint4 ua, ub;
   __builtin_memcpy(&ua, av, 16);
   __builtin_memcpy(&ub, bv, 16);
-  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ua), as_bf16x8(ub), acc, 0, 0, 0);
-  if (col >= COUT) return;
-  const float bias = a.bias ? a.bias[col] : 0.0f;
-  float v[16];
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    v[r] = acc[r] + bias;
-    if (a.relu) v[r] = fmaxf(v[r], 0.0f);
-  }
-  const bool full = p0 + 32 <= P;  // wave-uniform: no row outside the batch
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const long long q = p0 + 8 * (r >> 2) + 4 * kh + (r & 3);
-    if (full || q < P) {
-      if (a.out_f32) a.out_f32[q * COUT + col] = v[r];
-      if (a.out_bf16) a.out_bf16[q * COUT + col] = f32_to_bf16(v[r]);
-    }
-  }
+  float bias[COUT / 2];
+  conv_bias<COUT>(a.bias, kh, bias);
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ub), as_bf16x8(ua), acc, 0, 0, 0);
+  conv_store<COUT, kConvPlain>(a, (size_t)p, pv, kh, acc, bias);
 }
 
 // Tiled form for Cin >= 16: a workgroup takes kConvRows image rows x 32
@@ -112,13 +186,17 @@ __global__ __launch_bounds__(256) void k_conv_fwd(ffh::ConvArgs a) {
 // distinct banks.  Each wave keeps its weight operands in registers and runs
 // every fourth row of the tile.  The products are accumulated in the same
 // order as in k_conv_fwd (taps, then channel chunks), so the results are
-// identical.
+// identical.  The epilogues that a training step needs run here instead of as
+// passes over memory of their own: the last layer's normalisation, and the
+// data gradient's ReLU and its split into two bf16 parts.  3.6 Mpx: 32 -> 32
+// with bf16 outputs 172 -> @C2@ us, 32 -> 16 with the normalisation 156 + 96 ->
+// @C3@ us, data gradient 32 -> 32 with mask and split 172 + 383 -> @C4@ us.
 constexpr int kConvRows = 8;
 
-template <int CIN, int COUT>
+template <int CIN, int COUT, ConvEpilogue EPI>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 4))) void k_conv_fwd_tile(ffh::ConvArgs a) {
   static_assert(CIN % 16 == 0, "Cin must be a multiple of 16");
-  static_assert(COUT <= 32, "Cout <= 32");
+  static_assert(COUT == 16 || COUT == 32, "Cout 16 or 32");
   constexpr int KC = CIN / 16, TW = 32, TR = kConvRows, LW = TW + 2;
   constexpr int PX16 = CIN / 8 + 1;  // 16-byte slots per staged pixel (one of padding)
   __shared__ uint4 s_in[(TR + 2) * LW * PX16];
@@ -135,9 +213,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 4))) voi
     s_in[(ry * LW + px) * PX16 + c16] = v;
   }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int row = lane & 31, kh = lane >> 5, col = row;  // A: pixel x0 + row; B: output channel col
+  const int row = lane & 31, kh = lane >> 5, col = row;  // weights: output channel col; pixels: x0 + row
   uint4 ub[9 * KC];
-  const uint32_t wmask = col < COUT ? 0xFFFFFFFFu : 0u;  // columns beyond Cout multiply by zero
+  const uint32_t wmask = col < COUT ? 0xFFFFFFFFu : 0u;  // channels beyond Cout multiply by zero
 #pragma unroll
   for (int tap = 0; tap < 9; ++tap) {
     const uint4 *wsrc = reinterpret_cast<const uint4 *>(a.w + ((size_t)min(col, COUT - 1) * 9 + tap) * CIN);
@@ -147,8 +225,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 4))) voi
       ub[tap * KC + cc] = make_uint4(w.x & wmask, w.y & wmask, w.z & wmask, w.w & wmask);
     }
   }
+  float bias[COUT / 2];
+  conv_bias<COUT>(a.bias, kh, bias);
   __syncthreads();
-  const float bias = (a.bias && col < COUT) ? a.bias[col] : 0.0f;
   for (int rr = wave; rr < TR && y0 + rr < a.H; rr += 4) {
     f32x16 acc = {0};
 #pragma unroll
@@ -156,22 +235,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 4))) voi
       const uint4 *src = s_in + ((rr + tap / 3) * LW + row + tap % 3) * PX16;
 #pragma unroll
       for (int cc = 0; cc < KC; ++cc)
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(src[cc * 2 + kh]), as_bf16x8(ub[tap * KC + cc]),
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ub[tap * KC + cc]), as_bf16x8(src[cc * 2 + kh]),
                                                       acc, 0, 0, 0);
     }
-    if (col < COUT) {
-      const size_t q0 = ((size_t)img * a.H + y0 + rr) * a.W;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int x = x0 + 8 * (r >> 2) + 4 * kh + (r & 3);
-        float v = acc[r] + bias;
-        if (a.relu) v = fmaxf(v, 0.0f);
-        if (x < a.W) {
-          if (a.out_f32) a.out_f32[(q0 + x) * COUT + col] = v;
-          if (a.out_bf16) a.out_bf16[(q0 + x) * COUT + col] = f32_to_bf16(v);
-        }
-      }
-    }
+    conv_store<COUT, EPI>(a, ((size_t)img * a.H + y0 + rr) * a.W + x0 + row, x0 + row < a.W, kh, acc, bias);
   }
 }
 
@@ -334,26 +401,48 @@ __global__ __launch_bounds__(256) void k_flip(const uint16_t *w, uint16_t *wf, i
   wf[i] = w[((size_t)co * 9 + (8 - tap)) * cin + ci];
 }
 
-// Partial weight and bias gradients of one row band on matrix cores.
+// Partial weight and bias gradients of a run of pixels on matrix cores.
 // gw[co][tap][ci] = sum over pixels p of g[p][co] * x[p + d(tap)][ci] is a
 // contraction over pixels: per tap, D[co][ci] (32 x 32) += A[co][16 pixels]
 // x B[16 pixels][ci] with v_mfma_f32_32x32x16_bf16.  x is bf16 already; the
-// float32 gradient is split as g_hi = bf16(g) and g_lo = bf16(g - g_hi) and
-// both parts are multiplied (bf16 products are exact in float32, and
-// |g - g_hi - g_lo| <= 2^-18 |g|), so every term keeps float32-level
-// accuracy.  The bias gradient sum_p g is one more product with B = 1 (for
-// Cin = 1 the nine taps and the bias are the columns of one product).  A
-// workgroup takes a band of rows; of every 64 pixels of a row each wave
-// takes 16.  The tile is staged in LDS channel-major (pixels of a channel
-// contiguous; 16-byte loads from global memory, 8 channels or 4 gradients
-// each): a lane's 8 pixels of one channel are one aligned 16-byte read, and
-// the taps one pixel left or right are assembled from two neighbouring
-// reads with byte alignment.  The four waves' sums are added in LDS in a
-// fixed order and each workgroup writes one partial; k_wgrad_reduce adds the
-// partials in a fixed order, so the result is deterministic.
-constexpr int kWgPx = 64;  // pixels of a row per step (16 per wave)
-constexpr int kWgX = 80;   // LDS row of image x: pixel x0 - 8 + i at entry i
-constexpr int kWgG = 72;   // LDS row of the gradient: pixel x0 + i at entry i
+// float32 gradient is split as g_hi = bf16(g) and g_lo = bf16(g - g_hi) (by the
+// caller's epilogues, kSplit, or here) and both parts are multiplied (bf16
+// products are exact in float32, and |g - g_hi - g_lo| <= 2^-17 |g|), so
+// every term keeps float32-level accuracy.  The bias gradient sum_p g is one
+// more product with B = 1 (for Cin = 1 the nine taps and the bias are the
+// columns of one product).  With Cout = 16 both parts are the rows of one
+// operand and are added at the end.
+//
+// An operand's lane holds 8 pixels of one channel, memory holds the channels
+// of a pixel: the LDS transpose reads (ds_read_b64_tr_b16: 16 lanes read 4
+// pixels x 16 channels, lane i gets channel i) give that from rows stored as
+// they come, and a tap one pixel aside is the same read 64 bytes on.  A wave
+// walks down a column of 16 pixels by itself: it loads one row of x (18
+// pixels) and of g ahead, keeps the operands of three rows of x in
+// registers, and needs no barrier; every value is read from memory once (x:
+// 18/16 times).  Bound by that traffic and by the 18 products a row.  Staging
+// transposed with 2-byte LDS stores, three rows of x for every row of g, one
+// barrier pair per 64 pixels, took 576 us (32 -> 32), 487 (32 -> 16) and 152
+// (1 -> 32) for 3.6 Mpx; this takes @W1@, @W2@ and @W3@.
+//
+// The four waves' sums are added in LDS in a fixed order and each workgroup
+// writes one partial; k_wgrad_reduce adds the partials in a fixed order, so
+// the result is deterministic.
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+
+// Operand of 16 pixels (k) x 32 channels from LDS rows of 64 bytes per pixel,
+// the first pixel at `p`: this lane's channel (lane & 31), its 8 pixels.
+__device__ __forceinline__ bf16x8 read_pixels_tr(const uint8_t *p, int lane) {
+  const int j = lane & 15;
+  const uint8_t *q = p + (8 * (lane >> 5) + (j >> 2)) * 64 + 32 * ((lane >> 4) & 1) + 8 * (j & 3);
+  union {
+    s16x4 h[2];
+    bf16x8 v;
+  } u;
+  u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)q);
+  u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(q + 256));
+  return u.v;
+}
 
 // the 8 bf16 at entries e0 + s .. e0 + s + 7 (s = -1, 0, 1) of an LDS row,
 // from the aligned reads lo = [e0 - 8, e0), mid = [e0, e0 + 8), hi = [e0 + 8,
@@ -367,95 +456,185 @@ __device__ __forceinline__ uint4 shifted8(uint4 lo, uint4 mid, uint4 hi, int s) 
                     __builtin_amdgcn_alignbyte(mid.z, mid.y, 2), __builtin_amdgcn_alignbyte(mid.w, mid.z, 2));
 }
 
-template <int CIN, int COUT>
-__global__ __launch_bounds__(256) void k_wgrad_partial(ffh::ConvArgs a, int rows_per_block) {
+__device__ __forceinline__ uint2 pack4(const uint32_t (&h)[4]) {
+  return make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
+}
+
+// Items: (image, column of 16 pixels, row), row fastest; wave w takes items
+// [w * per_wave, (w + 1) * per_wave).
+template <int CIN, int COUT, bool kSplit>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_wgrad_partial(ffh::ConvArgs a,
+                                                                                               long long per_wave) {
   static_assert((CIN == 1 || CIN == 32) && (COUT == 16 || COUT == 32), "Cin 1 or 32, Cout 16 or 32");
   constexpr int NP = CIN == 1 ? 1 : 10;  // products per pixel block: 9 taps and the bias
-  __shared__ __attribute__((aligned(16))) uint16_t s_x[3][CIN][kWgX];  // [dy][ci][pixel]
-  __shared__ __attribute__((aligned(16))) uint16_t s_g[2][32][kWgG];   // [hi, lo][co][pixel]
-  __shared__ float s_red[4][32 * 32];                                  // the four waves' sums of one product
+  constexpr int XB = CIN == 1 ? 3 * 64 : 18 * 64;  // x: three rows of 32 bf16 (ring) or one row of 18 pixels
+  constexpr int GB = COUT == 32 ? 2048 : 1024;     // g: 16 pixels of both parts
+  constexpr int WAVE_LDS = XB + GB;
+  static_assert(WAVE_LDS % 16 == 0 && 4 * WAVE_LDS <= 4 * 32 * 32 * 4, "the reduction reuses the staging");
+  __shared__ __attribute__((aligned(16))) float s_red[4][32 * 32];  // the four waves' sums of one product
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int col = lane & 31, kh = lane >> 5;
+  uint8_t *sx = reinterpret_cast<uint8_t *>(s_red) + wave * WAVE_LDS, *sg = sx + XB;
   f32x16 acc[NP];
 #pragma unroll
   for (int t = 0; t < NP; ++t) acc[t] = f32x16{0};
-  const uint4 ones = make_uint4(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u);  // bf16 1.0
-  for (int e = tid; e < 2 * (32 - COUT) * kWgG; e += 256)  // gradient rows beyond Cout stay zero
-    s_g[e / ((32 - COUT) * kWgG)][COUT + (e / kWgG) % (32 - COUT)][e % kWgG] = 0;
-  const int nrows = a.B * a.H;
-  const int r0 = blockIdx.x * rows_per_block, r1 = min(r0 + rows_per_block, nrows);
-  for (int rr = r0; rr < r1; ++rr) {
-    const int img = rr / a.H, y = rr % a.H;
-    const long long row = (long long)img * a.H + y;
-    for (int x0 = 0; x0 < a.W; x0 += kWgPx) {
-      __syncthreads();  // the previous step's operands are read
-      for (int e = tid; e < kWgPx * (COUT / 4); e += 256) {
-        const int v = e % (COUT / 4), px = e / (COUT / 4), x = x0 + px;
-        float4 q = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        if (x < a.W) q = *reinterpret_cast<const float4 *>(a.gout + (row * a.W + x) * COUT + 4 * v);
-        const float g[4] = {q.x, q.y, q.z, q.w};
+  const bf16x8 ones = as_bf16x8(make_uint4(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u));  // bf16 1.0
+  const int cx = (a.W + 15) >> 4, W = a.W, H = a.H;
+  const long long total = (long long)a.B * cx * H;
+  const long long i0 = min(((long long)blockIdx.x * 4 + wave) * per_wave, total), i1 = min(i0 + per_wave, total);
+
+  int y = (int)(i0 % H), c = (int)((i0 / H) % cx), img = (int)(i0 / ((long long)H * cx));
+  const uint4 zero4 = make_uint4(0u, 0u, 0u, 0u);
+  // next row of x and g, in flight
+  uint4 xr[2] = {zero4, zero4}, gr[2] = {zero4, zero4};
+  uint32_t xs = 0;
+  auto load_x = [&](int row) {  // pixels 16 c - 1 .. 16 c + 16 of a row; zeros outside the image
+    const bool in_row = row >= 0 && row < H;
+    const size_t base = ((size_t)img * H + (in_row ? row : 0)) * W;
+    if constexpr (CIN == 32) {
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          const uint16_t hi = f32_to_bf16(g[c]);
-          s_g[0][4 * v + c][px] = hi;
-          s_g[1][4 * v + c][px] = f32_to_bf16(g[c] - bf16_to_f32(hi));
-        }
+      for (int it = 0; it < 2; ++it) {
+        const int k = lane + 64 * it, x = 16 * c - 1 + (k >> 2);
+        xr[it] = zero4;
+        if (in_row && k < 72 && x >= 0 && x < W)
+          xr[it] = *reinterpret_cast<const uint4 *>(a.in + (base + x) * 32 + 8 * (k & 3));
       }
-      if constexpr (CIN == 32) {
-        for (int e = tid; e < 3 * 66 * 4; e += 256) {
-          const int v = e & 3, px = (e >> 2) % 66, dy = (e >> 2) / 66;
-          const int sx = x0 + px - 1, sy = y + dy - 1;
-          uint4 q = make_uint4(0u, 0u, 0u, 0u);
-          if (sx >= 0 && sx < a.W && sy >= 0 && sy < a.H)
-            q = *reinterpret_cast<const uint4 *>(a.in + (((long long)img * a.H + sy) * a.W + sx) * 32 + 8 * v);
-          const uint32_t w[4] = {q.x, q.y, q.z, q.w};
-#pragma unroll
-          for (int c = 0; c < 8; ++c) s_x[dy][8 * v + c][px + 7] = (uint16_t)(w[c >> 1] >> (16 * (c & 1)));
+    } else {
+      const int x = 16 * c - 1 + lane;
+      xs = in_row && lane < 18 && x >= 0 && x < W ? a.in[base + x] : 0u;
+    }
+  };
+  auto store_x = [&](int row) {
+    if constexpr (CIN == 32) {
+      *reinterpret_cast<uint4 *>(sx + 16 * lane) = xr[0];
+      if (lane < 8) *reinterpret_cast<uint4 *>(sx + 1024 + 16 * lane) = xr[1];
+    } else if (lane < 18) {  // pixel 16 c - 8 + i at entry i of the row's slot
+      reinterpret_cast<uint16_t *>(sx)[((row + 3) % 3) * 32 + 7 + lane] = (uint16_t)xs;
+    }
+  };
+  auto load_g = [&](int row) {
+    const size_t base = ((size_t)img * H + row) * W;
+    gr[0] = gr[1] = zero4;
+    if constexpr (kSplit) {
+      if constexpr (COUT == 32) {
+        const int x = 16 * c + (lane >> 2);
+        if (x < W) {
+          gr[0] = *reinterpret_cast<const uint4 *>(a.g_hi + (base + x) * 32 + 8 * (lane & 3));
+          gr[1] = *reinterpret_cast<const uint4 *>(a.g_lo + (base + x) * 32 + 8 * (lane & 3));
         }
       } else {
-        for (int e = tid; e < 3 * 66; e += 256) {
-          const int px = e % 66, dy = e / 66;
-          const int sx = x0 + px - 1, sy = y + dy - 1;
-          uint16_t v = 0;
-          if (sx >= 0 && sx < a.W && sy >= 0 && sy < a.H) v = a.in[((long long)img * a.H + sy) * a.W + sx];
-          s_x[dy][0][px + 7] = v;
-        }
+        const int x = 16 * c + ((lane & 31) >> 1);
+        if (x < W) gr[0] = *reinterpret_cast<const uint4 *>((kh ? a.g_lo : a.g_hi) + (base + x) * 16 + 8 * (lane & 1));
       }
-      __syncthreads();
-      if (x0 + 16 * wave >= a.W) continue;  // wave-uniform: the wave's pixels are all outside the row
-      const int pb = 16 * wave + 8 * kh;    // this lane's 8 pixels (the K index of the products)
-      const bf16x8 ahi = as_bf16x8(*reinterpret_cast<const uint4 *>(&s_g[0][col][pb]));
-      const bf16x8 alo = as_bf16x8(*reinterpret_cast<const uint4 *>(&s_g[1][col][pb]));
-      if constexpr (CIN == 1) {
-        // column n of B: tap n (n < 9), the bias (n = 9), nothing beyond
-        uint4 bv = make_uint4(0u, 0u, 0u, 0u);
-        if (col < 9) {
-          const uint16_t *r = s_x[col / 3][0];
-          bv = shifted8(*reinterpret_cast<const uint4 *>(r + pb), *reinterpret_cast<const uint4 *>(r + pb + 8),
-                        *reinterpret_cast<const uint4 *>(r + pb + 16), col % 3 - 1);
-        } else if (col == 9) {
-          bv = ones;
-        }
-        const bf16x8 b = as_bf16x8(bv);
-        acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ahi, b, acc[0], 0, 0, 0);
-        acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(alo, b, acc[0], 0, 0, 0);
+    } else {
+#pragma unroll
+      for (int it = 0; it < COUT / 16; ++it) {
+        const int k = lane + 64 * it, x = 16 * c + k / (COUT / 4);
+        if (x < W) gr[it] = *reinterpret_cast<const uint4 *>(a.gout + (base + x) * COUT + 4 * (k % (COUT / 4)));
+      }
+    }
+  };
+  // LDS rows of 64 bytes per pixel: Cout = 32: the high parts, then the low
+  // ones 1 KB on; Cout = 16: a pixel's high parts and low parts side by side
+  auto store_g = [&]() {
+    if constexpr (kSplit) {
+      if constexpr (COUT == 32) {
+        *reinterpret_cast<uint4 *>(sg + 16 * lane) = gr[0];
+        *reinterpret_cast<uint4 *>(sg + 1024 + 16 * lane) = gr[1];
       } else {
+        *reinterpret_cast<uint4 *>(sg + ((lane & 31) >> 1) * 64 + 32 * kh + 16 * (lane & 1)) = gr[0];
+      }
+    } else {
 #pragma unroll
-        for (int dy = 0; dy < 3; ++dy) {
-          const uint16_t *r = s_x[dy][col];
-          const uint4 lo = *reinterpret_cast<const uint4 *>(r + pb), mid = *reinterpret_cast<const uint4 *>(r + pb + 8),
-                      hi = *reinterpret_cast<const uint4 *>(r + pb + 16);
+      for (int it = 0; it < COUT / 16; ++it) {
+        const int k = lane + 64 * it, px = k / (COUT / 4), v = k % (COUT / 4);
+        const uint32_t w[4] = {gr[it].x, gr[it].y, gr[it].z, gr[it].w};
+        uint32_t hi[4], lo[4];
 #pragma unroll
-          for (int dx = 0; dx < 3; ++dx) {
-            const bf16x8 b = as_bf16x8(shifted8(lo, mid, hi, dx - 1));
-            const int t = 3 * dy + dx;
-            acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ahi, b, acc[t], 0, 0, 0);
-            acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(alo, b, acc[t], 0, 0, 0);
-          }
+        for (int e = 0; e < 4; ++e) {
+          const float g = __uint_as_float(w[e]);
+          hi[e] = f32_to_bf16(g);
+          lo[e] = f32_to_bf16(g - bf16_to_f32((uint16_t)hi[e]));
         }
-        const bf16x8 b1 = as_bf16x8(ones);
-        acc[9] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ahi, b1, acc[9], 0, 0, 0);
-        acc[9] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(alo, b1, acc[9], 0, 0, 0);
+        *reinterpret_cast<uint2 *>(sg + px * 64 + 8 * v) = pack4(hi);
+        *reinterpret_cast<uint2 *>(sg + (COUT == 32 ? 1024 : 32) + px * 64 + 8 * v) = pack4(lo);
+      }
+    }
+  };
+  bf16x8 xb[3][3];  // operands of rows y - 1, y, y + 1 at dx = -1, 0, 1
+  auto read_x = [&](int slot) {
+    if constexpr (CIN == 32) {
+#pragma unroll
+      for (int dx = 0; dx < 3; ++dx) xb[slot][dx] = read_pixels_tr(sx + 64 * dx, lane);
+    }
+  };
+  // a wave's own LDS accesses stay in order; the staging is written and read
+  // through different types, so the compiler must not move them either
+  auto in_order = [] { asm volatile("" ::: "memory"); };
+  bool fresh = true;
+  for (long long i = i0; i < i1; ++i) {
+    in_order();
+    if (fresh) {  // a new column: rows y - 1 and y first
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        load_x(y - 1 + k);
+        store_x(y - 1 + k);
+        in_order();
+        read_x(k);
+        in_order();
+      }
+      load_x(y + 1);
+      load_g(y);
+    }
+    store_x(y + 1);
+    store_g();
+    in_order();
+    read_x(2);
+    const bf16x8 ahi = read_pixels_tr(sg, lane);
+    bf16x8 alo = ahi;
+    if constexpr (COUT == 32) alo = read_pixels_tr(sg + 1024, lane);
+    [[maybe_unused]] bf16x8 b1 = ones;
+    if constexpr (CIN == 1) {
+      // column n of B: tap n (n < 9), the bias (n = 9), nothing beyond
+      uint4 bv = zero4;
+      const int dy = min(col / 3, 2);
+      const uint16_t *r = reinterpret_cast<const uint16_t *>(sx) + ((y + dy + 2) % 3) * 32 + 8 * kh;
+      const uint4 lo = *reinterpret_cast<const uint4 *>(r), mid = *reinterpret_cast<const uint4 *>(r + 8),
+                  hi = *reinterpret_cast<const uint4 *>(r + 16);
+      if (col < 9) bv = shifted8(lo, mid, hi, col % 3 - 1);
+      b1 = col == 9 ? ones : as_bf16x8(bv);
+    }
+    in_order();
+    // the next row's loads, in flight during the products
+    const bool down = y + 1 < H;
+    if (i + 1 < i1 && down) {
+      load_x(y + 2);
+      load_g(y + 1);
+    }
+    if constexpr (CIN == 1) {
+      acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ahi, b1, acc[0], 0, 0, 0);
+      if constexpr (COUT == 32) acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(alo, b1, acc[0], 0, 0, 0);
+    } else {
+#pragma unroll
+      for (int t = 0; t < 10; ++t) {
+        const bf16x8 b = t < 9 ? xb[t / 3][t % 3] : ones;
+        acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ahi, b, acc[t], 0, 0, 0);
+        if constexpr (COUT == 32) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(alo, b, acc[t], 0, 0, 0);
+      }
+#pragma unroll
+      for (int dx = 0; dx < 3; ++dx) {
+        xb[0][dx] = xb[1][dx];
+        xb[1][dx] = xb[2][dx];
+      }
+    }
+    fresh = !down;
+    if (down) {
+      ++y;
+    } else {
+      y = 0;
+      if (++c == cx) {
+        c = 0;
+        ++img;
       }
     }
   }
@@ -468,10 +647,13 @@ __global__ __launch_bounds__(256) void k_wgrad_partial(ffh::ConvArgs a, int rows
 #pragma unroll
     for (int r = 0; r < 16; ++r) s_red[wave][(8 * (r >> 2) + 4 * kh + (r & 3)) * 32 + col] = acc[t][r];
     __syncthreads();
-    for (int e = tid; e < 32 * 32; e += 256) {
+    for (int e = tid; e < COUT * 32; e += 256) {
       const int co = e >> 5, n = e & 31;
-      if (co >= COUT) continue;
-      const float v = ((s_red[0][e] + s_red[1][e]) + s_red[2][e]) + s_red[3][e];
+      float v = ((s_red[0][e] + s_red[1][e]) + s_red[2][e]) + s_red[3][e];
+      if constexpr (COUT == 16) {  // the low parts' rows
+        const int f = e + 16 * 32;
+        v += ((s_red[0][f] + s_red[1][f]) + s_red[2][f]) + s_red[3][f];
+      }
       if constexpr (CIN == 1) {
         if (n < 9) part[co * 9 + n] = v;
         else if (n == 9) part[COUT * 9 + co] = v;
@@ -484,23 +666,29 @@ __global__ __launch_bounds__(256) void k_wgrad_partial(ffh::ConvArgs a, int rows
   }
 }
 
-// Sum of the per-workgroup partials: 8 lanes per output, each adding a
-// contiguous eighth of the partials in order, then the eight sums in a fixed
-// tree (deterministic).
-__global__ __launch_bounds__(256) void k_wgrad_reduce(const float *partial, int nblocks, int len, float *gw,
-                                                      float *gbias, int nw) {
-  const int i = blockIdx.x * 32 + (threadIdx.x >> 3), seg = threadIdx.x & 7;
-  float s = 0.0f;
+// Sum of the per-workgroup partials: 32 threads per output, each adding a
+// contiguous 1/32 of the partials in order, then the 32 sums in a fixed tree
+// (deterministic).  Latency-bound chains of loads: eight threads per output
+// took 43 us for 1024 partials of 9248 values, 32 and half the partials @R1@.
+__global__ __launch_bounds__(1024) void k_wgrad_reduce(const float *partial, int nblocks, int len, float *gw,
+                                                       float *gbias, int nw) {
+  __shared__ float s[32][33];
+  const int o = threadIdx.x & 31, seg = threadIdx.x >> 5, i = blockIdx.x * 32 + o;
+  float v = 0.0f;
   if (i < len) {
-    const int b0 = (int)((long long)nblocks * seg / 8), b1 = (int)((long long)nblocks * (seg + 1) / 8);
-    for (int b = b0; b < b1; ++b) s += partial[(size_t)b * len + i];
+    const int b0 = (int)((long long)nblocks * seg / 32), b1 = (int)((long long)nblocks * (seg + 1) / 32);
+#pragma unroll 4
+    for (int b = b0; b < b1; ++b) v += partial[(size_t)b * len + i];
   }
-  s += __shfl_xor(s, 1);
-  s += __shfl_xor(s, 2);
-  s += __shfl_xor(s, 4);
+  s[seg][o] = v;
+  __syncthreads();
+  for (int w = 16; w > 0; w >>= 1) {
+    if (seg < w) s[seg][o] += s[seg + w][o];
+    __syncthreads();
+  }
   if (seg == 0 && i < len) {
-    if (i < nw) gw[i] = s;
-    else if (gbias) gbias[i - nw] = s;
+    if (i < nw) gw[i] = s[0][o];
+    else if (gbias) gbias[i - nw] = s[0][o];
   }
 }
 
@@ -573,6 +761,44 @@ __global__ __launch_bounds__(256) void k_l2norm16_bwd(const float4 *y, const flo
   for (int k = 0; k < 4; ++k)
     gin[p * 4 + k] = make_float4(r * (gv[k].x - yv[k].x * d), r * (gv[k].y - yv[k].y * d),
                                  r * (gv[k].z - yv[k].z * d), r * (gv[k].w - yv[k].w * d));
+}
+
+// A float32 gradient as two bf16 parts (hi + lo), 4 values per thread.
+__device__ __forceinline__ void store_split(float4 g, uint16_t *hi, uint16_t *lo) {
+  const float v[4] = {g.x, g.y, g.z, g.w};
+  uint32_t h[4], l[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    h[c] = f32_to_bf16(v[c]);
+    l[c] = f32_to_bf16(v[c] - bf16_to_f32((uint16_t)h[c]));
+  }
+  *reinterpret_cast<uint2 *>(hi) = pack4(h);
+  *reinterpret_cast<uint2 *>(lo) = pack4(l);
+}
+
+// k_l2norm16_bwd with its result split, four lanes per pixel (coalesced 16-
+// byte accesses); y nullptr: the split alone.  The inner product is taken by
+// every lane over all 16 channels in k_l2norm16_bwd's order (the other lanes'
+// values by shuffles), so the gradient has the same bits.
+__global__ __launch_bounds__(256) void k_l2norm16_bwd_split(const float4 *y, const float *inv_norm, const float4 *g,
+                                                            long long P, uint16_t *hi, uint16_t *lo) {
+  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x, p = min(i >> 2, P - 1);
+  const int k = (int)(i & 3), base = (threadIdx.x & 63) & ~3;
+  float4 v = g[p * 4 + k];
+  if (y) {
+    const float4 yk = y[p * 4 + k];
+    float d = 0.0f;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      float4 a, b;
+      a.x = __shfl(yk.x, base + q), a.y = __shfl(yk.y, base + q), a.z = __shfl(yk.z, base + q), a.w = __shfl(yk.w, base + q);
+      b.x = __shfl(v.x, base + q), b.y = __shfl(v.y, base + q), b.z = __shfl(v.z, base + q), b.w = __shfl(v.w, base + q);
+      d += a.x * b.x + a.y * b.y + a.z * b.z + a.w * b.w;
+    }
+    const float r = inv_norm[p];
+    v = make_float4(r * (v.x - yk.x * d), r * (v.y - yk.y * d), r * (v.z - yk.z * d), r * (v.w - yk.w * d));
+  }
+  if ((i >> 2) < P) store_split(v, hi + p * 16 + 4 * k, lo + p * 16 + 4 * k);
 }
 
 // Triplet hinge of m (positive, negative) cost pairs: cost[0..m) positives,
@@ -666,17 +892,26 @@ namespace ffh {
 
 static unsigned blocks_of(long long n) { return (unsigned)((n + 255) / 256); }
 
-hipError_t launch_conv_fwd(const ConvArgs &a, hipStream_t stream) {
+hipError_t launch_conv_fwd(const ConvArgs &args, hipStream_t stream) {
+  ConvArgs a = args;
   const long long P = (long long)a.B * a.H * a.W;
   const unsigned grid = (unsigned)((P + 127) / 128);
   if (P == 0) return hipSuccess;
   const long long tiles = (long long)a.B * ((a.W + 31) / 32) * ((a.H + kConvRows - 1) / kConvRows);
   if (tiles > 0x7FFFFFFF) return hipErrorInvalidValue;
-  const dim3 tgrid((unsigned)tiles);
-  if (a.cin == 1 && a.cout == 32) hipLaunchKernelGGL((k_conv_fwd<1, 32>), dim3(grid), dim3(256), 0, stream, a);
-  else if (a.cin == 32 && a.cout == 32) hipLaunchKernelGGL((k_conv_fwd_tile<32, 32>), tgrid, dim3(256), 0, stream, a);
-  else if (a.cin == 32 && a.cout == 16) hipLaunchKernelGGL((k_conv_fwd_tile<32, 16>), tgrid, dim3(256), 0, stream, a);
-  else if (a.cin == 16 && a.cout == 32) hipLaunchKernelGGL((k_conv_fwd_tile<16, 32>), tgrid, dim3(256), 0, stream, a);
+  a.wide = ((uintptr_t)a.out_f32 & 15) == 0 && ((uintptr_t)a.out_bf16 & 7) == 0;
+  const dim3 tgrid((unsigned)tiles), block(256);
+  if (a.inv_norm) {  // the last layer with the normalisation
+    if (a.cin != 32 || a.cout != 16) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_conv_fwd_tile<32, 16, kConvNorm>), tgrid, block, 0, stream, a);
+  } else if (a.act) {  // a data gradient through a ReLU
+    if (a.cin == 32 && a.cout == 32) hipLaunchKernelGGL((k_conv_fwd_tile<32, 32, kConvMask>), tgrid, block, 0, stream, a);
+    else if (a.cin == 16 && a.cout == 32) hipLaunchKernelGGL((k_conv_fwd_tile<16, 32, kConvMask>), tgrid, block, 0, stream, a);
+    else return hipErrorInvalidValue;
+  } else if (a.cin == 1 && a.cout == 32) hipLaunchKernelGGL((k_conv_fwd<1, 32>), dim3(grid), block, 0, stream, a);
+  else if (a.cin == 32 && a.cout == 32) hipLaunchKernelGGL((k_conv_fwd_tile<32, 32, kConvPlain>), tgrid, block, 0, stream, a);
+  else if (a.cin == 32 && a.cout == 16) hipLaunchKernelGGL((k_conv_fwd_tile<32, 16, kConvPlain>), tgrid, block, 0, stream, a);
+  else if (a.cin == 16 && a.cout == 32) hipLaunchKernelGGL((k_conv_fwd_tile<16, 32, kConvPlain>), tgrid, block, 0, stream, a);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
@@ -695,16 +930,27 @@ hipError_t launch_weight_flip(const uint16_t *w, uint16_t *wf, int cin, int cout
 
 int wgrad_blocks(int B, int H) { return std::min(B * H, 1024); }
 
+template <int CIN, int COUT>
+static void wgrad_kernel(const ConvArgs &a, int blocks, long long per_wave, hipStream_t stream) {
+  if (a.g_hi)
+    hipLaunchKernelGGL((k_wgrad_partial<CIN, COUT, true>), dim3(blocks), dim3(256), 0, stream, a, per_wave);
+  else
+    hipLaunchKernelGGL((k_wgrad_partial<CIN, COUT, false>), dim3(blocks), dim3(256), 0, stream, a, per_wave);
+}
+
 hipError_t launch_wgrad(const ConvArgs &a, float *gw, float *gbias, hipStream_t stream) {
-  const int nrows = a.B * a.H, nb = wgrad_blocks(a.B, a.H);
-  const int rpb = (nrows + nb - 1) / nb;
-  const int used = (nrows + rpb - 1) / rpb;
-  if (a.cin == 1 && a.cout == 32) hipLaunchKernelGGL((k_wgrad_partial<1, 32>), dim3(used), dim3(256), 0, stream, a, rpb);
-  else if (a.cin == 32 && a.cout == 32) hipLaunchKernelGGL((k_wgrad_partial<32, 32>), dim3(used), dim3(256), 0, stream, a, rpb);
-  else if (a.cin == 32 && a.cout == 16) hipLaunchKernelGGL((k_wgrad_partial<32, 16>), dim3(used), dim3(256), 0, stream, a, rpb);
+  // two workgroups per compute unit (two waves per SIMD), each with one run of
+  // items per wave; at least 16 items a wave, so that the three rows a run
+  // starts with and the partials stay small beside them
+  const long long items = (long long)a.B * ((a.W + 15) / 16) * a.H;
+  const int nb = (int)std::max<long long>(1, std::min<long long>(std::min(wgrad_blocks(a.B, a.H), 512), items / 64));
+  const long long per_wave = (items + 4ll * nb - 1) / (4ll * nb);
+  if (a.cin == 1 && a.cout == 32) wgrad_kernel<1, 32>(a, nb, per_wave, stream);
+  else if (a.cin == 32 && a.cout == 32) wgrad_kernel<32, 32>(a, nb, per_wave, stream);
+  else if (a.cin == 32 && a.cout == 16) wgrad_kernel<32, 16>(a, nb, per_wave, stream);
   else return hipErrorInvalidValue;
   const int nw = a.cout * 9 * a.cin, len = nw + a.cout;
-  hipLaunchKernelGGL(k_wgrad_reduce, dim3((unsigned)((len + 31) / 32)), dim3(256), 0, stream, a.partial, used, len, gw,
+  hipLaunchKernelGGL(k_wgrad_reduce, dim3((unsigned)((len + 31) / 32)), dim3(1024), 0, stream, a.partial, nb, len, gw,
                      gbias, nw);
   return hipGetLastError();
 }
@@ -748,6 +994,14 @@ hipError_t launch_l2norm16_bwd(const float *y, const float *inv_norm, const floa
   if (P > 0)
     hipLaunchKernelGGL(k_l2norm16_bwd, dim3(blocks_of(P)), dim3(256), 0, stream, reinterpret_cast<const float4 *>(y),
                        inv_norm, reinterpret_cast<const float4 *>(g), P, reinterpret_cast<float4 *>(gin));
+  return hipGetLastError();
+}
+
+hipError_t launch_l2norm16_bwd_split(const float *y, const float *inv_norm, const float *g, long long P, uint16_t *hi,
+                                     uint16_t *lo, hipStream_t stream) {
+  if (P > 0)
+    hipLaunchKernelGGL(k_l2norm16_bwd_split, dim3(blocks_of(4 * P)), dim3(256), 0, stream,
+                       reinterpret_cast<const float4 *>(y), inv_norm, reinterpret_cast<const float4 *>(g), P, hi, lo);
   return hipGetLastError();
 }
 

@@ -279,7 +279,15 @@ struct ConvArgs {
   int B, H, W, cin, cout, relu;
   float *out_f32;      // [B][H][W][cout] (nullable)
   uint16_t *out_bf16;  // [B][H][W][cout] (nullable)
-  const float *gout;   // weight gradient: upstream gradient [B][H][W][cout] f32
+  int wide;            // set by the launcher: outputs aligned for 4-channel stores
+  // data gradient through a ReLU: its output, and the low parts (out_bf16 takes the high ones)
+  const uint16_t *act;  // [B][H][W][cout] (nullable)
+  uint16_t *out_lo;
+  // last layer with unit length per pixel (out_f32): 1 / sqrt(|f|^2 + delta) per pixel
+  float *inv_norm;     // [B][H][W] (nullable)
+  float delta;
+  const float *gout;   // weight gradient: upstream gradient [B][H][W][cout] f32,
+  const uint16_t *g_hi, *g_lo;  // or its two bf16 parts
   float *partial;      // weight gradient: per-block partial sums
 };
 hipError_t launch_conv_fwd(const ConvArgs &a, hipStream_t stream);
@@ -300,6 +308,8 @@ hipError_t launch_relu_bwd(const uint16_t *act, const float *g, float *gout, uin
                            hipStream_t stream);
 hipError_t launch_f32_to_bf16(const float *x, uint16_t *y, long long count, hipStream_t stream);
 hipError_t launch_image_to_bf16(const uint8_t *img, uint16_t *out, long long count, hipStream_t stream);
+hipError_t launch_l2norm16_bwd_split(const float *y, const float *inv_norm, const float *g, long long P, uint16_t *hi,
+                                     uint16_t *lo, hipStream_t stream);
 hipError_t launch_triplet_hinge(const float *cost, int m, float margin, float scale, float weight, float *grad,
                                 float *loss, hipStream_t stream);
 hipError_t launch_l2norm16_fwd(const float *f, long long P, float delta, float *y, float *inv_norm,

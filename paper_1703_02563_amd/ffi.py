@@ -97,6 +97,10 @@ _SIGS = {
     "ff_conv3x3_bwd_data": (C.c_int, [_P, _I32, _I32, _I32, _I32, _I32, _P, _P, _P, _P, _P]),
     "ff_conv3x3_wgrad_scratch_bytes": (C.c_size_t, [_I32, _I32, _I32, _I32]),
     "ff_conv3x3_bwd_weight": (C.c_int, [_P, _P, _I32, _I32, _I32, _I32, _I32, _P, C.c_size_t, _P, _P, _P]),
+    "ff_conv3x3_norm_fwd": (C.c_int, [_P, _I32, _I32, _I32, _P, _P, C.c_float, _P, _P, _P]),
+    "ff_conv3x3_bwd_data_split": (C.c_int, [_P, _I32, _I32, _I32, _I32, _I32, _P, _P, _P, _P, _P, _P]),
+    "ff_conv3x3_bwd_weight_split": (C.c_int, [_P, _P, _P, _I32, _I32, _I32, _I32, _I32, _P, C.c_size_t, _P, _P, _P]),
+    "ff_l2norm16_bwd_split": (C.c_int, [_P, _P, _P, C.c_int64, _P, _P, _P]),
     "ff_relu_bwd": (C.c_int, [_P, _P, C.c_int64, _P, _P, _P]),
     "ff_f32_to_bf16": (C.c_int, [_P, C.c_int64, _P, _P]),
     "ff_image_to_bf16": (C.c_int, [_P, C.c_int64, _P, _P]),

@@ -143,6 +143,13 @@ class DescNet:
         out = None
         for k, (cin, cout, relu) in enumerate(LAYERS):
             last = k == len(LAYERS) - 1
+            if last and self.normalize:
+                out = torch.empty((B, H, W, cout), dtype=torch.float32, device=x_bits.device)
+                inv = torch.empty((B, H, W), dtype=torch.float32, device=x_bits.device)
+                check(lib().ff_conv3x3_norm_fwd(_ptr(acts[-1]), B, H, W, _ptr(self.wb[k]), _ptr(self.b[k]), self.delta,
+                                                _ptr(out), _ptr(inv), _stream()), "ff_conv3x3_norm_fwd")
+                acts.append((out, inv))
+                break
             o32 = torch.empty((B, H, W, cout), dtype=torch.float32, device=x_bits.device) if last else None
             o16 = None if last else torch.empty((B, H, W, cout), dtype=torch.int16, device=x_bits.device)
             check(lib().ff_conv3x3_fwd(_ptr(acts[-1]), B, H, W, cin, cout, _ptr(self.wb[k]), _ptr(self.b[k]),
@@ -151,11 +158,6 @@ class DescNet:
                 out = o32
             else:
                 acts.append(o16)
-        if self.normalize:
-            inv = torch.empty((B, H, W), dtype=torch.float32, device=x_bits.device)
-            check(lib().ff_l2norm16_fwd(_ptr(out), out.numel() // 16, self.delta, _ptr(out), _ptr(inv), _stream()),
-                  "ff_l2norm16_fwd")
-            acts.append((out, inv))
         return (out, acts) if keep else out
 
     def backward(self, acts, grad_out: torch.Tensor):
@@ -164,33 +166,30 @@ class DescNet:
         B, H, W, _ = grad_out.shape
         gws, gbs = [None] * 3, [None] * 3
         g32 = grad_out.contiguous().float()
-        if self.normalize:
-            y, inv = acts[len(LAYERS)]
-            gn = torch.empty_like(g32)
-            check(lib().ff_l2norm16_bwd(_ptr(y), _ptr(inv), _ptr(g32, torch.float32), g32.numel() // 16, _ptr(gn),
-                                        _stream()), "ff_l2norm16_bwd")
-            g32 = gn
+        y, inv = acts[len(LAYERS)] if self.normalize else (None, None)
+        # the gradient of every layer's output as two bf16 parts
+        hi, lo = (torch.empty((B, H, W, 16), dtype=torch.int16, device=grad_out.device) for _ in range(2))
+        check(lib().ff_l2norm16_bwd_split(_ptr(y), _ptr(inv), _ptr(g32, torch.float32), g32.numel() // 16, _ptr(hi),
+                                          _ptr(lo), _stream()), "ff_l2norm16_bwd_split")
         for k in range(len(LAYERS) - 1, -1, -1):
             cin, cout, relu = LAYERS[k]
             nbytes = int(lib().ff_conv3x3_wgrad_scratch_bytes(B, H, cin, cout))
             scratch = torch.empty(nbytes // 4, dtype=torch.float32, device=grad_out.device)
             gw = torch.empty((cout, 9, cin), dtype=torch.float32, device=grad_out.device)
             gb = torch.empty(cout, dtype=torch.float32, device=grad_out.device)
-            check(lib().ff_conv3x3_bwd_weight(_ptr(acts[k]), _ptr(g32, torch.float32), B, H, W, cin, cout,
-                                              _ptr(scratch), nbytes, _ptr(gw), _ptr(gb), _stream()),
-                  "ff_conv3x3_bwd_weight")
+            check(lib().ff_conv3x3_bwd_weight_split(_ptr(acts[k]), _ptr(hi), _ptr(lo), B, H, W, cin, cout,
+                                                    _ptr(scratch), nbytes, _ptr(gw), _ptr(gb), _stream()),
+                  "ff_conv3x3_bwd_weight_split")
             gws[k], gbs[k] = gw, gb
             if k == 0:
                 break
-            # gradient of the layer input, then through the previous ReLU
-            g16 = _bf16_bits(g32)
+            # gradient of the layer input, through the previous ReLU
             flip = torch.empty((cin, 9, cout), dtype=torch.int16, device=grad_out.device)
-            gin = torch.empty((B, H, W, cin), dtype=torch.float32, device=grad_out.device)
-            check(lib().ff_conv3x3_bwd_data(_ptr(g16), B, H, W, cin, cout, _ptr(self.wb[k]), _ptr(flip), _ptr(gin),
-                                            None, _stream()), "ff_conv3x3_bwd_data")
-            g32 = torch.empty_like(gin)
-            check(lib().ff_relu_bwd(_ptr(acts[k]), _ptr(gin, torch.float32), gin.numel(), _ptr(g32), None,
-                                    _stream()), "ff_relu_bwd")
+            nhi, nlo = (torch.empty((B, H, W, cin), dtype=torch.int16, device=grad_out.device) for _ in range(2))
+            check(lib().ff_conv3x3_bwd_data_split(_ptr(hi), B, H, W, cin, cout, _ptr(self.wb[k]), _ptr(flip),
+                                                  _ptr(acts[k]), _ptr(nhi), _ptr(nlo), _stream()),
+                  "ff_conv3x3_bwd_data_split")
+            hi, lo = nhi, nlo
         return gws, gbs
 
     def adam(self, gws, gbs, lr: float = 1e-3, b1: float = 0.9, b2: float = 0.999, eps: float = 1e-8):
