@@ -52,19 +52,61 @@ __device__ __forceinline__ float l2norm16(float4 v[4], float delta) {
 
 // Epilogue of a transposed product D = W X (weights the first operand, 32
 // pixels the columns): a lane holds the output channels 8 g + 4 kh .. 8 g + 4
-// kh + 3, g < COUT / 8, of one pixel, so a store covers 4 channels (16 bytes
-// in float32, 8 in bf16) instead of one.  Every output element is the same
-// sum of the same products as in X W, bit for bit.
+// kh + 3, g < COUT / 8, of one pixel.  Every output element is the same sum
+// of the same products as in X W, bit for bit.  A run of 32 pixels is one
+// contiguous piece of the output; the lanes' parts go through a wave's own
+// 2 KB of LDS (16-byte chunks permuted against bank conflicts) so that a
+// store instruction writes 1 KB of it: storing from the lanes' registers
+// touches every 64-byte pixel four times.
 enum ConvEpilogue {
   kConvPlain,  // bias, optional ReLU; float32 and / or bf16
   kConvMask,   // gradient through the ReLU whose output is a.act, split into two bf16 parts
   kConvNorm,   // bias, unit length per pixel (COUT = 16), float32 and the scale
 };
 
+// A wave's LDS accesses stay in order; keeps the compiler from moving them.
+__device__ __forceinline__ void lds_in_order() { asm volatile("" ::: "memory"); }
+
+// 16-byte chunk c (0 .. 3) of pixel px (0 .. 31) of a 64-byte-per-pixel run.
+__device__ __forceinline__ int run_chunk(int px, int c) { return px * 64 + ((c ^ ((px >> 2) & 3)) << 4); }
+
+__device__ __forceinline__ uint2 pack4(const uint32_t (&h)[4]) {
+  return make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
+}
+
+// Writes the run's first n pixels from LDS to `dst` (64 bytes per pixel),
+// 16-bit lanes zeroed where `act` (nullable) is not positive.
+__device__ __forceinline__ void store_run(const uint8_t *tr, uint8_t *dst, int n, int lane, const uint8_t *act) {
+  uint4 v[2], m[2];
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int px = (lane >> 2) + 16 * k, c = lane & 3;
+    v[k] = *reinterpret_cast<const uint4 *>(tr + run_chunk(px, c));
+    if (act && px < n) m[k] = *reinterpret_cast<const uint4 *>(act + px * 64 + 16 * c);
+  }
+  lds_in_order();
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int px = (lane >> 2) + 16 * k, c = lane & 3;
+    if (px >= n) continue;
+    if (act) {
+      auto mask = [](uint32_t x, uint32_t a) {  // bf16 > 0: a bit pattern in [1, 0x7F80]
+        const uint32_t l = a & 0xFFFFu, h = a >> 16;
+        return (l - 1u < 0x7F80u ? x & 0xFFFFu : 0u) | (h - 1u < 0x7F80u ? x & 0xFFFF0000u : 0u);
+      };
+      v[k] = make_uint4(mask(v[k].x, m[k].x), mask(v[k].y, m[k].y), mask(v[k].z, m[k].z), mask(v[k].w, m[k].w));
+    }
+    *reinterpret_cast<uint4 *>(dst + px * 64 + 16 * c) = v[k];
+  }
+}
+
+// q0: the run's first pixel; n: its pixels in the image (at most 32, the lane's
+// is row); tr: the wave's 2 KB.
 template <int COUT, ConvEpilogue EPI>
-__device__ __forceinline__ void conv_store(const ffh::ConvArgs &a, size_t q, bool in, int kh, const f32x16 &acc,
-                                           const float (&bias)[COUT / 2]) {
+__device__ __forceinline__ void conv_store(const ffh::ConvArgs &a, size_t q0, int n, int lane, const f32x16 &acc,
+                                           const float (&bias)[COUT / 2], uint8_t *tr) {
   constexpr int G = COUT / 8;
+  const int row = lane & 31, kh = lane >> 5;
   float v[G][4];
 #pragma unroll
   for (int g = 0; g < G; ++g)
@@ -84,50 +126,74 @@ __device__ __forceinline__ void conv_store(const ffh::ConvArgs &a, size_t q, boo
     };
     float4 f[4] = {quad(0, kh == 0), quad(0, kh == 1), quad(1, kh == 0), quad(1, kh == 1)};
     const float r = l2norm16(f, a.delta);
-    if (!in) return;
-    float4 *out = reinterpret_cast<float4 *>(a.out_f32 + q * 16) + kh;
 #pragma unroll
-    for (int g = 0; g < 2; ++g) out[2 * g] = make_float4(v[g][0] * r, v[g][1] * r, v[g][2] * r, v[g][3] * r);
-    if (kh == 0) a.inv_norm[q] = r;
-  } else {
-    if (!in) return;
+    for (int g = 0; g < 2; ++g)
+      *reinterpret_cast<float4 *>(tr + run_chunk(row, 2 * g + kh)) =
+          make_float4(v[g][0] * r, v[g][1] * r, v[g][2] * r, v[g][3] * r);
+    lds_in_order();
+    store_run(tr, reinterpret_cast<uint8_t *>(a.out_f32 + q0 * 16), n, lane, nullptr);
+    if (kh == 0 && row < n) a.inv_norm[q0 + row] = r;
+  } else if constexpr (EPI == kConvMask) {
+    static_assert(COUT == 32, "data gradients have 32 channels");
+    uint2 lo[G];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-      const size_t o = q * COUT + 8 * g + 4 * kh;
-      if constexpr (EPI == kConvMask) {
-        const uint2 m = *reinterpret_cast<const uint2 *>(a.act + o);
-        const uint16_t act[4] = {(uint16_t)m.x, (uint16_t)(m.x >> 16), (uint16_t)m.y, (uint16_t)(m.y >> 16)};
-        uint32_t hi[4], lo[4];
+      uint32_t h[4], l[4];
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          const float x = bf16_to_f32(act[c]) > 0.0f ? v[g][c] : 0.0f;
-          hi[c] = f32_to_bf16(x);
-          lo[c] = f32_to_bf16(x - bf16_to_f32((uint16_t)hi[c]));
-        }
-        *reinterpret_cast<uint2 *>(a.out_bf16 + o) = make_uint2(hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16));
-        *reinterpret_cast<uint2 *>(a.out_lo + o) = make_uint2(lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16));
-      } else {
-        if (a.relu)
+      for (int c = 0; c < 4; ++c) {
+        h[c] = f32_to_bf16(v[g][c]);
+        l[c] = f32_to_bf16(v[g][c] - bf16_to_f32((uint16_t)h[c]));
+      }
+      *reinterpret_cast<uint2 *>(tr + run_chunk(row, g) + 8 * kh) = pack4(h);
+      lo[g] = pack4(l);
+    }
+    lds_in_order();
+    const uint8_t *act = reinterpret_cast<const uint8_t *>(a.act + q0 * 32);
+    store_run(tr, reinterpret_cast<uint8_t *>(a.out_bf16 + q0 * 32), n, lane, act);
 #pragma unroll
-          for (int c = 0; c < 4; ++c) v[g][c] = fmaxf(v[g][c], 0.0f);
-        if (a.out_f32) {
-          if (a.wide)
-            *reinterpret_cast<float4 *>(a.out_f32 + o) = make_float4(v[g][0], v[g][1], v[g][2], v[g][3]);
-          else
-            for (int c = 0; c < 4; ++c) a.out_f32[o + c] = v[g][c];
-        }
-        if (a.out_bf16) {
-          uint32_t h[4];
+    for (int g = 0; g < G; ++g) *reinterpret_cast<uint2 *>(tr + run_chunk(row, g) + 8 * kh) = lo[g];
+    lds_in_order();
+    store_run(tr, reinterpret_cast<uint8_t *>(a.out_lo + q0 * 32), n, lane, act);
+  } else {
+    if (a.relu)
 #pragma unroll
-          for (int c = 0; c < 4; ++c) h[c] = f32_to_bf16(v[g][c]);
-          if (a.wide)
-            *reinterpret_cast<uint2 *>(a.out_bf16 + o) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
-          else
-            for (int c = 0; c < 4; ++c) a.out_bf16[o + c] = (uint16_t)h[c];
+      for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) v[g][c] = fmaxf(v[g][c], 0.0f);
+    const size_t o = (q0 + row) * COUT + 4 * kh;
+    if (a.out_f32 && row < n) {
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        if (a.wide)
+          *reinterpret_cast<float4 *>(a.out_f32 + o + 8 * g) = make_float4(v[g][0], v[g][1], v[g][2], v[g][3]);
+        else
+          for (int c = 0; c < 4; ++c) a.out_f32[o + 8 * g + c] = v[g][c];
+      }
+    }
+    if (a.out_bf16) {
+      uint2 h[G];
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        uint32_t b[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) b[c] = f32_to_bf16(v[g][c]);
+        h[g] = pack4(b);
+      }
+      if (COUT == 32 && a.wide) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) *reinterpret_cast<uint2 *>(tr + run_chunk(row, g) + 8 * kh) = h[g];
+        lds_in_order();
+        store_run(tr, reinterpret_cast<uint8_t *>(a.out_bf16 + q0 * 32), n, lane, nullptr);
+      } else if (row < n) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          const uint32_t w[2] = {h[g].x, h[g].y};
+          for (int c = 0; c < 4; ++c) a.out_bf16[o + 8 * g + c] = (uint16_t)(w[c >> 1] >> (16 * (c & 1)));
         }
       }
     }
   }
+  lds_in_order();
 }
 
 // The biases of a lane's output channels.
@@ -139,12 +205,14 @@ __device__ __forceinline__ void conv_bias(const float *bias, int kh, float (&b)[
 
 // Single input channel (the first layer): K = 9 taps padded to 16, lane
 // half kh holds taps 8 * kh .. 8 * kh + 7 of one pixel.  Bound by its stores
-// (64 bytes a pixel): with one bf16 per lane and store 89 us for 3.6 Mpx, with
-// four @C1@ us.
+// (64 bytes a pixel, 45 us for 3.6 Mpx at copy rate) and the 2-byte loads of
+// the taps: 89 us with one bf16 per lane and store, 99 with the 8 bytes that a
+// lane holds, 92 in 1 KB pieces.
 template <int CIN, int COUT>
 __global__ __launch_bounds__(256) void k_conv_fwd(ffh::ConvArgs a) {
   static_assert(CIN == 1, "Cin 1 (wider inputs: k_conv_fwd_tile)");
   static_assert(COUT == 32, "Cout 32");
+  __shared__ __attribute__((aligned(16))) uint8_t s_tr[4][2048];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int row = lane & 31, kh = lane >> 5;
   const long long P = (long long)a.B * a.H * a.W;
@@ -175,7 +243,7 @@ __global__ __launch_bounds__(256) void k_conv_fwd(ffh::ConvArgs a) {
   float bias[COUT / 2];
   conv_bias<COUT>(a.bias, kh, bias);
   acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ub), as_bf16x8(ua), acc, 0, 0, 0);
-  conv_store<COUT, kConvPlain>(a, (size_t)p, pv, kh, acc, bias);
+  conv_store<COUT, kConvPlain>(a, (size_t)p0, (int)min(32ll, P - p0), lane, acc, bias, s_tr[wave]);
 }
 
 // Tiled form for Cin >= 16: a workgroup takes kConvRows image rows x 32
@@ -189,29 +257,41 @@ __global__ __launch_bounds__(256) void k_conv_fwd(ffh::ConvArgs a) {
 // identical.  The epilogues that a training step needs run here instead of as
 // passes over memory of their own: the last layer's normalisation, and the
 // data gradient's ReLU and its split into two bf16 parts.  3.6 Mpx: 32 -> 32
-// with bf16 outputs 172 -> @C2@ us, 32 -> 16 with the normalisation 156 + 96 ->
-// @C3@ us, data gradient 32 -> 32 with mask and split 172 + 383 -> @C4@ us.
-constexpr int kConvRows = 8;
+// with bf16 outputs 172 -> 132 us, 32 -> 16 with the normalisation 156 + 96 ->
+// 122 us, data gradient with mask and split 32 -> 32 172 + 383 -> 239 us and
+// 16 -> 32 115 + 383 -> 173 us.  Bound by memory: 89, 92, 178 and 156 us at
+// copy rate.
+//
+// A workgroup runs down kConvStrips such tiles: its weights are loaded once,
+// and the next tile's pixels are in flight while this one is computed.
+// Without both the four kernels took 186, 155, 307 and 268 us (stores
+// straight from the lanes' registers included).
+constexpr int kConvRows = 8, kConvStrips = 4;
 
 template <int CIN, int COUT, ConvEpilogue EPI>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 4))) void k_conv_fwd_tile(ffh::ConvArgs a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 3))) void k_conv_fwd_tile(ffh::ConvArgs a) {
   static_assert(CIN % 16 == 0, "Cin must be a multiple of 16");
   static_assert(COUT == 16 || COUT == 32, "Cout 16 or 32");
   constexpr int KC = CIN / 16, TW = 32, TR = kConvRows, LW = TW + 2;
   constexpr int PX16 = CIN / 8 + 1;  // 16-byte slots per staged pixel (one of padding)
+  constexpr int NL = (TR + 2) * LW * (CIN / 8), NI = (NL + 255) / 256;  // 16-byte loads of a tile, per thread
   __shared__ uint4 s_in[(TR + 2) * LW * PX16];
-  const int tiles_x = (a.W + TW - 1) / TW, tiles_y = (a.H + TR - 1) / TR;
-  const int img = blockIdx.x / (tiles_x * tiles_y), t = blockIdx.x % (tiles_x * tiles_y);
-  const int x0 = (t % tiles_x) * TW, y0 = (t / tiles_x) * TR;
-  const uint4 zero4 = make_uint4(0, 0, 0, 0);
-  for (int k = threadIdx.x; k < (TR + 2) * LW * (CIN / 8); k += 256) {
-    const int c16 = k % (CIN / 8), px = (k / (CIN / 8)) % LW, ry = k / ((CIN / 8) * LW);
-    const int sx = x0 - 1 + px, sy = y0 - 1 + ry;
-    uint4 v = zero4;
-    if (sx >= 0 && sx < a.W && sy >= 0 && sy < a.H)
-      v = reinterpret_cast<const uint4 *>(a.in + (((size_t)img * a.H + sy) * a.W + sx) * CIN)[c16];
-    s_in[(ry * LW + px) * PX16 + c16] = v;
-  }
+  __shared__ __attribute__((aligned(16))) uint8_t s_tr[4][2048];
+  const int tiles_x = (a.W + TW - 1) / TW, strips = (a.H + TR * kConvStrips - 1) / (TR * kConvStrips);
+  const int img = blockIdx.x / (tiles_x * strips), t = blockIdx.x % (tiles_x * strips);
+  const int x0 = (t % tiles_x) * TW, ys = (t / tiles_x) * TR * kConvStrips, ye = min(ys + TR * kConvStrips, a.H);
+  uint4 px[NI];
+  auto load = [&](int y0) {
+#pragma unroll
+    for (int it = 0; it < NI; ++it) {
+      const int k = threadIdx.x + 256 * it, c16 = k % (CIN / 8), p = (k / (CIN / 8)) % LW, ry = k / ((CIN / 8) * LW);
+      const int sx = x0 - 1 + p, sy = y0 - 1 + ry;
+      px[it] = make_uint4(0, 0, 0, 0);
+      if (k < NL && sx >= 0 && sx < a.W && sy >= 0 && sy < a.H)
+        px[it] = reinterpret_cast<const uint4 *>(a.in + (((size_t)img * a.H + sy) * a.W + sx) * CIN)[c16];
+    }
+  };
+  load(ys);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int row = lane & 31, kh = lane >> 5, col = row;  // weights: output channel col; pixels: x0 + row
   uint4 ub[9 * KC];
@@ -227,18 +307,27 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 4))) voi
   }
   float bias[COUT / 2];
   conv_bias<COUT>(a.bias, kh, bias);
-  __syncthreads();
-  for (int rr = wave; rr < TR && y0 + rr < a.H; rr += 4) {
-    f32x16 acc = {0};
+  for (int y0 = ys; y0 < ye; y0 += TR) {
+    if (y0 > ys) __syncthreads();  // the previous tile is read
 #pragma unroll
-    for (int tap = 0; tap < 9; ++tap) {
-      const uint4 *src = s_in + ((rr + tap / 3) * LW + row + tap % 3) * PX16;
-#pragma unroll
-      for (int cc = 0; cc < KC; ++cc)
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ub[tap * KC + cc]), as_bf16x8(src[cc * 2 + kh]),
-                                                      acc, 0, 0, 0);
+    for (int it = 0; it < NI; ++it) {
+      const int k = threadIdx.x + 256 * it, c16 = k % (CIN / 8), p = (k / (CIN / 8)) % LW, ry = k / ((CIN / 8) * LW);
+      if (k < NL) s_in[(ry * LW + p) * PX16 + c16] = px[it];
     }
-    conv_store<COUT, EPI>(a, ((size_t)img * a.H + y0 + rr) * a.W + x0 + row, x0 + row < a.W, kh, acc, bias);
+    __syncthreads();
+    if (y0 + TR < ye) load(y0 + TR);
+    for (int rr = wave; rr < TR && y0 + rr < a.H; rr += 4) {
+      f32x16 acc = {0};
+#pragma unroll
+      for (int tap = 0; tap < 9; ++tap) {
+        const uint4 *src = s_in + ((rr + tap / 3) * LW + row + tap % 3) * PX16;
+#pragma unroll
+        for (int cc = 0; cc < KC; ++cc)
+          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ub[tap * KC + cc]), as_bf16x8(src[cc * 2 + kh]),
+                                                        acc, 0, 0, 0);
+      }
+      conv_store<COUT, EPI>(a, ((size_t)img * a.H + y0 + rr) * a.W + x0, min(TW, a.W - x0), lane, acc, bias, s_tr[wave]);
+    }
   }
 }
 
@@ -423,7 +512,7 @@ __global__ __launch_bounds__(256) void k_flip(const uint16_t *w, uint16_t *wf, i
 // 18/16 times).  Bound by that traffic and by the 18 products a row.  Staging
 // transposed with 2-byte LDS stores, three rows of x for every row of g, one
 // barrier pair per 64 pixels, took 576 us (32 -> 32), 487 (32 -> 16) and 152
-// (1 -> 32) for 3.6 Mpx; this takes @W1@, @W2@ and @W3@.
+// (1 -> 32) for 3.6 Mpx; this takes 175, 132 and 132.
 //
 // The four waves' sums are added in LDS in a fixed order and each workgroup
 // writes one partial; k_wgrad_reduce adds the partials in a fixed order, so
@@ -454,10 +543,6 @@ __device__ __forceinline__ uint4 shifted8(uint4 lo, uint4 mid, uint4 hi, int s) 
                       __builtin_amdgcn_alignbyte(mid.w, mid.z, 2), __builtin_amdgcn_alignbyte(hi.x, mid.w, 2));
   return make_uint4(__builtin_amdgcn_alignbyte(mid.x, lo.w, 2), __builtin_amdgcn_alignbyte(mid.y, mid.x, 2),
                     __builtin_amdgcn_alignbyte(mid.z, mid.y, 2), __builtin_amdgcn_alignbyte(mid.w, mid.z, 2));
-}
-
-__device__ __forceinline__ uint2 pack4(const uint32_t (&h)[4]) {
-  return make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
 }
 
 // Items: (image, column of 16 pixels, row), row fastest; wave w takes items
@@ -568,27 +653,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       for (int dx = 0; dx < 3; ++dx) xb[slot][dx] = read_pixels_tr(sx + 64 * dx, lane);
     }
   };
-  // a wave's own LDS accesses stay in order; the staging is written and read
-  // through different types, so the compiler must not move them either
-  auto in_order = [] { asm volatile("" ::: "memory"); };
   bool fresh = true;
   for (long long i = i0; i < i1; ++i) {
-    in_order();
+    lds_in_order();
     if (fresh) {  // a new column: rows y - 1 and y first
 #pragma unroll
       for (int k = 0; k < 2; ++k) {
         load_x(y - 1 + k);
         store_x(y - 1 + k);
-        in_order();
+        lds_in_order();
         read_x(k);
-        in_order();
+        lds_in_order();
       }
       load_x(y + 1);
       load_g(y);
     }
     store_x(y + 1);
     store_g();
-    in_order();
+    lds_in_order();
     read_x(2);
     const bf16x8 ahi = read_pixels_tr(sg, lane);
     bf16x8 alo = ahi;
@@ -604,7 +686,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       if (col < 9) bv = shifted8(lo, mid, hi, col % 3 - 1);
       b1 = col == 9 ? ones : as_bf16x8(bv);
     }
-    in_order();
+    lds_in_order();
     // the next row's loads, in flight during the products
     const bool down = y + 1 < H;
     if (i + 1 < i1 && down) {
@@ -669,7 +751,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // Sum of the per-workgroup partials: 32 threads per output, each adding a
 // contiguous 1/32 of the partials in order, then the 32 sums in a fixed tree
 // (deterministic).  Latency-bound chains of loads: eight threads per output
-// took 43 us for 1024 partials of 9248 values, 32 and half the partials @R1@.
+// took 43 us for 1024 partials of 9248 values, 32 and half the partials 9.
 __global__ __launch_bounds__(1024) void k_wgrad_reduce(const float *partial, int nblocks, int len, float *gw,
                                                        float *gbias, int nw) {
   __shared__ float s[32][33];
@@ -897,9 +979,10 @@ hipError_t launch_conv_fwd(const ConvArgs &args, hipStream_t stream) {
   const long long P = (long long)a.B * a.H * a.W;
   const unsigned grid = (unsigned)((P + 127) / 128);
   if (P == 0) return hipSuccess;
-  const long long tiles = (long long)a.B * ((a.W + 31) / 32) * ((a.H + kConvRows - 1) / kConvRows);
+  constexpr int kRows = kConvRows * kConvStrips;
+  const long long tiles = (long long)a.B * ((a.W + 31) / 32) * ((a.H + kRows - 1) / kRows);
   if (tiles > 0x7FFFFFFF) return hipErrorInvalidValue;
-  a.wide = ((uintptr_t)a.out_f32 & 15) == 0 && ((uintptr_t)a.out_bf16 & 7) == 0;
+  a.wide = (((uintptr_t)a.out_f32 | (uintptr_t)a.out_bf16) & 15) == 0;
   const dim3 tgrid((unsigned)tiles), block(256);
   if (a.inv_norm) {  // the last layer with the normalisation
     if (a.cin != 32 || a.cout != 16) return hipErrorInvalidValue;

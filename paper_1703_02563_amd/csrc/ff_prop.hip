@@ -201,7 +201,7 @@ struct CandPtrs {
 // A wave per cell, eight lanes per candidate: the grid is small (1,457 cells
 // at 741 x 497) and one lane evaluating its cell's candidates one after
 // another is a chain of 56 dependent patch rows (140 us for eight candidates,
-// both directions; now @RR@ us).
+// both directions; now 42 us).
 template <int R, class Cost>
 __global__ __launch_bounds__(256) void k_rerank(ffh::LevelArgs a, CandPtrs c, int l) {
   static_assert(ffh::kTopLMax == 8, "eight lanes per candidate");
