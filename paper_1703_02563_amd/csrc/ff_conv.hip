@@ -31,6 +31,17 @@ __device__ __forceinline__ uint16_t f32_to_bf16(float f) {
   return (uint16_t)(u >> 16);
 }
 
+// Two at once, the first in the low half (v_cvt_pk_bf16_f32; the same
+// rounding for every non-NaN input, denormals included).
+__device__ __forceinline__ uint32_t f32x2_to_bf16(float lo, float hi) {
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  const bf16x2 h = __builtin_convertvector((f32x2){lo, hi}, bf16x2);
+  uint32_t u;
+  __builtin_memcpy(&u, &h, 4);
+  return u;
+}
+
 __device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
 __device__ __forceinline__ bf16x8 as_bf16x8(uint4 v) {
@@ -332,46 +343,50 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 3))) voi
 }
 
 // The whole network for inference in one launch (1 -> 32 -> 32 -> 16, ReLU
-// after the first two layers, optionally unit length per pixel): a
-// workgroup computes a tile of 60 x kNetRows output pixels; the first
-// layer's outputs on the tile plus two pixels on every side and the second
-// layer's plus one stay in LDS (zero outside the image, the "same" padding
-// of the next layer), so the activations never leave the chip.  Every
-// layer issues the matrix-core products of k_conv_fwd (first layer) and
+// after the first two layers, optionally unit length per pixel).  A workgroup
+// walks down columns of 60 pixels, kNetRows image rows a step; the first
+// layer's outputs (60 + 4 columns) and the second's stay in LDS in rings of
+// kNetRows + 2 rows (zero outside the image: the "same" padding of the next
+// layer), so the activations never leave the chip and only the columns'
+// borders and the two rows a run starts with are computed twice.  A wave
+// computes one row (two blocks of 32 pixels) per layer and step.  Every layer
+// issues the matrix-core products of k_conv_fwd (first layer) and
 // k_conv_fwd_tile (32 pixels of a row per product, taps then channel chunks,
-// the same operands, here as the transposed product) and the same bias,
-// ReLU and bf16 rounding, and the normalisation is l2norm16: the features
-// are bit for bit those of the three convolution launches and the
-// normalisation launch.
-constexpr int kNetRows = 4, kNetTW = 60, kNetCols = 64, kNetPX = 5;  // 16-byte slots per staged pixel
+// the same operands) and the same bias, ReLU and bf16 rounding, and the
+// normalisation is l2norm16: the features are bit for bit those of the three
+// convolution launches and the normalisation launch.
+//
+// Bound by the matrix cores (74 products a wave and step), the LDS reads that
+// feed them (one 16-byte read per lane and product) and the epilogues' vector
+// instructions, which overlap only between the two workgroups of a compute
+// unit (registers: 36 weight operands).  Tiles of 60 x 4 with their borders
+// computed for each took 523 us for ten 1024 x 436 images; this takes 210.
+constexpr int kNetRows = 4, kNetTW = 60, kNetCols = 64, kNetRing = kNetRows + 2;
+constexpr int kNetPX = 80, kNetRowB = kNetCols * kNetPX;  // bytes per staged pixel (16 of padding) and row
+constexpr int kNetInC = kNetCols + 2;
 
-__global__ __launch_bounds__(256) void k_descnet_fwd(ffh::NetArgs a) {
-  constexpr int R1 = kNetRows + 4, R2 = kNetRows + 2, R0 = kNetRows + 6, C0 = kNetCols + 2;
-  __shared__ uint16_t s_in[R0][C0];                    // network input, tile + 3 pixels
-  __shared__ uint4 s_a1[R1 * kNetCols * kNetPX];         // first layer's outputs, tile + 2 pixels
-  __shared__ uint4 s_a2[R2 * kNetCols * kNetPX];         // second layer's outputs, tile + 1 pixel
-  float *s_out = reinterpret_cast<float *>(s_a1);        // third layer's outputs (after s_a1 is read)
-  const int W = a.W, H = a.H;
-  const int tiles_x = (W + kNetTW - 1) / kNetTW, tiles_y = (H + kNetRows - 1) / kNetRows;
-  const int img = blockIdx.x / (tiles_x * tiles_y), t = blockIdx.x % (tiles_x * tiles_y);
-  const int x0 = (t % tiles_x) * kNetTW, y0 = (t / tiles_x) * kNetRows;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+__global__ __launch_bounds__(256, 2) void k_descnet_fwd(ffh::NetArgs a) {
+  // two pixels more: blocks read past a row's last column (results not used)
+  __shared__ __attribute__((aligned(16))) uint8_t s_a1[kNetRing * kNetRowB + 2 * kNetPX];
+  __shared__ __attribute__((aligned(16))) uint8_t s_a2[kNetRing * kNetRowB + 2 * kNetPX];
+  __shared__ __attribute__((aligned(16))) uint8_t s_tr[4][2048];
+  __shared__ __attribute__((aligned(16))) float s_bias[80];
+  // input rows of a step; two rows and two pixels more for the lanes that
+  // hold the ninth tap only
+  __shared__ uint16_t s_in[(kNetRows + 4) * kNetInC + 4];
+  const int W = a.W, H = a.H, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int row = lane & 31, kh = lane >> 5, col = row;
-  const size_t plane = (size_t)img * H * W;
-  auto inside = [&](int y, int x) { return y >= 0 && y < H && x >= 0 && x < W; };
-  // a tile whose first-layer region lies inside the image needs no border
-  // zeros (wave-uniform)
-  const bool interior = y0 >= 2 && y0 + kNetRows + 2 <= H && x0 >= 2 && x0 + kNetCols - 2 <= W;
-  // every weight operand first (the three layers' loads in flight together
-  // with the input tile's)
+  const int tiles_x = (W + kNetTW - 1) / kNetTW, steps = (H + kNetRows - 1) / kNetRows;
+  const long long i0 = blockIdx.x * a.per_wg, i1 = min(i0 + a.per_wg, (long long)a.B * tiles_x * steps);
   uint16_t bw1[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     const int tap = 8 * kh + e;
     bw1[e] = tap < 9 ? a.w1[col * 9 + tap] : (uint16_t)0;
   }
-  uint4 ub2[18], ub3[18];
-  const uint32_t wmask = col < 16 ? 0xFFFFFFFFu : 0u;  // third layer: columns beyond the 16 outputs multiply by zero
+  uint4 ub1, ub2[18], ub3[18];
+  __builtin_memcpy(&ub1, bw1, 16);
+  const uint32_t wmask = col < 16 ? 0xFFFFFFFFu : 0u;  // third layer: rows beyond the 16 outputs multiply by zero
 #pragma unroll
   for (int tap = 0; tap < 9; ++tap)
 #pragma unroll
@@ -380,105 +395,141 @@ __global__ __launch_bounds__(256) void k_descnet_fwd(ffh::NetArgs a) {
       const uint4 w = reinterpret_cast<const uint4 *>(a.w3 + ((size_t)min(col, 15) * 9 + tap) * 32)[cc * 2 + kh];
       ub3[tap * 2 + cc] = make_uint4(w.x & wmask, w.y & wmask, w.z & wmask, w.w & wmask);
     }
-  uint4 ub1;
-  __builtin_memcpy(&ub1, bw1, 16);
-  for (int k = tid; k < R0 * C0; k += 256) {
-    const int ry = k / C0, cx = k % C0, y = y0 - 3 + ry, x = x0 - 3 + cx;
-    s_in[ry][cx] = inside(y, x) ? a.in[plane + (size_t)y * W + x] : (uint16_t)0;
-  }
-  __syncthreads();
-  // The products are taken transposed, D = W X (weights the first operand,
-  // the 32 pixels the columns): a lane then holds 16 output channels of one
-  // pixel, channels 8 g + 4 kh .. 8 g + 4 kh + 3 for g = 0..3, and writes
-  // them with four 8-byte stores.  Every output element is the same sum of
-  // the same products as in the per-layer kernels.
-  // bf16 outputs of one pixel (zero outside the image: the next layer's
-  // padding) into a staged map
-  // the biases of a lane's 16 output channels, per layer
-  auto lane_bias = [&](const float *b, int nout, float (&bl)[16]) {
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int co = 8 * (r >> 2) + 4 * kh + (r & 3);
-      bl[r] = co < nout ? b[co] : 0.0f;
-    }
-  };
-  auto store_bf16 = [&](uint4 *map, int ry, int c, const f32x16 &acc, const float (&bl)[16], bool in_image) {
-    uint8_t *px = reinterpret_cast<uint8_t *>(&map[(ry * kNetCols + c) * kNetPX]);
+  if (tid < 80) s_bias[tid] = tid < 32 ? a.b1[tid] : tid < 64 ? a.b2[tid - 32] : a.b3[tid - 64];
+
+  // bias, ReLU and bf16 of one pixel's 16 channels of this lane (8 g + 4 kh +
+  // q), zero where `keep` is (outside the image)
+  auto store_bf16 = [&](uint8_t *px, const f32x16 &acc, const float *bias, uint32_t keep) {
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
-      uint32_t h[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) h[q] = in_image ? f32_to_bf16(fmaxf(acc[4 * g + q] + bl[4 * g + q], 0.0f)) : 0u;
-      *reinterpret_cast<uint2 *>(px + 16 * g + 8 * kh) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
+      const float4 b = *reinterpret_cast<const float4 *>(bias + 8 * g + 4 * kh);
+      const uint32_t h0 = f32x2_to_bf16(fmaxf(acc[4 * g] + b.x, 0.0f), fmaxf(acc[4 * g + 1] + b.y, 0.0f));
+      const uint32_t h1 = f32x2_to_bf16(fmaxf(acc[4 * g + 2] + b.z, 0.0f), fmaxf(acc[4 * g + 3] + b.w, 0.0f));
+      *reinterpret_cast<uint2 *>(px + 16 * g + 8 * kh) = make_uint2(h0 & keep, h1 & keep);
     }
   };
-  // first layer: K = 9 taps padded to 16, lane half kh holds taps 8 kh .. 8 kh + 7
-  float bl[16];
-  lane_bias(a.b1, 32, bl);
-  for (int item = wave; item < 2 * R1; item += 4) {
-    const int ry = item >> 1, c = 32 * (item & 1) + row;  // this lane's pixel (y0 - 2 + ry, x0 - 2 + c)
-    uint16_t av[8];
+  auto ring = [](int slot) { return slot >= kNetRing ? slot - kNetRing : slot; };
+  // both blocks of row `wave`: the map's rows base + wave .. base + wave + 2
+  auto products = [&](const uint8_t *map, int base, const uint4(&ub)[18], f32x16 &acc0, f32x16 &acc1) {
+    acc0 = acc1 = f32x16{0};
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int tap = 8 * kh + e;
-      av[e] = tap < 9 ? s_in[ry + tap / 3][c + tap % 3] : (uint16_t)0;
-    }
-    uint4 ua;
-    __builtin_memcpy(&ua, av, 16);
-    f32x16 acc = {0};
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ub1), as_bf16x8(ua), acc, 0, 0, 0);
-    store_bf16(s_a1, ry, c, acc, bl, interior || inside(y0 - 2 + ry, x0 - 2 + c));
-  }
-  __syncthreads();
-  // second and third layers: 9 taps x 2 channel chunks of 16 per product, a
-  // wave running two row blocks at once (independent accumulator chains)
-  auto layer = [&](const uint4 *src_map, const uint4(&ub)[18], int nrows, auto &&store) {
-    for (int item = 2 * wave; item < 2 * nrows; item += 8) {
-      const int i2 = min(item + 1, 2 * nrows - 1);  // the pair's second block (a repeat when there is none)
-      const int ra = item >> 1, ba = 32 * (item & 1), rb = i2 >> 1, bb = 32 * (i2 & 1);
-      f32x16 acc0 = {0}, acc1 = {0};
+    for (int dy = 0; dy < 3; ++dy) {
+      const uint8_t *p = map + ring(base + wave + dy) * kNetRowB + row * kNetPX + 16 * kh;
 #pragma unroll
-      for (int tap = 0; tap < 9; ++tap) {
-        const uint4 *s0 = src_map + ((ra + tap / 3) * kNetCols + min(ba + row + tap % 3, kNetCols - 1)) * kNetPX;
-        const uint4 *s1 = src_map + ((rb + tap / 3) * kNetCols + min(bb + row + tap % 3, kNetCols - 1)) * kNetPX;
-#pragma unroll
-        for (int cc = 0; cc < 2; ++cc) {
-          acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ub[tap * 2 + cc]), as_bf16x8(s0[cc * 2 + kh]), acc0,
-                                                         0, 0, 0);
-          acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ub[tap * 2 + cc]), as_bf16x8(s1[cc * 2 + kh]), acc1,
-                                                         0, 0, 0);
-        }
+      for (int k = 0; k < 6; ++k) {  // dx, then channel chunk
+        const uint4 v0 = *reinterpret_cast<const uint4 *>(p + (k >> 1) * kNetPX + 32 * (k & 1));
+        const uint4 v1 = *reinterpret_cast<const uint4 *>(p + (32 + (k >> 1)) * kNetPX + 32 * (k & 1));
+        acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ub[dy * 6 + k]), as_bf16x8(v0), acc0, 0, 0, 0);
+        acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ub[dy * 6 + k]), as_bf16x8(v1), acc1, 0, 0, 0);
       }
-      store(ra, ba + row, acc0);
-      if (i2 != item) store(rb, bb + row, acc1);
     }
   };
-  lane_bias(a.b2, 32, bl);
-  layer(s_a1, ub2, R2, [&](int ry, int c, const f32x16 &acc) {  // pixel (y0 - 1 + ry, x0 - 1 + c)
-    store_bf16(s_a2, ry, c, acc, bl, interior || inside(y0 - 1 + ry, x0 - 1 + c));
-  });
-  lane_bias(a.b3, 16, bl);
-  __syncthreads();  // s_a2 complete; s_a1 no longer read
-  layer(s_a2, ub3, kNetRows, [&](int ry, int c, const f32x16 &acc) {  // pixel (y0 + ry, x0 + c): channels < 16
-    float *px = s_out + (ry * kNetCols + c) * 16;
+
+  for (long long i = i0; i < i1;) {
+    const int c = (int)(i / steps), s0 = (int)(i % steps), s1 = (int)min((long long)steps, s0 + (i1 - i));
+    i += s1 - s0;
+    const int img = c / tiles_x, x0 = (c % tiles_x) * kNetTW;
+    const size_t plane = (size_t)img * H * W;
+    uint16_t nx[2];
+    auto load = [&](int s) {  // input rows 4 s + 1 .. 4 s + 6, columns from x0 - 3
 #pragma unroll
-    for (int g = 0; g < 2; ++g) {
-      const int co = 8 * g + 4 * kh;
-      *reinterpret_cast<float4 *>(px + co) = make_float4(acc[4 * g] + bl[4 * g], acc[4 * g + 1] + bl[4 * g + 1],
-                                                         acc[4 * g + 2] + bl[4 * g + 2], acc[4 * g + 3] + bl[4 * g + 3]);
+      for (int j = 0; j < 2; ++j) {
+        const int k = tid + 256 * j, y = kNetRows * s + 1 + k / kNetInC, x = x0 - 3 + k % kNetInC;
+        nx[j] = 0;
+        if (k < (kNetRows + 2) * kNetInC && y >= 0 && y < H && x >= 0 && x < W) nx[j] = a.in[plane + (size_t)y * W + x];
+      }
+    };
+    auto put = [&] {
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        if (tid + 256 * j < (kNetRows + 2) * kNetInC) s_in[tid + 256 * j] = nx[j];
+    };
+    load(s0 - 1);
+    put();  // the previous run's input is read (its last step's first barrier)
+    __syncthreads();
+    // The step before the first computes the rows above: with y = 4 s, a step
+    // adds rows y + 2 .. y + 5 of the first layer and y + 1 .. y + 4 of the
+    // second (two of them from rows that a run's first step does not have;
+    // they are not used), and writes y .. y + 3.  Slot `base` holds row y of
+    // the first layer's ring and y - 1 of the second's.
+    int base = 0;
+    for (int s = s0 - 1; s < s1; ++s, base = ring(base + kNetRows)) {
+      const int y = kNetRows * s;
+      const int put_row = ring(base + 2 + wave) * kNetRowB;
+#pragma unroll
+      for (int blk = 0; blk < 2; ++blk) {
+        // K = 9 taps padded to 16, lane half kh holds taps 8 kh .. 8 kh + 7
+        const uint16_t *p = s_in + (wave + 2 * kh) * kNetInC + 32 * blk + row + 2 * kh;
+        uint16_t av[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) av[e] = p[(e / 3) * kNetInC + e % 3];
+        uint4 ua;
+        __builtin_memcpy(&ua, av, 16);
+        const uint32_t rest = kh ? 0u : 0xFFFFFFFFu;
+        ua = make_uint4(ua.x & (rest | 0xFFFFu), ua.y & rest, ua.z & rest, ua.w & rest);
+        f32x16 acc = {0};
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ub1), as_bf16x8(ua), acc, 0, 0, 0);
+        const int py = y + 2 + wave, px = x0 - 2 + 32 * blk + row;
+        store_bf16(s_a1 + put_row + (32 * blk + row) * kNetPX, acc, s_bias,
+                   py >= 0 && py < H && px >= 0 && px < W ? 0xFFFFFFFFu : 0u);
+      }
+      if (s + 1 < s1) load(s + 1);
+      __syncthreads();
+      f32x16 acc0, acc1;
+      products(s_a1, base, ub2, acc0, acc1);
+      {
+        const int py = y + 1 + wave, px = x0 - 1 + row;
+        const bool in = py >= 0 && py < H;
+        uint8_t *q = s_a2 + put_row + row * kNetPX;
+        store_bf16(q, acc0, s_bias + 32, in && px >= 0 && px < W ? 0xFFFFFFFFu : 0u);
+        store_bf16(q + 32 * kNetPX, acc1, s_bias + 32, in && px + 32 < W ? 0xFFFFFFFFu : 0u);
+      }
+      if (s + 1 < s1) put();
+      __syncthreads();
+      if (s < s0) continue;
+      products(s_a2, base, ub3, acc0, acc1);
+      const int n = y + wave < H ? min(kNetTW, W - x0) : 0;
+#pragma unroll
+      for (int blk = 0; blk < 2; ++blk) {
+        const f32x16 &acc = blk ? acc1 : acc0;
+        float v[2][4], o[2][4];
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+          const float4 b = *reinterpret_cast<const float4 *>(s_bias + 64 + 8 * g + 4 * kh);
+          v[g][0] = acc[4 * g] + b.x;
+          v[g][1] = acc[4 * g + 1] + b.y;
+          v[g][2] = acc[4 * g + 2] + b.z;
+          v[g][3] = acc[4 * g + 3] + b.w;
+        }
+        if (a.normalize) {  // over all 16 channels: the other lane half holds the other 8
+#pragma unroll
+          for (int g = 0; g < 2; ++g)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) o[g][q] = __shfl_xor(v[g][q], 32);
+          float4 f[4];
+#pragma unroll
+          for (int g = 0; g < 2; ++g) {
+            const float4 mine = make_float4(v[g][0], v[g][1], v[g][2], v[g][3]);
+            const float4 theirs = make_float4(o[g][0], o[g][1], o[g][2], o[g][3]);
+            f[2 * g] = kh ? theirs : mine;
+            f[2 * g + 1] = kh ? mine : theirs;
+          }
+          const float r = l2norm16(f, a.delta);
+#pragma unroll
+          for (int g = 0; g < 2; ++g)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[g][q] *= r;
+        }
+#pragma unroll
+        for (int g = 0; g < 2; ++g)
+          *reinterpret_cast<float4 *>(s_tr[wave] + run_chunk(row, 2 * g + kh)) =
+              make_float4(v[g][0], v[g][1], v[g][2], v[g][3]);
+        lds_in_order();
+        store_run(s_tr[wave], reinterpret_cast<uint8_t *>(a.out + (plane + (size_t)(y + wave) * W + x0 + 32 * blk) * 16),
+                  n - 32 * blk, lane, nullptr);
+        lds_in_order();
+      }
     }
-  });
-  __syncthreads();
-  for (int k = tid; k < kNetRows * kNetTW; k += 256) {
-    const int ry = k / kNetTW, c = k % kNetTW, y = y0 + ry, x = x0 + c;
-    if (!inside(y, x)) continue;
-    float4 v[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) v[q] = reinterpret_cast<const float4 *>(s_out + (ry * kNetCols + c) * 16)[q];
-    if (a.normalize) l2norm16(v, a.delta);
-    float4 *dst = reinterpret_cast<float4 *>(a.out + (plane + (size_t)y * W + x) * 16);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) dst[q] = v[q];
   }
 }
 
@@ -999,10 +1050,12 @@ hipError_t launch_conv_fwd(const ConvArgs &args, hipStream_t stream) {
   return hipGetLastError();
 }
 
-hipError_t launch_descnet_fwd(const NetArgs &a, hipStream_t stream) {
-  const long long tiles = (long long)a.B * ((a.W + kNetTW - 1) / kNetTW) * ((a.H + kNetRows - 1) / kNetRows);
-  if (tiles <= 0 || tiles > INT32_MAX) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_descnet_fwd, dim3((unsigned)tiles), dim3(256), 0, stream, a);
+hipError_t launch_descnet_fwd(NetArgs a, hipStream_t stream) {
+  // two workgroups per compute unit, each with one run of steps
+  const long long items = (long long)a.B * ((a.W + kNetTW - 1) / kNetTW) * ((a.H + kNetRows - 1) / kNetRows);
+  if (items <= 0 || items > INT32_MAX) return hipErrorInvalidValue;
+  a.per_wg = (items + 511) / 512;
+  hipLaunchKernelGGL(k_descnet_fwd, dim3((unsigned)((items + a.per_wg - 1) / a.per_wg)), dim3(256), 0, stream, a);
   return hipGetLastError();
 }
 

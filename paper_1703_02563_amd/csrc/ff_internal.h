@@ -299,8 +299,9 @@ struct NetArgs {
   int B, H, W, normalize;
   float delta;
   float *out;                     // [B][H][W][16]
+  long long per_wg;               // set by the launcher: steps per workgroup
 };
-hipError_t launch_descnet_fwd(const NetArgs &a, hipStream_t stream);
+hipError_t launch_descnet_fwd(NetArgs a, hipStream_t stream);
 hipError_t launch_weight_flip(const uint16_t *w, uint16_t *wf, int cin, int cout, hipStream_t stream);
 int wgrad_blocks(int B, int H);
 hipError_t launch_wgrad(const ConvArgs &a, float *gw, float *gbias, hipStream_t stream);
