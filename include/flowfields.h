@@ -178,6 +178,12 @@ const char *ff_status_str(ff_status s);
 ff_status ff_descriptors(const uint8_t *img, int32_t W, int32_t H, int32_t n, uint16_t *hsum,
                          uint8_t *blurred, uint8_t *desc, uint8_t *desc_rowmajor, uint8_t *wform, void *stream);
 
+/* The blurred images of ff_descriptors for n = 1, 2, 4 .. 2^(levels-1) of two
+ * images of one size, in one launch: out [2 * levels][H][W], img1's first.
+ * 1 <= levels <= 7. */
+ff_status ff_scale_images(const uint8_t *img1, const uint8_t *img2, int32_t W, int32_t H, int32_t levels,
+                          uint8_t *out, void *stream);
+
 /* Bytes of a descriptor map of scale n (host): (W + 8n) * (H + 8n) * 16;
  * 0 for invalid sizes. */
 size_t ff_descriptor_map_bytes(int32_t W, int32_t H, int32_t n);

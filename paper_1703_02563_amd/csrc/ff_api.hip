@@ -422,6 +422,18 @@ ff_status ff_descriptors(const uint8_t *img, int32_t W, int32_t H, int32_t n, ui
   return from_hip(ffh::launch_descriptors(jobs, (hipStream_t)stream));
 }
 
+ff_status ff_scale_images(const uint8_t *img1, const uint8_t *img2, int32_t W, int32_t H, int32_t levels, uint8_t *out,
+                          void *stream) {
+  if (!img1 || !img2 || !out || !dims_ok(W, H) || levels < 1 || levels > kMaxLevels) return FF_ERR_ARG;
+  ffh::DescJobs jobs{};
+  jobs.W = W;
+  jobs.H = H;
+  for (const uint8_t *img : {img1, img2})
+    for (int lv = 0; lv < levels; ++lv, ++jobs.count)
+      jobs.job[jobs.count] = {img, out + (size_t)jobs.count * W * H, nullptr, nullptr, nullptr, 1 << lv};
+  return from_hip(ffh::launch_blur(jobs, (hipStream_t)stream));
+}
+
 ff_status ff_init_nn(const uint8_t *desc_a1, const uint8_t *desc_b1, const uint8_t *desc_ac, const uint8_t *desc_bc,
                      int32_t W, int32_t H, int32_t nc, int32_t radius, int32_t *nb_scratch, uint64_t *nn_key,
                      int16_t *flow, uint32_t *cost, uint64_t *n_evals, void *stream) {
@@ -1040,13 +1052,16 @@ ff_status ff_flow_fields_f32(const float *const *feat1, const float *const *feat
   if (r == 3) {
     // temporally blocked level kernels on maps in phase order (image order at n = 1)
     const float *pf[2][kMaxLevels];
+    ffh::PhaseJobs pj{};
+    pj.W = W;
+    pj.H = H;
     for (int im = 0; im < 2; ++im)
       for (int lv = 0; lv < L; ++lv) {
         float *m = lv ? reinterpret_cast<float *>(base + lay.pf[im][lv]) : nullptr;
-        if (lv && (e = ffh::launch_phase_features(feat[im][lv], W, H, 1 << lv, m, s)) != hipSuccess)
-          return FF_ERR_LAUNCH;
+        if (lv) pj.job[pj.count++] = {feat[im][lv], m, lv};
         pf[im][lv] = lv ? m : feat[im][lv];
       }
+    if ((e = ffh::launch_phase_features(pj, s)) != hipSuccess) return FF_ERR_LAUNCH;
     int32_t *sflow[kMaxLevels][2];
     uint32_t *scost[kMaxLevels][2];
     carve_second_grids(base, lay.sgrids, W, H, L, sflow, scost);

@@ -344,21 +344,25 @@ __global__ __launch_bounds__(256) void k_cost_poison(ffh::CostArgs a, long long 
 
 // Copy of a float feature map with the pixels of every row in phase order
 // (desc_col): one thread per 16-byte quarter of an entry, so consecutive lanes
-// store consecutive bytes.
-__global__ __launch_bounds__(256) void k_phase_features(const float4 *f, int W, int log2n, float4 *out) {
-  const int q = blockIdx.x * blockDim.x + threadIdx.x, c = q >> 2;
+// store consecutive bytes.  All maps of a call in one launch: eight of
+// 1024 x 436, a launch each 8 x 14.9 us, together 89 us, the rate of a copy.
+__global__ __launch_bounds__(256) void k_phase_features(ffh::PhaseJobs jobs) {
+  const int q = blockIdx.x * blockDim.x + threadIdx.x, c = q >> 2, W = jobs.W;
   if (c >= W) return;
+  const ffh::PhaseJob &jb = jobs.job[blockIdx.z];
+  const float4 *f = reinterpret_cast<const float4 *>(jb.f);
   const size_t row = (size_t)blockIdx.y * W;
-  out[(row + c) * 4 + (q & 3)] = f[(row + ffk::desc_pixel(c, log2n, W)) * 4 + (q & 3)];
+  reinterpret_cast<float4 *>(jb.out)[(row + c) * 4 + (q & 3)] =
+      f[(row + ffk::desc_pixel(c, jb.log2n, W)) * 4 + (q & 3)];
 }
 
 }  // namespace
 
 namespace ffh {
 
-hipError_t launch_phase_features(const float *f, int W, int H, int n, float *out, hipStream_t stream) {
-  hipLaunchKernelGGL(k_phase_features, dim3((4 * W + 255) / 256, H), dim3(256), 0, stream,
-                     reinterpret_cast<const float4 *>(f), W, __builtin_ctz(n), reinterpret_cast<float4 *>(out));
+hipError_t launch_phase_features(const PhaseJobs &jobs, hipStream_t stream) {
+  if (jobs.count <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_phase_features, dim3((4 * jobs.W + 255) / 256, jobs.H, jobs.count), dim3(256), 0, stream, jobs);
   return hipGetLastError();
 }
 

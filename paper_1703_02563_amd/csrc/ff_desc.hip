@@ -253,17 +253,25 @@ hipError_t launch_batch_descriptors(const BatchStage &tiles, const BatchStage &r
   return hipGetLastError();
 }
 
-hipError_t launch_descriptors(const DescJobs &jobs, hipStream_t stream) {
+// Five scales of two 1024 x 436 images in one launch: 16 us; a blur and a
+// descriptor launch for each, of which only the blurred image is wanted, 140.
+hipError_t launch_blur(const DescJobs &jobs, hipStream_t stream) {
   if (jobs.count <= 0) return hipSuccess;
   for (int k = 0; k < jobs.count; ++k)
     if (jobs.job[k].n < 1 || jobs.job[k].n > 2 * kBHmax + 1) return hipErrorInvalidValue;
+  if (5 * (size_t)desc_row_stride(jobs.W) > 160 * 1024) return hipErrorInvalidValue;  // as launch_descriptors
   const dim3 gb((jobs.W + kBT - 1) / kBT, (jobs.H + kBT - 1) / kBT, jobs.count);
   hipLaunchKernelGGL(k_blur, gb, dim3(256), 0, stream, jobs);
+  return hipGetLastError();
+}
+
+hipError_t launch_descriptors(const DescJobs &jobs, hipStream_t stream) {
+  if (jobs.count <= 0) return hipSuccess;
+  size_t lds;
+  hipError_t e = desc_lds(reinterpret_cast<const void *>(k_desc), jobs.W, &lds);
+  if (e != hipSuccess || (e = launch_blur(jobs, stream)) != hipSuccess) return e;
   int pmax = 0;
   for (int k = 0; k < jobs.count; ++k) pmax = std::max(pmax, ffk::desc_pad(jobs.job[k].n));
-  size_t lds;
-  const hipError_t e = desc_lds(reinterpret_cast<const void *>(k_desc), jobs.W, &lds);
-  if (e != hipSuccess) return e;
   const dim3 gpad(jobs.H + 2 * pmax, jobs.count);
   hipLaunchKernelGGL(k_desc, gpad, dim3(256), lds, stream, jobs);
   return hipGetLastError();

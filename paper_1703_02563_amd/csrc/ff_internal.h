@@ -27,6 +27,7 @@ struct DescJobs {
   int W, H;
 };
 hipError_t launch_descriptors(const DescJobs &jobs, hipStream_t stream);
+hipError_t launch_blur(const DescJobs &jobs, hipStream_t stream);  // the blurred images only
 
 // Fills `count` 64-bit words with `value`.
 hipError_t launch_fill_u64(uint64_t *dst, uint64_t value, int64_t count, hipStream_t stream);
@@ -174,7 +175,17 @@ struct LevelKArgs {
 };
 // Copy of a float [H][W][16] feature map with its rows in the phase order of
 // scale n.
-hipError_t launch_phase_features(const float *f, int W, int H, int n, float *out, hipStream_t stream);
+struct PhaseJob {
+  const float *f;  // [H][W][16]
+  float *out;
+  int log2n;
+};
+struct PhaseJobs {
+  PhaseJob job[kMaxJobs];
+  int count;
+  int W, H;
+};
+hipError_t launch_phase_features(const PhaseJobs &jobs, hipStream_t stream);
 hipError_t launch_level(LevelKArgs a, hipStream_t stream);
 // per-scale launchers of the blocked kernels (ff_level_s<log2n>.hip)
 struct BatchStage;

@@ -325,8 +325,13 @@ def train_step(net: DescNet, batch, rng, samples: int = 4096, margin: float = 1.
 def scale_images(img1: torch.Tensor, img2: torch.Tensor, levels: int) -> torch.Tensor:
     """Scale-space images B_n (n = 2^l) of both images, uint8 [2L, H, W]:
     rows 0..L-1 are img1's scales, rows L..2L-1 img2's."""
-    from .flowfields import descriptors
-    return torch.stack([descriptors(img, 1 << lv)[0] for img in (img1, img2) for lv in range(levels)])
+    H, W = img1.shape
+    if levels < 1 or img2.shape != img1.shape or img2.device != img1.device:
+        raise RuntimeError("scale_images: at least one level and two images of one size on one device")
+    out = torch.empty((2 * levels, H, W), dtype=torch.uint8, device=img1.device)
+    check(lib().ff_scale_images(_ptr(img1, torch.uint8, "img"), _ptr(img2, torch.uint8, "img"), W, H, levels, _ptr(out),
+                                _stream()), "ff_scale_images")
+    return out
 
 
 def learned_features(net: DescNet, scales: torch.Tensor) -> torch.Tensor:
