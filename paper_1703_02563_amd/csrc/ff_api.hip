@@ -52,7 +52,10 @@ ffh::Tuning call_tables(const ff_params *p, const int (*sizes)[2], int count, in
 
 ffh::Tuning call_tables(const ff_params *p, int W, int H, int ndir) {
   const int size[1][2] = {{W, H}};
-  return call_tables(p, size, 1, ndir);
+  ffh::Tuning t = call_tables(p, size, 1, ndir);
+  if (!p->tuning)
+    for (int lv = 0; lv < ffh::kTuneScales; ++lv) t.variant_f32[lv] = ffh::level_pick_f32(lv, W, H, ndir);
+  return t;
 }
 
 bool params_ok(const ff_params *p) {

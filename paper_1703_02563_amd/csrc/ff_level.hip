@@ -90,10 +90,11 @@ hipError_t dispatch(const ffh::LevelKArgs &a, const ffh::BatchStage *batch, int 
 
 // Window halo of every variant of the float-feature level kernel (image a's
 // samples staged in LDS, 64 bytes each; launch_nf32 in ff_level_kernels.h
-// maps each index to its tile and kernel): 16x16 / 8x8 / 8x8 / 8x8 / 16x16.
-constexpr int kHaloF32[] = {2, 2, 4, 6, 4};
+// maps each index to its tile and kernel): 16x16 / 8x8 / 8x8 / 8x8 / 16x16,
+// and 4x4, which a caller's table cannot name.
+constexpr int kHaloF32[] = {2, 2, 4, 6, 4, 2};
 constexpr int kNumVariantsF32 = 5;
-static_assert(sizeof(kHaloF32) / sizeof(kHaloF32[0]) == kNumVariantsF32, "float variant table");
+static_assert(sizeof(kHaloF32) / sizeof(kHaloF32[0]) == kNumVariantsF32 + 1, "float variant table");
 
 // The built-in launch tables.  Byte descriptors: weight-class evaluations
 // on 32x12 tiles (256 threads, six workgroups per compute unit; two steps
@@ -156,6 +157,23 @@ int level_pick_variant(int log2n, const int (*sizes)[2], int count, int ndir) {
   return log2n == 0 && workgroups(32, 12) >= 4 * kUnits ? 31 : 11;
 }
 
+// The same for float features (one step per launch), from how many workgroups
+// a tile gives; us per call of six steps a scale, both sides:
+//  * 16x16 tiles from two workgroups per unit on (600 workgroups at 320x240,
+//    n = 1: 642 against 717 on 8x8; 896 at 1024x436, n = 2: 1826 against
+//    1905; 224 at n = 4: 1862 against 1832; 160 at 320x240, n = 2: 711
+//    against 642);
+//  * 4x4 tiles where 8x8 ones give less than half of the units a workgroup (64
+//    at 1024x436, n = 16: 1836 against 1857; 40 at 320x240, n = 8: 721 against
+//    747; 160 at n = 4: 766 against 716).
+int level_pick_f32(int log2n, int W, int H, int ndir) {
+  constexpr long long kUnits = 256;
+  const long long Wn = (W + (1 << log2n) - 1) >> log2n, Hn = (H + (1 << log2n) - 1) >> log2n;
+  auto workgroups = [&](int t) { return (Wn + t - 1) / t * ((Hn + t - 1) / t) * ndir; };
+  if (workgroups(16) >= 2 * kUnits) return 0;
+  return 2 * workgroups(8) < kUnits ? 5 : 1;
+}
+
 int level_variant_count() { return kNumVariants + 1; }  // + the step-wise schedule
 
 int level_variant_count_f32() { return kNumVariantsF32; }
@@ -182,7 +200,7 @@ static int log2_of(int n) {
 }
 
 int level_window_halo_f32(int variant) {
-  return (variant >= 0 && variant < kNumVariantsF32) ? kHaloF32[variant] : 2;
+  return (variant >= 0 && variant <= kNumVariantsF32) ? kHaloF32[variant] : 2;
 }
 
 int level_window_halo(int variant) {

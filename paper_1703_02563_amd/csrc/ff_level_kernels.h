@@ -429,20 +429,37 @@ __device__ __forceinline__ uint32_t eval_wform_spx(const uint4 *pa, int step, __
 // The wave leaves together, after the row that puts its last quad above; the
 // value returned is then some number above the limit.  A row's loads are
 // issued before the previous row is summed.  Infinities and NaN never decide.
-template <int LOG2N, int DW>
-__device__ __forceinline__ uint32_t eval_quad_f32(const float4 *pa, const float4 *__restrict__ B, int W, int H, int bx,
-                                                  int by, int r, uint32_t limit) {
+//
+// Targets 3n inside the image (a wave of them takes eval_quad_f32_rows with
+// kInside) need one address per patch row: the samples of a row are adjacent
+// and the rows n image rows apart.  Clamping and addressing every sample
+// doubles the vector instructions (16 a sample instead of 8): 142 -> 139 us a
+// launch at 1024x436, n = 1, and 68 -> 64 us at n = 2.
+template <int LOG2N, int DW, bool kInside>
+__device__ __forceinline__ uint32_t eval_quad_f32_rows(const float4 *pa, const float4 *__restrict__ B, int W, int H,
+                                                       int bx, int by, int r, uint32_t limit) {
   constexpr int n = 1 << LOG2N, K = 2 * kR + 1;
   const float4 *ra = pa + (-kR * DW - kR) * 4 + r;
   int xo[K];
+  const float4 *next = B;
+  if constexpr (kInside) {
+    next += ((size_t)(by - kR * n) * W + ffk::desc_col(bx - kR * n, LOG2N, W)) * 4 + r;
+  } else {
 #pragma unroll
-  for (int u = 0; u < K; ++u) xo[u] = 4 * ffk::desc_col(clampi(bx + (u - kR) * n, W - 1), LOG2N, W) + r;
+    for (int u = 0; u < K; ++u) xo[u] = 4 * ffk::desc_col(clampi(bx + (u - kR) * n, W - 1), LOG2N, W) + r;
+  }
   constexpr int D = 3;  // rows in flight, the summed one included
   float4 y[D][K];
-  auto fetch = [&](int v, float4 (&row)[K]) {
-    const float4 *p = B + (size_t)clampi(by + (v - kR) * n, H - 1) * W * 4;
+  auto fetch = [&](int v, float4 (&row)[K]) {  // rows in turn
+    if constexpr (kInside) {
 #pragma unroll
-    for (int u = 0; u < K; ++u) row[u] = p[xo[u]];
+      for (int u = 0; u < K; ++u) row[u] = next[4 * u];
+      next += (size_t)n * W * 4;
+    } else {
+      const float4 *p = B + (size_t)clampi(by + (v - kR) * n, H - 1) * W * 4;
+#pragma unroll
+      for (int u = 0; u < K; ++u) row[u] = p[xo[u]];
+    }
   };
   auto total = [](float s) {
     s += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(s), 0xB1, 0xF, 0xF, false));  // quad_perm [1,0,3,2]
@@ -474,6 +491,15 @@ __device__ __forceinline__ uint32_t eval_quad_f32(const float4 *pa, const float4
     }
   }
   return __float_as_uint(total(s));
+}
+
+template <int LOG2N, int DW>
+__device__ __forceinline__ uint32_t eval_quad_f32(const float4 *pa, const float4 *__restrict__ B, int W, int H, int bx,
+                                                  int by, int r, uint32_t limit) {
+  constexpr int m = kR << LOG2N;
+  if (!__ballot(bx < m || bx >= W - m || by < m || by >= H - m))
+    return eval_quad_f32_rows<LOG2N, DW, true>(pa, B, W, H, bx, by, r, limit);
+  return eval_quad_f32_rows<LOG2N, DW, false>(pa, B, W, H, bx, by, r, limit);
 }
 
 // The run of passes for tile `tile` of one direction `d` (a holds the
@@ -1279,7 +1305,10 @@ hipError_t launch_f32(const ffh::LevelKArgs &a, hipStream_t stream) {
 // Float-feature variant index -> kernel; kHaloF32 in ff_level.hip lists the
 // window halo of every index, which must match.  16x16 or 8x8 tiles (the
 // latter for the small grids of the coarse scales); a halo of 2 allows one
-// step per launch, 4 two and 6 three.
+// step per launch, 4 two and 6 three.  Index 5, 4x4 tiles, is level_pick_f32's
+// only.  Latency counts: with 512 or 1024 threads (and fewer rows in flight)
+// the coarse scales of 1024x436 take 25 % longer, with all seven rows in
+// flight they take the same.
 template <int LOG2N>
 hipError_t launch_nf32(const ffh::LevelKArgs &a, int variant, hipStream_t stream) {
   switch (variant) {
@@ -1288,6 +1317,7 @@ hipError_t launch_nf32(const ffh::LevelKArgs &a, int variant, hipStream_t stream
     case 2: return launch_f32<LOG2N, 8, 8, 256, 4>(a, stream);
     case 3: return launch_f32<LOG2N, 8, 8, 256, 6>(a, stream);
     case 4: return launch_f32<LOG2N, 16, 16, 256, 4>(a, stream);
+    case 5: return launch_f32<LOG2N, 4, 4, 256, 2>(a, stream);
     default: return hipErrorInvalidValue;
   }
 }
