@@ -401,7 +401,7 @@ __device__ __forceinline__ int batch_pair(const int *prefix, int npairs, int ite
   return lo;
 }
 
-// Persistent launch over `total` work items: XCD x (workgroups b with
+// Launch over `total` work items: XCD x (workgroups b with
 // b % 8 == x) owns one contiguous range of items and its workgroups stride
 // through it.  The grid size must be a positive multiple of 8.
 template <typename F>

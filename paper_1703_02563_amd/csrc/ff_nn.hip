@@ -548,7 +548,7 @@ static int persistent_grid(int total, int cap) { return ((std::min(std::max(tota
 hipError_t launch_batch_nn(const BatchStage &fill, const BatchStage &nn, const BatchStage &resolve,
                            hipStream_t stream) {
   hipLaunchKernelGGL(k_nn_fill_batch, dim3(persistent_grid(fill.total, 4096)), dim3(256), 0, stream, fill);
-  hipLaunchKernelGGL(k_nn_batch, dim3(persistent_grid(nn.total, 2048)), dim3(64 * kWaves), 0, stream, nn);
+  hipLaunchKernelGGL(k_nn_batch, dim3(persistent_grid(nn.total, INT_MAX - 7)), dim3(64 * kWaves), 0, stream, nn);
   hipLaunchKernelGGL(k_nn_resolve_batch, dim3(persistent_grid(resolve.total, 2048)), dim3(256), 0, stream, resolve);
   return hipGetLastError();
 }
