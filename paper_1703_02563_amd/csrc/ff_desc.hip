@@ -127,28 +127,64 @@ __device__ __forceinline__ uint4 wform_entry(const uint8_t *row, int W, int n, i
 // samples from there.  Entries that are image pixels also go to the
 // row-major copy when one is requested.  The weight-class row map has the
 // same rows (y + 3n); its row yp is written from a fifth staged row, the
-// blurred row y itself.  Dynamic LDS: 5 * row_stride(W).
+// blurred row y itself.  Dynamic LDS: five rows of Ws bytes.
+//
+// Bound by the stores and by the vector instructions that gather an entry.
+// Rows are read in aligned dwords whatever their width (a staged row keeps its
+// address modulo 4), and an entry's pixel is found with multiplications by
+// reciprocals.  Before: 33 us for 741 x 497 (5 scales, both images), 38 for
+// 1242 x 375, 230 for eight pairs of 2.1 Mpx; now 25, 25
+// and 191 (and 25 -> 23 for 1024 x 436, 145 -> 132 for 1920 x 1080, six scales).  Rows staged in phase
+// order, so that the samples of a row gy are adjacent bytes (two aligned LDS
+// reads, two shifts and a permute), cost more in staging than they save (30, 32
+// and 233 us), with unaligned LDS reads much more (46, 55 and 333).
 __host__ __device__ __forceinline__ int desc_row_stride(int W) { return (W + 15) & ~15; }
 
-__device__ __forceinline__ void desc_row(uint8_t *s_rows, const ffh::DescJob &jb, int W, int H, int yp) {
+__device__ __forceinline__ void desc_row(uint8_t *s_rows, int Ws, const ffh::DescJob &jb, int W, int H, int yp) {
   const int n = jb.n, l2 = ffk::map_log2(n);
   const int P = ffk::desc_pad(n), Wp = W + 2 * P;
-  const int Ws = desc_row_stride(W);
   const int yr = yp - P, y = clampi(yr, H - 1);
   // staged rows g = 0..3: y + n(2g - 3); g = 4: y itself (weight-class map)
   const int nrows = jb.wform ? 5 : 4;
-  auto src_row = [&](int g) { return g < 4 ? clampi(y + n * (2 * g - 3), H - 1) : y; };
-  if ((W & 3) == 0) {  // rows start on 4-byte boundaries: dword loads
-    const int wq = W >> 2;
-    for (int k = threadIdx.x; k < nrows * wq; k += blockDim.x) {
-      const int g = k / wq, q = k - g * wq;
-      const uint32_t *row = reinterpret_cast<const uint32_t *>(jb.blurred + (size_t)src_row(g) * W);
-      reinterpret_cast<uint32_t *>(s_rows + g * Ws)[q] = row[q];
+  const uint8_t *src[5];
+  int off[5], mis = 0;  // a row's address modulo 4
+#pragma unroll
+  for (int g = 0; g < 5; ++g) {
+    src[g] = jb.blurred + (size_t)(g < 4 ? clampi(y + n * (2 * g - 3), H - 1) : y) * W;
+    off[g] = (int)(reinterpret_cast<uintptr_t>(src[g]) & 3);
+    mis |= off[g];
+  }
+  if (!mis && (W & 3) == 0) {
+    for (int q = threadIdx.x; 4 * q < W; q += blockDim.x)
+#pragma unroll
+      for (int g = 0; g < 5; ++g)
+        if (g < nrows)
+          reinterpret_cast<uint32_t *>(s_rows + g * Ws)[q] = reinterpret_cast<const uint32_t *>(src[g])[q];
+  } else if (Ws >= W + 3) {
+    for (int q = threadIdx.x; 4 * q < W + 3; q += blockDim.x) {
+      uint32_t v[5];
+#pragma unroll
+      for (int g = 0; g < 5; ++g) {
+        const int x = 4 * q - off[g];
+        v[g] = 0;
+        if (g >= nrows) continue;
+        if (x >= 0 && x + 4 <= W) {
+          v[g] = *reinterpret_cast<const uint32_t *>(src[g] + x);
+        } else {  // the row's own bytes of its first and last dword
+          for (int j = 0; j < 4; ++j)
+            if (x + j >= 0 && x + j < W) v[g] |= (uint32_t)src[g][x + j] << (8 * j);
+        }
+      }
+#pragma unroll
+      for (int g = 0; g < 5; ++g)
+        if (g < nrows) reinterpret_cast<uint32_t *>(s_rows + g * Ws)[q] = v[g];
     }
   } else {
+#pragma unroll
+    for (int g = 0; g < 5; ++g) off[g] = 0;
     for (int k = threadIdx.x; k < nrows * W; k += blockDim.x) {
       const int g = k / W, x = k - g * W;
-      s_rows[g * Ws + x] = jb.blurred[(size_t)src_row(g) * W + x];
+      s_rows[g * Ws + x] = jb.blurred[(size_t)(g < 4 ? clampi(y + n * (2 * g - 3), H - 1) : y) * W + x];
     }
   }
   __syncthreads();
@@ -157,15 +193,21 @@ __device__ __forceinline__ void desc_row(uint8_t *s_rows, const ffh::DescJob &jb
   const int ywf = yr + ffk::kWformPad * n;
   if (jb.wform && ywf >= 0 && ywf < H + 2 * ffk::kWformPad * n) {
     uint4 *wout = reinterpret_cast<uint4 *>(jb.wform) + (size_t)ywf * W;
-    for (int x = threadIdx.x; x < W; x += blockDim.x) wout[x] = wform_entry(s_rows + 4 * Ws, W, n, x, jb.wradius);
+    for (int x = threadIdx.x; x < W; x += blockDim.x) wout[x] = wform_entry(s_rows + 4 * Ws + off[4], W, n, x, jb.wradius);
   }
   uint4 *out = reinterpret_cast<uint4 *>(jb.desc) + (size_t)yp * Wp;
+  // desc_pixel with its quotients by reciprocals, exact for columns below 2^16
+  const int q = Wp >> l2, m = Wp & ((1 << l2) - 1);
+  const uint32_t rq = 0xFFFFFFFFu / (uint32_t)q + 1, rq1 = 0xFFFFFFFFu / (uint32_t)(q + 1) + 1;
   for (int c = threadIdx.x; c < Wp; c += blockDim.x) {
-    const int xr = ffk::desc_pixel(c, l2, Wp) - P, x = clampi(xr, W - 1);
+    const bool lead = c < (q + 1) * m;  // phases with one entry more
+    const int c2 = lead ? c : c - (q + 1) * m;
+    const int f = (int)__umulhi((uint32_t)c2, lead ? rq1 : rq);
+    const int xr = (lead ? f : m + f) + ((c2 - f * (lead ? q + 1 : q)) << l2) - P, x = clampi(xr, W - 1);
     uint32_t w[4];
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
-      const uint8_t *row = s_rows + g * Ws;
+      const uint8_t *row = s_rows + g * Ws + off[g];
       uint32_t v = 0;
 #pragma unroll
       for (int gx = 0; gx < 4; ++gx) v |= (uint32_t)row[clampi(x + n * (2 * gx - 3), W - 1)] << (8 * gx);
@@ -178,18 +220,19 @@ __device__ __forceinline__ void desc_row(uint8_t *s_rows, const ffh::DescJob &jb
   }
 }
 
-__global__ __launch_bounds__(256) void k_desc(ffh::DescJobs jobs) {
+__global__ __launch_bounds__(256) void k_desc(ffh::DescJobs jobs, int Ws) {
   extern __shared__ uint8_t s_rows[];
   const ffh::DescJob &jb = jobs.job[blockIdx.y];
   if ((int)blockIdx.x >= jobs.H + 2 * ffk::desc_pad(jb.n)) return;  // workgroup-uniform
-  desc_row(s_rows, jb, jobs.W, jobs.H, blockIdx.x);
+  desc_row(s_rows, Ws, jb, jobs.W, jobs.H, blockIdx.x);
 }
 
-// ---- batches: persistent launches over the same work units ---------------
+// ---- batches: the same work units, one workgroup each --------------------
 // (pixel-wise separable sums through a row-sum buffer and descriptors straight
 // from global memory took 624 us for eight pairs of 2.1 Mpx in all, weight-class
 // maps of every scale included; the units of the single-pair kernels, and
-// those maps only where a variant reads them, 306 us)
+// those maps only where a variant reads them, 242 us; 2048 or 4096 workgroups
+// striding through the items cost 28 us more than one for each)
 
 // Items (pair, image * L + scale, 64 x 64 tile).
 __global__ __launch_bounds__(256) void k_blur_batch(ffh::BatchStage st) {
@@ -205,7 +248,7 @@ __global__ __launch_bounds__(256) void k_blur_batch(ffh::BatchStage st) {
 }
 
 // Items (pair, scale, image, stored row).
-__global__ __launch_bounds__(256) void k_desc_batch(ffh::BatchStage st) {
+__global__ __launch_bounds__(256) void k_desc_batch(ffh::BatchStage st, int Ws) {
   extern __shared__ uint8_t s_rows[];
   ffk::for_items(st.total, [&](int item) {
     const int p = ffk::batch_pair(st.prefix, st.npairs, item);
@@ -215,7 +258,7 @@ __global__ __launch_bounds__(256) void k_desc_batch(ffh::BatchStage st) {
     const int Hp = bp.H + 2 * ffk::desc_pad(1 << lv), im = local / Hp;
     const ffh::DescJob jb = {bp.img[im], bp.blur[im][lv], bp.desc[im][lv], lv == 0 ? bp.desc1[im] : nullptr,
                              (st.wform_scales >> lv) & 1 ? bp.wform[im][lv] : nullptr, 1 << lv, 3};
-    desc_row(s_rows, jb, bp.W, bp.H, local % Hp);
+    desc_row(s_rows, Ws, jb, bp.W, bp.H, local % Hp);
     __syncthreads();  // the next item stages its rows
   });
 }
@@ -233,8 +276,11 @@ int batch_desc_items(int H, int L) {
 }
 
 // Dynamic LDS of the descriptor rows of a W-wide image.
-static hipError_t desc_lds(const void *kernel, int W, size_t *lds) {
-  *lds = 5 * (size_t)desc_row_stride(W);
+// *Ws: bytes per row, with three for its alignment where they fit.
+static hipError_t desc_lds(const void *kernel, int W, int *Ws, size_t *lds) {
+  *Ws = desc_row_stride(W + 3);
+  if (5 * (size_t)*Ws > 160 * 1024) *Ws = desc_row_stride(W);
+  *lds = 5 * (size_t)*Ws;
   if (*lds > 160 * 1024) return hipErrorInvalidValue;
   if (*lds > 64 * 1024)  // rows wider than 12 K pixels
     return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)*lds);
@@ -245,11 +291,12 @@ hipError_t launch_batch_descriptors(const BatchStage &tiles, const BatchStage &r
                                     hipStream_t stream) {
   if (tiles.total <= 0 || rows.total <= 0) return hipSuccess;
   size_t lds;
-  const hipError_t e = desc_lds(reinterpret_cast<const void *>(k_desc_batch), max_width, &lds);
+  int Ws;
+  const hipError_t e = desc_lds(reinterpret_cast<const void *>(k_desc_batch), max_width, &Ws, &lds);
   if (e != hipSuccess) return e;
-  auto grid = [](int total) { return dim3(((std::min(total, 4096) + 7) / 8) * 8); };
+  auto grid = [](int total) { return dim3(((total + 7) / 8) * 8); };
   hipLaunchKernelGGL(k_blur_batch, grid(tiles.total), dim3(256), 0, stream, tiles);
-  hipLaunchKernelGGL(k_desc_batch, grid(rows.total), dim3(256), lds, stream, rows);
+  hipLaunchKernelGGL(k_desc_batch, grid(rows.total), dim3(256), lds, stream, rows, Ws);
   return hipGetLastError();
 }
 
@@ -268,12 +315,13 @@ hipError_t launch_blur(const DescJobs &jobs, hipStream_t stream) {
 hipError_t launch_descriptors(const DescJobs &jobs, hipStream_t stream) {
   if (jobs.count <= 0) return hipSuccess;
   size_t lds;
-  hipError_t e = desc_lds(reinterpret_cast<const void *>(k_desc), jobs.W, &lds);
+  int Ws;
+  hipError_t e = desc_lds(reinterpret_cast<const void *>(k_desc), jobs.W, &Ws, &lds);
   if (e != hipSuccess || (e = launch_blur(jobs, stream)) != hipSuccess) return e;
   int pmax = 0;
   for (int k = 0; k < jobs.count; ++k) pmax = std::max(pmax, ffk::desc_pad(jobs.job[k].n));
   const dim3 gpad(jobs.H + 2 * pmax, jobs.count);
-  hipLaunchKernelGGL(k_desc, gpad, dim3(256), lds, stream, jobs);
+  hipLaunchKernelGGL(k_desc, gpad, dim3(256), lds, stream, jobs, Ws);
   return hipGetLastError();
 }
 
