@@ -462,7 +462,7 @@ ff_status ff_batch_table(const ff_pair *pairs, int32_t npairs, const ff_params *
                          size_t ws_bytes, void *table_host, size_t table_bytes);
 
 /* Forward and backward Flow Fields plus consistency masks of every pair of a
- * batch (pairs of different sizes), each stage as one persistent launch over
+ * batch (pairs of different sizes), each stage as one launch over
  * all pairs' work items (rows, NN blocks, tiles); per pair the results are
  * those of ff_flow_fields.  pairs: host array (sizes, for the launch
  * geometry); table: device copy of ff_batch_table's output; radius must be 3

@@ -2,7 +2,7 @@
 
 BatchFlowFields owns the device buffers of a batch (images, outputs, the
 workspace and the device copy of the pair table) and runs
-ff_flow_fields_batched: every stage of the schedule is one persistent launch
+ff_flow_fields_batched: every stage of the schedule is one launch
 over the work items of all pairs.  capture() records one call into a HIP
 graph (torch.cuda.CUDAGraph); replay() re-runs it with no host work beyond
 the graph launch.

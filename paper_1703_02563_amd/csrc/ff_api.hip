@@ -914,7 +914,7 @@ ff_status ff_flow_fields_batched(const ff_pair *pairs, int32_t npairs, const ff_
     set(resolve, [&](int W, int H) { return ffh::batch_nn_resolve_items(W, H, L); });
   }
   if ((e = ffh::launch_batch_nn(keysf, nn, resolve, s)) != hipSuccess) return FF_ERR_LAUNCH;
-  // scales, coarse to fine: one persistent launch per run of passes
+  // scales, coarse to fine: one launch per run of passes
   for (int lv = L - 1; lv >= 0; --lv) {
     const int n = 1 << lv;
     bool maps_fit = true;

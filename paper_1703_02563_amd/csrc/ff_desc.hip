@@ -294,9 +294,8 @@ hipError_t launch_batch_descriptors(const BatchStage &tiles, const BatchStage &r
   int Ws;
   const hipError_t e = desc_lds(reinterpret_cast<const void *>(k_desc_batch), max_width, &Ws, &lds);
   if (e != hipSuccess) return e;
-  auto grid = [](int total) { return dim3(((total + 7) / 8) * 8); };
-  hipLaunchKernelGGL(k_blur_batch, grid(tiles.total), dim3(256), 0, stream, tiles);
-  hipLaunchKernelGGL(k_desc_batch, grid(rows.total), dim3(256), lds, stream, rows, Ws);
+  hipLaunchKernelGGL(k_blur_batch, dim3(item_groups(tiles.total)), dim3(256), 0, stream, tiles);
+  hipLaunchKernelGGL(k_desc_batch, dim3(item_groups(rows.total)), dim3(256), lds, stream, rows, Ws);
   return hipGetLastError();
 }
 

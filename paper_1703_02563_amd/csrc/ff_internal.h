@@ -243,6 +243,13 @@ struct BatchPair {
 };
 
 // Work items of one stage: pair p owns items [prefix[p], prefix[p+1]).
+// Workgroups of a launch over work items (for_items), a multiple of 8: one per
+// item, as far as 1024 threads each stay below 2^32 in all.
+inline unsigned item_groups(int total) {
+  constexpr int kMost = 1 << 21;
+  return (unsigned)(((total < 1 ? 1 : total < kMost ? total : kMost) + 7) / 8 * 8);
+}
+
 struct BatchStage {
   const BatchPair *pairs;
   int npairs, total;

@@ -1278,11 +1278,11 @@ hipError_t launch_v(const ffh::LevelKArgs &a, const ffh::BatchStage *batch, hipS
     if (batch) return hipErrorInvalidValue;  // batches run radius 3
   } else if (batch) {
     if (batch->total <= 0) return hipSuccess;
-    // a workgroup per item, a multiple of 8 (for_items): 2048 workgroups, more
-    // than are resident at once, left a second round a third full (n = 1, eight
-    // pairs of 2.1 Mpx in all: 476 us a launch against 397)
-    const int grid = ((batch->total + 7) / 8) * 8;
-    hipLaunchKernelGGL((k_level_batch<LOG2N, TW, TH, THREADS, EV, HALO>), dim3(grid), dim3(THREADS), 0, stream, a,
+    // a workgroup per item: 2048 workgroups, more than are resident at once,
+    // left a second round a third full (n = 1, eight pairs of 2.1 Mpx in all:
+    // 476 us a launch against 397)
+    const dim3 grid(ffh::item_groups(batch->total));
+    hipLaunchKernelGGL((k_level_batch<LOG2N, TW, TH, THREADS, EV, HALO>), grid, dim3(THREADS), 0, stream, a,
                        *batch);
     return hipGetLastError();
   }

@@ -24,7 +24,7 @@
 // staged in LDS (stages of 32 tiles, double-buffered; the norms are computed
 // while staging).  With QB = 8 query blocks per wave each tile's five 16-byte
 // LDS reads feed eight products; the VALU is then busy 64 % of the time and
-// the matrix cores 50 %, at the 1.94 GHz that the card holds under this load.
+// the matrix cores 44 %, at the 1.94 GHz that the card holds under this load.
 //
 // Ties: within a lane the first unit that reaches the maximum is kept, units
 // merge by (score, unit), and inside the unit the smallest index of that
@@ -543,13 +543,13 @@ int batch_nn_resolve_items(int W, int H, int L) {
   return 2 * ((((W + nc - 1) / nc) * ((H + nc - 1) / nc) + kResolveQ - 1) / kResolveQ);
 }
 
-static int persistent_grid(int total, int cap) { return ((std::min(std::max(total, 1), cap) + 7) / 8) * 8; }
+static int strided_grid(int total, int cap) { return ((std::min(std::max(total, 1), cap) + 7) / 8) * 8; }
 
 hipError_t launch_batch_nn(const BatchStage &fill, const BatchStage &nn, const BatchStage &resolve,
                            hipStream_t stream) {
-  hipLaunchKernelGGL(k_nn_fill_batch, dim3(persistent_grid(fill.total, 4096)), dim3(256), 0, stream, fill);
-  hipLaunchKernelGGL(k_nn_batch, dim3(persistent_grid(nn.total, INT_MAX - 7)), dim3(64 * kWaves), 0, stream, nn);
-  hipLaunchKernelGGL(k_nn_resolve_batch, dim3(persistent_grid(resolve.total, 2048)), dim3(256), 0, stream, resolve);
+  hipLaunchKernelGGL(k_nn_fill_batch, dim3(strided_grid(fill.total, 4096)), dim3(256), 0, stream, fill);
+  hipLaunchKernelGGL(k_nn_batch, dim3(item_groups(nn.total)), dim3(64 * kWaves), 0, stream, nn);
+  hipLaunchKernelGGL(k_nn_resolve_batch, dim3(strided_grid(resolve.total, 2048)), dim3(256), 0, stream, resolve);
   return hipGetLastError();
 }
 
