@@ -960,11 +960,31 @@ __global__ __launch_bounds__(1024) void k_triplet_hinge(const float *cost, int m
   if (threadIdx.x == 0) *loss = weight * s_part[0];
 }
 
+// One map or the two of a pair, quantised with one range.
+struct QuantMaps {
+  const float *f[2];
+  uint8_t *q[2];
+  long long count;
+  int wide;  // 16-byte aligned maps, 4-byte aligned outputs
+};
+
 // Per-map range of float features (block partials, then one block).
-__global__ __launch_bounds__(256) void k_minmax_partial(const float *f, long long count, float *part) {
+// (blockIdx.y selects the map; both maps of a pair in one launch and four
+// floats a load: two of 1024 x 436 x 16 in 13 instead of 24 us.)
+__global__ __launch_bounds__(256) void k_minmax_partial(QuantMaps m, float *part) {
   __shared__ float s_lo[256], s_hi[256];
+  const float *f = m.f[blockIdx.y];
+  part += 2 * (size_t)blockIdx.y * gridDim.x;
   float lo = INFINITY, hi = -INFINITY;
-  for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < count; i += (long long)gridDim.x * 256) {
+  const long long first = (long long)blockIdx.x * 256 + threadIdx.x, step = (long long)gridDim.x * 256;
+  const long long n4 = m.wide ? m.count >> 2 : 0;
+#pragma unroll 4
+  for (long long i = first; i < n4; i += step) {
+    const float4 v = reinterpret_cast<const float4 *>(f)[i];
+    lo = fminf(lo, fminf(fminf(v.x, v.y), fminf(v.z, v.w)));
+    hi = fmaxf(hi, fmaxf(fmaxf(v.x, v.y), fmaxf(v.z, v.w)));
+  }
+  for (long long i = 4 * n4 + first; i < m.count; i += step) {
     lo = fminf(lo, f[i]);
     hi = fmaxf(hi, f[i]);
   }
@@ -1009,14 +1029,23 @@ __global__ __launch_bounds__(256) void k_minmax_final(float *part, int nparts) {
   }
 }
 
-// q = clamp(rint((f - lo) * (255 / (hi - lo))), 0, 255).
-__global__ __launch_bounds__(256) void k_quantize(const float *f, long long count, const float *range, uint8_t *q) {
+// q = clamp(rint((f - lo) * (255 / (hi - lo))), 0, 255).  Four values a
+// thread, the maps of a pair in one launch (as above: 26 -> 13 us).
+__global__ __launch_bounds__(256) void k_quantize(QuantMaps m, const float *range) {
   const float lo = range[0], hi = range[1];
   const float s = hi > lo ? 255.0f / (hi - lo) : 0.0f;
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= count) return;
-  const float t = rintf((f[i] - lo) * s);
-  q[i] = (uint8_t)fminf(fmaxf(t, 0.0f), 255.0f);
+  const float *f = m.f[blockIdx.y];
+  uint8_t *q = m.q[blockIdx.y];
+  auto level = [&](float v) { return (uint8_t)fminf(fmaxf(rintf((v - lo) * s), 0.0f), 255.0f); };
+  const long long i = 4 * ((long long)blockIdx.x * blockDim.x + threadIdx.x);
+  if (m.wide && i + 4 <= m.count) {
+    const float4 v = *reinterpret_cast<const float4 *>(f + i);
+    *reinterpret_cast<uint32_t *>(q + i) = (uint32_t)level(v.x) | (uint32_t)level(v.y) << 8 |
+                                           (uint32_t)level(v.z) << 16 | (uint32_t)level(v.w) << 24;
+    return;
+  }
+  for (int e = 0; e < 4; ++e)
+    if (i + e < m.count) q[i + e] = level(f[i + e]);
 }
 
 }  // namespace
@@ -1149,11 +1178,17 @@ hipError_t launch_triplet_hinge(const float *cost, int m, float margin, float sc
 
 constexpr int kQuantParts = 1024;
 
+static void quantize_maps(QuantMaps m, int maps, float *part, hipStream_t stream) {
+  m.wide = (((uintptr_t)m.f[0] | (uintptr_t)m.f[1]) & 15) == 0 && (((uintptr_t)m.q[0] | (uintptr_t)m.q[1]) & 3) == 0;
+  float *range = part + 2 * maps * kQuantParts;
+  hipLaunchKernelGGL(k_minmax_partial, dim3(kQuantParts, maps), dim3(256), 0, stream, m, part);
+  hipLaunchKernelGGL(k_minmax_final, dim3(1), dim3(256), 0, stream, part, maps * kQuantParts);
+  hipLaunchKernelGGL(k_quantize, dim3(blocks_of((m.count + 3) / 4), maps), dim3(256), 0, stream, m, range);
+}
+
 hipError_t launch_quantize(const float *f, long long count, float *part, uint8_t *q, hipStream_t stream) {
   if (count <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_minmax_partial, dim3(kQuantParts), dim3(256), 0, stream, f, count, part);
-  hipLaunchKernelGGL(k_minmax_final, dim3(1), dim3(256), 0, stream, part, kQuantParts);
-  hipLaunchKernelGGL(k_quantize, dim3(blocks_of(count)), dim3(256), 0, stream, f, count, part + 2 * kQuantParts, q);
+  quantize_maps({{f, f}, {q, q}, count, 0}, 1, part, stream);
   return hipGetLastError();
 }
 
@@ -1162,12 +1197,7 @@ hipError_t launch_quantize(const float *f, long long count, float *part, uint8_t
 hipError_t launch_quantize_pair(const float *f1, const float *f2, long long count, float *part, uint8_t *q1,
                                 uint8_t *q2, hipStream_t stream) {
   if (count <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_minmax_partial, dim3(kQuantParts), dim3(256), 0, stream, f1, count, part);
-  hipLaunchKernelGGL(k_minmax_partial, dim3(kQuantParts), dim3(256), 0, stream, f2, count, part + 2 * kQuantParts);
-  hipLaunchKernelGGL(k_minmax_final, dim3(1), dim3(256), 0, stream, part, 2 * kQuantParts);
-  const float *range = part + 4 * kQuantParts;
-  hipLaunchKernelGGL(k_quantize, dim3(blocks_of(count)), dim3(256), 0, stream, f1, count, range, q1);
-  hipLaunchKernelGGL(k_quantize, dim3(blocks_of(count)), dim3(256), 0, stream, f2, count, range, q2);
+  quantize_maps({{f1, f2}, {q1, q2}, count, 0}, 2, part, stream);
   return hipGetLastError();
 }
 
