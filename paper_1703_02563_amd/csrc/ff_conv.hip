@@ -149,14 +149,15 @@ __device__ __forceinline__ void conv_store(const ffh::ConvArgs &a, size_t q0, in
     uint2 lo[G];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-      uint32_t h[4], l[4];
+      uint32_t h[2], l[2];
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        h[c] = f32_to_bf16(v[g][c]);
-        l[c] = f32_to_bf16(v[g][c] - bf16_to_f32((uint16_t)h[c]));
+      for (int c = 0; c < 2; ++c) {
+        const float a0 = v[g][2 * c], a1 = v[g][2 * c + 1];
+        h[c] = f32x2_to_bf16(a0, a1);
+        l[c] = f32x2_to_bf16(a0 - bf16_to_f32((uint16_t)h[c]), a1 - __uint_as_float(h[c] & 0xFFFF0000u));
       }
-      *reinterpret_cast<uint2 *>(tr + run_chunk(row, g) + 8 * kh) = pack4(h);
-      lo[g] = pack4(l);
+      *reinterpret_cast<uint2 *>(tr + run_chunk(row, g) + 8 * kh) = make_uint2(h[0], h[1]);
+      lo[g] = make_uint2(l[0], l[1]);
     }
     lds_in_order();
     const uint8_t *act = reinterpret_cast<const uint8_t *>(a.act + q0 * 32);
@@ -184,12 +185,8 @@ __device__ __forceinline__ void conv_store(const ffh::ConvArgs &a, size_t q0, in
     if (a.out_bf16) {
       uint2 h[G];
 #pragma unroll
-      for (int g = 0; g < G; ++g) {
-        uint32_t b[4];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) b[c] = f32_to_bf16(v[g][c]);
-        h[g] = pack4(b);
-      }
+      for (int g = 0; g < G; ++g)
+        h[g] = make_uint2(f32x2_to_bf16(v[g][0], v[g][1]), f32x2_to_bf16(v[g][2], v[g][3]));
       if (COUT == 32 && a.wide) {
 #pragma unroll
         for (int g = 0; g < G; ++g) *reinterpret_cast<uint2 *>(tr + run_chunk(row, g) + 8 * kh) = h[g];
@@ -218,7 +215,7 @@ __device__ __forceinline__ void conv_bias(const float *bias, int kh, float (&b)[
 // half kh holds taps 8 * kh .. 8 * kh + 7 of one pixel.  Bound by its stores
 // (64 bytes a pixel, 45 us for 3.6 Mpx at copy rate) and the 2-byte loads of
 // the taps: 89 us with one bf16 per lane and store, 99 with the 8 bytes that a
-// lane holds, 92 in 1 KB pieces.
+// lane holds, 92 in 1 KB pieces, 87 with two values rounded at a time.
 template <int CIN, int COUT>
 __global__ __launch_bounds__(256) void k_conv_fwd(ffh::ConvArgs a) {
   static_assert(CIN == 1, "Cin 1 (wider inputs: k_conv_fwd_tile)");
@@ -268,15 +265,16 @@ __global__ __launch_bounds__(256) void k_conv_fwd(ffh::ConvArgs a) {
 // identical.  The epilogues that a training step needs run here instead of as
 // passes over memory of their own: the last layer's normalisation, and the
 // data gradient's ReLU and its split into two bf16 parts.  3.6 Mpx: 32 -> 32
-// with bf16 outputs 172 -> 132 us, 32 -> 16 with the normalisation 156 + 96 ->
-// 122 us, data gradient with mask and split 32 -> 32 172 + 383 -> 239 us and
-// 16 -> 32 115 + 383 -> 173 us.  Bound by memory: 89, 92, 178 and 156 us at
+// with bf16 outputs 172 -> 123 us, 32 -> 16 with the normalisation 156 + 96 ->
+// 120 us, data gradient with mask and split 32 -> 32 172 + 383 -> 228 us and
+// 16 -> 32 115 + 383 -> 167 us.  Bound by memory: 89, 92, 178 and 156 us at
 // copy rate.
 //
 // A workgroup runs down kConvStrips such tiles: its weights are loaded once,
 // and the next tile's pixels are in flight while this one is computed.
 // Without both the four kernels took 186, 155, 307 and 268 us (stores
-// straight from the lanes' registers included).
+// straight from the lanes' registers included); rounding value by value 132,
+// 122, 239 and 173 us.
 constexpr int kConvRows = 8, kConvStrips = 4;
 
 template <int CIN, int COUT, ConvEpilogue EPI>
