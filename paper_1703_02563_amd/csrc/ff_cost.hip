@@ -131,9 +131,10 @@ __global__ __launch_bounds__(256) void k_fixed_to_float(const int64_t *acc, cons
 // an atomic cursor.
 struct CostBins {
   int32_t *start[2];  // [Hb][Wb + 1]: counts, then first records (last column: end of the row)
-  int32_t *rank[2];   // [count]: the entry's place inside its bin, -1: no contribution
+  int32_t *rank[2];   // [count]: the entry's place inside its bin, -1: no contribution;
+                      // once the records stand: the crowded pixels
   int4 *rec[2];       // [count]: (flow to the other map, gradient bits, entry)
-  int32_t *cursor;    // [2]
+  int32_t *cursor;    // [4]: records placed, then crowded pixels, per side
   int Wb, Hb, rn, log2n;
 };
 
@@ -198,6 +199,11 @@ __global__ __launch_bounds__(256) void k_cost_fill(ffh::CostArgs a, CostBins b) 
 struct CostSum {
   long long s[4] = {0, 0, 0, 0};
   unsigned terms = 0, sums = 0;  // terms out of range; sums that left the int64 range
+  __device__ __forceinline__ void put(int c, long long fx) {
+    const long long t = (long long)((unsigned long long)s[c] + (unsigned long long)fx);
+    sums += ((s[c] ^ t) & (fx ^ t)) < 0;
+    s[c] = t;
+  }
   __device__ __forceinline__ void add(float g, float4 own, float4 other) {
     const double g2 = 2.0 * (double)g;
     const float p[4] = {own.x, own.y, own.z, own.w}, q[4] = {other.x, other.y, other.z, other.w};
@@ -208,23 +214,79 @@ struct CostSum {
         ++terms;
         continue;
       }
-      const long long fx = __double2ll_rn(d * kFix);
-      const long long t = (long long)((unsigned long long)s[c] + (unsigned long long)fx);
-      sums += ((s[c] ^ t) & (fx ^ t)) < 0;
-      s[c] = t;
+      put(c, __double2ll_rn(d * kFix));
+    }
+  }
+  __device__ __forceinline__ void merge(const CostSum &o) {
+    terms += o.terms;
+    sums += o.sums;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) put(c, o.s[c]);
+  }
+  // The sums of the wave's 16 quads, in every quad.
+  __device__ __forceinline__ void wave_sum() {
+#pragma unroll
+    for (int off = 4; off < 64; off <<= 1) {
+      CostSum o;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) o.s[c] = __shfl_xor(s[c], off);
+      o.terms = __shfl_xor(terms, off);
+      o.sums = __shfl_xor(sums, off);
+      merge(o);
     }
   }
 };
 
-// Gradient of one side (blockIdx.z): a workgroup takes 16 x 4 pixels, four
-// lanes per pixel with four channels each.  Bound by float64 arithmetic (a
+// A finished pixel: this lane's four channels, and what left the range (a
+// term out of range is seen from both sides and counted on the first).
+__device__ __forceinline__ void cost_write(const ffh::CostArgs &a, int side, size_t px, const CostSum &sum) {
+  const unsigned bad = sum.sums + (side == 0 ? sum.terms : 0u);
+  if (bad) atomicAdd(reinterpret_cast<unsigned long long *>(a.overflow), (unsigned long long)bad);
+  constexpr double inv = 1.0 / kFix;
+  reinterpret_cast<float4 *>(side ? a.grad_f2 : a.grad_f1)[px] =
+      make_float4((float)((double)sum.s[0] * inv), (float)((double)sum.s[1] * inv), (float)((double)sum.s[2] * inv),
+                  (float)((double)sum.s[3] * inv));
+}
+
+// Terms of an interior pixel that its quad sums alone; more make it crowded.
+// At least the 225 samples of the largest patch, so that the crowded pixels of a
+// side are no more than its entries (the length of their list).
+constexpr int kCrowded = 256;
+constexpr int kCrowdGroups = 512;  // workgroups for them, per side
+
+// The terms of interior pixel (x, y): every sample that lands there is exactly
+// (x, y), one term per entry of 2R + 1 ranges of records.  Term i of the
+// sequence in row v is record first[v] + i, at[v] <= i < at[v + 1].
+template <int K>
+__device__ __forceinline__ void cost_terms(const CostBins &b, int side, int n, int x, int y, int (&first)[K],
+                                           int (&at)[K + 1]) {
+  const int stride = b.Wb + 1;
+  const int32_t *row = b.start[side] + (size_t)y * stride + ffk::desc_col(x, b.log2n, b.Wb);
+  at[0] = 0;
+#pragma unroll
+  for (int v = 0; v < K; ++v) {
+    const int lo = row[(size_t)v * n * stride], hi = row[(size_t)v * n * stride + K];
+    first[v] = lo - at[v];
+    at[v + 1] = at[v] + (hi - lo);
+  }
+}
+template <int K>
+__device__ __forceinline__ int cost_record(const int (&first)[K], const int (&at)[K + 1], int i) {
+  int f = first[0];
+#pragma unroll
+  for (int v = 1; v < K; ++v) f = i >= at[v] ? first[v] : f;
+  return f + i;
+}
+
+// Interior pixels of one side (blockIdx.z): a workgroup takes 16 x 4 pixels,
+// four lanes per pixel with four channels each; crowded ones are listed for
+// k_cost_rest.  Bound by float64 arithmetic (a
 // term is formed and rounded in float64 as in the atomic form) and by the
 // latency of record -> other map's pixel, both prefetched one term ahead.
 // The terms of the 2R + 1 ranges run as one sequence, so that the 16 pixels
 // of a wave differ only in their total.  With every |term| below 2^19 (51
 // bits of fixed point) adding 3 * 2^51 rounds it to an integer whose bits are
-// summed as they are; a pixel with a larger term, or with so many that the
-// sum could leave 63 bits, takes the checked additions.
+// summed as they are; a pixel with a larger term takes the checked additions.
 // 65,536 entries at radius 3 on 1024 x 436: the whole backward, sorting
 // included, 4.59 ms -> 0.33 ms
 // (this kernel 0.29 ms, both sides).
@@ -234,102 +296,198 @@ __global__ __launch_bounds__(256) void k_cost_gather(ffh::CostArgs a, CostBins b
   constexpr double kMagic = 6755399441055744.0;  // 3 * 2^51: adding it rounds to an integer
   const int k = threadIdx.x & 3, side = blockIdx.z;
   const int x = blockIdx.x * 16 + ((threadIdx.x >> 2) & 15), y = blockIdx.y * 4 + (threadIdx.x >> 6);
-  if (x >= a.W || y >= a.H) return;
-  const int W = a.W, H = a.H, Wm = W - 1, Hm = H - 1, n = a.n;
+  const int W = a.W, H = a.H, Wm = W - 1, Hm = H - 1;
+  if (x <= 0 || x >= Wm || y <= 0 || y >= Hm) return;
   const size_t px = ((size_t)y * W + x) * 4 + k;
   const float4 *fo = reinterpret_cast<const float4 *>(side ? a.f1 : a.f2) + k;
   const float4 own = reinterpret_cast<const float4 *>(side ? a.f2 : a.f1)[px];
   const int4 *rec = b.rec[side];
-  const int32_t *start = b.start[side];
-  const int stride = b.Wb + 1;
-  CostSum sum;
-  if (x > 0 && x < Wm && y > 0 && y < Hm) {
-    // every sample that lands here is exactly (x, y): one term per entry of
-    // the 2R + 1 ranges, against the other map at (x, y) + flow
-    int first[K], at[K + 1];  // term i of the sequence in row v is record first[v] + i, at[v] <= i < at[v + 1]
-    const int32_t *row = start + (size_t)y * stride + ffk::desc_col(x, b.log2n, b.Wb);
-    at[0] = 0;
-#pragma unroll
-    for (int v = 0; v < K; ++v) {
-      const int lo = row[(size_t)v * n * stride], hi = row[(size_t)v * n * stride + K];
-      first[v] = lo - at[v];
-      at[v + 1] = at[v] + (hi - lo);
-    }
-    const int total = at[K];
-    auto record = [&](int i) {
-      int f = first[0];
-#pragma unroll
-      for (int v = 1; v < K; ++v) f = i >= at[v] ? first[v] : f;
-      return rec[f + i];
-    };
-    auto other = [&](int4 r) { return fo[((size_t)clampi(y + r.y, Hm) * W + clampi(x + r.x, Wm)) * 4]; };
-    bool checked = total > 2047;
-    if (total > 0 && !checked) {
-      const double o0 = own.x, o1 = own.y, o2 = own.z, o3 = own.w;
-      int4 r0 = record(0), r1 = record(min(1, total - 1));
-      float4 q0 = other(r0);
-      bool small = true;
-      unsigned long long acc[4] = {0, 0, 0, 0};
-      for (int i = 0; i < total; ++i) {
-        const float4 q1 = other(r1);
-        const int4 r2 = record(min(i + 2, total - 1));
-        {
-#pragma clang fp contract(off)
-          const double g = (double)__int_as_float(r0.z) * (2.0 * kFix);
-          const double d0 = g * (o0 - (double)q0.x), d1 = g * (o1 - (double)q0.y);
-          const double d2 = g * (o2 - (double)q0.z), d3 = g * (o3 - (double)q0.w);
-          constexpr double kSmall = 2251799813685248.0;  // 2^51
-          small = small && fabs(d0) < kSmall && fabs(d1) < kSmall && fabs(d2) < kSmall && fabs(d3) < kSmall;
-          acc[0] += (unsigned long long)__double_as_longlong(d0 + kMagic);
-          acc[1] += (unsigned long long)__double_as_longlong(d1 + kMagic);
-          acc[2] += (unsigned long long)__double_as_longlong(d2 + kMagic);
-          acc[3] += (unsigned long long)__double_as_longlong(d3 + kMagic);
-        }
-        r0 = r1;
-        r1 = r2;
-        q0 = q1;
-      }
-      const unsigned long long bias = (unsigned long long)__double_as_longlong(kMagic) * (unsigned long long)total;
-#pragma unroll
-      for (int c = 0; c < 4; ++c) sum.s[c] = (long long)(acc[c] - bias);
-      checked = !small;
-    }
-    if (checked) {
-      sum = CostSum();
-      for (int i = 0; i < total; ++i) {
-        const int4 r = record(i);
-        sum.add(__int_as_float(r.z), own, other(r));
-      }
-    }
-  } else {
-    // border pixels also take the samples outside the image that clamp to
-    // them: all bins within rn of the pixel along the axis it borders
-    const int sy = (y == 0 || y == Hm) ? 1 : n, np = R > 0 && (x == 0 || x == Wm) ? n : 1;
-    for (int yb = y; yb <= y + 2 * b.rn; yb += sy)
-      for (int ph = 0; ph < np; ++ph) {
-        // centres x - rn + ph, then every n-th: at most K adjacent bins, one more for phase 0
-        const int32_t *p = start + (size_t)yb * stride + ffk::desc_col(x + ph, b.log2n, b.Wb);
-        const int lo = p[0], hi = p[ph == 0 ? K : K - 1];
-        for (int i = lo; i < hi; ++i) {
-          const int4 r = rec[i], en = a.entries[r.w];
-          const int cx = side ? en.x + en.z : en.x, cy = side ? en.y + en.w : en.y;
-          const float g = __int_as_float(r.z);
-          for (int v = -R; v <= R; ++v) {
-            if (clampi(cy + n * v, Hm) != y) continue;
-            const size_t orow = (size_t)clampi(cy + n * v + r.y, Hm) * W;
-            for (int u = -R; u <= R; ++u)
-              if (clampi(cx + n * u, Wm) == x) sum.add(g, own, fo[(orow + clampi(cx + n * u + r.x, Wm)) * 4]);
-          }
-        }
-      }
+  int first[K], at[K + 1];
+  cost_terms<K>(b, side, a.n, x, y, first, at);
+  const int total = at[K];
+  if (total > kCrowded) {
+    if (k == 0) b.rank[side][atomicAdd(b.cursor + 2 + side, 1)] = y * W + x;
+    return;
   }
-  // a term out of range is seen from both sides and counted on the first
-  const unsigned bad = sum.sums + (side == 0 ? sum.terms : 0u);
-  if (bad) atomicAdd(reinterpret_cast<unsigned long long *>(a.overflow), (unsigned long long)bad);
-  constexpr double inv = 1.0 / kFix;
-  float4 *out = reinterpret_cast<float4 *>(side ? a.grad_f2 : a.grad_f1);
-  out[px] = make_float4((float)((double)sum.s[0] * inv), (float)((double)sum.s[1] * inv),
-                        (float)((double)sum.s[2] * inv), (float)((double)sum.s[3] * inv));
+  auto record = [&](int i) { return rec[cost_record<K>(first, at, i)]; };
+  auto other = [&](int4 r) { return fo[((size_t)clampi(y + r.y, Hm) * W + clampi(x + r.x, Wm)) * 4]; };
+  CostSum sum;
+  bool checked = false;
+  if (total > 0) {
+    const double o0 = own.x, o1 = own.y, o2 = own.z, o3 = own.w;
+    int4 r0 = record(0), r1 = record(min(1, total - 1));
+    float4 q0 = other(r0);
+    bool small = true;
+    unsigned long long acc[4] = {0, 0, 0, 0};
+    for (int i = 0; i < total; ++i) {
+      const float4 q1 = other(r1);
+      const int4 r2 = record(min(i + 2, total - 1));
+      {
+#pragma clang fp contract(off)
+        const double g = (double)__int_as_float(r0.z) * (2.0 * kFix);
+        const double d0 = g * (o0 - (double)q0.x), d1 = g * (o1 - (double)q0.y);
+        const double d2 = g * (o2 - (double)q0.z), d3 = g * (o3 - (double)q0.w);
+        constexpr double kSmall = 2251799813685248.0;  // 2^51
+        small = small && fabs(d0) < kSmall && fabs(d1) < kSmall && fabs(d2) < kSmall && fabs(d3) < kSmall;
+        acc[0] += (unsigned long long)__double_as_longlong(d0 + kMagic);
+        acc[1] += (unsigned long long)__double_as_longlong(d1 + kMagic);
+        acc[2] += (unsigned long long)__double_as_longlong(d2 + kMagic);
+        acc[3] += (unsigned long long)__double_as_longlong(d3 + kMagic);
+      }
+      r0 = r1;
+      r1 = r2;
+      q0 = q1;
+    }
+    const unsigned long long bias = (unsigned long long)__double_as_longlong(kMagic) * (unsigned long long)total;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) sum.s[c] = (long long)(acc[c] - bias);
+    checked = !small;
+  }
+  if (checked) {
+    sum = CostSum();
+    for (int i = 0; i < total; ++i) {
+      const int4 r = record(i);
+      sum.add(__int_as_float(r.z), own, other(r));
+    }
+  }
+  cost_write(a, side, px, sum);
+}
+
+// A border pixel, by a wave.  It also takes the samples outside the image that
+// clamp to it: the records of all bins within rn of the pixel along the axis it
+// borders.  The ranges of 16 bins at a time, their records dealt out to the 16
+// quads, so that neither many empty bins nor one crowded bin is walked by one
+// quad.
+template <int R>
+__device__ __forceinline__ void cost_border(const ffh::CostArgs &a, const CostBins &b, int side, int x, int y) {
+  constexpr int K = 2 * R + 1;
+  const int lane = threadIdx.x & 63, quad = lane >> 2, k = lane & 3;
+  const int W = a.W, Wm = W - 1, Hm = a.H - 1, n = a.n;
+  const size_t px = ((size_t)y * W + x) * 4 + k;
+  const float4 *fo = reinterpret_cast<const float4 *>(side ? a.f1 : a.f2) + k;
+  const float4 own = reinterpret_cast<const float4 *>(side ? a.f2 : a.f1)[px];
+  const int4 *rec = b.rec[side];
+  CostSum sum;
+  const int sy = (y == 0 || y == Hm) ? 1 : n, np = R > 0 && (x == 0 || x == Wm) ? n : 1;
+  const int ranges = (2 * b.rn / sy + 1) * np;
+  for (int base = 0; base < ranges; base += 16) {
+    const int j = base + quad;
+    int lo = 0, len = 0;
+    if (j < ranges) {
+      // centres x - rn + ph, then every n-th: at most K adjacent bins, one more for phase 0
+      const int ph = j % np;
+      const int32_t *p =
+          b.start[side] + (size_t)(y + j / np * sy) * (b.Wb + 1) + ffk::desc_col(x + ph, b.log2n, b.Wb);
+      lo = p[0];
+      len = p[ph == 0 ? K : K - 1] - lo;
+    }
+    int incl = len;
+#pragma unroll
+    for (int off = 4; off < 64; off <<= 1) {
+      const int o = __shfl_up(incl, off);
+      if (lane >= off) incl += o;
+    }
+    const int total = __shfl(incl, 63), at = lo - (incl - len);  // item i of a range is record at + i
+    for (int i0 = 0; i0 < total; i0 += 16) {
+      const int i = i0 + quad;
+      int z = 0;  // the range that holds item i
+#pragma unroll
+      for (int step = 8; step > 0; step >>= 1) z += __shfl(incl, 4 * (z + step - 1)) <= i ? step : 0;
+      const int record = __shfl(at, 4 * z) + i;
+      if (i >= total) continue;
+      const int4 r = rec[record], en = a.entries[r.w];
+      const int cx = side ? en.x + en.z : en.x, cy = side ? en.y + en.w : en.y;
+      const float g = __int_as_float(r.z);
+      for (int v = -R; v <= R; ++v) {
+        if (clampi(cy + n * v, Hm) != y) continue;
+        const size_t orow = (size_t)clampi(cy + n * v + r.y, Hm) * W;
+        float4 q[K];
+#pragma unroll
+        for (int u = -R; u <= R; ++u) q[u + R] = fo[(orow + clampi(cx + n * u + r.x, Wm)) * 4];
+#pragma unroll
+        for (int u = -R; u <= R; ++u)
+          if (clampi(cx + n * u, Wm) == x) sum.add(g, own, q[u + R]);
+      }
+    }
+  }
+  sum.wave_sum();
+  if (quad == 0) cost_write(a, side, px, sum);
+}
+
+// Border pixels of an image, and the i-th.
+inline __host__ __device__ long long cost_border_count(int W, int H) {
+  return W == 1 || H == 1 ? (long long)W * H : 2ll * (W + H - 2);
+}
+__device__ __forceinline__ void cost_border_pixel(int i, int W, int H, int &x, int &y) {
+  if (W == 1 || H == 1) {
+    x = W == 1 ? 0 : i;
+    y = W == 1 ? i : 0;
+  } else if (i < 2 * W) {
+    x = i < W ? i : i - W;
+    y = i < W ? 0 : H - 1;
+  } else {
+    x = (i & 1) ? W - 1 : 0;  // 2 W is even
+    y = 1 + ((i - 2 * W) >> 1);
+  }
+}
+
+// The pixels that would keep one quad busy while the others wait: the border
+// pixels, a wave each (the first `border` workgroups), and the crowded ones, a
+// workgroup each (the others stride through the list).  Integer sums: any order
+// gives the same bits.
+template <int R>
+__global__ __launch_bounds__(256) void k_cost_rest(ffh::CostArgs a, CostBins b, int border) {
+  constexpr int K = 2 * R + 1, T = 4;  // terms in flight
+  __shared__ long long s_sum[4][4][5];  // of a wave's quads: four channels; terms and sums out of range
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, k = lane & 3, side = blockIdx.y;
+  const int W = a.W, Wm = W - 1, Hm = a.H - 1;
+  if ((int)blockIdx.x < border) {
+    const long long i = (long long)blockIdx.x * 4 + wave;
+    if (i >= cost_border_count(W, a.H)) return;
+    int x, y;
+    cost_border_pixel((int)i, W, a.H, x, y);
+    cost_border<R>(a, b, side, x, y);
+    return;
+  }
+  const float4 *fo = reinterpret_cast<const float4 *>(side ? a.f1 : a.f2) + k;
+  const int4 *rec = b.rec[side];
+  const int crowded = b.cursor[2 + side], groups = (int)gridDim.x - border;
+  for (int c = (int)blockIdx.x - border; c < crowded; c += groups) {
+    const int p = b.rank[side][c], x = p % W, y = p / W;
+    const float4 own = reinterpret_cast<const float4 *>(side ? a.f2 : a.f1)[(size_t)p * 4 + k];
+    int first[K], at[K + 1];
+    cost_terms<K>(b, side, a.n, x, y, first, at);
+    const int total = at[K];
+    CostSum sum;
+    for (int i0 = threadIdx.x >> 2; i0 < total; i0 += 64 * T) {
+      int4 r[T];
+      float4 q[T];
+#pragma unroll
+      for (int j = 0; j < T; ++j) r[j] = rec[cost_record<K>(first, at, min(i0 + 64 * j, total - 1))];
+#pragma unroll
+      for (int j = 0; j < T; ++j) q[j] = fo[((size_t)clampi(y + r[j].y, Hm) * W + clampi(x + r[j].x, Wm)) * 4];
+#pragma unroll
+      for (int j = 0; j < T; ++j)
+        if (i0 + 64 * j < total) sum.add(__int_as_float(r[j].z), own, q[j]);
+    }
+    sum.wave_sum();
+    if (lane < 4) {
+      for (int e = 0; e < 4; ++e) s_sum[wave][k][e] = sum.s[e];
+      s_sum[wave][k][4] = (long long)sum.terms << 32 | sum.sums;
+    }
+    __syncthreads();
+    if (threadIdx.x < 4) {
+      for (int w = 1; w < 4; ++w) {
+        CostSum o;
+        for (int e = 0; e < 4; ++e) o.s[e] = s_sum[w][k][e];
+        o.terms = (unsigned)(s_sum[w][k][4] >> 32);
+        o.sums = (unsigned)s_sum[w][k][4];
+        sum.merge(o);
+      }
+      cost_write(a, side, (size_t)p * 4 + k, sum);
+    }
+    __syncthreads();  // the next pixel's sums
+  }
 }
 
 // Both gradients become NaN when the overflow word is nonzero.
@@ -393,30 +551,36 @@ static bool cost_bins(const CostArgs &a, CostBins *b, size_t *clear_words) {
   const size_t bins = ((size_t)b->Hb * (b->Wb + 1) + 1) & ~(size_t)1, entries = ((size_t)a.count + 1) & ~(size_t)1;
   // records first (16-byte aligned), then the counts and the cursor, then the ranks
   const uintptr_t base = ((uintptr_t)a.acc1 + 15) & ~(uintptr_t)15;
-  const size_t total = (base - (uintptr_t)a.acc1) + 2 * entries * 16 + (2 * bins + 2) * 4 + 2 * entries * 4;
+  const size_t total = (base - (uintptr_t)a.acc1) + 2 * entries * 16 + (2 * bins + 4) * 4 + 2 * entries * 4;
   if (total > (size_t)2 * a.W * a.H * 16 * 8) return false;
   b->rec[0] = reinterpret_cast<int4 *>(base);
   b->rec[1] = b->rec[0] + entries;
   b->start[0] = reinterpret_cast<int32_t *>(b->rec[1] + entries);
   b->start[1] = b->start[0] + bins;
   b->cursor = b->start[1] + bins;
-  b->rank[0] = b->cursor + 2;
+  b->rank[0] = b->cursor + 4;
   b->rank[1] = b->rank[0] + entries;
-  *clear_words = bins + 1;
+  *clear_words = bins + 2;
   return true;
 }
 
+template <int R>
+static void launch_cost_sums(const CostArgs &a, const CostBins &b, hipStream_t stream) {
+  const int border = (int)((cost_border_count(a.W, a.H) + 3) / 4);
+  hipLaunchKernelGGL(k_cost_gather<R>, dim3((a.W + 15) / 16, (a.H + 3) / 4, 2), dim3(256), 0, stream, a, b);
+  hipLaunchKernelGGL(k_cost_rest<R>, dim3(border + kCrowdGroups, 2), dim3(256), 0, stream, a, b, border);
+}
+
 static hipError_t launch_cost_gather(const CostArgs &a, const CostBins &b, hipStream_t stream) {
-  const dim3 grid((a.W + 15) / 16, (a.H + 3) / 4, 2);
   switch (a.radius) {
-    case 0: hipLaunchKernelGGL(k_cost_gather<0>, grid, dim3(256), 0, stream, a, b); break;
-    case 1: hipLaunchKernelGGL(k_cost_gather<1>, grid, dim3(256), 0, stream, a, b); break;
-    case 2: hipLaunchKernelGGL(k_cost_gather<2>, grid, dim3(256), 0, stream, a, b); break;
-    case 3: hipLaunchKernelGGL(k_cost_gather<3>, grid, dim3(256), 0, stream, a, b); break;
-    case 4: hipLaunchKernelGGL(k_cost_gather<4>, grid, dim3(256), 0, stream, a, b); break;
-    case 5: hipLaunchKernelGGL(k_cost_gather<5>, grid, dim3(256), 0, stream, a, b); break;
-    case 6: hipLaunchKernelGGL(k_cost_gather<6>, grid, dim3(256), 0, stream, a, b); break;
-    case 7: hipLaunchKernelGGL(k_cost_gather<7>, grid, dim3(256), 0, stream, a, b); break;
+    case 0: launch_cost_sums<0>(a, b, stream); break;
+    case 1: launch_cost_sums<1>(a, b, stream); break;
+    case 2: launch_cost_sums<2>(a, b, stream); break;
+    case 3: launch_cost_sums<3>(a, b, stream); break;
+    case 4: launch_cost_sums<4>(a, b, stream); break;
+    case 5: launch_cost_sums<5>(a, b, stream); break;
+    case 6: launch_cost_sums<6>(a, b, stream); break;
+    case 7: launch_cost_sums<7>(a, b, stream); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
