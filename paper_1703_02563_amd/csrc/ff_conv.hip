@@ -1103,10 +1103,12 @@ static void wgrad_kernel(const ConvArgs &a, int blocks, long long per_wave, hipS
 
 hipError_t launch_wgrad(const ConvArgs &a, float *gw, float *gbias, hipStream_t stream) {
   // two workgroups per compute unit (two waves per SIMD), each with one run of
-  // items per wave; at least 16 items a wave, so that the three rows a run
-  // starts with and the partials stay small beside them
+  // items per wave; at least two items a wave: the three rows a run starts with
+  // and the partials cost less than idle units (32 -> 32, us a call with at least
+  // 16, 4 and 2: 64 x 48 21.8, 12.9 and 11.3; two of 160 x 120 24.4, 15.5 and
+  // 16.7; two of 320 x 240 24.9, 23.0 and 22.9)
   const long long items = (long long)a.B * ((a.W + 15) / 16) * a.H;
-  const int nb = (int)std::max<long long>(1, std::min<long long>(std::min(wgrad_blocks(a.B, a.H), 512), items / 64));
+  const int nb = (int)std::max<long long>(1, std::min<long long>(std::min(wgrad_blocks(a.B, a.H), 512), items / 8));
   const long long per_wave = (items + 4ll * nb - 1) / (4ll * nb);
   if (a.cin == 1 && a.cout == 32) wgrad_kernel<1, 32>(a, nb, per_wave, stream);
   else if (a.cin == 32 && a.cout == 32) wgrad_kernel<32, 32>(a, nb, per_wave, stream);
