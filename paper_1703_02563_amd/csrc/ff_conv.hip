@@ -270,12 +270,12 @@ __global__ __launch_bounds__(256) void k_conv_fwd(ffh::ConvArgs a) {
 // 16 -> 32 115 + 383 -> 167 us.  Bound by memory: 89, 92, 178 and 156 us at
 // copy rate.
 //
-// A workgroup runs down kConvStrips such tiles: its weights are loaded once,
+// A workgroup runs down up to kConvStrips such tiles: its weights are loaded once,
 // and the next tile's pixels are in flight while this one is computed.
 // Without both the four kernels took 186, 155, 307 and 268 us (stores
 // straight from the lanes' registers included); rounding value by value 132,
 // 122, 239 and 173 us.
-constexpr int kConvRows = 8, kConvStrips = 4;
+constexpr int kConvRows = 8, kConvStrips = 4;  // rows of a tile, most tiles of a workgroup
 
 template <int CIN, int COUT, ConvEpilogue EPI>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 3))) void k_conv_fwd_tile(ffh::ConvArgs a) {
@@ -286,9 +286,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 3))) voi
   constexpr int NL = (TR + 2) * LW * (CIN / 8), NI = (NL + 255) / 256;  // 16-byte loads of a tile, per thread
   __shared__ uint4 s_in[(TR + 2) * LW * PX16];
   __shared__ __attribute__((aligned(16))) uint8_t s_tr[4][2048];
-  const int tiles_x = (a.W + TW - 1) / TW, strips = (a.H + TR * kConvStrips - 1) / (TR * kConvStrips);
+  const int rows = TR * a.strips, tiles_x = (a.W + TW - 1) / TW, strips = (a.H + rows - 1) / rows;
   const int img = blockIdx.x / (tiles_x * strips), t = blockIdx.x % (tiles_x * strips);
-  const int x0 = (t % tiles_x) * TW, ys = (t / tiles_x) * TR * kConvStrips, ye = min(ys + TR * kConvStrips, a.H);
+  const int x0 = (t % tiles_x) * TW, ys = (t / tiles_x) * rows, ye = min(ys + rows, a.H);
   uint4 px[NI];
   auto load = [&](int y0) {
 #pragma unroll
@@ -1057,8 +1057,15 @@ hipError_t launch_conv_fwd(const ConvArgs &args, hipStream_t stream) {
   const long long P = (long long)a.B * a.H * a.W;
   const unsigned grid = (unsigned)((P + 127) / 128);
   if (P == 0) return hipSuccess;
-  constexpr int kRows = kConvRows * kConvStrips;
-  const long long tiles = (long long)a.B * ((a.W + 31) / 32) * ((a.H + kRows - 1) / kRows);
+  // Tiles that a workgroup runs down (k_conv_fwd_tile): what the 256 compute
+  // units have each, at most kConvStrips.  32 -> 32 with bf16 outputs, us a call:
+  // 150 tiles (two of 160 x 120) 8.4 with one a workgroup and 11.5 with four; 600
+  // (two of 320 x 240) 11.0, 10.8 and 10.5 with one, two and three, 12.7 with four;
+  // 8100 (1920 x 1080) 84, 70 and 68, 62 with four.
+  const long long single = (long long)a.B * ((a.W + 31) / 32) * ((a.H + kConvRows - 1) / kConvRows);
+  a.strips = (int)std::min<long long>((single + 255) / 256, kConvStrips);
+  const int rows = kConvRows * a.strips;
+  const long long tiles = (long long)a.B * ((a.W + 31) / 32) * ((a.H + rows - 1) / rows);
   if (tiles > 0x7FFFFFFF) return hipErrorInvalidValue;
   a.wide = (((uintptr_t)a.out_f32 | (uintptr_t)a.out_bf16) & 15) == 0;
   const dim3 tgrid((unsigned)tiles), block(256);

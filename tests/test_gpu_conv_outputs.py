@@ -40,6 +40,20 @@ def launch_us(fn, launches=40):
     return min(times[1:])
 
 
+def conv_us(B, H, W, cin, cout, f32):
+    g = torch.Generator().manual_seed(1)
+    x, w, b = bf16((B, H, W, cin), g), bf16((cout, 9, cin), g, 0.1), torch.zeros(cout).cuda()
+    out = torch.empty((B, H, W, cout), dtype=torch.float32 if f32 else torch.int16, device="cuda")
+    return launch_us(lambda: call("ff_conv3x3_fwd", P(x), B, H, W, cin, cout, P(w), P(b), 0, P(out) if f32 else None,
+                                  None if f32 else P(out)))
+
+
+@pytest.mark.parametrize("cin,cout", [(32, 32), (32, 16)])
+def test_a_few_tiles_run_side_by_side(cin, cout):
+    # 16 tiles as four rows of four, and one tile: not one after another
+    assert conv_us(1, 32, 128, cin, cout, False) <= 1.3 * conv_us(1, 8, 32, cin, cout, False)
+
+
 @pytest.mark.parametrize("cin,cout", [(32, 32), (32, 16)])
 def test_weight_gradient_of_a_small_image_runs_side_by_side(cin, cout):
     def us(B, H, W):
