@@ -68,9 +68,12 @@ __device__ __forceinline__ float l2norm16(float4 v[4], float delta) {
 // contiguous piece of the output; the lanes' parts go through a wave's own
 // 2 KB of LDS (16-byte chunks permuted against bank conflicts) so that a
 // store instruction writes 1 KB of it: storing from the lanes' registers
-// touches every 64-byte pixel four times.
+// touches every 64-byte pixel four times.  (Float32 outputs of 32 channels: 64 of
+// a pixel's 128 bytes at a time.  Two 640 x 480 images, 32 -> 32: 65 us from the
+// registers, 29 this way.)
 enum ConvEpilogue {
-  kConvPlain,  // bias, optional ReLU; float32 and / or bf16
+  kConvPlain,  // bias, optional ReLU; float32 and / or bf16, aligned for 16-byte stores
+  kConvAny,    // the same for outputs aligned to an element only: from X W (below)
   kConvMask,   // gradient through the ReLU whose output is a.act, split into two bf16 parts
   kConvNorm,   // bias, unit length per pixel (COUT = 16), float32 and the scale
 };
@@ -85,30 +88,31 @@ __device__ __forceinline__ uint2 pack4(const uint32_t (&h)[4]) {
   return make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
 }
 
-// Writes the run's first n pixels from LDS to `dst` (64 bytes per pixel),
-// 16-bit lanes zeroed where `act` (nullable) is not positive.
+// Writes the run's first n pixels from LDS to `dst` (64 bytes per pixel,
+// STRIDE bytes from pixel to pixel), 16-bit lanes zeroed where `act` (nullable)
+// is not positive.
+template <int STRIDE = 64>
 __device__ __forceinline__ void store_run(const uint8_t *tr, uint8_t *dst, int n, int lane, const uint8_t *act) {
-  uint4 v[2], m[2];
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const int px = (lane >> 2) + 16 * k, c = lane & 3;
-    v[k] = *reinterpret_cast<const uint4 *>(tr + run_chunk(px, c));
-    if (act && px < n) m[k] = *reinterpret_cast<const uint4 *>(act + px * 64 + 16 * c);
+  const int px = lane >> 2, c = lane & 3;  // and pixel px + 16
+  uint4 v0 = *reinterpret_cast<const uint4 *>(tr + run_chunk(px, c));
+  uint4 v1 = *reinterpret_cast<const uint4 *>(tr + run_chunk(px + 16, c));
+  if (act) {
+    uint4 m0 = make_uint4(0, 0, 0, 0), m1 = m0;
+    if (px < n) m0 = *reinterpret_cast<const uint4 *>(act + px * 64 + 16 * c);
+    if (px + 16 < n) m1 = *reinterpret_cast<const uint4 *>(act + (px + 16) * 64 + 16 * c);
+    auto mask = [](uint32_t x, uint32_t a) {  // bf16 > 0: a bit pattern in [1, 0x7F80]
+      const uint32_t l = a & 0xFFFFu, h = a >> 16;
+      return (l - 1u < 0x7F80u ? x & 0xFFFFu : 0u) | (h - 1u < 0x7F80u ? x & 0xFFFF0000u : 0u);
+    };
+    auto mask4 = [&](uint4 x, uint4 m) {
+      return make_uint4(mask(x.x, m.x), mask(x.y, m.y), mask(x.z, m.z), mask(x.w, m.w));
+    };
+    v0 = mask4(v0, m0);
+    v1 = mask4(v1, m1);
   }
   lds_in_order();
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const int px = (lane >> 2) + 16 * k, c = lane & 3;
-    if (px >= n) continue;
-    if (act) {
-      auto mask = [](uint32_t x, uint32_t a) {  // bf16 > 0: a bit pattern in [1, 0x7F80]
-        const uint32_t l = a & 0xFFFFu, h = a >> 16;
-        return (l - 1u < 0x7F80u ? x & 0xFFFFu : 0u) | (h - 1u < 0x7F80u ? x & 0xFFFF0000u : 0u);
-      };
-      v[k] = make_uint4(mask(v[k].x, m[k].x), mask(v[k].y, m[k].y), mask(v[k].z, m[k].z), mask(v[k].w, m[k].w));
-    }
-    *reinterpret_cast<uint4 *>(dst + px * 64 + 16 * c) = v[k];
-  }
+  if (px < n) *reinterpret_cast<uint4 *>(dst + px * STRIDE + 16 * c) = v0;
+  if (px + 16 < n) *reinterpret_cast<uint4 *>(dst + (px + 16) * STRIDE + 16 * c) = v1;
 }
 
 // q0: the run's first pixel; n: its pixels in the image (at most 32, the lane's
@@ -172,36 +176,53 @@ __device__ __forceinline__ void conv_store(const ffh::ConvArgs &a, size_t q0, in
       for (int g = 0; g < G; ++g)
 #pragma unroll
         for (int c = 0; c < 4; ++c) v[g][c] = fmaxf(v[g][c], 0.0f);
-    const size_t o = (q0 + row) * COUT + 4 * kh;
-    if (a.out_f32 && row < n) {
+    if (a.out_f32) {
 #pragma unroll
-      for (int g = 0; g < G; ++g) {
-        if (a.wide)
-          *reinterpret_cast<float4 *>(a.out_f32 + o + 8 * g) = make_float4(v[g][0], v[g][1], v[g][2], v[g][3]);
-        else
-          for (int c = 0; c < 4; ++c) a.out_f32[o + 8 * g + c] = v[g][c];
+      for (int h = 0; h < G; h += 2) {  // 16 channels at a time: 64 bytes of every pixel
+#pragma unroll
+        for (int g = 0; g < 2; ++g)
+          *reinterpret_cast<float4 *>(tr + run_chunk(row, 2 * g + kh)) =
+              make_float4(v[h + g][0], v[h + g][1], v[h + g][2], v[h + g][3]);
+        lds_in_order();
+        store_run<4 * COUT>(tr, reinterpret_cast<uint8_t *>(a.out_f32 + q0 * COUT + 8 * h), n, lane, nullptr);
+        lds_in_order();
       }
     }
     if (a.out_bf16) {
-      uint2 h[G];
 #pragma unroll
-      for (int g = 0; g < G; ++g)
-        h[g] = make_uint2(f32x2_to_bf16(v[g][0], v[g][1]), f32x2_to_bf16(v[g][2], v[g][3]));
-      if (COUT == 32 && a.wide) {
-#pragma unroll
-        for (int g = 0; g < G; ++g) *reinterpret_cast<uint2 *>(tr + run_chunk(row, g) + 8 * kh) = h[g];
+      for (int g = 0; g < G; ++g) {
+        const uint2 h = make_uint2(f32x2_to_bf16(v[g][0], v[g][1]), f32x2_to_bf16(v[g][2], v[g][3]));
+        if constexpr (COUT == 32)
+          *reinterpret_cast<uint2 *>(tr + run_chunk(row, g) + 8 * kh) = h;
+        else if (row < n)
+          *reinterpret_cast<uint2 *>(a.out_bf16 + (q0 + row) * COUT + 8 * g + 4 * kh) = h;
+      }
+      if constexpr (COUT == 32) {
         lds_in_order();
         store_run(tr, reinterpret_cast<uint8_t *>(a.out_bf16 + q0 * 32), n, lane, nullptr);
-      } else if (row < n) {
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-          const uint32_t w[2] = {h[g].x, h[g].y};
-          for (int c = 0; c < 4; ++c) a.out_bf16[o + 8 * g + c] = (uint16_t)(w[c >> 1] >> (16 * (c & 1)));
-        }
       }
     }
   }
   lds_in_order();
+}
+
+// Epilogue of the product X W: a lane holds output channel col = lane & 31 of
+// the pixels 8 g + 4 kh + c, so that 32 lanes store 32 channels of a pixel
+// element by element, one after another.
+template <int COUT>
+__device__ __forceinline__ void conv_store_any(const ffh::ConvArgs &a, size_t q0, int n, int lane, const f32x16 &acc,
+                                               float bias) {
+  const int col = lane & 31, kh = lane >> 5;
+  if (col >= COUT) return;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int px = 8 * (r >> 2) + 4 * kh + (r & 3);
+    float v = acc[r] + bias;
+    if (a.relu) v = fmaxf(v, 0.0f);
+    if (px >= n) continue;
+    if (a.out_f32) a.out_f32[(q0 + px) * COUT + col] = v;
+    if (a.out_bf16) a.out_bf16[(q0 + px) * COUT + col] = (uint16_t)f32x2_to_bf16(v, 0.0f);
+  }
 }
 
 // The biases of a lane's output channels.
@@ -216,7 +237,7 @@ __device__ __forceinline__ void conv_bias(const float *bias, int kh, float (&b)[
 // (64 bytes a pixel, 45 us for 3.6 Mpx at copy rate) and the 2-byte loads of
 // the taps: 89 us with one bf16 per lane and store, 99 with the 8 bytes that a
 // lane holds, 92 in 1 KB pieces, 87 with two values rounded at a time.
-template <int CIN, int COUT>
+template <int CIN, int COUT, ConvEpilogue EPI>
 __global__ __launch_bounds__(256) void k_conv_fwd(ffh::ConvArgs a) {
   static_assert(CIN == 1, "Cin 1 (wider inputs: k_conv_fwd_tile)");
   static_assert(COUT == 32, "Cout 32");
@@ -248,10 +269,16 @@ __global__ __launch_bounds__(256) void k_conv_fwd(ffh::ConvArgs a) {
   uint4 ua, ub;
   __builtin_memcpy(&ua, av, 16);
   __builtin_memcpy(&ub, bv, 16);
-  float bias[COUT / 2];
-  conv_bias<COUT>(a.bias, kh, bias);
-  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ub), as_bf16x8(ua), acc, 0, 0, 0);
-  conv_store<COUT, kConvPlain>(a, (size_t)p0, (int)min(32ll, P - p0), lane, acc, bias, s_tr[wave]);
+  const int n = (int)min(32ll, P - p0);
+  if constexpr (EPI == kConvAny) {
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ua), as_bf16x8(ub), acc, 0, 0, 0);
+    conv_store_any<COUT>(a, (size_t)p0, n, lane, acc, a.bias ? a.bias[row] : 0.0f);
+  } else {
+    float bias[COUT / 2];
+    conv_bias<COUT>(a.bias, kh, bias);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ub), as_bf16x8(ua), acc, 0, 0, 0);
+    conv_store<COUT, kConvPlain>(a, (size_t)p0, n, lane, acc, bias, s_tr[wave]);
+  }
 }
 
 // Tiled form for Cin >= 16: a workgroup takes kConvRows image rows x 32
@@ -271,14 +298,15 @@ __global__ __launch_bounds__(256) void k_conv_fwd(ffh::ConvArgs a) {
 // copy rate.
 //
 // A workgroup runs down up to kConvStrips such tiles: its weights are loaded once,
-// and the next tile's pixels are in flight while this one is computed.
+// and the next tile's pixels are in flight while this one is computed (not with
+// element stores, which leave no registers for them: 168 -> 139 us without).
 // Without both the four kernels took 186, 155, 307 and 268 us (stores
 // straight from the lanes' registers included); rounding value by value 132,
 // 122, 239 and 173 us.
 constexpr int kConvRows = 8, kConvStrips = 4;  // rows of a tile, most tiles of a workgroup
 
 template <int CIN, int COUT, ConvEpilogue EPI>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 3))) void k_conv_fwd_tile(ffh::ConvArgs a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, EPI == kConvAny ? 4 : 3))) void k_conv_fwd_tile(ffh::ConvArgs a) {
   static_assert(CIN % 16 == 0, "Cin must be a multiple of 16");
   static_assert(COUT == 16 || COUT == 32, "Cout 16 or 32");
   constexpr int KC = CIN / 16, TW = 32, TR = kConvRows, LW = TW + 2;
@@ -314,28 +342,39 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 3))) voi
       ub[tap * KC + cc] = make_uint4(w.x & wmask, w.y & wmask, w.z & wmask, w.w & wmask);
     }
   }
-  float bias[COUT / 2];
-  conv_bias<COUT>(a.bias, kh, bias);
+  [[maybe_unused]] float bias[COUT / 2], bias_col = 0.0f;
+  if constexpr (EPI == kConvAny)
+    bias_col = a.bias && col < COUT ? a.bias[col] : 0.0f;
+  else
+    conv_bias<COUT>(a.bias, kh, bias);
   for (int y0 = ys; y0 < ye; y0 += TR) {
     if (y0 > ys) __syncthreads();  // the previous tile is read
+    if (EPI == kConvAny && y0 > ys) load(y0);
 #pragma unroll
     for (int it = 0; it < NI; ++it) {
       const int k = threadIdx.x + 256 * it, c16 = k % (CIN / 8), p = (k / (CIN / 8)) % LW, ry = k / ((CIN / 8) * LW);
       if (k < NL) s_in[(ry * LW + p) * PX16 + c16] = px[it];
     }
     __syncthreads();
-    if (y0 + TR < ye) load(y0 + TR);
+    if (EPI != kConvAny && y0 + TR < ye) load(y0 + TR);
     for (int rr = wave; rr < TR && y0 + rr < a.H; rr += 4) {
       f32x16 acc = {0};
 #pragma unroll
       for (int tap = 0; tap < 9; ++tap) {
         const uint4 *src = s_in + ((rr + tap / 3) * LW + row + tap % 3) * PX16;
 #pragma unroll
-        for (int cc = 0; cc < KC; ++cc)
-          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ub[tap * KC + cc]), as_bf16x8(src[cc * 2 + kh]),
-                                                        acc, 0, 0, 0);
+        for (int cc = 0; cc < KC; ++cc) {
+          const bf16x8 w = as_bf16x8(ub[tap * KC + cc]), x = as_bf16x8(src[cc * 2 + kh]);
+          acc = EPI == kConvAny ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, w, acc, 0, 0, 0)
+                                : __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, x, acc, 0, 0, 0);
+        }
       }
-      conv_store<COUT, EPI>(a, ((size_t)img * a.H + y0 + rr) * a.W + x0, min(TW, a.W - x0), lane, acc, bias, s_tr[wave]);
+      const size_t q0 = ((size_t)img * a.H + y0 + rr) * a.W + x0;
+      const int n = min(TW, a.W - x0);
+      if constexpr (EPI == kConvAny)
+        conv_store_any<COUT>(a, q0, n, lane, acc, bias_col);
+      else
+        conv_store<COUT, EPI>(a, q0, n, lane, acc, bias, s_tr[wave]);
     }
   }
 }
@@ -1057,31 +1096,37 @@ hipError_t launch_conv_fwd(const ConvArgs &args, hipStream_t stream) {
   const long long P = (long long)a.B * a.H * a.W;
   const unsigned grid = (unsigned)((P + 127) / 128);
   if (P == 0) return hipSuccess;
+  const bool wide = (((uintptr_t)a.out_f32 | (uintptr_t)a.out_bf16) & 15) == 0;
   // Tiles that a workgroup runs down (k_conv_fwd_tile): what the 256 compute
   // units have each, at most kConvStrips.  32 -> 32 with bf16 outputs, us a call:
   // 150 tiles (two of 160 x 120) 8.4 with one a workgroup and 11.5 with four; 600
   // (two of 320 x 240) 11.0, 10.8 and 10.5 with one, two and three, 12.7 with four;
-  // 8100 (1920 x 1080) 84, 70 and 68, 62 with four.
+  // 8100 (1920 x 1080) 84, 70 and 68, 62 with four.  Stores element by element
+  // gain less from it, four times as many tiles each: 600 tiles 11.7 with one
+  // and 12.8 with three, 8100 tiles 89 and, with four, 71.
   const long long single = (long long)a.B * ((a.W + 31) / 32) * ((a.H + kConvRows - 1) / kConvRows);
-  a.strips = (int)std::min<long long>((single + 255) / 256, kConvStrips);
+  a.strips = (int)std::min<long long>(wide ? (single + 255) / 256 : single / 1024 + 1, kConvStrips);
   const int rows = kConvRows * a.strips;
   const long long tiles = (long long)a.B * ((a.W + 31) / 32) * ((a.H + rows - 1) / rows);
   if (tiles > 0x7FFFFFFF) return hipErrorInvalidValue;
-  a.wide = (((uintptr_t)a.out_f32 | (uintptr_t)a.out_bf16) & 15) == 0;
-  const dim3 tgrid((unsigned)tiles), block(256);
-  if (a.inv_norm) {  // the last layer with the normalisation
-    if (a.cin != 32 || a.cout != 16) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_conv_fwd_tile<32, 16, kConvNorm>), tgrid, block, 0, stream, a);
-  } else if (a.act) {  // a data gradient through a ReLU
-    if (a.cin == 32 && a.cout == 32) hipLaunchKernelGGL((k_conv_fwd_tile<32, 32, kConvMask>), tgrid, block, 0, stream, a);
-    else if (a.cin == 16 && a.cout == 32) hipLaunchKernelGGL((k_conv_fwd_tile<16, 32, kConvMask>), tgrid, block, 0, stream, a);
-    else return hipErrorInvalidValue;
-  } else if (a.cin == 1 && a.cout == 32) hipLaunchKernelGGL((k_conv_fwd<1, 32>), dim3(grid), block, 0, stream, a);
-  else if (a.cin == 32 && a.cout == 32) hipLaunchKernelGGL((k_conv_fwd_tile<32, 32, kConvPlain>), tgrid, block, 0, stream, a);
-  else if (a.cin == 32 && a.cout == 16) hipLaunchKernelGGL((k_conv_fwd_tile<32, 16, kConvPlain>), tgrid, block, 0, stream, a);
-  else if (a.cin == 16 && a.cout == 32) hipLaunchKernelGGL((k_conv_fwd_tile<16, 32, kConvPlain>), tgrid, block, 0, stream, a);
-  else return hipErrorInvalidValue;
-  return hipGetLastError();
+  auto launch = [&](auto kernel, unsigned groups) {
+    hipLaunchKernelGGL(kernel, dim3(groups), dim3(256), 0, stream, a);
+    return hipGetLastError();
+  };
+#define TILE(CIN, COUT, EPI) launch(k_conv_fwd_tile<CIN, COUT, EPI>, (unsigned)tiles)
+  if (a.inv_norm)  // the last layer with the normalisation
+    return a.cin == 32 && a.cout == 16 ? TILE(32, 16, kConvNorm) : hipErrorInvalidValue;
+  if (a.act) {  // a data gradient through a ReLU
+    if (a.cout != 32 || (a.cin != 32 && a.cin != 16)) return hipErrorInvalidValue;
+    return a.cin == 32 ? TILE(32, 32, kConvMask) : TILE(16, 32, kConvMask);
+  }
+  if (a.cin == 1 && a.cout == 32)
+    return wide ? launch(k_conv_fwd<1, 32, kConvPlain>, grid) : launch(k_conv_fwd<1, 32, kConvAny>, grid);
+  if (a.cin == 32 && a.cout == 32) return wide ? TILE(32, 32, kConvPlain) : TILE(32, 32, kConvAny);
+  if (a.cin == 32 && a.cout == 16) return wide ? TILE(32, 16, kConvPlain) : TILE(32, 16, kConvAny);
+  if (a.cin == 16 && a.cout == 32) return wide ? TILE(16, 32, kConvPlain) : TILE(16, 32, kConvAny);
+#undef TILE
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_descnet_fwd(NetArgs a, hipStream_t stream) {

@@ -298,7 +298,6 @@ struct ConvArgs {
   int B, H, W, cin, cout, relu;
   float *out_f32;      // [B][H][W][cout] (nullable)
   uint16_t *out_bf16;  // [B][H][W][cout] (nullable)
-  int wide;            // set by the launcher: outputs aligned for 4-channel stores
   int strips;          // set by the launcher: tiles that a workgroup runs down (k_conv_fwd_tile)
   // data gradient through a ReLU: its output, and the low parts (out_bf16 takes the high ones)
   const uint16_t *act;  // [B][H][W][cout] (nullable)
