@@ -304,17 +304,23 @@ __global__ __launch_bounds__(256) void k_nn_resolve(ffh::NNArgs a) {
 
 // ---- batches -----------------------------------------------------------
 
-// Chunks of one pair (the part words of a direction, nchunk * M, lie in the
+// Chunks of one pair.  The part words of a direction, nchunk * M, lie in the
 // Npad words of its nb scratch; where they do not fit, one 64-bit atomic per
-// query and chunk merges them).
+// query and chunk merges them.  Fine seed grids leave room for few chunks (one
+// where every pixel is a query): a search of its own (alone) takes the atomics
+// where more than three times as many are wanted.  One scale, a direction, us a
+// call: 160 x 120 46 against 164 with one chunk, 480 x 270 (four wanted) 555
+// against 960; 256 x 192 at n = 8 (three times as many wanted) 85 against 82,
+// the fill included.  Batches have other pairs to fill the units: 1920 x 1080
+// at n = 4 17.0 ms against 17.7 with the atomics.
 struct NNPlan {
   int chunk_tiles, nchunk, atomic;
 };
-__host__ __device__ __forceinline__ NNPlan nn_plan(int M, int N, int want_chunks) {
+__host__ __device__ __forceinline__ NNPlan nn_plan(int M, int N, int want_chunks, bool alone) {
   const int ntiles = (N + 31) >> 5;
   const int fit = (ntiles * 32) / M, need = (ntiles + kMaxChunkTiles - 1) / kMaxChunkTiles;
   NNPlan p;
-  p.atomic = need > fit;
+  p.atomic = need > fit || (alone && want_chunks > 3 * fit);
   int c = p.atomic ? want_chunks : (want_chunks < fit ? want_chunks : fit);
   c = c < need ? need : c;
   c = c < 1 ? 1 : c;
@@ -323,7 +329,7 @@ __host__ __device__ __forceinline__ NNPlan nn_plan(int M, int N, int want_chunks
   return p;
 }
 __host__ __device__ __forceinline__ NNPlan nn_batch_plan(int M, int N) {
-  return nn_plan(M, N, (((N + 31) >> 5) + kBatchChunkTiles - 1) / kBatchChunkTiles);
+  return nn_plan(M, N, (((N + 31) >> 5) + kBatchChunkTiles - 1) / kBatchChunkTiles, false);
 }
 
 // Key initialisation (items: pair, direction, 256 queries); the first item of
@@ -603,7 +609,7 @@ static int nn_want_chunks(int ntiles, int per_chunk_wgs, int qb) {
 hipError_t launch_nn(const NNArgs &args_in, hipStream_t stream) {
   NNArgs args = args_in;
   const int qb = nn_query_blocks(args.M), nqb = nn_qblocks(args.M, qb);
-  const NNPlan p = nn_plan(args.M, args.N, nn_want_chunks((args.N + 31) / 32, nqb * args.ndir, qb));
+  const NNPlan p = nn_plan(args.M, args.N, nn_want_chunks((args.N + 31) / 32, nqb * args.ndir, qb), true);
   args.chunk_tiles = p.chunk_tiles;
   args.nchunk = p.nchunk;
   args.atomic = p.atomic;
