@@ -199,7 +199,7 @@ def roofline_level0(ff, torch, img1, img2, params, reps):
     launch(cnt, work)  # the same call once more, counted (the counts do not vary between calls)
     torch.cuda.synchronize()
     # one call = `launches` launches of the scale-1 level kernel
-    launches = ff.level_launches(params, 0)
+    launches = ff.level_launches(params, 0, size=(W, H))
     ms = sum(a.elapsed_time(b) for a, b in ev) / reps / launches
     evals = int(cnt.sum().item()) / launches
     w_owned, w_all = (int(v) / launches for v in work.cpu())

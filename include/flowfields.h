@@ -648,9 +648,15 @@ int32_t ff_level_variant_count_f32(void);
 
 /* Number of blocked launches the tables give one scale 2^log2n of a
  * schedule with `iters` propagation steps, for the byte descriptors
- * (cost_kind 0) or the float features (1); tuning NULL = the built-in table
- * (host); -1 if out of range. */
+ * (cost_kind 0) or the float features (1); tuning NULL = the built-in table, as
+ * ff_default_tuning gives it (host); -1 if out of range.  A call whose
+ * params->tuning is NULL chooses by its frames: ff_call_launches. */
 int32_t ff_level_launches(const ff_tuning *tuning, int32_t iters, int32_t log2n, int32_t cost_kind);
+
+/* The same of a call on W x H frames in `ndir` directions (1 or 2): of the
+ * tables' launches, or with tuning NULL of those that the call chooses. */
+int32_t ff_call_launches(const ff_tuning *tuning, int32_t W, int32_t H, int32_t ndir, int32_t iters, int32_t log2n,
+                         int32_t cost_kind);
 
 /* Bytes of device workspace ff_flow_fields needs for a W x H pair (host). */
 size_t ff_workspace_bytes(int32_t W, int32_t H, const ff_params *params);

@@ -40,9 +40,9 @@ ffh::Tuning tuning_of(const ff_tuning *t) {
 
 // The tables of a call on `count` frames (W, H): the caller's, or the built-in
 // run lengths with the variants of these grid sizes.
-ffh::Tuning call_tables(const ff_params *p, const int (*sizes)[2], int count, int ndir) {
-  ffh::Tuning t = tuning_of(p->tuning);
-  if (!p->tuning)
+ffh::Tuning call_tables(const ff_tuning *given, const int (*sizes)[2], int count, int ndir) {
+  ffh::Tuning t = tuning_of(given);
+  if (!given)
     for (int lv = 0; lv < ffh::kTuneScales; ++lv) {
       t.variant[lv] = ffh::level_pick_variant(lv, sizes, count, ndir);
       t.passes[lv] = 3;
@@ -50,10 +50,10 @@ ffh::Tuning call_tables(const ff_params *p, const int (*sizes)[2], int count, in
   return t;
 }
 
-ffh::Tuning call_tables(const ff_params *p, int W, int H, int ndir) {
+ffh::Tuning call_tables(const ff_tuning *given, int W, int H, int ndir) {
   const int size[1][2] = {{W, H}};
-  ffh::Tuning t = call_tables(p, size, 1, ndir);
-  if (!p->tuning)
+  ffh::Tuning t = call_tables(given, size, 1, ndir);
+  if (!given)
     for (int lv = 0; lv < ffh::kTuneScales; ++lv) t.variant_f32[lv] = ffh::level_pick_f32(lv, W, H, ndir);
   return t;
 }
@@ -276,7 +276,7 @@ hipError_t run_level_blocked(ffh::LevelKArgs k, int W, int H, int lv, const ff_p
   k.seed = p->seed;
   k.T = T;
   k.radius = p->radius;
-  const ffh::Tuning tun = call_tables(p, W, H, k.ndir);
+  const ffh::Tuning tun = call_tables(p->tuning, W, H, k.ndir);
   k.variant = k.fcost ? tun.variant_f32[lv] : tun.variant[lv];
   int runs[64][2];
   const int m = level_runs(tun, lv, T, k.fcost, runs);
@@ -892,7 +892,7 @@ ff_status ff_flow_fields_batched(const ff_pair *pairs, int32_t npairs, const ff_
     sizes[i][1] = pairs[i].H;
     max_width = pairs[i].W > max_width ? pairs[i].W : max_width;
   }
-  const ffh::Tuning tun = call_tables(params, sizes, npairs, 2);
+  const ffh::Tuning tun = call_tables(params->tuning, sizes, npairs, 2);
   // descriptors: blur (pair, image * L + scale, tile), then the maps' rows
   fill([&](int W, int H) { return ffh::batch_blur_items(W, H, L); });
   const ffh::BatchStage blur = st;
@@ -1347,13 +1347,21 @@ void ff_default_tuning(ff_tuning *out) {
   }
 }
 
-int32_t ff_level_launches(const ff_tuning *tuning, int32_t iters, int32_t log2n, int32_t cost_kind) {
-  const ffh::Tuning tun = tuning_of(tuning);
-  if (iters < 1 || iters > 64 || log2n < 0 || log2n >= ffh::kTuneScales || (cost_kind != 0 && cost_kind != 1) ||
-      !ffh::tuning_ok(tun))
-    return -1;
+static int32_t launches_of(const ffh::Tuning &tun, int32_t iters, int32_t log2n, int32_t cost_kind) {
+  if (iters < 1 || iters > 64 || log2n < 0 || log2n >= ffh::kTuneScales || (cost_kind != 0 && cost_kind != 1)) return -1;
   int runs[64][2];
   return level_runs(tun, log2n, iters, cost_kind, runs);
+}
+
+int32_t ff_level_launches(const ff_tuning *tuning, int32_t iters, int32_t log2n, int32_t cost_kind) {
+  const ffh::Tuning tun = tuning_of(tuning);
+  return ffh::tuning_ok(tun) ? launches_of(tun, iters, log2n, cost_kind) : -1;
+}
+
+int32_t ff_call_launches(const ff_tuning *tuning, int32_t W, int32_t H, int32_t ndir, int32_t iters, int32_t log2n,
+                         int32_t cost_kind) {
+  if (!dims_ok(W, H) || (ndir != 1 && ndir != 2) || !ffh::tuning_ok(tuning_of(tuning))) return -1;
+  return launches_of(call_tables(tuning, W, H, ndir), iters, log2n, cost_kind);
 }
 
 size_t ff_workspace_bytes(int32_t W, int32_t H, const ff_params *params) {
@@ -1381,7 +1389,7 @@ ff_status ff_flow_fields(const uint8_t *img1, const uint8_t *img2, int32_t W, in
 
   // descriptors of both images at every scale; the weight-class row maps
   // only where the table's level-kernel variant evaluates on them
-  const ffh::Tuning tun = call_tables(params, W, H, nd);
+  const ffh::Tuning tun = call_tables(params->tuning, W, H, nd);
   // subpixel flows on the blocked kernels: radius 3, checkerboard order, maps
   // addressed with 32-bit offsets
   bool spx = sb != 0 && r == 3 && !params->raster && !params->subscales;

@@ -120,6 +120,7 @@ _SIGS = {
     "ff_level_variant_count_f32": (C.c_int32, []),
     "ff_default_tuning": (None, [C.POINTER(FFTuning)]),
     "ff_level_launches": (C.c_int32, [C.POINTER(FFTuning), _I32, _I32, _I32]),
+    "ff_call_launches": (C.c_int32, [C.POINTER(FFTuning), _I32, _I32, _I32, _I32, _I32, _I32]),
     "ff_flow_fields": (C.c_int, [_P, _P, _I32, _I32, C.POINTER(FFParams), _P, C.c_size_t, _P, _P, _P, _P, _P, _P,
                                  _P, _P]),
 }

@@ -296,10 +296,16 @@ def run_level_pair(desc_a, desc_b, level: int, params: Params, mode: int, flows,
                                   _stream()), "ff_run_level_pair")
 
 
-def level_launches(params: Params, level: int, cost_kind: int = 0) -> int:
-    """Blocked launches the call's tables give one scale (ff_level_launches)."""
+def level_launches(params: Params, level: int, cost_kind: int = 0, size: tuple | None = None, ndir: int = 2) -> int:
+    """Blocked launches of one scale.  size = (W, H): those of a call on such
+    frames in `ndir` directions (ff_call_launches; without a table it chooses
+    by the size); None: those of params.tuning or the built-in table
+    (ff_level_launches)."""
     t = params.tuning.to_c() if params.tuning is not None else None
-    return int(lib().ff_level_launches(ctypes.byref(t) if t is not None else None, params.iters, level, cost_kind))
+    p = ctypes.byref(t) if t is not None else None
+    if size is None:
+        return int(lib().ff_level_launches(p, params.iters, level, cost_kind))
+    return int(lib().ff_call_launches(p, size[0], size[1], ndir, params.iters, level, cost_kind))
 
 
 def consistency_filter(flow_a, cost_a, flow_b, cost_b, eps: float = 1.0, both: bool = True):
