@@ -43,10 +43,7 @@ ffh::Tuning tuning_of(const ff_tuning *t) {
 ffh::Tuning call_tables(const ff_tuning *given, const int (*sizes)[2], int count, int ndir) {
   ffh::Tuning t = tuning_of(given);
   if (!given)
-    for (int lv = 0; lv < ffh::kTuneScales; ++lv) {
-      t.variant[lv] = ffh::level_pick_variant(lv, sizes, count, ndir);
-      t.passes[lv] = 3;
-    }
+    for (int lv = 0; lv < ffh::kTuneScales; ++lv) ffh::level_pick(lv, sizes, count, ndir, &t.variant[lv], &t.passes[lv]);
   return t;
 }
 

@@ -84,9 +84,9 @@ struct Tuning {
   int passes_f32[kTuneScales];
 };
 const Tuning &default_tuning();
-// Variant of scale 2^log2n for `count` frames (W, H) in `ndir` directions each,
-// where the caller gives no table.
-int level_pick_variant(int log2n, const int (*sizes)[2], int count, int ndir);
+// Variant and most steps per launch of scale 2^log2n for `count` frames (W, H)
+// in `ndir` directions each, where the caller gives no table.
+void level_pick(int log2n, const int (*sizes)[2], int count, int ndir, int *variant, int *passes);
 int level_pick_f32(int log2n, int W, int H, int ndir);
 bool tuning_ok(const Tuning &t);
 

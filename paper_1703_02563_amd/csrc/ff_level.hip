@@ -139,7 +139,7 @@ const Tuning &default_tuning() { return kDefaultTuning; }
 //  * above, 16x16 descriptor quads, and at n = 1 the weight-class kernel on
 //    32x12 tiles once they give four workgroups per unit (640x480: 563 against
 //    602; 480x270: 407 against 400).
-int level_pick_variant(int log2n, const int (*sizes)[2], int count, int ndir) {
+static int level_pick_variant(int log2n, const int (*sizes)[2], int count, int ndir) {
   constexpr long long kUnits = 256;
   auto workgroups = [&](int tw, int th) {
     long long t = 0;
@@ -155,6 +155,17 @@ int level_pick_variant(int log2n, const int (*sizes)[2], int count, int ndir) {
   if (big <= kUnits && 4 * big >= 3 * kUnits) return 30;
   if (workgroups(8, 8) <= 4 * kUnits) return 14;
   return log2n == 0 && workgroups(32, 12) >= 4 * kUnits ? 31 : 11;
+}
+
+// Three steps per launch at most (the halo's redundant cells), but as many as
+// the widest halo takes on grids of a single cell, which have none: 64x48 at n =
+// 64, six and twelve steps, 18 and 38 against 24 and 49 (4x4 tiles) and 24 and
+// 49 (8x8 ones).
+void level_pick(int log2n, const int (*sizes)[2], int count, int ndir, int *variant, int *passes) {
+  bool single = true;
+  for (int k = 0; k < count; ++k) single = single && std::max(sizes[k][0], sizes[k][1]) <= 1 << log2n;
+  *variant = single ? 13 : level_pick_variant(log2n, sizes, count, ndir);
+  *passes = single ? 0 : 3;
 }
 
 // The same for float features (one step per launch), from how many workgroups

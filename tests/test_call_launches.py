@@ -9,6 +9,8 @@ import paper_1703_02563_amd as ff
     (160, 120, 0, 6, 2),    # 8x8 tiles, a halo of 6, three steps per launch
     (1024, 436, 0, 6, 3),   # 32x12 tiles, a halo of 2: two steps
     (1024, 436, 4, 6, 2),   # 4x4 tiles, a halo of 4, three steps
+    (64, 48, 6, 6, 1),      # one cell: as many steps as a halo of 6 takes
+    (64, 48, 6, 12, 2), (65, 48, 6, 6, 2), (64, 65, 6, 6, 2), (33, 20, 6, 4, 1), (16, 9, 4, 6, 1),
 ])
 def test_launches_of_a_call_without_a_table(W, H, level, iters, expect):
     assert ff.level_launches(ff.Params(iters=iters), level, size=(W, H)) == expect
