@@ -32,12 +32,16 @@ constexpr double kFix = 4294967296.0;  // 2^32
 
 // A quad of lanes per entry: lane k owns channels 4k .. 4k+3, so one load of a
 // quad covers a pixel's 64 bytes and the four partial sums of the fixed order
-// are the four lanes' own.  Latency-bound (49 dependent additions per lane):
-// four times the lanes of one thread per entry hide it better: 62 -> 12 us for
-// 2,048 entries at radius 3 on 1024 x 436 (65,536 scattered entries: 64 us
-// either way, 411 MB of patch rows at 6.3 TB/s).
+// are the four lanes' own.  Latency-bound (49 dependent additions per lane) with
+// few entries: 2,048 at radius 3 on 1024 x 436 62 us with one thread per entry,
+// 12 with four.  With many, scattered, bound by the pixels' cache lines, whose
+// halves more waves read at different times: up to radius 3 the next row is in
+// flight instead (65,536 entries 64.3 -> 62.3 us, one thread per entry 62.3; a
+// million 947 -> 912 and 1363); beyond, its registers cost more than they give
+// (radius 4, 16,384 entries: 46 against 44).
 template <int R>
 __global__ __launch_bounds__(256) void k_cost_fwd(ffh::CostArgs a) {
+  constexpr int K = 2 * R + 1, D = R <= 3 ? 2 : 1;  // rows in flight
   const long long gid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   const int e = (int)min(gid >> 2, (long long)a.count - 1), k = (int)(gid & 3);
   const int4 en = a.entries[e];
@@ -45,25 +49,40 @@ __global__ __launch_bounds__(256) void k_cost_fwd(ffh::CostArgs a) {
   const float4 *f1 = reinterpret_cast<const float4 *>(a.f1) + k;
   const float4 *f2 = reinterpret_cast<const float4 *>(a.f2) + k;
   float acc = 0.0f;
-  for (int v = -R; v <= R; ++v) {
+  float4 x[D][K], y[D][K];
+  auto load = [&](int v, float4 (&xr)[K], float4 (&yr)[K]) {
     const size_t qrow = (size_t)clampi(en.y + n * v, Hm) * a.W;
     const size_t trow = (size_t)clampi(en.y + en.w + n * v, Hm) * a.W;
-    float4 x[2 * R + 1], y[2 * R + 1];
 #pragma unroll
     for (int u = -R; u <= R; ++u) {
-      x[u + R] = f1[(qrow + clampi(en.x + n * u, Wm)) * 4];
-      y[u + R] = f2[(trow + clampi(en.x + en.z + n * u, Wm)) * 4];
+      xr[u + R] = f1[(qrow + clampi(en.x + n * u, Wm)) * 4];
+      yr[u + R] = f2[(trow + clampi(en.x + en.z + n * u, Wm)) * 4];
     }
+  };
+  auto add = [&](const float4 (&xr)[K], const float4 (&yr)[K]) {
 #pragma unroll
-    for (int u = 0; u <= 2 * R; ++u) {
-      float d = x[u].x - y[u].x;
+    for (int u = 0; u < K; ++u) {
+      float d = xr[u].x - yr[u].x;
       acc = __fmaf_rn(d, d, acc);
-      d = x[u].y - y[u].y;
+      d = xr[u].y - yr[u].y;
       acc = __fmaf_rn(d, d, acc);
-      d = x[u].z - y[u].z;
+      d = xr[u].z - yr[u].z;
       acc = __fmaf_rn(d, d, acc);
-      d = x[u].w - y[u].w;
+      d = xr[u].w - yr[u].w;
       acc = __fmaf_rn(d, d, acc);
+    }
+  };
+  if constexpr (D == 2) {
+    load(-R, x[0], y[0]);
+#pragma unroll
+    for (int v = 0; v < K; ++v) {
+      if (v + 1 < K) load(v + 1 - R, x[(v + 1) & 1], y[(v + 1) & 1]);
+      add(x[v & 1], y[v & 1]);
+    }
+  } else {
+    for (int v = -R; v <= R; ++v) {
+      load(v, x[0], y[0]);
+      add(x[0], y[0]);
     }
   }
   acc += __shfl_xor(acc, 1);  // s0 + s1 (and s2 + s3 in the quad's upper half)
