@@ -543,8 +543,19 @@ hipError_t launch_phase_features(const PhaseJobs &jobs, hipStream_t stream) {
   return hipGetLastError();
 }
 
-hipError_t launch_cost_fwd(const CostArgs &a, hipStream_t stream) {
-  if (a.count <= 0) return hipSuccess;
+hipError_t launch_cost_fwd(const CostArgs &all, hipStream_t stream) {
+  if (all.count <= 0) return hipSuccess;
+  constexpr int kMost = 1 << 29;  // entries of a launch: four threads each, fewer than 2^32
+  CostArgs a = all;
+  if (all.count > kMost) {
+    a.entries += kMost;
+    a.cost += kMost;
+    a.count -= kMost;
+    const hipError_t e = launch_cost_fwd(a, stream);
+    if (e != hipSuccess) return e;
+    a = all;
+    a.count = kMost;
+  }
   const dim3 grid((unsigned)(((long long)a.count * 4 + 255) / 256));
   switch (a.radius) {
     case 0: hipLaunchKernelGGL(k_cost_fwd<0>, grid, dim3(256), 0, stream, a); break;

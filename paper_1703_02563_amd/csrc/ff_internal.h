@@ -48,6 +48,10 @@ struct NNArgs {
 };
 hipError_t launch_nn(const NNArgs &args, hipStream_t stream);
 
+// Items of one launch of the kernels with more than one thread per item (a
+// launch has fewer than 2^32 threads).
+constexpr int kItemsPerLaunch = 1 << 20;
+
 // The l nearest references of every query (1 <= l <= kTopLMax): the NN
 // kernel's scores per group of references, then the groups that can hold the
 // l nearest ranked (see ff_nn.hip).

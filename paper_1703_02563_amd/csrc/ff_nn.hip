@@ -444,13 +444,13 @@ __device__ __forceinline__ int rank_list(unsigned long long *list, int count, in
 }
 
 // cand[m * l + k] = (squared distance << 32) | q of the k-th nearest
-// reference, ~0 past the last reference.
-__global__ __launch_bounds__(256) void k_topl_rank(ffh::TopLArgs a) {
+// reference, ~0 past the last reference; queries from `first` on.
+__global__ __launch_bounds__(256) void k_topl_rank(ffh::TopLArgs a, int first) {
   __shared__ int32_t score[kTopQ][kTopGroups + 1];
   __shared__ unsigned long long lists[kWaves][kTopList];
   const ffh::TopLDir d = a.dir[blockIdx.y];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int m0 = blockIdx.x * kTopQ;
+  const int m0 = first + blockIdx.x * kTopQ;
   for (int g = tid / kTopQ; g < a.ngroups; g += 256 / kTopQ) {
     const int m = min(m0 + tid % kTopQ, a.M - 1);
     score[tid % kTopQ][g] = d.gmax[(size_t)g * a.M + m];
@@ -665,7 +665,10 @@ hipError_t launch_topl(const TopLArgs &args_in, hipStream_t stream) {
     hipLaunchKernelGGL(k_nn_groups<2>, grid, dim3(64 * kWaves), 0, stream, a);
   else
     hipLaunchKernelGGL(k_nn_groups<1>, grid, dim3(64 * kWaves), 0, stream, a);
-  hipLaunchKernelGGL(k_topl_rank, dim3((a.M + kTopQ - 1) / kTopQ, a.ndir), dim3(256), 0, stream, a);
+  // 64 threads a query: a launch of 2^26 queries would have 2^32 threads
+  for (int first = 0; first < a.M; first += kItemsPerLaunch)
+    hipLaunchKernelGGL(k_topl_rank, dim3((std::min(a.M - first, kItemsPerLaunch) + kTopQ - 1) / kTopQ, a.ndir),
+                       dim3(256), 0, stream, a, first);
   return hipGetLastError();
 }
 

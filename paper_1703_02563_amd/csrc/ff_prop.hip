@@ -204,10 +204,10 @@ struct CandPtrs {
 // another is a chain of 56 dependent patch rows (140 us for eight candidates,
 // both directions; now 15 us).
 template <int R, class Cost>
-__global__ __launch_bounds__(256) void k_rerank(ffh::LevelArgs a, CandPtrs c, int l) {
+__global__ __launch_bounds__(256) void k_rerank(ffh::LevelArgs a, CandPtrs c, int l, int first) {
   static_assert(ffh::kTopLMax == 8, "eight lanes per candidate");
   const ffh::LevelDir d = a.dir[blockIdx.z];
-  const int m = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int m = first + blockIdx.x * 4 + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63, rank = lane >> 3;
   const int x = (m % a.Wn) * a.n, y = (m / a.Wn) * a.n;
   const uint64_t key = m < a.Wn * a.Hn && rank < l ? c.cand[blockIdx.z][(size_t)m * l + rank] : ~0ull;
@@ -619,14 +619,17 @@ hipError_t launch_rerank(const LevelArgs &a, const uint64_t *const *cand, int l,
   if (l < 1 || l > kTopLMax) return hipErrorInvalidValue;
   CandPtrs c{};
   for (int dr = 0; dr < a.ndir; ++dr) c.cand[dr] = cand[dr];
-  dim3 grid((a.Wn * a.Hn + 3) / 4, 1, a.ndir);
-#define CALL(R, C) hipLaunchKernelGGL((k_rerank<R, C>), grid, dim3(256), 0, stream, a, c, l)
-  if (a.fcost == 2) {
-    FF_RADIUS_SWITCH_C(a.radius, CALL, ffk::CostU8Sub)
-  } else if (a.fcost == 0) {
-    FF_RADIUS_SWITCH_C(a.radius, CALL, ffk::CostU8)
-  } else {
-    return hipErrorInvalidValue;
+  const int cells = a.Wn * a.Hn;
+#define CALL(R, C) hipLaunchKernelGGL((k_rerank<R, C>), grid, dim3(256), 0, stream, a, c, l, first)
+  for (int first = 0; first < cells; first += kItemsPerLaunch) {
+    const dim3 grid((std::min(cells - first, kItemsPerLaunch) + 3) / 4, 1, a.ndir);
+    if (a.fcost == 2) {
+      FF_RADIUS_SWITCH_C(a.radius, CALL, ffk::CostU8Sub)
+    } else if (a.fcost == 0) {
+      FF_RADIUS_SWITCH_C(a.radius, CALL, ffk::CostU8)
+    } else {
+      return hipErrorInvalidValue;
+    }
   }
 #undef CALL
   return hipGetLastError();
