@@ -1216,9 +1216,13 @@ hipError_t launch_l2norm16_bwd(const float *y, const float *inv_norm, const floa
 
 hipError_t launch_l2norm16_bwd_split(const float *y, const float *inv_norm, const float *g, long long P, uint16_t *hi,
                                      uint16_t *lo, hipStream_t stream) {
-  if (P > 0)
-    hipLaunchKernelGGL(k_l2norm16_bwd_split, dim3(blocks_of(4 * P)), dim3(256), 0, stream,
-                       reinterpret_cast<const float4 *>(y), inv_norm, reinterpret_cast<const float4 *>(g), P, hi, lo);
+  constexpr long long kMost = 1ll << 29;  // pixels of a launch: four threads each, fewer than 2^32
+  for (long long p = 0; p < P; p += kMost) {
+    const long long n = std::min(P - p, kMost);
+    hipLaunchKernelGGL(k_l2norm16_bwd_split, dim3(blocks_of(4 * n)), dim3(256), 0, stream,
+                       reinterpret_cast<const float4 *>(y ? y + 16 * p : nullptr), y ? inv_norm + p : nullptr,
+                       reinterpret_cast<const float4 *>(g + 16 * p), n, hi + 16 * p, lo + 16 * p);
+  }
   return hipGetLastError();
 }
 

@@ -1,13 +1,21 @@
 """Calls with more items than one launch takes: patch costs of more than 2^30
-entries (four threads each), seed candidates and their reranking on grids of
+entries and split gradients of more than 2^30 pixels (four threads each), seed
+candidates and their reranking on grids of
 more than 2^20 cells (a wave each)."""
 import pytest
 import torch
 
 import paper_1703_02563_amd as ff
+from paper_1703_02563_amd import learned as Lm
 from paper_1703_02563_amd.learned import cost_f32
 
 pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def give_memory_back():
+    yield
+    torch.cuda.empty_cache()
 
 
 def test_more_than_2_30_entries():
@@ -28,6 +36,23 @@ def test_more_than_2_30_entries():
     rest = cost.view(torch.int32) != zero.view(torch.int32)
     rest[at] = False
     assert not bool(rest.any())
+
+
+def test_more_than_2_30_pixels():
+    pixels = (1 << 30) + 3
+    if torch.cuda.mem_get_info()[0] < 150 << 30:
+        pytest.skip("needs 150 GB of device memory")
+    grad = torch.zeros((pixels, 16), device="cuda")
+    at = torch.tensor([0, 1, (1 << 29) - 1, 1 << 29, (1 << 30) - 1, 1 << 30, pixels - 1], device="cuda")
+    few = torch.randn((len(at), 16), generator=torch.Generator().manual_seed(0)).cuda()
+    grad[at] = few
+    hi, lo = (torch.full((pixels, 16), -1, dtype=torch.int16, device="cuda") for _ in range(2))
+    ff.ffi.check(ff.lib().ff_l2norm16_bwd_split(None, None, Lm._ptr(grad), pixels, Lm._ptr(hi), Lm._ptr(lo),
+                                                Lm._stream()), "ff_l2norm16_bwd_split")
+    want = Lm._bf16_bits(few)
+    assert torch.equal(hi[at], want) and torch.equal(lo[at], Lm._bf16_bits(few - Lm.bf16_bits_to_f32(want)))
+    hi[at], lo[at] = 0, 0
+    assert all(not bool(t.view(torch.int64).any()) for t in (hi, lo))
 
 
 def test_more_than_2_20_cells():
