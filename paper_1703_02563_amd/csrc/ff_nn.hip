@@ -31,6 +31,7 @@
 // score is taken: the smallest reference index of the smallest distance.
 // References at or beyond N score -(2^20 - 1), below every real one.
 #include <algorithm>
+#include <atomic>
 #include <climits>
 
 #include "ff_device.h"
@@ -569,16 +570,17 @@ hipError_t launch_fill_u64(uint64_t *dst, uint64_t value, int64_t count, hipStre
 // the kernel is compiled for = workgroups of four waves per compute unit); the
 // count of compute units is cached per device.
 static int nn_resident_workgroups(int qb) {
-  static int cache[64] = {0};
+  static std::atomic<int> cache[64] = {};  // calls of several threads fill it with the same value
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256 * nn_waves(qb);
-  if (cache[dev] == 0) {
-    int cus = 0;
+  int cus = cache[dev].load(std::memory_order_relaxed);
+  if (cus == 0) {
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
       return 256 * nn_waves(qb);
-    cache[dev] = std::max(cus, 1);
+    cus = std::max(cus, 1);
+    cache[dev].store(cus, std::memory_order_relaxed);
   }
-  return cache[dev] * nn_waves(qb);
+  return cus * nn_waves(qb);
 }
 
 // Query blocks of 32 per wave: 8 while that leaves a wave with work in every
