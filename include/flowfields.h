@@ -96,12 +96,14 @@ typedef struct {
      * image b's descriptors bilinearly interpolated at the target with
      * weights in 1/64, costs 64 times Eq. 3 (exact integers).  Requires
      * W, H <= 4095 (int16 flows); other values FF_ERR_ARG.  Runs on the
-     * per-step kernels; ff_flow_fields_batched and ff_flow_fields_f32
+     * blocked level kernels at radius 3 in checkerboard order without
+     * sub-scales, where every scale's descriptor map is below 2^31 bytes, else on
+     * the per-step kernels; ff_flow_fields_batched and ff_flow_fields_f32
      * return FF_ERR_UNSUPPORTED for it. */
     int32_t subpixel;
     /* host, nullable: launch tables of this call; an entry out of range is
-     * FF_ERR_ARG.  NULL: the built-in run lengths, with the byte-descriptor
-     * variant of every scale chosen by its grid's size. */
+     * FF_ERR_ARG.  NULL: the built-in run lengths, with the variant of every
+     * scale (byte descriptors and float features) chosen by its grid's size. */
     const ff_tuning *tuning;
     /* Seed candidates (Sec. 3.1: the l entries of a kd-tree leaf, ranked by
      * matching error, Eq. 1 / Eq. 4; l = 8 in Sec. 4.1): 0 or 1 = the exact
@@ -158,9 +160,8 @@ const char *ff_status_str(ff_status s);
  * blurred[y][x] = round-half-up mean of img over the (2h+1)^2 window,
  * h = max(1, n/2), replicate border; desc[y][x][4*gy+gx] =
  * blurred[clamp(y + n*(2gy-3))][clamp(x + n*(2gx-3))], gx, gy in 0..3.
- * img: [H][W]; blurred: [H][W] output; hsum: [H][W] uint16 scratch
- * (required; this single-image path keeps its row sums in LDS and leaves it
- * untouched);
+ * img: [H][W]; blurred: [H][W] output; hsum: not NULL, neither read nor
+ * written (the row sums stay in LDS);
  * desc: the descriptor MAP of scale n (output, ff_descriptor_map_bytes);
  * desc_rowmajor (nullable): the same descriptors as plain [H][W][16] (the
  * input of ff_init_nn's nearest-neighbour search); wform (nullable): the
@@ -233,7 +234,7 @@ size_t ff_nn_topl_scratch_bytes(int32_t W, int32_t H, int32_t nc);
  * Computed exactly: ff_init_nn's matrix-core search leaves the nearest distance
  * of every group of pixels, and the l groups that can hold the l nearest are
  * ranked pixel by pixel.  desc_a1, desc_b1: as for ff_init_nn;
- * nb_scratch: as for ff_init_nn; scratch: device, ff_nn_topl_scratch_bytes
+ * nb_scratch: not NULL, neither read nor written; scratch: device, ff_nn_topl_scratch_bytes
  * (FF_ERR_WORKSPACE if smaller); 1 <= l <= 8. */
 ff_status ff_nn_topl(const uint8_t *desc_a1, const uint8_t *desc_b1, int32_t W, int32_t H, int32_t nc, int32_t l,
                      int32_t *nb_scratch, void *scratch, size_t scratch_bytes, uint64_t *cand, void *stream);
@@ -243,7 +244,7 @@ ff_status ff_nn_topl(const uint8_t *desc_a1, const uint8_t *desc_b1, int32_t W, 
  * the earlier rank on equal cost; n_evals grows by the number of
  * candidates.  nn_key receives the winner in ff_init_nn's format.  nn_l 0
  * or 1: ff_init_nn (scratch unused); 2..8: scratch of
- * ff_nn_topl_scratch_bytes bytes. */
+ * ff_nn_topl_scratch_bytes bytes (nb_scratch as for ff_nn_topl). */
 ff_status ff_init_nn_l(const uint8_t *desc_a1, const uint8_t *desc_b1, const uint8_t *desc_ac,
                        const uint8_t *desc_bc, int32_t W, int32_t H, int32_t nc, int32_t radius, int32_t nn_l,
                        int32_t *nb_scratch, void *scratch, size_t scratch_bytes, uint64_t *nn_key,

@@ -161,7 +161,7 @@ Layout layout(int W, int H, const ff_params *p) {
   if (p->fast_x2) off = align256(off + 2 * (size_t)ceil_div(W, 2) * ceil_div(H, 2) * 16);
   l.nb = off; off = align256(off + 2 * l.Npad * sizeof(int32_t));
   l.keys = off; off = align256(off + 2 * l.M * sizeof(uint64_t));
-  // seed rerank: bound, collection and ranked candidates of both directions
+  // seed rerank: group scores and ranked candidates of both directions
   l.topl = off;
   if (p->nn_l > 1) off = align256(off + 2 * ffh::topl_scratch_bytes((int)l.M, (long long)l.N));
   l.cand = off;
@@ -1415,7 +1415,7 @@ ff_status ff_flow_fields(const uint8_t *img1, const uint8_t *img2, int32_t W, in
   hipError_t e = ffh::launch_descriptors(jobs, s);
   if (e != hipSuccess) return FF_ERR_LAUNCH;
   // sub-scales: the maps of patch scale 3n/2 (after the jobs above on the
-  // same stream, so their row-sum and blur scratch can be reused)
+  // same stream, so their blurred images can be overwritten)
   uint8_t *sdesc[2][kMaxLevels] = {}, *swform[2][kMaxLevels] = {};
   if (params->subscales && L > 2) {
     ffh::DescJobs sj{};

@@ -307,8 +307,8 @@ __device__ __forceinline__ int cost_record(const int (&first)[K], const int (&at
 // bits of fixed point) adding 3 * 2^51 rounds it to an integer whose bits are
 // summed as they are; a pixel with a larger term takes the checked additions.
 // 65,536 entries at radius 3 on 1024 x 436: the whole backward, sorting
-// included, 4.59 ms -> 0.33 ms
-// (this kernel 0.29 ms, both sides).
+// included, 4.59 ms in the atomic form, 0.33 with border and crowded pixels
+// here as well (72 registers, and waves that wait for one quad), now 0.14.
 template <int R>
 __global__ __launch_bounds__(256) void k_cost_gather(ffh::CostArgs a, CostBins b) {
   constexpr int K = 2 * R + 1;
@@ -453,7 +453,11 @@ __device__ __forceinline__ void cost_border_pixel(int i, int W, int H, int &x, i
 // The pixels that would keep one quad busy while the others wait: the border
 // pixels, a wave each (the first `border` workgroups), and the crowded ones, a
 // workgroup each (the others stride through the list).  Integer sums: any order
-// gives the same bits.
+// gives the same bits.  One quad each, all in one kernel, against this and the
+// atomic form, the whole backward at radius 3: 65,536 entries on a corner 709, 21.5
+// and 129 ms, on one inner pixel of 1024 x 436 37, 1.9 and 22 ms, in 16 x 16 pixels
+// of 160 x 120 7.3, 0.30 and 6.5 ms; 8,192 along an edge of 160 x 120 3.0, 0.12 and
+// 0.82 ms; 512 spread over 64 x 48 at n = 4 222, 43 and 64 us.
 template <int R>
 __global__ __launch_bounds__(256) void k_cost_rest(ffh::CostArgs a, CostBins b, int border) {
   constexpr int K = 2 * R + 1, T = 4;  // terms in flight
@@ -620,8 +624,10 @@ hipError_t launch_cost_bwd(const CostArgs &a, hipStream_t stream) {
   const long long px = (long long)a.W * a.H * 16;
   // Gathering needs the bins to fit the scratch (they do unless the image is
   // tiny against the patch or holds more than about 6 entries per pixel), 16-byte loads of
-  // the maps, and few phases (a corner pixel walks n (2 n radius + 1) ranges
-  // one after another, 0.3 us each: n <= 4 keeps that below 70 us).
+  // the maps, and few phases: a corner pixel walks n (2 n radius + 1) ranges.
+  // Radius 3, 160 x 120, atomics against gathering: 512 entries 57 and 74 us at n =
+  // 8, 85 and 163 at n = 16; 1024 x 436 at n = 64 108 and 1006 us, and with 8,192
+  // entries 875 and 2083 (at n = 8, many entries: 662 and 127).
   CostBins b;
   size_t clear = 0;
   const uintptr_t align = (uintptr_t)a.f1 | (uintptr_t)a.f2 | (uintptr_t)a.grad_f1 | (uintptr_t)a.grad_f2;

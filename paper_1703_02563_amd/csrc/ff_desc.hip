@@ -3,8 +3,7 @@
 //
 // I^n: integer box filter of half-width h = max(1, n/2), rounded half up,
 // computed separably (row sums, then column sums of the row sums; both are
-// exact in integers), per 64 x 64 tile in LDS (batches: through a row-sum
-// buffer).  Descriptor of scale n: the 16 samples of I^n on a 4x4
+// exact in integers), per 64 x 64 tile in LDS.  Descriptor of scale n: the 16 samples of I^n on a 4x4
 // grid with spacing 2n around the pixel, stored as one 16-byte vector per
 // pixel so that a patch position costs one 128-bit load; the pixels of each
 // row are stored in phase order (x mod n, then x / n), and the map carries a

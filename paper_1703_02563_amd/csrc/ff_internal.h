@@ -246,7 +246,6 @@ struct BatchPair {
   unsigned long long *evals;  // [2]
 };
 
-// Work items of one stage: pair p owns items [prefix[p], prefix[p+1]).
 // Workgroups of a launch over work items (for_items), a multiple of 8: one per
 // item, as far as 1024 threads each stay below 2^32 in all.
 inline unsigned item_groups(int total) {
@@ -254,6 +253,7 @@ inline unsigned item_groups(int total) {
   return (unsigned)(((total < 1 ? 1 : total < kMost ? total : kMost) + 7) / 8 * 8);
 }
 
+// Work items of one stage: pair p owns items [prefix[p], prefix[p+1]).
 struct BatchStage {
   const BatchPair *pairs;
   int npairs, total;

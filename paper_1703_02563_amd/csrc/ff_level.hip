@@ -129,9 +129,12 @@ const Tuning &default_tuning() { return kDefaultTuning; }
 //  * 8x8 tiles with 1024 threads while those fit one round (4800 cells at
 //    160x120, n = 2: 147 against 150 with 256 threads and 170 on 16x16; 8160
 //    cells, 270 workgroups: 429 against 398);
-//  * 16x16 tiles with 1024 threads where those fill three quarters of a round
-//    (27904 cells of 1024x436 at n = 4: 655 as with the next, and the costlier
-//    evaluations gain: 1684 against 1731 for subpixel flows);
+//  * 16x16 tiles with 1024 threads where those fill three quarters of a round,
+//    against the next, in workgroups: 192 to 256 at n = 1 and 2 2 to 6 %
+//    (256x128, n = 1: 213 against 226; 320x320, n = 2: 294 against 302), at n =
+//    4 1 to 2 % (1024x436: 652 against 659), at n = 8 equal; 162 to 180 2 % at n =
+//    1 and 2, but at n = 4 and 8 1 % slower (640x570: 556 against 553); subpixel
+//    flows 8 % at 256 (256x128: 430 against 468), 1 to 2 % slower up to 240;
 //  * 8x8 tiles with 256 threads while four per unit are resident at once
 //    (19200 cells at 160x120, n = 1: 146 against 158 on 16x16; 32400 cells at
 //    480x270, n = 2: 398 against 418; 49152 cells at 256x192, n = 1: 310

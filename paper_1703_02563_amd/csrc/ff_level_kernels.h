@@ -1234,7 +1234,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 3))
   level_body<LOG2N, TW, TH, kThreads, 1, true, HALO>(a, a.dir[wg / tiles], wg % tiles);
 }
 
-// Persistent launch over the (pair, direction, tile) items of a batch.
+// Launch over the (pair, direction, tile) items of a batch.
 template <int LOG2N, int TW, int TH, int kThreads, int EV, int HALO>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
     EV >= 3 ? level_waves<TW, TH, kThreads, EV, HALO>() : 1, level_waves<TW, TH, kThreads, EV, HALO>()))) void k_level_batch(

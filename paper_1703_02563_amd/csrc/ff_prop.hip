@@ -17,7 +17,7 @@
 //
 // One lane per cell; both directions of a pair run in one launch
 // (blockIdx.z).  Each kernel counts the patch-cost evaluations it performs
-// with one atomic per wave.
+// with one atomic per wave (k_rerank, k_rescore: per workgroup).
 #include <algorithm>
 #include <type_traits>
 
