@@ -159,7 +159,8 @@ Layout layout(int W, int H, const ff_params *p) {
   // Fast x2: the NN's references, the even pixels of both images
   l.desc1e = off;
   if (p->fast_x2) off = align256(off + 2 * (size_t)ceil_div(W, 2) * ceil_div(H, 2) * 16);
-  l.nb = off; off = align256(off + 2 * l.Npad * sizeof(int32_t));
+  l.nb = off;
+  if (p->nn_l <= 1) off = align256(off + 2 * l.Npad * sizeof(int32_t));
   l.keys = off; off = align256(off + 2 * l.M * sizeof(uint64_t));
   // seed rerank: group scores and ranked candidates of both directions
   l.topl = off;

@@ -114,14 +114,14 @@ def descriptors(img: torch.Tensor, n: int, rowmajor: bool = False, wform: bool =
     (ff_wform_map_bytes).  Returns (blurred, desc[, plain][, wform])."""
     H, W = img.shape
     P = 4 * n
-    hsum = torch.empty((H, W), dtype=torch.int16, device=img.device)
     blurred = torch.empty((H, W), dtype=torch.uint8, device=img.device)
     desc = torch.empty((H + 2 * P, W + 2 * P, 16), dtype=torch.uint8, device=img.device)
     plain = torch.empty((H, W, 16), dtype=torch.uint8, device=img.device) if rowmajor else None
     wf = torch.empty((H + 6 * n, W, 16), dtype=torch.uint8, device=img.device) if wform else None  # 3n border rows
     assert desc.numel() == int(lib().ff_descriptor_map_bytes(W, H, n))
     assert wf is None or wf.numel() == int(lib().ff_wform_map_bytes(W, H, n))
-    check(lib().ff_descriptors(_ptr(img, torch.uint8, "img"), W, H, n, _ptr(hsum), _ptr(blurred), _ptr(desc),
+    # (the row-sum argument is not used: any pointer)
+    check(lib().ff_descriptors(_ptr(img, torch.uint8, "img"), W, H, n, _ptr(blurred), _ptr(blurred), _ptr(desc),
                                _ptr(plain), _ptr(wf), _stream()), "ff_descriptors")
     out = (blurred, desc)
     if rowmajor:
@@ -166,11 +166,11 @@ def nn_topl(desc_a1, desc_b1, nc: int, l: int):
     dev = desc_a1.device
     if tuple(desc_b1.shape) != (H, W, 16):
         raise ValueError("nn_topl: level-1 descriptors [H, W, 16] of two images of one size")
-    nb = torch.empty(((W * H + 31) // 32) * 32, dtype=torch.int32, device=dev)
     nbytes = int(lib().ff_nn_topl_scratch_bytes(W, H, nc))
     scratch = torch.empty(max(nbytes, 1), dtype=torch.uint8, device=dev)
     cand = torch.empty((Hc, Wc, l), dtype=torch.int64, device=dev)
-    check(lib().ff_nn_topl(_ptr(desc_a1, torch.uint8), _ptr(desc_b1, torch.uint8), W, H, nc, l, _ptr(nb),
+    # (the nb_scratch argument is not used: any pointer)
+    check(lib().ff_nn_topl(_ptr(desc_a1, torch.uint8), _ptr(desc_b1, torch.uint8), W, H, nc, l, _ptr(scratch),
                            _ptr(scratch), nbytes, _ptr(cand), _stream()), "ff_nn_topl")
     return cand
 
