@@ -299,9 +299,10 @@ __device__ __forceinline__ int cost_record(const int (&first)[K], const int (&at
 
 // Interior pixels of one side (blockIdx.z): a workgroup takes 16 x 4 pixels,
 // four lanes per pixel with four channels each; crowded ones are listed for
-// k_cost_rest.  Bound by float64 arithmetic (a
-// term is formed and rounded in float64 as in the atomic form) and by the
-// latency of record -> other map's pixel, both prefetched one term ahead.
+// k_cost_rest.  Bound by its vector instructions, issued in 98 % of the cycles
+// where every pixel has terms (a term is formed and rounded in float64 as in the
+// atomic form and added in 64 bits); record and other map's pixel are both
+// prefetched one term ahead.
 // The terms of the 2R + 1 ranges run as one sequence, so that the 16 pixels
 // of a wave differ only in their total.  With every |term| below 2^19 (51
 // bits of fixed point) adding 3 * 2^51 rounds it to an integer whose bits are
