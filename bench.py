@@ -132,7 +132,7 @@ L1_PEAK_TBPS = 256 * 64 * 2.4e9 / 1e12
 # SQ_BUSY_CU_CYCLES (profiles/level_kernel_sq_1024x436.md); valid for the
 # ff_nn.hip it was measured on.
 NN_COUNTERS = {"mfma_busy": 0.440, "valu_issue": 0.642, "mfma_instructions": 1590848}
-NN_SOURCES_SHA = "b9321f16d5d0900c"
+NN_SOURCES_SHA = "6f49d5cc38668109"
 LEVEL_SOURCES = ("paper_1703_02563_amd/csrc/ff_level.hip", "paper_1703_02563_amd/csrc/ff_level_kernels.h",
                  "paper_1703_02563_amd/csrc/ff_level_s0.hip", "paper_1703_02563_amd/csrc/ff_device.h",
                  "paper_1703_02563_amd/csrc/ff_internal.h")

@@ -439,7 +439,7 @@ __device__ __forceinline__ int rank_list(unsigned long long *list, int count, in
     for (int z = 0; z < kTopList / 64; ++z)
       if (k[z] == m) k[z] = ~0ull;
   }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
   return n;
 }
@@ -508,7 +508,7 @@ __global__ __launch_bounds__(256) void k_topl_rank(ffh::TopLArgs a, int first) {
         if (mask) {
           if (in) list[count + __popcll(mask & ((1ull << lane) - 1))] = key;
           count += __popcll(mask);
-          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
           __builtin_amdgcn_wave_barrier();
           if (count > kTopList - 64) {  // keep the l nearest so far; nothing past the l-th is needed any more
             count = rank_list(list, count, a.l, lane);
