@@ -153,7 +153,7 @@ struct CostBins {
   int32_t *rank[2];   // [count]: the entry's place inside its bin, -1: no contribution;
                       // once the records stand: the crowded pixels
   int4 *rec[2];       // [count]: (flow to the other map, gradient bits, entry)
-  int32_t *cursor;    // [4]: records placed, then crowded pixels, per side
+  int32_t *cursor;    // [5]: records placed, then crowded pixels, per side; workgroups done with them
   int Wb, Hb, rn, log2n;
 };
 
@@ -256,6 +256,41 @@ struct CostSum {
   }
 };
 
+constexpr double kMagic = 6755399441055744.0;  // 3 * 2^51: adding it rounds to an integer
+constexpr double kSmall = 2251799813685248.0;  // 2^51: terms of 2^19 in fixed point
+
+// The same with short additions for terms below 2^19 (kMagic's bits summed as
+// they are), at most 2047 of them before they join the checked sum.
+struct CostFastSum {
+  CostSum sum;
+  unsigned long long acc[4] = {0, 0, 0, 0};
+  unsigned n = 0;
+  __device__ __forceinline__ void flush() {
+    const unsigned long long bias = (unsigned long long)__double_as_longlong(kMagic) * n;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      sum.put(c, (long long)(acc[c] - bias));
+      acc[c] = 0;
+    }
+    n = 0;
+  }
+  __device__ __forceinline__ void add(float g, float4 own, float4 other) {
+#pragma clang fp contract(off)
+    const double g2 = (double)g * (2.0 * kFix);
+    const double d0 = g2 * ((double)own.x - (double)other.x), d1 = g2 * ((double)own.y - (double)other.y);
+    const double d2 = g2 * ((double)own.z - (double)other.z), d3 = g2 * ((double)own.w - (double)other.w);
+    if (fabs(d0) < kSmall && fabs(d1) < kSmall && fabs(d2) < kSmall && fabs(d3) < kSmall) {
+      acc[0] += (unsigned long long)__double_as_longlong(d0 + kMagic);
+      acc[1] += (unsigned long long)__double_as_longlong(d1 + kMagic);
+      acc[2] += (unsigned long long)__double_as_longlong(d2 + kMagic);
+      acc[3] += (unsigned long long)__double_as_longlong(d3 + kMagic);
+      if (++n == 2047) flush();
+    } else {
+      sum.add(g, own, other);
+    }
+  }
+};
+
 // A finished pixel: this lane's four channels, and what left the range (a
 // term out of range is seen from both sides and counted on the first).
 __device__ __forceinline__ void cost_write(const ffh::CostArgs &a, int side, size_t px, const CostSum &sum) {
@@ -271,7 +306,7 @@ __device__ __forceinline__ void cost_write(const ffh::CostArgs &a, int side, siz
 // At least the 225 samples of the largest patch, so that the crowded pixels of a
 // side are no more than its entries (the length of their list).
 constexpr int kCrowded = 256;
-constexpr int kCrowdGroups = 512;  // workgroups for them, per side
+constexpr int kTailGroups = 512;  // workgroups for them (1024: the same, 2048: 20 % slower)
 
 // The terms of interior pixel (x, y): every sample that lands there is exactly
 // (x, y), one term per entry of 2R + 1 ranges of records.  Term i of the
@@ -297,87 +332,13 @@ __device__ __forceinline__ int cost_record(const int (&first)[K], const int (&at
   return f + i;
 }
 
-// Interior pixels of one side (blockIdx.z): a workgroup takes 16 x 4 pixels,
-// four lanes per pixel with four channels each; crowded ones are listed for
-// k_cost_rest.  Bound by its vector instructions, issued in 98 % of the cycles
-// where every pixel has terms (a term is formed and rounded in float64 as in the
-// atomic form and added in 64 bits); record and other map's pixel are both
-// prefetched one term ahead.
-// The terms of the 2R + 1 ranges run as one sequence, so that the 16 pixels
-// of a wave differ only in their total.  With every |term| below 2^19 (51
-// bits of fixed point) adding 3 * 2^51 rounds it to an integer whose bits are
-// summed as they are; a pixel with a larger term takes the checked additions.
-// 65,536 entries at radius 3 on 1024 x 436: the whole backward, sorting
-// included, 4.59 ms in the atomic form, 0.33 with border and crowded pixels
-// here as well (72 registers, and waves that wait for one quad), now 0.14.
-template <int R>
-__global__ __launch_bounds__(256) void k_cost_gather(ffh::CostArgs a, CostBins b) {
-  constexpr int K = 2 * R + 1;
-  constexpr double kMagic = 6755399441055744.0;  // 3 * 2^51: adding it rounds to an integer
-  const int k = threadIdx.x & 3, side = blockIdx.z;
-  const int x = blockIdx.x * 16 + ((threadIdx.x >> 2) & 15), y = blockIdx.y * 4 + (threadIdx.x >> 6);
-  const int W = a.W, H = a.H, Wm = W - 1, Hm = H - 1;
-  if (x <= 0 || x >= Wm || y <= 0 || y >= Hm) return;
-  const size_t px = ((size_t)y * W + x) * 4 + k;
-  const float4 *fo = reinterpret_cast<const float4 *>(side ? a.f1 : a.f2) + k;
-  const float4 own = reinterpret_cast<const float4 *>(side ? a.f2 : a.f1)[px];
-  const int4 *rec = b.rec[side];
-  int first[K], at[K + 1];
-  cost_terms<K>(b, side, a.n, x, y, first, at);
-  const int total = at[K];
-  if (total > kCrowded) {
-    if (k == 0) b.rank[side][atomicAdd(b.cursor + 2 + side, 1)] = y * W + x;
-    return;
-  }
-  auto record = [&](int i) { return rec[cost_record<K>(first, at, i)]; };
-  auto other = [&](int4 r) { return fo[((size_t)clampi(y + r.y, Hm) * W + clampi(x + r.x, Wm)) * 4]; };
-  CostSum sum;
-  bool checked = false;
-  if (total > 0) {
-    const double o0 = own.x, o1 = own.y, o2 = own.z, o3 = own.w;
-    int4 r0 = record(0), r1 = record(min(1, total - 1));
-    float4 q0 = other(r0);
-    bool small = true;
-    unsigned long long acc[4] = {0, 0, 0, 0};
-    for (int i = 0; i < total; ++i) {
-      const float4 q1 = other(r1);
-      const int4 r2 = record(min(i + 2, total - 1));
-      {
-#pragma clang fp contract(off)
-        const double g = (double)__int_as_float(r0.z) * (2.0 * kFix);
-        const double d0 = g * (o0 - (double)q0.x), d1 = g * (o1 - (double)q0.y);
-        const double d2 = g * (o2 - (double)q0.z), d3 = g * (o3 - (double)q0.w);
-        constexpr double kSmall = 2251799813685248.0;  // 2^51
-        small = small && fabs(d0) < kSmall && fabs(d1) < kSmall && fabs(d2) < kSmall && fabs(d3) < kSmall;
-        acc[0] += (unsigned long long)__double_as_longlong(d0 + kMagic);
-        acc[1] += (unsigned long long)__double_as_longlong(d1 + kMagic);
-        acc[2] += (unsigned long long)__double_as_longlong(d2 + kMagic);
-        acc[3] += (unsigned long long)__double_as_longlong(d3 + kMagic);
-      }
-      r0 = r1;
-      r1 = r2;
-      q0 = q1;
-    }
-    const unsigned long long bias = (unsigned long long)__double_as_longlong(kMagic) * (unsigned long long)total;
-#pragma unroll
-    for (int c = 0; c < 4; ++c) sum.s[c] = (long long)(acc[c] - bias);
-    checked = !small;
-  }
-  if (checked) {
-    sum = CostSum();
-    for (int i = 0; i < total; ++i) {
-      const int4 r = record(i);
-      sum.add(__int_as_float(r.z), own, other(r));
-    }
-  }
-  cost_write(a, side, px, sum);
-}
-
 // A border pixel, by a wave.  It also takes the samples outside the image that
 // clamp to it: the records of all bins within rn of the pixel along the axis it
 // borders.  The ranges of 16 bins at a time, their records dealt out to the 16
 // quads, so that neither many empty bins nor one crowded bin is walked by one
-// quad.
+// quad.  (Short additions as for the inner pixels would take 34 registers more,
+// which the inner pixels pay for: 127 -> 148 us where the corner case below gains
+// a fifth.)
 template <int R>
 __device__ __forceinline__ void cost_border(const ffh::CostArgs &a, const CostBins &b, int side, int x, int y) {
   constexpr int K = 2 * R + 1;
@@ -421,12 +382,8 @@ __device__ __forceinline__ void cost_border(const ffh::CostArgs &a, const CostBi
       for (int v = -R; v <= R; ++v) {
         if (clampi(cy + n * v, Hm) != y) continue;
         const size_t orow = (size_t)clampi(cy + n * v + r.y, Hm) * W;
-        float4 q[K];
-#pragma unroll
-        for (int u = -R; u <= R; ++u) q[u + R] = fo[(orow + clampi(cx + n * u + r.x, Wm)) * 4];
-#pragma unroll
         for (int u = -R; u <= R; ++u)
-          if (clampi(cx + n * u, Wm) == x) sum.add(g, own, q[u + R]);
+          if (clampi(cx + n * u, Wm) == x) sum.add(g, own, fo[(orow + clampi(cx + n * u + r.x, Wm)) * 4]);
       }
     }
   }
@@ -451,38 +408,119 @@ __device__ __forceinline__ void cost_border_pixel(int i, int W, int H, int &x, i
   }
 }
 
-// The pixels that would keep one quad busy while the others wait: the border
-// pixels, a wave each (the first `border` workgroups), and the crowded ones, a
-// workgroup each (the others stride through the list).  Integer sums: any order
-// gives the same bits.  One quad each, all in one kernel, against this and the
-// atomic form, the whole backward at radius 3: 65,536 entries on a corner 709, 21.5
-// and 129 ms, on one inner pixel of 1024 x 436 37, 1.9 and 22 ms, in 16 x 16 pixels
-// of 160 x 120 7.3, 0.30 and 6.5 ms; 8,192 along an edge of 160 x 120 3.0, 0.12 and
-// 0.82 ms; 512 spread over 64 x 48 at n = 4 222, 43 and 64 us.
+// Gradient of one side (blockIdx.z).  The first `border_rows` rows of
+// workgroups take the border pixels, a wave each; the others 16 x 4 inner pixels,
+// four lanes per pixel with four channels each; crowded ones are listed for
+// k_cost_tail.  Bound by its vector instructions, issued in 98 % of the cycles
+// where every pixel has terms (a term is formed and rounded in float64 as in the
+// atomic form and added in 64 bits); record and other map's pixel are both
+// prefetched one term ahead.
+// The terms of the 2R + 1 ranges run as one sequence, so that the 16 pixels
+// of a wave differ only in their total.  With every |term| below 2^19 (51
+// bits of fixed point) adding 3 * 2^51 rounds it to an integer whose bits are
+// summed as they are; a pixel with a larger term takes the checked additions.
+// 65,536 entries at radius 3 on 1024 x 436: the whole backward, sorting
+// included, 4.59 ms in the atomic form, 0.33 with border and crowded pixels
+// walked by one quad each (waves wait for it), now 0.13.
 template <int R>
-__global__ __launch_bounds__(256) void k_cost_rest(ffh::CostArgs a, CostBins b, int border) {
-  constexpr int K = 2 * R + 1, T = 4;  // terms in flight
-  __shared__ long long s_sum[4][4][5];  // of a wave's quads: four channels; terms and sums out of range
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, k = lane & 3, side = blockIdx.y;
-  const int W = a.W, Wm = W - 1, Hm = a.H - 1;
-  if ((int)blockIdx.x < border) {
-    const long long i = (long long)blockIdx.x * 4 + wave;
-    if (i >= cost_border_count(W, a.H)) return;
-    int x, y;
-    cost_border_pixel((int)i, W, a.H, x, y);
-    cost_border<R>(a, b, side, x, y);
+__global__ __launch_bounds__(256) void k_cost_gather(ffh::CostArgs a, CostBins b, int border_rows) {
+  constexpr int K = 2 * R + 1;
+  const int k = threadIdx.x & 3, side = blockIdx.z;
+  if ((int)blockIdx.y < border_rows) {
+    const long long i = ((long long)blockIdx.y * gridDim.x + blockIdx.x) * 4 + (threadIdx.x >> 6);
+    if (i >= cost_border_count(a.W, a.H)) return;
+    int bx, by;
+    cost_border_pixel((int)i, a.W, a.H, bx, by);
+    cost_border<R>(a, b, side, bx, by);
     return;
   }
+  const int x = blockIdx.x * 16 + ((threadIdx.x >> 2) & 15), y = (blockIdx.y - border_rows) * 4 + (threadIdx.x >> 6);
+  const int W = a.W, H = a.H, Wm = W - 1, Hm = H - 1;
+  if (x <= 0 || x >= Wm || y <= 0 || y >= Hm) return;
+  const size_t px = ((size_t)y * W + x) * 4 + k;
   const float4 *fo = reinterpret_cast<const float4 *>(side ? a.f1 : a.f2) + k;
+  const float4 own = reinterpret_cast<const float4 *>(side ? a.f2 : a.f1)[px];
   const int4 *rec = b.rec[side];
-  const int crowded = b.cursor[2 + side], groups = (int)gridDim.x - border;
-  for (int c = (int)blockIdx.x - border; c < crowded; c += groups) {
-    const int p = b.rank[side][c], x = p % W, y = p / W;
+  int first[K], at[K + 1];
+  cost_terms<K>(b, side, a.n, x, y, first, at);
+  const int total = at[K];
+  if (total > kCrowded) {
+    if (k == 0) b.rank[side][atomicAdd(b.cursor + 2 + side, 1)] = y * W + x;
+    return;
+  }
+  auto record = [&](int i) { return rec[cost_record<K>(first, at, i)]; };
+  auto other = [&](int4 r) { return fo[((size_t)clampi(y + r.y, Hm) * W + clampi(x + r.x, Wm)) * 4]; };
+  CostSum sum;
+  bool checked = false;
+  if (total > 0) {
+    const double o0 = own.x, o1 = own.y, o2 = own.z, o3 = own.w;
+    int4 r0 = record(0), r1 = record(min(1, total - 1));
+    float4 q0 = other(r0);
+    bool small = true;
+    unsigned long long acc[4] = {0, 0, 0, 0};
+    for (int i = 0; i < total; ++i) {
+      const float4 q1 = other(r1);
+      const int4 r2 = record(min(i + 2, total - 1));
+      {
+#pragma clang fp contract(off)
+        const double g = (double)__int_as_float(r0.z) * (2.0 * kFix);
+        const double d0 = g * (o0 - (double)q0.x), d1 = g * (o1 - (double)q0.y);
+        const double d2 = g * (o2 - (double)q0.z), d3 = g * (o3 - (double)q0.w);
+        small = small && fabs(d0) < kSmall && fabs(d1) < kSmall && fabs(d2) < kSmall && fabs(d3) < kSmall;
+        acc[0] += (unsigned long long)__double_as_longlong(d0 + kMagic);
+        acc[1] += (unsigned long long)__double_as_longlong(d1 + kMagic);
+        acc[2] += (unsigned long long)__double_as_longlong(d2 + kMagic);
+        acc[3] += (unsigned long long)__double_as_longlong(d3 + kMagic);
+      }
+      r0 = r1;
+      r1 = r2;
+      q0 = q1;
+    }
+    const unsigned long long bias = (unsigned long long)__double_as_longlong(kMagic) * (unsigned long long)total;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) sum.s[c] = (long long)(acc[c] - bias);
+    checked = !small;
+  }
+  if (checked) {
+    sum = CostSum();
+    for (int i = 0; i < total; ++i) {
+      const int4 r = record(i);
+      sum.add(__int_as_float(r.z), own, other(r));
+    }
+  }
+  cost_write(a, side, px, sum);
+}
+
+// The crowded pixels, which would keep one quad busy while the others wait: a
+// workgroup each, striding through the two sides' lists (integer sums: any order
+// gives the same bits).  Then, with the overflow word nonzero, NaN over both
+// gradients: by every workgroup where there are no crowded pixels, else by the last
+// one that had any, once their gradients are written.
+//
+// The whole backward at radius 3 with a quad for every pixel, with waves for the
+// border and workgroups for crowded pixels, and in the atomic form: 65,536
+// entries on a corner 709, 27 and 129 ms, on one inner pixel of 1024 x 436 37, 1.7
+// and 22 ms, in 16 x 16 pixels of 160 x 120 7.3, 0.29 and 6.5 ms; 8,192 along an
+// edge of 160 x 120 3.0, 0.15 and 0.82 ms; 512 spread over 64 x 48 at n = 4 222, 35
+// and 64 us.  Where neither happens: 8,192 in 64 x 64 inner pixels of 1024 x 436
+// 110, 115 us.
+template <int R>
+__global__ __launch_bounds__(256) void k_cost_tail(ffh::CostArgs a, CostBins b, long long count) {
+  constexpr int K = 2 * R + 1, T = 4;  // terms in flight
+  __shared__ long long s_sum[4][4][5];  // of a wave's quads: four channels; terms and sums out of range
+  __shared__ int s_last;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, k = lane & 3;
+  const int W = a.W, Wm = W - 1, Hm = a.H - 1, groups = (int)gridDim.x;
+  const int crowded = b.cursor[2] + b.cursor[3];  // side 0's, then side 1's
+  for (int c = blockIdx.x; c < crowded; c += groups) {
+    const int side = c >= b.cursor[2], p = b.rank[side][side ? c - b.cursor[2] : c], x = p % W, y = p / W;
+    const float4 *fo = reinterpret_cast<const float4 *>(side ? a.f1 : a.f2) + k;
+    const int4 *rec = b.rec[side];
     const float4 own = reinterpret_cast<const float4 *>(side ? a.f2 : a.f1)[(size_t)p * 4 + k];
     int first[K], at[K + 1];
     cost_terms<K>(b, side, a.n, x, y, first, at);
     const int total = at[K];
-    CostSum sum;
+    CostFastSum fast;
     for (int i0 = threadIdx.x >> 2; i0 < total; i0 += 64 * T) {
       int4 r[T];
       float4 q[T];
@@ -492,8 +530,10 @@ __global__ __launch_bounds__(256) void k_cost_rest(ffh::CostArgs a, CostBins b, 
       for (int j = 0; j < T; ++j) q[j] = fo[((size_t)clampi(y + r[j].y, Hm) * W + clampi(x + r[j].x, Wm)) * 4];
 #pragma unroll
       for (int j = 0; j < T; ++j)
-        if (i0 + 64 * j < total) sum.add(__int_as_float(r[j].z), own, q[j]);
+        if (i0 + 64 * j < total) fast.add(__int_as_float(r[j].z), own, q[j]);
     }
+    fast.flush();
+    CostSum &sum = fast.sum;
     sum.wave_sum();
     if (lane < 4) {
       for (int e = 0; e < 4; ++e) s_sum[wave][k][e] = sum.s[e];
@@ -512,13 +552,25 @@ __global__ __launch_bounds__(256) void k_cost_rest(ffh::CostArgs a, CostBins b, 
     }
     __syncthreads();  // the next pixel's sums
   }
-}
-
-// Both gradients become NaN when the overflow word is nonzero.
-__global__ __launch_bounds__(256) void k_cost_poison(ffh::CostArgs a, long long count) {
-  if (*a.overflow == 0) return;
-  const long long step = (long long)gridDim.x * blockDim.x;
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += step) {
+  long long first = (long long)blockIdx.x * 256, step = (long long)groups * 256;
+  if (crowded > 0) {
+    if ((int)blockIdx.x >= crowded) return;
+    if (threadIdx.x == 0) s_last = 0;
+    __syncthreads();
+    if (threadIdx.x < 4) {  // the threads that wrote
+      __threadfence();
+      if (threadIdx.x == 0) {
+        s_last = atomicAdd(b.cursor + 4, 1) == min(groups, crowded) - 1;
+        __threadfence();
+      }
+    }
+    __syncthreads();
+    if (!s_last) return;
+    first = 0;
+    step = 256;
+  }
+  if (__hip_atomic_load(a.overflow, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) return;
+  for (long long i = first + threadIdx.x; i < count; i += step) {
     a.grad_f1[i] = __builtin_nanf("");
     a.grad_f2[i] = __builtin_nanf("");
   }
@@ -586,24 +638,26 @@ static bool cost_bins(const CostArgs &a, CostBins *b, size_t *clear_words) {
   const size_t bins = ((size_t)b->Hb * (b->Wb + 1) + 1) & ~(size_t)1, entries = ((size_t)a.count + 1) & ~(size_t)1;
   // records first (16-byte aligned), then the counts and the cursor, then the ranks
   const uintptr_t base = ((uintptr_t)a.acc1 + 15) & ~(uintptr_t)15;
-  const size_t total = (base - (uintptr_t)a.acc1) + 2 * entries * 16 + (2 * bins + 4) * 4 + 2 * entries * 4;
+  const size_t total = (base - (uintptr_t)a.acc1) + 2 * entries * 16 + (2 * bins + 6) * 4 + 2 * entries * 4;
   if (total > (size_t)2 * a.W * a.H * 16 * 8) return false;
   b->rec[0] = reinterpret_cast<int4 *>(base);
   b->rec[1] = b->rec[0] + entries;
   b->start[0] = reinterpret_cast<int32_t *>(b->rec[1] + entries);
   b->start[1] = b->start[0] + bins;
   b->cursor = b->start[1] + bins;
-  b->rank[0] = b->cursor + 4;
+  b->rank[0] = b->cursor + 6;
   b->rank[1] = b->rank[0] + entries;
-  *clear_words = bins + 2;
+  *clear_words = bins + 3;
   return true;
 }
 
 template <int R>
 static void launch_cost_sums(const CostArgs &a, const CostBins &b, hipStream_t stream) {
-  const int border = (int)((cost_border_count(a.W, a.H) + 3) / 4);
-  hipLaunchKernelGGL(k_cost_gather<R>, dim3((a.W + 15) / 16, (a.H + 3) / 4, 2), dim3(256), 0, stream, a, b);
-  hipLaunchKernelGGL(k_cost_rest<R>, dim3(border + kCrowdGroups, 2), dim3(256), 0, stream, a, b, border);
+  const int tx = (a.W + 15) / 16;
+  const int border_rows = (int)((cost_border_count(a.W, a.H) + 4ll * tx - 1) / (4ll * tx));
+  hipLaunchKernelGGL(k_cost_gather<R>, dim3(tx, (a.H + 3) / 4 + border_rows, 2), dim3(256), 0, stream, a, b,
+                     border_rows);
+  hipLaunchKernelGGL(k_cost_tail<R>, dim3(kTailGroups), dim3(256), 0, stream, a, b, (long long)a.W * a.H * 16);
 }
 
 static hipError_t launch_cost_gather(const CostArgs &a, const CostBins &b, hipStream_t stream) {
@@ -639,11 +693,7 @@ hipError_t launch_cost_bwd(const CostArgs &a, hipStream_t stream) {
     hipLaunchKernelGGL(k_cost_count, ge, dim3(256), 0, stream, a, b);
     hipLaunchKernelGGL(k_cost_rows, dim3(b.Hb, 2), dim3(256), 0, stream, b);
     hipLaunchKernelGGL(k_cost_fill, ge, dim3(256), 0, stream, a, b);
-    e = launch_cost_gather(a, b, stream);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_cost_poison, dim3((unsigned)std::min<long long>((px + 255) / 256, 1024)), dim3(256), 0,
-                       stream, a, px);
-    return hipGetLastError();
+    return launch_cost_gather(a, b, stream);
   }
   // acc1, acc2 and the overflow word after them are one array
   hipError_t e = launch_fill_u64(reinterpret_cast<uint64_t *>(a.acc1), 0, 2 * px + 1, stream);

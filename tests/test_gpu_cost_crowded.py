@@ -32,6 +32,7 @@ def crowd(place, W, H, count, rng):
 @pytest.mark.parametrize("W,H,n,r,count,place,scale", [
     (64, 48, 1, 3, 256, "pixel", 1.0), (64, 48, 1, 3, 257, "pixel", 1.0), (64, 48, 2, 1, 4000, "pixel", 1.0),
     (67, 53, 4, 7, 700, "pixel", 1.0), (64, 48, 1, 3, 900, "pixel", 3e5),
+    (160, 140, 1, 0, 140000, "pixel", 1.0),  # more than 2047 terms for each of a workgroup's 64 quads
     (64, 48, 1, 3, 900, "corner", 1.0), (67, 53, 4, 2, 900, "corner", 1.0), (40, 30, 2, 0, 900, "corner", 1.0),
     (64, 48, 1, 3, 1500, "edge", 1.0), (67, 53, 4, 3, 1500, "edge", 1.0), (53, 67, 2, 2, 1500, "column", 1.0),
     (96, 64, 1, 3, 4000, "patch", 1.0), (1, 160, 1, 1, 600, "edge", 1.0), (160, 1, 2, 1, 600, "column", 1.0),
